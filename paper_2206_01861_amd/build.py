@@ -13,10 +13,9 @@ SOURCES = [
     "zq_api.hip",
     "zq_quant_kernels.hip",
     "zq_gemm_dispatch.hip",
-    "zq_gemm_simple.hip",
+    "zq_gemm_direct.hip",
     "zq_gemm_skinny.hip",
     "zq_gemm_tile.hip",
-    "zq_gemm_a16.hip",
     "zq_probe.hip",
 ]
 

@@ -263,6 +263,8 @@ zq_status zq_gemm_w8a16_dequant(const void *x_fp16, const int8_t *wq, const floa
                             workspace_bytes >= zq::gemm_a16_tile_split_workspace(M, N, K);
     if (tile_split) {
         e = zq::launch_gemm_a16_tile(a, st);
+    } else if (M <= 64 && ((K % 256) != 0 || zq::direct_pays(M, N, K, 8, 2))) {
+        e = zq::launch_gemm_a16_direct(a, st);
     } else if (M <= kA16StreamTokens && (K % 256) == 0) {
         // Weight streaming holds up to 64 tokens per launch; 65..128 tokens run as two launches over
         // row halves (the weights are read twice, which is still well ahead of the tiled schedule on
@@ -279,7 +281,7 @@ zq_status zq_gemm_w8a16_dequant(const void *x_fp16, const int8_t *wq, const floa
     } else if ((long)M * N * K > (1L << 27)) {
         e = zq::launch_gemm_a16_tile(a, st);
     } else {
-        e = zq::launch_gemm_a16_simple(a, st);
+        e = zq::launch_gemm_a16_direct(a, st);
     }
     return e == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
 }

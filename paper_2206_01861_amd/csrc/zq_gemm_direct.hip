@@ -1,0 +1,461 @@
+// Direct GeMM: no activation tile in LDS, K divided over the waves of a
+// workgroup (Sec. 4.3: at small batch the latency is the time to load the
+// weights; App. D: the schedule is chosen from batch x sequence length).  Takes
+// every legal shape: any M, any K the ABI accepts, INT8 or packed INT4 weights
+// under INT8 activations, and INT8 weights under FP16 activations (W8A16, Sec. 5).
+//
+// What bounds these problems is latency: a few megabytes of weights, gone in a
+// few microseconds, of which a launch takes 1.6.  So a workgroup asks for all of
+// its operands at once and waits once.  It owns up to 32 weight rows and 16 to
+// 64 tokens; stage s of K (256 values) belongs to wave s % NW, which loads its
+// weights and activations straight into registers and multiplies; the waves add
+// their accumulators through LDS at the end.  There is no producer wave, no
+// barrier before that sum and no exchange between workgroups; the rows are dealt
+// so that (nearly) every compute unit gets the same number of them.
+//
+// Measured against the streaming kernel with its activation ring (weights from
+// HBM, one token): 2048x2048 4.3 -> 3.6 us, 2048x8192 7.3 (K split over
+// workgroups) -> 6.4, 16384x4096 16.9 -> 14.0, INT4 2048x8192 10.6 -> 5.2, INT4
+// 16384x4096 10.1 -> 8.6, W8A16 6144x2048 6.5 -> 5.7; a read-only kernel over the
+// same bytes takes 2.4, 4.3, 14, 3.0, 8.0 and 3.6.  Against one wave per 16x16
+// tile: 768x768 at 128 tokens 4.5 -> 3.3; 1600x1600 at 5 tokens 5.2 -> 3.1.
+// Against 128x128 tiles, where K is no multiple of 256: 6400x1600 at 27 tokens
+// 12.2 -> 6.0.
+//
+// What it pays for that: every workgroup reads its tokens' activations from L2
+// for at most 32 weight rows, so with many tokens or a long K that traffic
+// outgrows the weights (direct_pays() says where).
+#include <type_traits>
+
+#include "zq_device.h"
+#include "zq_internal.h"
+
+namespace zq {
+
+namespace {
+
+constexpr uint32_t kRsrcFlags = 0x00020000u;   // raw 32-bit buffer, gfx9 encoding
+constexpr int kStageK = 256;                   // values of K per stage
+constexpr int kCUs = 256;
+[[maybe_unused]] constexpr int kTileInts = 384;  // a 16x16 accumulator tile in LDS: four groups of columns, 96 ints apart
+
+typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32x4 make_srd(const void *p, uint32_t bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    uint32x4 d;
+    d[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
+    d[2] = __builtin_amdgcn_readfirstlane(bytes);    // bounds: reads past the matrix return 0, never fault
+    d[3] = kRsrcFlags;
+    return d;
+}
+
+// The loads are asm statements, so that they stay in flight across the loop's back-edge (the
+// compiler's own waits drain the queue there); the wait names the registers, so no use of the data can
+// be scheduled above it.
+template <int IMM>
+__device__ __forceinline__ void load16(int32x4 &dst, int voff, uint32x4 srd, int soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen offset:%4"
+                 : "=&v"(dst)
+                 : "v"(voff), "s"(srd), "s"(soff), "n"(IMM));
+}
+__device__ __forceinline__ void load_dword(uint32_t &dst, const void *p) {
+    asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p));
+}
+__device__ __forceinline__ void landed(uint32_t &v) { asm volatile("" : "+v"(v)); }
+
+// Eight nibbles -> two words of int8 (value x16) in natural k order.
+__device__ __forceinline__ void unpack8_nat(uint32_t p, uint32_t &d0, uint32_t &d1) {
+    const uint32_t lo = (p << 4) & 0xf0f0f0f0u;   // k 0,2,4,6
+    const uint32_t hi = p & 0xf0f0f0f0u;          // k 1,3,5,7
+    d0 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
+    d1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
+}
+
+// One stage of one wave: LW weight loads per strip of 16 rows, LX activation loads per 16 tokens.
+template <int RT, int MT, int LW, int LX>
+struct Stage {
+    int32x4 w[RT][LW];
+    int32x4 x[MT][LX];
+};
+
+template <int N, int RT, int MT, int LW, int LX>
+__device__ __forceinline__ void stage_wait(Stage<RT, MT, LW, LX> &s) {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N));
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int i = 0; i < LW; ++i) asm volatile("" : "+v"(s.w[t][i]));
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int i = 0; i < LX; ++i) asm volatile("" : "+v"(s.x[t][i]));
+}
+
+}  // namespace
+
+// MT: 16-token tiles, RT: 16-row strips of the weights, XB: bytes of an activation (1 INT8, 2 FP16), D: stages a
+// wave keeps in flight, NW: waves.  rows: weight rows of a workgroup, even, at most 16 * RT.
+template <int MT, int RT, int WBITS, int XB, int D, int NW>
+__global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void gemm_direct_kernel(
+    const uint8_t *__restrict__ xq, const float *__restrict__ s_tok, const uint8_t *__restrict__ wq,
+    const float *__restrict__ s_w, int gs, const half_t *__restrict__ bias, int M, int N, int K, int rows,
+    half_t *__restrict__ out, int32_t *__restrict__ acc_out, int act) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
+    static_assert(XB == 1 || WBITS == 8, "FP16 activations go with INT8 weights");
+    static_assert(D <= 2, "the drain is written out for two stages");
+    constexpr int LW = (WBITS == 8) ? 4 : 2;
+    constexpr int LX = (XB == 1) ? 4 : 8;
+    constexpr int NT = 64 * NW;
+    using AccT = typename std::conditional<XB == 2, float32x4, int32x4>::type;
+    __shared__ __attribute__((aligned(16))) int32_t part[NW * RT * MT * kTileInts];
+
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int r = lane % 16, j = lane / 16;
+    const int n_base = (int)blockIdx.x * rows;
+    const int n_end = n_base + rows < N ? n_base + rows : N;
+    const int m_base = (int)blockIdx.y * 16 * MT;
+
+    const int wrow = (WBITS == 8) ? K : K / 2;              // bytes of a weight row
+    const uint32x4 rs_w = make_srd(wq, (uint32_t)((size_t)N * wrow));
+    const uint32x4 rs_x = make_srd(xq, (uint32_t)((size_t)M * K * XB));
+    constexpr int kNowhere = 0x7ffffff0;                    // past the end of either buffer: loads give 0
+    // Weight loads run chunk-fastest (lane = 4 * row + 16-byte chunk), so that four consecutive lanes read 64
+    // contiguous bytes; one cross-lane permutation per register restores the operand layout (lane = row + 16
+    // * chunk).  Activations are loaded in operand layout: with few tokens most lanes have no row to read.
+    const int wc = (lane % 4) * 16;
+    int voff_w[RT], voff_x[MT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int n = n_base + 16 * t + lane / 4;
+        voff_w[t] = n < n_end ? n * wrow + wc : kNowhere;
+    }
+    // The sixteen values of K that a lane multiplies in a step: INT8 weights, step i: 64i + 16j ..; INT4, step
+    // 2i + h: 128i + 32j + 16h .. (16 packed bytes serve two steps); W8A16, eight values, step 2i + h: 64i +
+    // 16j + 8h ...  Both operands use the same order, and a sum over K does not depend on it.
+    constexpr int XJ = (XB == 1 && WBITS == 8) ? 16 : 32;   // bytes between the activations of neighbouring j
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int m = m_base + 16 * t + r;
+        voff_x[t] = m < M ? m * K * XB + j * XJ : kNowhere;
+    }
+    const int pull = 4 * (4 * r + j);
+
+    Stage<RT, MT, LW, LX> st[D];
+    // Stage s of K belongs to wave s % NW: the workgroup reads its rows front to back.  (A contiguous range of K per
+    // wave, which deals K out more evenly, measured 3-7 % slower: 6144x6144 at one token 9.4 -> 10.1 us.)  Past the end
+    // of K nothing is read and the operands are zeros.
+    const int stages = (wrow + 64 * LW - 1) / (64 * LW);
+    auto issue = [&](int i, Stage<RT, MT, LW, LX> &s) __attribute__((always_inline)) {
+        const int b = (wave + i * NW) * (64 * LW);
+        const int lim = wrow - b;                           // bytes of the row that are left
+        const int so_w = lim > 0 ? b : 0;
+        const int so_x = lim > 0 ? b * (8 / WBITS) * XB : 0;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            load16<0>(s.w[t][0], wc < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+            load16<64>(s.w[t][1], wc + 64 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+            if constexpr (LW == 4) {
+                load16<128>(s.w[t][2], wc + 128 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+                load16<192>(s.w[t][3], wc + 192 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+            }
+        }
+        // INT8 activations past the end of a row (less than a load) are whatever follows: their weights are zero.
+        // FP16 ones have to be zero themselves (0 * NaN is not 0), so the test is made per lane.
+#pragma unroll
+        for (int t = 0; t < MT; ++t) {
+            const int xl = lim - (XB == 2 ? 16 * j : 0);
+            const int v0 = 0 < xl ? voff_x[t] : kNowhere, v1 = 64 < xl ? voff_x[t] : kNowhere;
+            if constexpr (WBITS == 4) {
+                load16<0>(s.x[t][0], v0, rs_x, so_x);
+                load16<16>(s.x[t][1], v0, rs_x, so_x);
+                load16<128>(s.x[t][2], v1, rs_x, so_x);
+                load16<144>(s.x[t][3], v1, rs_x, so_x);
+            } else {
+                const int v2 = 128 < xl ? voff_x[t] : kNowhere, v3 = 192 < xl ? voff_x[t] : kNowhere;
+                if constexpr (XB == 1) {
+                    load16<0>(s.x[t][0], v0, rs_x, so_x);
+                    load16<64>(s.x[t][1], v1, rs_x, so_x);
+                    load16<128>(s.x[t][2], v2, rs_x, so_x);
+                    load16<192>(s.x[t][3], v3, rs_x, so_x);
+                } else {
+                    load16<0>(s.x[t][0], v0, rs_x, so_x);
+                    load16<16>(s.x[t][1], v0, rs_x, so_x);
+                    load16<128>(s.x[t][2], v1, rs_x, so_x);
+                    load16<144>(s.x[t][3], v1, rs_x, so_x);
+                    load16<256>(s.x[t][4], v2, rs_x, so_x);
+                    load16<272>(s.x[t][5], v2, rs_x, so_x);
+                    load16<384>(s.x[t][6], v3, rs_x, so_x);
+                    load16<400>(s.x[t][7], v3, rs_x, so_x);
+                }
+            }
+        }
+    };
+
+    AccT acc[RT][MT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[t][m][e] = 0;
+    auto compute = [&](const Stage<RT, MT, LW, LX> &s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int i = 0; i < LW; ++i) {
+                int32x4 w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) w[e] = __builtin_amdgcn_ds_bpermute(pull, s.w[t][i][e]);
+                if constexpr (XB == 1 && WBITS == 8) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, s.x[m][i], acc[t][m], 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        if constexpr (XB == 1) {
+                            uint32_t d0, d1, d2, d3;
+                            unpack8_nat((uint32_t)w[2 * h], d0, d1);
+                            unpack8_nat((uint32_t)w[2 * h + 1], d2, d3);
+                            const int32x4 a = {(int)d0, (int)d1, (int)d2, (int)d3};
+#pragma unroll
+                            for (int m = 0; m < MT; ++m)
+                                acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, s.x[m][2 * i + h], acc[t][m], 0, 0, 0);
+                        } else {
+                            const half8 a = cvt8_i8_f16((uint32_t)w[2 * h], (uint32_t)w[2 * h + 1]);
+#pragma unroll
+                            for (int m = 0; m < MT; ++m)
+                                acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                                    a, __builtin_bit_cast(half8, s.x[m][2 * i + h]), acc[t][m], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+    };
+
+    // Every wave runs the same number of stages, in groups of D: everything that touches the registers with
+    // loads in flight is unconditional, so the compiler never copies or merges one.
+    constexpr int L = RT * LW + MT * LX;                    // loads of a stage
+    const int n_pad = ((stages + NW - 1) / NW + D - 1) / D * D;
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue(d, st[d]);
+    for (int i = D; i < n_pad; i += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            stage_wait<(D - 1) * L>(st[d]);
+            compute(st[d]);
+            issue(i + d, st[d]);
+        }
+    }
+    // Operands of the epilogue, fetched under the last stages.  Thread t of an output tile finishes columns 2 *
+    // (t % 8), + 1 of token t / 8 (an even column and the next lie in one weight group); indices past the edge are
+    // clamped, loaded and not used; without a bias its load reads a valid dummy.
+    constexpr int ITEMS = RT * MT * 128, IT = (ITEMS + NT - 1) / NT;
+    uint32_t e_sw[IT], e_st[IT], e_b[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int idx = (int)threadIdx.x + it * NT;
+        const int t = idx / 128, q = idx % 128;
+        int n = n_base + (t / MT) * 16 + 2 * (q % 8), m = m_base + (t % MT) * 16 + q / 8;
+        if (n > N - 2) n = N - 2;
+        if (m > M - 1) m = M - 1;
+        load_dword(e_sw[it], s_w + n / gs);
+        if constexpr (XB == 1) load_dword(e_st[it], s_tok + m);
+        load_dword(e_b[it], bias != nullptr ? static_cast<const void *>(bias + n) : s_w);
+    }
+    if constexpr (D == 2) {
+        stage_wait<L>(st[0]);                               // (stricter than needed: the operands above are younger)
+        compute(st[0]);
+    }
+    stage_wait<0>(st[D - 1]);
+    compute(st[D - 1]);
+
+    // Accumulator layout: register v of lane l is weight row 4*(l/16)+v of the strip and token l%16 of the tile.
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+            *reinterpret_cast<AccT *>(part + ((wave * RT + t) * MT + m) * kTileInts + j * 96 + r * 4) = acc[t][m];
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        landed(e_sw[it]);
+        landed(e_b[it]);
+        if constexpr (XB == 1) landed(e_st[it]);
+        const int idx = (int)threadIdx.x + it * NT;
+        if (idx >= ITEMS) break;
+        const int t = idx / 128, q = idx % 128;
+        const int nl = 2 * (q % 8), ml = q / 8;
+        const int n = n_base + (t / MT) * 16 + nl, m = m_base + (t % MT) * 16 + ml;
+        const int32_t *p = part + t * kTileInts + (nl / 4) * 96 + ml * 4 + nl % 4;
+        // the waves in order: the fp32 sums are the same in every call
+        typename std::conditional<XB == 2, float, int32_t>::type a0 = 0, a1 = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int2 v = *reinterpret_cast<const int2 *>(p + w * RT * MT * kTileInts);
+            if constexpr (XB == 2) {
+                a0 += __int_as_float(v.x);
+                a1 += __int_as_float(v.y);
+            } else {
+                a0 += v.x;
+                a1 += v.y;
+            }
+        }
+        if constexpr (WBITS == 4) {                         // exact: every product carried the factor 16
+            a0 >>= 4;
+            a1 >>= 4;
+        }
+        typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+        const half2_t b2 = __builtin_bit_cast(half2_t, e_b[it]);
+        const float sw = __uint_as_float(e_sw[it]);
+        const float sc = (XB == 1) ? __uint_as_float(e_st[it]) * sw : sw;
+        float f[2] = {__builtin_fmaf((float)a0, sc, bias != nullptr ? (float)b2[0] : 0.0f),
+                      __builtin_fmaf((float)a1, sc, bias != nullptr ? (float)b2[1] : 0.0f)};
+        apply_activation_n<2>(f, act);
+        half2_t o;
+        o[0] = (half_t)f[0];
+        o[1] = (half_t)f[1];
+        if (m < M && n < n_end) {
+            *reinterpret_cast<half2_t *>(out + (size_t)m * N + n) = o;
+            if constexpr (XB == 1) {
+                if (acc_out != nullptr) *reinterpret_cast<int2 *>(acc_out + (size_t)m * N + n) = make_int2(a0, a1);
+            }
+        }
+    }
+#endif
+}
+
+namespace {
+
+struct DirectPlan {
+    int rows;      // weight rows of a workgroup
+    int mt;        // 16-token tiles of a workgroup
+};
+
+// Up to 64 tokens (32 of FP16) all of them go to one workgroup and the rows are dealt evenly over a whole number of
+// workgroups per compute unit, 32 rows each at most (2048 rows: 8 each; 6144: 24; 24576: three times 32).  At up to 8
+// tokens INT8 weights go in strips of at most 16 where that leaves them nearly full: twice as many workgroups are in
+// flight and each is done sooner (8192x2048 at one token 5.9 -> 5.4 us, 16384x4096 15.8 -> 13.7), but strips of 10 or 12
+// rows waste a third of every load (6144x6144 at one token 9.4 us in workgroups of 24 rows, 10.1 in strips of 12); half
+// as many bytes per row make it 32 rows for INT4 (16384x4096 at 8 tokens 9.9 us, 11.4 in strips of 16).
+// With more tokens the problem is a tiny one (several workgroups share the weights in L2), and 16 tokens per workgroup
+// spread it best: 768x768 at 128 tokens 3.3 us in 192 workgroups of 32 rows, 3.4 in 384 of 16.
+DirectPlan plan_direct(int M, int N, int w_bits, int xb) {
+    const int tiles = (M + 15) / 16;
+    DirectPlan p;
+    if (tiles <= (xb == 1 ? 4 : 2)) {
+        auto deal = [&](int most) {
+            const int per_cu = (N + most * kCUs - 1) / (most * kCUs);
+            const int rows = (N + kCUs * per_cu - 1) / (kCUs * per_cu);
+            return rows < 8 ? 8 : (rows + 1) / 2 * 2;
+        };
+        p.mt = tiles == 3 ? 4 : tiles;
+        p.rows = deal(32);
+        if (M <= 8 && w_bits == 8 && p.rows > 16 && deal(16) >= 14) p.rows = deal(16);
+        // four token tiles: the activations are read once per 32 rows (6400x1600 at 64 tokens 7.9 us, 9.4 in strips of 16)
+        if (p.mt == 4) p.rows = 32;
+    } else {
+        p.mt = xb == 1 ? 1 : 2;
+        p.rows = (long)(N / 16) * ((tiles + p.mt - 1) / p.mt) <= kCUs ? 16 : 32;
+    }
+    return p;
+}
+
+template <int MT, int RT, int WBITS, int XB, int D, int NW>
+hipError_t launch_direct_t(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
+                           const void *bias, int M, int N, int K, int rows, void *out, int32_t *acc_out, int act,
+                           hipStream_t st) {
+    hipLaunchKernelGGL((gemm_direct_kernel<MT, RT, WBITS, XB, D, NW>),
+                       dim3((N + rows - 1) / rows, (M + 16 * MT - 1) / (16 * MT)), dim3(64 * NW), 0, st,
+                       static_cast<const uint8_t *>(x), s_tok, static_cast<const uint8_t *>(wq), s_w, N / groups,
+                       static_cast<const half_t *>(bias), M, N, K, rows, static_cast<half_t *>(out), acc_out, act);
+    return hipGetLastError();
+}
+
+template <int WBITS, int XB>
+hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
+                         const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int act, hipStream_t st) {
+    const DirectPlan p = plan_direct(M, N, WBITS, XB);
+    const int nst = (K + kStageK - 1) / kStageK;
+    const int rt = p.rows > 16 ? 2 : 1;
+    // Eight waves, four where K has no stage for more (768x768 at 64 tokens: 2.9 us against 3.2).  INT4 stages are half
+    // as many bytes: with few tokens a wave keeps two in flight, unless that leaves one of them empty (2048x8192 at one
+    // token 5.7 -> 5.3 us; for INT8 it measured level).
+    const int nw = nst <= 4 ? 4 : 8;
+    [[maybe_unused]] const bool two = M <= 8 && ((nst + nw - 1) / nw) % 2 == 0;
+#define ZQ_DK(MT, RT, D, NW)                                                                                         \
+    return launch_direct_t<MT, RT, WBITS, XB, D, NW>(x, s_tok, wq, s_w, groups, bias, M, N, K, p.rows, out, acc_out, \
+                                                     act, st)
+    if (p.mt == 1) {
+        if (nw == 4) {
+            if (rt == 1) ZQ_DK(1, 1, 1, 4);
+            ZQ_DK(1, 2, 1, 4);
+        }
+        if constexpr (WBITS == 4) {
+            if (two && rt == 1) ZQ_DK(1, 1, 2, 8);
+            if (two) ZQ_DK(1, 2, 2, 8);
+        }
+        if (rt == 1) ZQ_DK(1, 1, 1, 8);
+        ZQ_DK(1, 2, 1, 8);
+    }
+    if (p.mt == 2) {
+        if (nw == 4) {
+            if (rt == 1) ZQ_DK(2, 1, 1, 4);
+            ZQ_DK(2, 2, 1, 4);
+        }
+        if (rt == 1) ZQ_DK(2, 1, 1, 8);
+        ZQ_DK(2, 2, 1, 8);
+    }
+    if constexpr (XB == 1) {
+        if (nw == 4) ZQ_DK(4, 2, 1, 4);
+        ZQ_DK(4, 2, 1, 8);
+    }
+#undef ZQ_DK
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// Whether the direct kernel beats the streaming kernels for a shape that both take (K a multiple of 256).  Its
+// workgroups read M x K activation bytes each, from L2, which stays hidden behind the weights only up to some 130 to
+// 270 KB per compute unit; the streaming kernel shares one activation tile among up to 128 rows.  On the other side the
+// streaming kernel leaves compute units idle on matrices of few rows, or pays for an exchange between workgroups where it
+// splits K.  The lines below follow 130 shapes (1536 to 24576 rows, K 1024 to 24576) at 1 to 32 tokens; in
+// microseconds, streaming / direct:
+//   INT4   2048x8192 at 16 tokens 10.7 / 7.0, 8192x8192 at 32 (262 KB) 17.4 / 13.4, 16384x4096 at 8 11.1 / 9.9; beyond:
+//          4096x16384 at 24 (393 KB) 14.2 / 16.1, 16384x4096 at 32 (262 KB) 12.3 / 13.3
+//   W8A16  3072x4096 at 8 8.5 / 6.5, 6144x4096 at 16 (131 KB) 10.4 / 9.8; beyond: 12288x2048 at 12 (98 KB) 8.8 / 9.7
+//   INT8   2048x2048 at 1 4.2 / 3.6, 2560x10240 at 4 9.6 / 8.4, 16384x4096 at 1 16.8 / 13.7, 3072x6144 at 16 8.4 / 7.2,
+//          4096x2048 at 24 5.5 / 5.0; beyond: 4096x4096 at 16 5.9 / 6.4, 12288x4096 at 8 12.1 / 12.9, 24576x6144 at 64
+//          31.8 / 47.5.  Where the stages do not fill the waves (ten stages on eight), the second round is mostly empty:
+//          10240x2560 at 1 8.0 / 9.0.
+bool direct_pays(int M, int N, int K, int w_bits, int xb) {
+    if (M > 32) return false;
+    const long load = (long)M * K * xb * ((N + 32 * kCUs - 1) / (32 * kCUs));
+    const bool one_round = N <= 32 * kCUs;
+    if (xb == 2) return load <= (one_round ? 131072 : 65536);
+    if (w_bits == 4) return load <= (one_round ? 270000 : 200000);
+    const int stages = (K + kStageK - 1) / kStageK, last = stages % 8;
+    if (M <= 8) {
+        const bool filled = stages <= 8 || last == 0 || last > 4;
+        return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);
+    }
+    if (M <= 16) return K <= 2560 ? N <= 4096 : (K >= 5120 && N >= 2560 && one_round && load <= 131072);
+    return K <= 2048 && N <= 4096;
+}
+
+hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st) {
+    if (a.w_bits == 8)
+        return launch_direct<8, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out,
+                                   a.act, st);
+    return launch_direct<4, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out, a.act, st);
+}
+
+hipError_t launch_gemm_a16_direct(const A16Args &a, hipStream_t st) {
+    return launch_direct<8, 2>(a.x, nullptr, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, nullptr, 0, st);
+}
+
+}  // namespace zq

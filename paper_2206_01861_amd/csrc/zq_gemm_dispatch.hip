@@ -11,7 +11,7 @@ namespace zq {
 
 constexpr int kStreamMaxTokens = 128;   // the weight-streaming schedules hold up to eight 16-token tiles
 
-hipError_t launch_gemm_simple(const GemmArgs &a, hipStream_t st);
+hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st);
 hipError_t launch_gemm_tile(const GemmArgs &a, int block, hipStream_t st);
 hipError_t launch_gemm_skinny(const GemmArgs &a, bool split_k, hipStream_t st);
 size_t stream_workspace_bytes(int M, int N, int K, int w_bits);
@@ -76,7 +76,7 @@ bool gemm_variant_supports(int variant, int M, int N, int K, int w_bits, size_t 
 
 hipError_t launch_gemm(int variant, const GemmArgs &a, hipStream_t st) {
     switch (variant) {
-        case kGemmSimple: return launch_gemm_simple(a, st);
+        case kGemmSimple: return launch_gemm_direct(a, st);
         case kGemmTile128: return launch_gemm_tile(a, 128, st);
         case kGemmTile256: return launch_gemm_tile(a, 256, st);
         case kGemmTile256x128: return launch_gemm_tile(a, 192, st);
@@ -105,10 +105,13 @@ extern "C" int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t wo
             gemm_variant_workspace(kGemmSkinnySplitK, M, N, K, w_bits) > 0)
             return kGemmSkinnySplitK;
         if (gemm_variant_supports(kGemmSkinny, M, N, K, w_bits, 0)) return kGemmSkinny;
-        // K not a multiple of 256: the tiled schedules below take it
     }
-    // Tiny problems (a BERT-base layer at 128 tokens) are all latency: one wave per 16x16 tile straight
-    // from global memory starts and finishes sooner than a handful of LDS-tiled workgroups (6.2 vs 6.8 us).
+    // Up to 64 tokens and K not a multiple of 256: the direct kernel, which takes any K (6400x1600 at 27 tokens
+    // 6.0 us, 12.2 on 128x128 tiles), except where many tokens meet so many rows that its activation traffic
+    // costs more than the tiles' empty half (16416x5472 at 64 tokens: 45 us, 38 on tiles; 12672x3168: 22.6, 24.8).
+    if (M <= 32 || (M <= 64 && N <= 16384)) return kGemmSimple;
+    // Tiny problems (a BERT-base layer at 128 tokens) are all latency: the direct kernel starts and finishes
+    // sooner than a handful of LDS-tiled workgroups (768x768 at 128 tokens 3.3 us, 6.8 on tiles).
     if ((long)M * N * K <= (1L << 27)) return kGemmSimple;
     // Few tiles against a long K (some hundred tokens, a few thousand columns): split K over the idle
     // compute units when the caller's workspace holds the partial products.

@@ -68,7 +68,7 @@ hipError_t launch_weight_quant(const void *w, int N, int K, int groups, int bits
 
 // GeMM schedules.  The order is part of the test/tuning hook of the C ABI.
 enum GemmVariant {
-    kGemmSimple = 0,      // one wave per 16x16 tile, operands from global; any legal shape
+    kGemmSimple = 0,      // direct: operands from global to registers, K divided over the waves of a workgroup; any legal shape
     kGemmTile128 = 1,     // 128x128 block tile, eight waves
     kGemmTile256 = 2,     // 256x256 block tile, eight waves
     kGemmSkinny = 3,      // M <= 128, K % 256 == 0: weight streaming, whole K in one workgroup
@@ -108,6 +108,9 @@ hipError_t launch_gemm_tile_splitk(const GemmArgs &a, hipStream_t st);
 bool gemm_tile_quant_supported(int M, int N, size_t workspace_bytes);
 hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st);
 
+// Whether the direct kernel beats the streaming kernels (few tokens, K % 256 == 0); xb: bytes of an activation.
+bool direct_pays(int M, int N, int K, int w_bits, int xb);
+
 // A caller-supplied cut of the streaming schedules for this shape, if one was registered.
 bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_splits);
 
@@ -123,7 +126,7 @@ struct A16Args {
     void *workspace;      // fp32 partials of the K split
     size_t workspace_bytes;
 };
-hipError_t launch_gemm_a16_simple(const A16Args &a, hipStream_t st);
+hipError_t launch_gemm_a16_direct(const A16Args &a, hipStream_t st);                     // any shape
 hipError_t launch_gemm_a16_stream(const A16Args &a, bool allow_split, hipStream_t st);   // M <= 64, K % 256 == 0
 size_t stream_a16_workspace_bytes(int M, int N, int K);                                   // of that schedule's K split
 void stream_a16_plan(int M, int N, int K, bool allow_split, int *row_blocks, int *k_splits, int *consumers);
