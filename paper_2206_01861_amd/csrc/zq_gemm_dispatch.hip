@@ -12,7 +12,6 @@ namespace zq {
 constexpr int kStreamMaxTokens = 128;   // the weight-streaming schedules hold up to eight 16-token tiles
 
 hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st);
-hipError_t launch_gemm_tile(const GemmArgs &a, int block, hipStream_t st);
 hipError_t launch_gemm_skinny(const GemmArgs &a, bool split_k, hipStream_t st);
 size_t stream_workspace_bytes(int M, int N, int K, int w_bits);
 void stream_plan(int M, int N, int K, int w_bits, bool allow_split, int *row_blocks, int *k_splits, int *consumers,
@@ -74,13 +73,38 @@ bool gemm_variant_supports(int variant, int M, int N, int K, int w_bits, size_t 
     return false;
 }
 
+namespace {
+TileKind tile_kind(int w_bits) { return w_bits == 8 ? kTileI8 : kTileI4; }
+
+// The tile shapes that stand behind a tiled variant, and the variant a shape belongs to.
+unsigned shapes_of(int variant) {
+    switch (variant) {
+        case kGemmTile128: return 1u << kTile128x64 | 1u << kTile128x128;
+        case kGemmTile256x128: return 1u << kTile192x128 | 1u << kTile256x128;
+        case kGemmTile256x192: return 1u << kTile256x192;
+    }
+    return 1u << kTile256x256;
+}
+int variant_of(TileShape shape) {
+    switch (shape) {
+        case kTile128x64:
+        case kTile128x128: return kGemmTile128;
+        case kTile192x128:
+        case kTile256x128: return kGemmTile256x128;
+        case kTile256x192: return kGemmTile256x192;
+        default: return kGemmTile256;
+    }
+}
+}  // namespace
+
 hipError_t launch_gemm(int variant, const GemmArgs &a, hipStream_t st) {
     switch (variant) {
         case kGemmSimple: return launch_gemm_direct(a, st);
-        case kGemmTile128: return launch_gemm_tile(a, 128, st);
-        case kGemmTile256: return launch_gemm_tile(a, 256, st);
-        case kGemmTile256x128: return launch_gemm_tile(a, 192, st);
-        case kGemmTile256x192: return launch_gemm_tile(a, 256192, st);
+        case kGemmTile128:
+        case kGemmTile256:
+        case kGemmTile256x128:
+        case kGemmTile256x192:
+            return launch_gemm_tile(a, choose_tile(tile_kind(a.w_bits), a.M, a.N, a.K, shapes_of(variant), nullptr), st);
         case kGemmTileSplitK: return launch_gemm_tile_splitk(a, st);
         case kGemmSkinny: return launch_gemm_skinny(a, false, st);
         case kGemmSkinnySplitK: return launch_gemm_skinny(a, true, st);
@@ -116,21 +140,7 @@ extern "C" int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t wo
     // Few tiles against a long K (some hundred tokens, a few thousand columns): split K over the idle
     // compute units when the caller's workspace holds the partial products.
     if (gemm_variant_supports(kGemmTileSplitK, M, N, K, w_bits, workspace_bytes)) return kGemmTileSplitK;
-    // Tiled schedules.  The tiles of a launch all take the same time and a compute unit holds one of
-    // them, so a launch lasts (rounds of tiles) x (time of a tile), and the time of a tile goes with
-    // its area times a factor for the operand bytes it moves per product.  Factors fitted to one-round
-    // measurements at K = 2048..6144 (256x256 = 1): 256x192 1.15, 128x128 1.85.
-    constexpr long kComputeUnits = 256;
-    const long rows256 = (M + 255) / 256;
-    const long t256 = rows256 * ((N + 255) / 256);
-    const long t192 = rows256 * ((N + 191) / 192);
-    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
-    auto rounds = [](long tiles, long slots) { return (tiles + slots - 1) / slots; };
-    const long c256 = rounds(t256, kComputeUnits) * 65536 * 100;
-    const long c192 = rounds(t192, kComputeUnits) * 49152 * 115;
-    const long c128 = rounds(t128, kComputeUnits) * 16384 * 185;
-    if (c128 <= c256 && c128 <= c192) return kGemmTile128;
-    return (c192 < c256) ? kGemmTile256x192 : kGemmTile256;
+    return variant_of(choose_tile(tile_kind(w_bits), M, N, K, kAllTileShapes, nullptr));
 }
 
 extern "C" int zq_gemm_stream_plan(int M, int N, int K, int w_bits, size_t workspace_bytes, int *row_blocks,

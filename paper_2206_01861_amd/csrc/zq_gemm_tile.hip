@@ -1068,6 +1068,60 @@ int tile_splits(int M, int N, int K, int x_bytes) {
     return best;
 }
 
+// Tile shapes, and the time a launch of them takes.  A compute unit holds one workgroup, so a launch lasts (rounds of
+// tiles) x (time of a tile): a + rounds * stages * b + (rounds - 1) * c microseconds, with a stage of 128 bytes of an
+// activation row.  b grows from b0, with few compute units at work, to b1 with all of them (power, L2 and memory shared):
+// the last, partly filled round is charged in between.  Fitted to 317 shapes each (72 to 8192 tokens, 768 to 24576
+// columns, K 768 to 24576; 70 for FP16 activations): within 3 to 9 % rms, and the choice by it costs 0.1 to 0.4 % on
+// average over the best shape.
+// What the smaller shapes are for, INT8, in microseconds: 128x64 and 128x128 fill the chip at some hundred tokens
+// (4096x4096 at 333 tokens: 15.6 on 128x64 tiles, 20.2 on 128x128, 41 on 256x192), 192x128 and 256x128 carry a third
+// stage in flight, which tiles of 256x192 have no LDS for and weights that come from HBM need (12288x4096 at 333: 28.2 on
+// 192x128, 41.0 on 256x192; 6144x2048 at 1024: 18.2 on 256x128, 24.3), and they fill one round where larger ones leave
+// a part of the chip idle (4096x4096 at 1237: 29.3 on 224 tiles of 192x128, 41.1 on 110 of 256x192).
+struct TileCost {
+    int bm, bn;
+    double a, b0, b1, c;
+};
+constexpr TileCost kTileCost[3][kTileShapes] = {
+    // INT8 weights
+    {{128, 64, 4.62, 0.265, 0.370, 2.19}, {128, 128, 5.60, 0.338, 0.542, 3.37}, {192, 128, 4.76, 0.577, 0.819, 3.50},
+     {256, 128, 5.34, 0.644, 0.974, 4.56}, {256, 192, 5.84, 0.842, 1.311, 6.46}, {256, 256, 6.07, 1.003, 1.659, 6.78}},
+    // INT4 weights
+    {{128, 64, 4.41, 0.430, 0.465, 2.54}, {128, 128, 4.25, 0.428, 0.571, 2.71}, {192, 128, 4.83, 0.545, 0.759, 3.95},
+     {256, 128, 4.78, 0.751, 0.991, 4.48}, {256, 192, 5.82, 0.981, 1.320, 6.88}, {256, 256, 6.12, 1.048, 1.520, 9.83}},
+    // FP16 activations
+    {{128, 64, 5.10, 0.414, 0.476, 2.16}, {128, 128, 4.74, 0.389, 0.599, 2.38}, {192, 128, 5.24, 0.540, 0.783, 3.91},
+     {256, 128, 5.96, 0.632, 0.998, 5.49}, {256, 192, 6.54, 0.911, 1.398, 6.56}, {256, 256, 6.91, 1.051, 1.644, 9.34}},
+};
+
+double tile_time(const TileCost &t, int M, int N, int K, int x_bytes) {
+    const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const double stages = (double)(((long)K * x_bytes + 127) / 128);
+    const long full = tiles / 256, rem = tiles % 256;
+    double us = t.a + (double)full * stages * t.b1 + (double)((tiles + 255) / 256 - 1) * t.c;
+    if (rem > 0) us += stages * (t.b0 + (t.b1 - t.b0) * (double)rem / 256.0);
+    return us;
+}
+
+}  // namespace
+
+TileShape choose_tile(TileKind kind, int M, int N, int K, unsigned shapes, double *us) {
+    int best = kTile256x256;
+    double best_us = 1e30;
+    for (int i = 0; i < kTileShapes; ++i) {
+        if (((shapes >> i) & 1u) == 0) continue;
+        const double t = tile_time(kTileCost[kind][i], M, N, K, kind == kTileA16 ? 2 : 1);
+        if (t < best_us) {
+            best_us = t;
+            best = i;
+        }
+    }
+    if (us != nullptr) *us = best_us;
+    return (TileShape)best;
+}
+
+namespace {
 // Tile edge of the schedule that quantizes its output in the kernel: 256 where the plain call
 // would use it or where 128x128 tiles would outnumber what eight-wave workgroups hold at once.
 int quant_tile_edge(int M, int N) {
@@ -1078,31 +1132,33 @@ int quant_tile_edge(int M, int N) {
 
 }  // namespace
 
-// block: 256 = 256x256 tile, eight waves; 256192 = 256x192 tile, eight waves (4 x 2, wave tile 64 x 96);
-//        192 = 256x128 tile, four waves, two workgroups per CU;
-//        128 = 128x128 tile, eight waves on a deep ring of 128-byte stages (two waves per SIMD); INT8 weights: two K teams.
-hipError_t launch_gemm_tile(const GemmArgs &a, int block, hipStream_t st) {
-    if (block == 256) {
-        if (a.w_bits == 8) return launch_tile_t<256, 256, 2, 4, 128, 2, 8>(a, st);
-        return launch_tile_t<256, 256, 2, 4, 128, 2, 4>(a, st);
+// INT8 weights on 128 x 128 and 128 x 64 tiles: two K teams of 2 x 2 waves (wave tile 64 x 64, 64 x 32); measured 5-8 %
+// ahead of eight waves side by side on 4096x1024x4096 and 2048x2048x8192, level on 2048x2048x2048.  INT4 weights measured
+// 2-3 % slower with teams on 128 x 128 (the nibble unpack already fills the stage boundary) and keep the 2 x 4 layout.
+// On tiles of up to 192 x 128 the nibbles stay packed in LDS (XT = 3): these tiles wait for their operand loads, and half
+// the weight bytes measured 5-14 % faster (2048x2048x2048 13.5 -> 12.8 us, 4096x1024x4096 27.1 -> 23.7 us; 192x128 on
+// 16384x4096 at 333 tokens 32.5 -> 29.5).  On 256 x 128 both ways are level, and on 256 x 256 tiles, which run at the
+// chip's power limit, the register-side unpack measured 5 % slower than unpacking on the way into LDS (4096x16384x4096
+// 233 -> 245 us), so they keep that.
+hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st) {
+    if (a.w_bits == 8) {
+        switch (shape) {
+            case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 5, 8, 0, 0, 0, 2>(a, st);
+            case kTile128x128: return launch_tile_t<128, 128, 2, 2, 128, 4, 8, 0, 0, 0, 2>(a, st);
+            case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 3, 8>(a, st);
+            case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 8>(a, st);
+            case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 8>(a, st);
+            default: return launch_tile_t<256, 256, 2, 4, 128, 2, 8>(a, st);
+        }
     }
-    if (block == 256192) {
-        if (a.w_bits == 8) return launch_tile_t<256, 192, 4, 2, 128, 2, 8>(a, st);
-        return launch_tile_t<256, 192, 4, 2, 128, 2, 4>(a, st);
+    switch (shape) {
+        case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 5, 4, 3>(a, st);
+        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3>(a, st);
+        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 3>(a, st);
+        case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 4>(a, st);
+        case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 4>(a, st);
+        default: return launch_tile_t<256, 256, 2, 4, 128, 2, 4>(a, st);
     }
-    if (block == 192) {
-        if (a.w_bits == 8) return launch_tile_t<256, 128, 2, 2, 64, 3, 8>(a, st);
-        return launch_tile_t<256, 128, 2, 2, 64, 3, 4>(a, st);
-    }
-    // INT8 weights: two K teams of 2 x 2 waves (wave tile 64 x 64); measured 5-8 % ahead of eight waves side by
-    // side on 4096x1024x4096 and 2048x2048x8192, level on 2048x2048x2048.  INT4 weights measured 2-3 % slower with
-    // teams (the nibble unpack already fills the stage boundary) and keep the 2 x 4 layout, with the nibbles
-    // packed in LDS (XT = 3): these tiles wait for their operand loads, and half the weight bytes measured
-    // 5-14 % faster (2048x2048x2048 13.5 -> 12.8 us, 4096x1024x4096 27.1 -> 23.7 us).  On 256 x 256 tiles, which
-    // run at the chip's power limit, the register-side unpack measured 5 % slower than unpacking on the way
-    // into LDS (4096x16384x4096 233 -> 245 us), so they keep that.
-    if (a.w_bits == 8) return launch_tile_t<128, 128, 2, 2, 128, 4, 8, 0, 0, 0, 2>(a, st);
-    return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3>(a, st);
 }
 
 // The 128x128-tile schedule with K split over workgroups and a second kernel for the epilogue: for
@@ -1228,17 +1284,16 @@ hipError_t launch_gemm_a16_tile(const A16Args &a16, hipStream_t st) {
         if (hipError_t e = launch_tile_t<128, 128, 2, 4, 128, 4, 8, 1, 0, 1>(a, st, ks); e != hipSuccess) return e;
         return launch_splitk_finish<1>(a, ks, st);
     }
-    // the tile is chosen like the INT8 call's: rounds of tiles x area x a factor per tile shape
-    const long rows256 = (a.M + 255) / 256;
-    auto rounds = [](long tiles) { return (tiles + 255) / 256; };
-    const long c256 = rounds(rows256 * ((a.N + 255) / 256)) * 65536 * 100;
-    const long c192 = rounds(rows256 * ((a.N + 191) / 192)) * 49152 * 115;
-    const long c128 = rounds((long)((a.M + 127) / 128) * ((a.N + 127) / 128)) * 16384 * 185;
-    if (c128 <= c256 && c128 <= c192) return launch_tile_t<128, 128, 2, 4, 128, 4, 8, 1>(a, st);
-    // the 256x192 tile keeps its weights FP16 in LDS (XT = 2): with three weight fragments per wave the
-    // register-side conversion made the compiler copy the accumulators every stage
-    if (c192 < c256) return launch_tile_t<256, 192, 4, 2, 128, 2, 8, 2>(a, st);
-    return launch_tile_t<256, 256, 2, 4, 128, 2, 8, 1>(a, st);
+    switch (choose_tile(kTileA16, a.M, a.N, a.K, kAllTileShapes, nullptr)) {
+        case kTile128x64: return launch_tile_t<128, 64, 4, 2, 128, 5, 8, 1>(a, st);
+        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 8, 1>(a, st);
+        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 8, 1>(a, st);
+        case kTile256x128: return launch_tile_t<256, 128, 2, 4, 128, 3, 8, 1>(a, st);
+        // the 256x192 tile keeps its weights FP16 in LDS (XT = 2): with three weight fragments per wave the
+        // register-side conversion made the compiler copy the accumulators every stage
+        case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 8, 2>(a, st);
+        default: return launch_tile_t<256, 256, 2, 4, 128, 2, 8, 1>(a, st);
+    }
 }
 
 }  // namespace zq

@@ -69,12 +69,12 @@ hipError_t launch_weight_quant(const void *w, int N, int K, int groups, int bits
 // GeMM schedules.  The order is part of the test/tuning hook of the C ABI.
 enum GemmVariant {
     kGemmSimple = 0,      // direct: operands from global to registers, K divided over the waves of a workgroup; any legal shape
-    kGemmTile128 = 1,     // 128x128 block tile, eight waves
-    kGemmTile256 = 2,     // 256x256 block tile, eight waves
+    kGemmTile128 = 1,     // 128x128 or 128x64 block tile
+    kGemmTile256 = 2,     // 256x256 block tile
     kGemmSkinny = 3,      // M <= 128, K % 256 == 0: weight streaming, whole K in one workgroup
     kGemmSkinnySplitK = 4,// same, K also split across workgroups (needs workspace)
-    kGemmTile256x128 = 5, // 256x128 block tile, four waves, two workgroups per CU
-    kGemmTile256x192 = 6, // 256x192 block tile, eight waves: for grids that 256x256 tiles fill badly
+    kGemmTile256x128 = 5, // 256x128 or 192x128 block tile
+    kGemmTile256x192 = 6, // 256x192 block tile
     kGemmTileSplitK = 7,  // 128x128 block tile, K split over workgroups, epilogue in a second kernel (needs workspace)
     kGemmVariantCount = 8
 };
@@ -96,6 +96,14 @@ struct GemmArgs {
     int8_t *q_out = nullptr;       // launch_gemm_tile_quant: int8 [M,N] codes of the output rows
     float *q_scale_out = nullptr;  //                         fp32 [M] their scales
 };
+
+// Tiles of the tiled schedules (tokens x columns), and which of them a launch takes: the shape with the lowest
+// modelled time among those whose bit is set in `shapes` (see zq_gemm_tile.hip).
+enum TileShape { kTile128x64, kTile128x128, kTile192x128, kTile256x128, kTile256x192, kTile256x256, kTileShapes };
+constexpr unsigned kAllTileShapes = (1u << kTileShapes) - 1u;
+enum TileKind { kTileI8, kTileI4, kTileA16 };
+TileShape choose_tile(TileKind kind, int M, int N, int K, unsigned shapes, double *us);
+hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st);
 
 // 128x128 tiles with a K split: how many splits pay for a shape (1 = none), the workspace they
 // need, and the launch (two kernels).
