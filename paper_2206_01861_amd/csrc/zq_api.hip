@@ -52,7 +52,8 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
     if (workspace == nullptr) workspace_bytes = 0;
 
     int variant = g_forced_variant.load();
-    if (variant >= 0) {
+    const bool forced = variant >= 0;
+    if (forced) {
         if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
     } else {
         variant = zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
@@ -70,6 +71,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         a.q_out = out_q; a.q_scale_out = out_s_tok;
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
+    if (!forced && zq::gemm_goes_direct(M, N, K, w_bits)) variant = zq::kGemmSimple;
     if (zq::launch_gemm(variant, a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
@@ -261,10 +263,10 @@ zq_status zq_gemm_w8a16_dequant(const void *x_fp16, const int8_t *wq, const floa
     hipError_t e;
     const bool tile_split = a16_tiles_with_split(M, N, K) &&
                             workspace_bytes >= zq::gemm_a16_tile_split_workspace(M, N, K);
-    if (tile_split) {
-        e = zq::launch_gemm_a16_tile(a, st);
-    } else if (M <= 64 && ((K % 256) != 0 || zq::direct_pays(M, N, K, 8, 2))) {
+    if ((M <= 64 && (K % 256) != 0) || zq::direct_pays(M, N, K, 8, 2)) {
         e = zq::launch_gemm_a16_direct(a, st);
+    } else if (tile_split) {
+        e = zq::launch_gemm_a16_tile(a, st);
     } else if (M <= kA16StreamTokens && (K % 256) == 0) {
         // Weight streaming holds up to 64 tokens per launch; 65..128 tokens run as two launches over
         // row halves (the weights are read twice, which is still well ahead of the tiled schedule on

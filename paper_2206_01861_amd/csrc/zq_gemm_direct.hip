@@ -7,7 +7,7 @@
 // What bounds these problems is latency: a few megabytes of weights, gone in a
 // few microseconds, of which a launch takes 1.6.  So a workgroup asks for all of
 // its operands at once and waits once.  It owns up to 32 weight rows and 16 to
-// 64 tokens; stage s of K (256 values) belongs to wave s % NW, which loads its
+// 32 tokens; stage s of K (256 values) belongs to wave s % NW, which loads its
 // weights and activations straight into registers and multiplies; the waves add
 // their accumulators through LDS at the end.  There is no producer wave, no
 // barrier before that sum and no exchange between workgroups; the rows are dealt
@@ -36,6 +36,7 @@ namespace {
 
 constexpr uint32_t kRsrcFlags = 0x00020000u;   // raw 32-bit buffer, gfx9 encoding
 constexpr int kStageK = 256;                   // values of K per stage
+constexpr int kMidStageK = 128;                // ... and in gemm_mid_kernel
 constexpr int kCUs = 256;
 [[maybe_unused]] constexpr int kTileInts = 384;  // a 16x16 accumulator tile in LDS: four groups of columns, 96 ints apart
 
@@ -328,6 +329,236 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
 #endif
 }
 
+// The same idea for more tokens: square-ish tiles of up to 64 x 64, still one per workgroup with K dealt to its waves, still
+// no operand in LDS.  Both operands are loaded 64 contiguous bytes per four lanes and turned into operand layout by
+// cross-lane permutations (in operand order the vector cache delivers 38 GB/s per compute unit, a quarter of its rate).
+// What bounds it: the bytes through the vector cache, 115 GB/s per compute unit, and at these sizes still latency: the
+// launch, one or two memory round trips, the sum over the waves.  The tiled schedules move fewer bytes per product but
+// spend 5 us outside their main loop and start to fill the chip only with more tiles.
+// The loads are compiler builtins: the compiler counts them, so it may keep values in accumulation registers.
+// MT, RT: 16-token tiles, 16-row strips; D: stages a wave keeps in flight; NW: waves.
+template <int MT, int RT, int WBITS, int XB, int D, int NW>
+__global__ __launch_bounds__(64 * NW, (MT * RT <= 8) ? 2 : 1) void gemm_mid_kernel(
+    const uint8_t *__restrict__ xq, const float *__restrict__ s_tok, const uint8_t *__restrict__ wq,
+    const float *__restrict__ s_w, int gs, const half_t *__restrict__ bias, int M, int N, int K, int tiles_m,
+    half_t *__restrict__ out, int32_t *__restrict__ acc_out, int act) {
+#if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
+    constexpr int LW = kMidStageK * WBITS / 512;            // 16-byte loads per lane and stage: of a strip ...
+    constexpr int LX = kMidStageK * XB / 64;                // ... and of 16 tokens
+    constexpr int T = RT * MT, TPW = T / NW;                // tiles of the workgroup; those that one wave finishes
+    static_assert(T % NW == 0 && LW >= 1, "");
+    using AccT = typename std::conditional<XB == 2, float32x4, int32x4>::type;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    AccT *part = reinterpret_cast<AccT *>(smem);            // [wave][tile][lane]
+
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int r = lane % 16, j = lane / 16;
+    const int n_base = ((int)blockIdx.x / tiles_m) * 16 * RT;
+    const int m_base = ((int)blockIdx.x % tiles_m) * 16 * MT;
+    const int wrow = (WBITS == 8) ? K : K / 2;
+    const __amdgpu_buffer_rsrc_t rs_w =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(wq), 0, (int)((size_t)N * wrow), kRsrcFlags);
+    const __amdgpu_buffer_rsrc_t rs_x =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(xq), 0, (int)((size_t)M * K * XB), kRsrcFlags);
+    constexpr uint32_t kNowhere = 0x80000000u;              // past the end of either buffer: loads give 0
+    constexpr bool PLAIN = XB == 1 && WBITS == 8;           // (see gemm_direct_kernel for the order of K)
+    constexpr int XJ = PLAIN ? 16 : 32;
+    const int wc = (lane % 4) * 16;
+    uint32_t voff_w[RT], voff_x[MT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        const int n = n_base + 16 * t + lane / 4;
+        voff_w[t] = n < N ? (uint32_t)(n * wrow + wc) : kNowhere;
+    }
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+        const int m = m_base + 16 * t + lane / 4;
+        voff_x[t] = m < M ? (uint32_t)(m * K * XB + (lane % 4) * XJ) : kNowhere;
+    }
+    const int pull = 4 * (4 * r + j);
+
+    // The epilogue's operands first: their round trip runs under the main loop.
+    float e_sc[TPW];
+    half4 e_b[TPW];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+        const int tile = wave * TPW + q;
+        int n = n_base + (tile / MT) * 16 + 4 * j, m = m_base + (tile % MT) * 16 + r;
+        if (n > N - 4) n = N - 4;
+        if (m > M - 1) m = M - 1;
+        e_sc[q] = (XB == 1) ? s_tok[m] * s_w[n / gs] : s_w[n / gs];
+        e_b[q] = half4{0, 0, 0, 0};
+        if (bias != nullptr) e_b[q] = *reinterpret_cast<const half4 *>(bias + n);
+    }
+
+    Stage<RT, MT, LW, LX> st[D];
+    const int stages = (wrow + 64 * LW - 1) / (64 * LW);
+    auto load = [&](__amdgpu_buffer_rsrc_t rs, uint32_t vo, int so) __attribute__((always_inline)) {
+        return __builtin_bit_cast(int32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)vo, so, 0));
+    };
+    auto issue = [&](int i, Stage<RT, MT, LW, LX> &s) __attribute__((always_inline)) {
+        const int b = (wave + i * NW) * (64 * LW);
+        const int lim = wrow - b;
+        const int so_w = lim > 0 ? b : 0;
+        const int so_x = lim > 0 ? b * (8 / WBITS) * XB : 0;
+#pragma unroll
+        for (int t = 0; t < RT; ++t)
+#pragma unroll
+            for (int u = 0; u < LW; ++u) s.w[t][u] = load(rs_w, (wc + 64 * u < lim ? voff_w[t] : kNowhere) + 64 * u, so_w);
+        // as in gemm_direct_kernel: FP16 activations past the end of a row are zeros, INT8 ones meet zero weights
+        const int xl = lim - (XB == 2 ? wc : 0);
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+            for (int u = 0; u < LX; ++u) {
+                constexpr int H = PLAIN ? 1 : 2;            // steps per weight load
+                const int imm = PLAIN ? 64 * u : 128 * (u / 2) + 16 * (u % 2);
+                s.x[t][u] = load(rs_x, (64 * (u / H) < xl ? voff_x[t] : kNowhere) + imm, so_x);
+            }
+    };
+    auto pulled = [&](const int32x4 &v) __attribute__((always_inline)) {
+        int32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = __builtin_amdgcn_ds_bpermute(pull, v[e]);
+        return o;
+    };
+
+    AccT acc[RT][MT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[t][m][e] = 0;
+    auto compute = [&](const Stage<RT, MT, LW, LX> &s) __attribute__((always_inline)) {
+        constexpr int H = PLAIN ? 1 : 2;
+#pragma unroll
+        for (int u = 0; u < LX; ++u) {                      // k step u; H steps share a weight load
+            int32x4 x[MT];
+#pragma unroll
+            for (int m = 0; m < MT; ++m) x[m] = pulled(s.x[m][u]);
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                if constexpr (PLAIN) {
+                    const int32x4 w = pulled(s.w[t][u]);
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, x[m], acc[t][m], 0, 0, 0);
+                } else {
+                    // the eight bytes of this step only: two permutations
+                    const int h = u % H;
+                    const uint32_t p0 = (uint32_t)__builtin_amdgcn_ds_bpermute(pull, s.w[t][u / H][2 * h]);
+                    const uint32_t p1 = (uint32_t)__builtin_amdgcn_ds_bpermute(pull, s.w[t][u / H][2 * h + 1]);
+                    if constexpr (XB == 1) {
+                        uint32_t d0, d1, d2, d3;
+                        unpack8_nat(p0, d0, d1);
+                        unpack8_nat(p1, d2, d3);
+                        const int32x4 a = {(int)d0, (int)d1, (int)d2, (int)d3};
+#pragma unroll
+                        for (int m = 0; m < MT; ++m)
+                            acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, x[m], acc[t][m], 0, 0, 0);
+                    } else {
+                        const half8 a = cvt8_i8_f16(p0, p1);
+#pragma unroll
+                        for (int m = 0; m < MT; ++m)
+                            acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, __builtin_bit_cast(half8, x[m]),
+                                                                               acc[t][m], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    };
+
+    const int n_pad = ((stages + NW - 1) / NW + D - 1) / D * D;
+#pragma unroll
+    for (int d = 0; d < D; ++d) issue(d, st[d]);
+    for (int i = D; i < n_pad; i += D) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            compute(st[d]);
+            issue(i + d, st[d]);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) compute(st[d]);
+
+    // Every wave hands over its accumulators of the tiles that other waves finish, and adds theirs to its own, in the
+    // waves' order (the fp32 sums are the same in every call).
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+            if (XB == 2 || (t * MT + m) / TPW != wave) part[(wave * T + t * MT + m) * kWave + lane] = acc[t][m];
+    __syncthreads();
+    // a token's 16 columns from four consecutive lanes (see the streaming kernel)
+    const int pull_out = 4 * ((lane % 4) * 16 + lane / 4);
+    auto finish = [&](auto w_c) __attribute__((always_inline)) {
+        constexpr int W = decltype(w_c)::value;
+        if constexpr (W < NW) {
+            if (wave != W) return;
+#pragma unroll
+            for (int q = 0; q < TPW; ++q) {
+                constexpr int base = W * TPW;
+                AccT v = acc[(base + q) / MT][(base + q) % MT];
+                if constexpr (XB == 2) v = AccT{0, 0, 0, 0};
+#pragma unroll
+                for (int o = 0; o < NW; ++o)
+                    if (XB == 2 || o != W) v += part[(o * T + base + q) * kWave + lane];
+                if constexpr (WBITS == 4) {                 // exact: every product carried the factor 16
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] >>= 4;
+                }
+                float f[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) f[e] = __builtin_fmaf((float)v[e], e_sc[q], (float)e_b[q][e]);
+                apply_activation_n<4>(f, act);
+                half4 o4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o4[e] = (half_t)f[e];
+                uint2 ob = __builtin_bit_cast(uint2, o4);
+                ob.x = (uint32_t)__builtin_amdgcn_ds_bpermute(pull_out, (int)ob.x);
+                ob.y = (uint32_t)__builtin_amdgcn_ds_bpermute(pull_out, (int)ob.y);
+                const int n0 = n_base + ((base + q) / MT) * 16, m0 = m_base + ((base + q) % MT) * 16;
+                const int ms = m0 + lane / 4, ns = n0 + 4 * (lane % 4);
+                if (ms < M && ns < N) *reinterpret_cast<uint2 *>(out + (size_t)ms * N + ns) = ob;
+                if constexpr (XB == 1) {
+                    const int m = m0 + r, n = n0 + 4 * j;
+                    if (acc_out != nullptr && m < M && n < N)
+                        *reinterpret_cast<int32x4 *>(acc_out + (size_t)m * N + n) = v;
+                }
+            }
+        }
+    };
+    finish(std::integral_constant<int, 0>{});
+    finish(std::integral_constant<int, 1>{});
+    finish(std::integral_constant<int, 2>{});
+    finish(std::integral_constant<int, 3>{});
+    finish(std::integral_constant<int, 4>{});
+    finish(std::integral_constant<int, 5>{});
+    finish(std::integral_constant<int, 6>{});
+    finish(std::integral_constant<int, 7>{});
+#endif
+}
+
+namespace {
+
+template <int MT, int RT, int WBITS, int XB, int D, int NW>
+hipError_t launch_mid_t(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
+                        const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int act, hipStream_t st) {
+    constexpr size_t lds = (size_t)NW * RT * MT * kWave * 16;
+    static std::atomic<uint64_t> configured{0};
+    const void *kernel = reinterpret_cast<const void *>(&gemm_mid_kernel<MT, RT, WBITS, XB, D, NW>);
+    if (hipError_t e = ensure_dynamic_lds(kernel, lds, configured); e != hipSuccess) return e;
+    const int tiles_m = (M + 16 * MT - 1) / (16 * MT), tiles_n = (N + 16 * RT - 1) / (16 * RT);
+    hipLaunchKernelGGL((gemm_mid_kernel<MT, RT, WBITS, XB, D, NW>), dim3(tiles_m * tiles_n), dim3(64 * NW), lds, st,
+                       static_cast<const uint8_t *>(x), s_tok, static_cast<const uint8_t *>(wq), s_w, N / groups,
+                       static_cast<const half_t *>(bias), M, N, K, tiles_m, static_cast<half_t *>(out), acc_out, act);
+    return hipGetLastError();
+}
+
+}  // namespace
+
 namespace {
 
 struct DirectPlan {
@@ -335,28 +566,26 @@ struct DirectPlan {
     int mt;        // 16-token tiles of a workgroup
 };
 
-// Up to 64 tokens (32 of FP16) all of them go to one workgroup and the rows are dealt evenly over a whole number of
+// Up to 32 tokens all of them go to one workgroup and the rows are dealt evenly over a whole number of
 // workgroups per compute unit, 32 rows each at most (2048 rows: 8 each; 6144: 24; 24576: three times 32).  At up to 8
 // tokens INT8 weights go in strips of at most 16 where that leaves them nearly full: twice as many workgroups are in
 // flight and each is done sooner (8192x2048 at one token 5.9 -> 5.4 us, 16384x4096 15.8 -> 13.7), but strips of 10 or 12
 // rows waste a third of every load (6144x6144 at one token 9.4 us in workgroups of 24 rows, 10.1 in strips of 12); half
 // as many bytes per row make it 32 rows for INT4 (16384x4096 at 8 tokens 9.9 us, 11.4 in strips of 16).
-// With more tokens the problem is a tiny one (several workgroups share the weights in L2), and 16 tokens per workgroup
+// With more tokens the problem is a small one (several workgroups share the weights in L2), and 16 tokens per workgroup
 // spread it best: 768x768 at 128 tokens 3.3 us in 192 workgroups of 32 rows, 3.4 in 384 of 16.
 DirectPlan plan_direct(int M, int N, int w_bits, int xb) {
     const int tiles = (M + 15) / 16;
     DirectPlan p;
-    if (tiles <= (xb == 1 ? 4 : 2)) {
+    if (tiles <= 2) {
         auto deal = [&](int most) {
             const int per_cu = (N + most * kCUs - 1) / (most * kCUs);
             const int rows = (N + kCUs * per_cu - 1) / (kCUs * per_cu);
             return rows < 8 ? 8 : (rows + 1) / 2 * 2;
         };
-        p.mt = tiles == 3 ? 4 : tiles;
+        p.mt = tiles;
         p.rows = deal(32);
         if (M <= 8 && w_bits == 8 && p.rows > 16 && deal(16) >= 14) p.rows = deal(16);
-        // four token tiles: the activations are read once per 32 rows (6400x1600 at 64 tokens 7.9 us, 9.4 in strips of 16)
-        if (p.mt == 4) p.rows = 32;
     } else {
         p.mt = xb == 1 ? 1 : 2;
         p.rows = (long)(N / 16) * ((tiles + p.mt - 1) / p.mt) <= kCUs ? 16 : 32;
@@ -401,25 +630,80 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
         if (rt == 1) ZQ_DK(1, 1, 1, 8);
         ZQ_DK(1, 2, 1, 8);
     }
-    if (p.mt == 2) {
-        if (nw == 4) {
-            if (rt == 1) ZQ_DK(2, 1, 1, 4);
-            ZQ_DK(2, 2, 1, 4);
-        }
-        if (rt == 1) ZQ_DK(2, 1, 1, 8);
-        ZQ_DK(2, 2, 1, 8);
+    if (nw == 4) {
+        if (rt == 1) ZQ_DK(2, 1, 1, 4);
+        ZQ_DK(2, 2, 1, 4);
     }
-    if constexpr (XB == 1) {
-        if (nw == 4) ZQ_DK(4, 2, 1, 4);
-        ZQ_DK(4, 2, 1, 8);
-    }
+    if (rt == 1) ZQ_DK(2, 1, 1, 8);
+    ZQ_DK(2, 2, 1, 8);
 #undef ZQ_DK
-    return hipErrorInvalidValue;
+}
+
+// The tile of gemm_mid_kernel for a shape: the one with the lowest modelled time among those whose workgroups all run at
+// once (one per compute unit; two of the 32 x 32 ones).  A second round of them loses to the LDS-tiled kernels.  The
+// model: a start, the rounds of stages that a wave goes through, the bytes a compute unit pulls through its vector cache
+// (in 115 KB, which take a microsecond) and the weights from memory (in 5 MB).  Fitted to 32 shapes (768 to 24576 rows, K
+// 768 to 24576) at 24 to 1024 tokens; it follows the one-round times to 5-8 %.
+enum MidShape { kMid32x32, kMid64x32, kMid64x64, kMidShapes };
+struct MidCost {
+    int bm, bn, waves, depth;
+    double start, stage, cache, memory;
+};
+constexpr MidCost kMidCost[3][kMidShapes] = {
+    {{32, 32, 4, 2, 2.92, 0.374, 0.84, 0.22}, {64, 32, 8, 2, 2.88, 1.298, 0.92, 0.0}, {64, 64, 4, 1, 4.09, 0.875, 0.70, 0.23}},
+    {{32, 32, 4, 2, 3.00, 0.405, 0.04, 0.27}, {64, 32, 8, 2, 3.47, 0.910, 0.58, 0.0}, {64, 64, 8, 1, 4.13, 1.261, 0.64, 0.01}},
+    {{32, 32, 4, 2, 3.23, 0.597, 0.61, 0.26}, {64, 32, 8, 2, 1.06, 3.392, 0.30, 0.0}, {64, 64, 8, 1, 4.03, 2.807, 0.57, 0.0}},
+};
+
+MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
+    int best = kMidShapes;
+    double best_us = 1e30;
+    for (int i = 0; i < kMidShapes; ++i) {
+        const MidCost &c = kMidCost[xb == 2 ? kTileA16 : w_bits == 8 ? kTileI8 : kTileI4][i];
+        const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        if (tiles > (i == kMid32x32 ? 2 : 1) * kCUs) continue;
+        const int per_wave = (K + kMidStageK * c.waves - 1) / (kMidStageK * c.waves);
+        const int stages = (per_wave + c.depth - 1) / c.depth * c.depth * (tiles > kCUs ? 2 : 1);
+        const double per_cu = (double)tiles / kCUs * K * (c.bm * xb + c.bn * w_bits / 8.0);
+        const double t = c.start + stages * c.stage + c.cache * per_cu / 115e3 + c.memory * N * K * (w_bits / 8.0) / 5e6;
+        if (t < best_us) {
+            best_us = t;
+            best = i;
+        }
+    }
+    if (us != nullptr) *us = best_us;
+    return (MidShape)best;
+}
+
+template <int WBITS, int XB>
+hipError_t launch_mid(MidShape shape, const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
+                      const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int act, hipStream_t st) {
+#define ZQ_MK(MT, RT, D, NW) \
+    return launch_mid_t<MT, RT, WBITS, XB, D, NW>(x, s_tok, wq, s_w, groups, bias, M, N, K, out, acc_out, act, st)
+    if (shape == kMid32x32) ZQ_MK(2, 2, 2, 4);
+    if (shape == kMid64x32) ZQ_MK(4, 2, 2, 8);
+    // Eight waves on 64 x 64 where a stage is half or twice the bytes of an INT8 one (INT4: 2560x10240 at 256 tokens 21.1
+    // us, 26.6 with four; W8A16: 6144x2048 at 128 tokens 10.5, 13.5), four for INT8 (1600x6400 at 450 18.8, 21.0)
+    if constexpr (WBITS == 8 && XB == 1)
+        ZQ_MK(4, 4, 1, 4);
+    else
+        ZQ_MK(4, 4, 1, 8);
+#undef ZQ_MK
+}
+
+// More than 64 tokens, but so few rows that workgroups of 16 x 32 fill the chip once: the first kernel, whose waves take
+// eight ways of K, is still the quickest (1024x4096 at 128 tokens 6.3 us, 6.7 on 32 x 32 tiles; 3072x768 at 128 tokens,
+// three workgroups per compute unit: 5.35, 5.16), until the activations that each of them reads grow too long
+// (1600x6400 at 80 tokens 10.6, 9.5).
+bool short_problem(int M, int N, int K, int xb) {
+    return xb == 1 && M > 64 && K <= 4096 && (long)((M + 15) / 16) * ((N + 31) / 32) <= kCUs;
 }
 
 }  // namespace
 
-// Whether the direct kernel beats the streaming kernels for a shape that both take (K a multiple of 256).  Its
+// Whether the kernels of this file beat the streaming and the tiled ones.
+//
+// Up to 32 tokens: the direct kernel against streaming (K a multiple of 256).  Its
 // workgroups read M x K activation bytes each, from L2, which stays hidden behind the weights only up to some 130 to
 // 270 KB per compute unit; the streaming kernel shares one activation tile among up to 128 rows.  On the other side the
 // streaming kernel leaves compute units idle on matrices of few rows, or pays for an exchange between workgroups where it
@@ -432,8 +716,32 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
 //          4096x2048 at 24 5.5 / 5.0; beyond: 4096x4096 at 16 5.9 / 6.4, 12288x4096 at 8 12.1 / 12.9, 24576x6144 at 64
 //          31.8 / 47.5.  Where the stages do not fill the waves (ten stages on eight), the second round is mostly empty:
 //          10240x2560 at 1 8.0 / 9.0.
+//
+// More tokens, as long as one round of small tiles covers the output (choose_mid): streaming was built for a weight
+// stream that 128 tokens no longer are, and the LDS tiles leave most compute units idle or split K through memory.  The
+// small tiles lose where K is so long that their traffic per product, two to four times that of a 128 x 128 tile, is the
+// time, and, up to 64 tokens, where the matrix is large enough to keep the streaming kernel busy.  Microseconds,
+// what ran before / small tiles:
+//   INT8   2048x2048 at 64 tokens 6.5 / 4.9, at 128 10.7 / 5.7, at 256 9.2 / 6.6; 768x3072 at 128 12.8 / 5.9; 1600x6400
+//          at 128 14.3 / 10.0; 4096x4096 at 192 17.4 / 14.4; beyond: 7680x2560 at 64 9.5 / 11.4, 2048x8192 at 64 10.5 /
+//          12.2, 2560x10240 at 128 18.8 / 24.8, 2048x2048 at 512 (K tiles as good) 9.3 / 9.9
+//   INT4   2048x2048 at 128 10.7 / 5.3, 1024x4096 at 1024 18.4 / 10.7, 16384x4096 at 64 15.9 / 11.5, 6144x6144 at 64
+//          19.3 / 11.8, 2560x10240 at 256 26.6 / 21.1; beyond: 4096x16384 at 128 21.6 / 23.6
+//   W8A16  6144x2048 at 64 10.6 / 8.6, at 128 18.7 / 10.5; 4800x1600 at 192 17.4 / 10.8; beyond: 7680x2560 at 64 12.6 /
+//          17.8, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
-    if (M > 32) return false;
+    if (M > 32) {
+        double us, tile_us;
+        if (short_problem(M, N, K, xb)) return true;
+        const MidShape shape = choose_mid(M, N, K, w_bits, xb, &us);
+        if (shape == kMidShapes) return false;
+        const bool int8 = w_bits == 8 && xb == 1;
+        if (K > (xb == 2 ? 4096 : w_bits == 4 ? 12288 : shape == kMid64x64 ? 5120 : M <= 64 || shape == kMid64x32 ? 6656 : 8192))
+            return false;
+        if (M <= 64) return w_bits == 4 || (K % 256) != 0 || ((long)N * K <= (1L << 24) && (int8 || K <= 3072));
+        choose_tile(xb == 2 ? kTileA16 : int8 ? kTileI8 : kTileI4, M, N, K, kAllTileShapes, &tile_us);
+        return us < (int8 ? 0.94 : 1.0) * tile_us;
+    }
     const long load = (long)M * K * xb * ((N + 32 * kCUs - 1) / (32 * kCUs));
     const bool one_round = N <= 32 * kCUs;
     if (xb == 2) return load <= (one_round ? 131072 : 65536);
@@ -447,15 +755,26 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     return K <= 2048 && N <= 4096;
 }
 
+namespace {
+template <int WBITS, int XB>
+hipError_t launch_small(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
+                        const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int act, hipStream_t st) {
+    const MidShape shape =
+        M <= 32 || short_problem(M, N, K, XB) ? kMidShapes : choose_mid(M, N, K, WBITS, XB, nullptr);
+    if (shape != kMidShapes)
+        return launch_mid<WBITS, XB>(shape, x, s_tok, wq, s_w, groups, bias, M, N, K, out, acc_out, act, st);
+    return launch_direct<WBITS, XB>(x, s_tok, wq, s_w, groups, bias, M, N, K, out, acc_out, act, st);
+}
+}  // namespace
+
 hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st) {
     if (a.w_bits == 8)
-        return launch_direct<8, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out,
-                                   a.act, st);
-    return launch_direct<4, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out, a.act, st);
+        return launch_small<8, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out, a.act, st);
+    return launch_small<4, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out, a.act, st);
 }
 
 hipError_t launch_gemm_a16_direct(const A16Args &a, hipStream_t st) {
-    return launch_direct<8, 2>(a.x, nullptr, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, nullptr, 0, st);
+    return launch_small<8, 2>(a.x, nullptr, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, nullptr, 0, st);
 }
 
 }  // namespace zq

@@ -47,6 +47,11 @@ bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_
     return true;
 }
 
+bool gemm_goes_direct(int M, int N, int K, int w_bits) {
+    TuneEntry e;
+    return direct_pays(M, N, K, w_bits, 1) && !tune_lookup(M, N, K, w_bits, &e);
+}
+
 size_t gemm_variant_workspace(int variant, int M, int N, int K, int w_bits) {
     if (variant == kGemmTileSplitK) return gemm_tile_split_workspace(M, N, K);
     if (variant != kGemmSkinnySplitK || M > kStreamMaxTokens || (K % 256) != 0) return 0;
@@ -120,6 +125,8 @@ extern "C" int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t wo
     if (tune_lookup(M, N, K, w_bits, &tuned) &&
         gemm_variant_supports(tuned.variant, M, N, K, w_bits, workspace_bytes))
         return tuned.variant;
+    // These are the classes of schedules that a workspace is sized for and a table entry can name; the calls themselves
+    // take the small-tile kernels instead wherever those are ahead (gemm_goes_direct).
     // Up to 64 tokens every shape is bound by the weight stream; up to 128 tokens the streaming
     // schedules still win once K is long enough that the activation tile is a small part of the traffic.
     if (M <= 64 || (M <= kStreamMaxTokens && K >= 2048 && (K % 256) == 0)) {
@@ -130,9 +137,8 @@ extern "C" int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t wo
             return kGemmSkinnySplitK;
         if (gemm_variant_supports(kGemmSkinny, M, N, K, w_bits, 0)) return kGemmSkinny;
     }
-    // Up to 64 tokens and K not a multiple of 256: the direct kernel, which takes any K (6400x1600 at 27 tokens
-    // 6.0 us, 12.2 on 128x128 tiles), except where many tokens meet so many rows that its activation traffic
-    // costs more than the tiles' empty half (16416x5472 at 64 tokens: 45 us, 38 on tiles; 12672x3168: 22.6, 24.8).
+    // Up to 64 tokens and K not a multiple of 256: the direct kernels, which take any K (6400x1600 at 27 tokens
+    // 6.0 us, 12.2 on 128x128 tiles), except where many tokens meet more rows than 64 x 64 tiles cover in one round.
     if (M <= 32 || (M <= 64 && N <= 16384)) return kGemmSimple;
     // Tiny problems (a BERT-base layer at 128 tokens) are all latency: the direct kernel starts and finishes
     // sooner than a handful of LDS-tiled workgroups (768x768 at 128 tokens 3.3 us, 6.8 on tiles).

@@ -44,8 +44,6 @@
 
 namespace zq {
 
-hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st);
-
 namespace {
 
 constexpr uint32_t kRsrcFlags = 0x00020000u;   // raw 32-bit buffer, gfx9 encoding
@@ -893,9 +891,6 @@ hipError_t launch_gemm_a16_stream(const A16Args &a, bool allow_split, hipStream_
 }
 
 hipError_t launch_gemm_skinny(const GemmArgs &a, bool allow_split, hipStream_t st) {
-    int rb = 0, ks = 0;
-    if (direct_pays(a.M, a.N, a.K, a.w_bits, 1) && !tuned_stream_plan(a.M, a.N, a.K, a.w_bits, &rb, &ks))
-        return launch_gemm_direct(a, st);
     const StreamPlan plan = plan_stream(a.M, a.N, a.K, a.w_bits, allow_split);
     const int mt = token_tiles(a.M);
 #define ZQ_SK(MT, WB) return launch_stream_t<MT, WB>(a, plan, st)

@@ -116,8 +116,10 @@ hipError_t launch_gemm_tile_splitk(const GemmArgs &a, hipStream_t st);
 bool gemm_tile_quant_supported(int M, int N, size_t workspace_bytes);
 hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st);
 
-// Whether the direct kernel beats the streaming kernels (few tokens, K % 256 == 0); xb: bytes of an activation.
+// Whether the small-tile kernels of zq_gemm_direct.hip beat the streaming and the tiled ones; xb: bytes of an activation.
+// gemm_goes_direct: the same for INT8 activations, unless a schedule is registered for the shape.
 bool direct_pays(int M, int N, int K, int w_bits, int xb);
+bool gemm_goes_direct(int M, int N, int K, int w_bits);
 
 // A caller-supplied cut of the streaming schedules for this shape, if one was registered.
 bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_splits);
