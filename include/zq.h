@@ -310,7 +310,8 @@ int zq_debug_force_gemm_variant(int variant);
  * inside the GeMM kernel (see zq_gemm_gelu_quant_tokenwise), else 0.
  *
  * zq_debug_set_in_kernel_quant: test and ablation hook; on = 0 makes every
- * call use the second kernel.  Process-wide; returns the previous value.
+ * call use the second kernel, and no workgroup of the weight quantizer wait
+ * for another.  Process-wide; returns the previous value.
  *
  * zq_quant_wait_expired: *count_out receives the number of threads (one per
  * tile and token row) whose bounded wait ran out in calls on this workspace

@@ -109,7 +109,7 @@ zq_status zq_quantize_weight_groupwise(const void *w_fp16, int N, int K, int gro
     if ((N % groups) != 0 || ((N / groups) % 16) != 0) return ZQ_ERR_SHAPE;
     if ((K % (bits == 4 ? 32 : 16)) != 0) return ZQ_ERR_SHAPE;
     if (misaligned(w_fp16) || misaligned(wq_out) || misaligned(s_w_out)) return ZQ_ERR_ALIGN;
-    hipError_t e = zq::launch_weight_quant(w_fp16, N, K, groups, bits, wq_out, s_w_out,
+    hipError_t e = zq::launch_weight_quant(w_fp16, N, K, groups, bits, g_in_kernel_quant.load() != 0, wq_out, s_w_out,
                                            reinterpret_cast<hipStream_t>(stream));
     return e == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
 }

@@ -63,7 +63,9 @@ hipError_t launch_rowquant(RowOp op, const void *in, const void *p0, const void 
 hipError_t launch_dequant(const int32_t *acc, const float *s_tok, const float *s_w, int groups, const void *bias, int M,
                           int N, void *out, hipStream_t st);
 
-hipError_t launch_weight_quant(const void *w, int N, int K, int groups, int bits, void *wq, float *s_w,
+// wait: workgroups of a group may wait for each other; without it each one that is not the last to arrive reads its
+// whole group.
+hipError_t launch_weight_quant(const void *w, int N, int K, int groups, int bits, bool wait, void *wq, float *s_w,
                                hipStream_t st);
 
 // GeMM schedules.  The order is part of the test/tuning hook of the C ABI.

@@ -9,7 +9,11 @@
 #include "zq_device.h"
 #include "zq_internal.h"
 
+#include <limits.h>
+
 namespace zq {
+
+int compute_units();                                    // of the current device
 
 // ---------------------------------------------------------------------------
 // Row front-ends.  A row is handled by TPR threads (one wave, or the whole
@@ -271,54 +275,196 @@ hipError_t launch_dequant(const int32_t *acc, const float *s_tok, const float *s
 
 // ---------------------------------------------------------------------------
 // Group-wise weight quantization.  A group is a contiguous chunk of gs*K fp16
-// values.  Four launches: clear, absmax (integer atomic max on the fp32 bit
-// pattern, exact and order independent), quantize, and turn absmax into the
-// scale in place.  s_w doubles as the absmax scratch, so nothing is allocated.
+// values.
+//
+// Groups of up to 16 MB: wq_group_kernel, one pass over the weights.  A group
+// is cut into slices of at most 64 KB, one workgroup each, which keeps its
+// slice in registers while the workgroups of the group agree on their maximum.
+// Bound: HBM, 2 + bits/8 bytes per weight.  Up to five workgroups on a compute
+// unit keep 80 MB in flight on the chip, so that loads of later groups cover
+// the exchange of earlier ones.  Reading the weights twice (absmax, then
+// codes) against this, weights from HBM, per call: INT8 12288x4096 57 -> 34 us
+// (4.4 TB/s), 24576x6144 157 -> 98, 4096x4096 34 -> 17; INT4 16384x4096 63 -> 41,
+// 8192x2048 32 -> 16; 512 threads or 48 KB slices measured level or behind.
+//
+// The exchange is one 32-bit word per group: the maximum (15 bits, the pattern
+// of |fp16|) above the count of slices that arrived and the count of those
+// that have read the maximum (8 bits each, hence at most 255 slices).  A slice
+// either raises the maximum and counts itself in one compare-and-swap or, if
+// it raises nothing, in one addition.  The word stands in the first 128-byte
+// line of the group's codes: nothing is allocated, and the words of different
+// groups lie far apart (side by side in s_w they shared a memory channel, and
+// 12288x4096 took 146 us).  Nobody stores that line's codes except the slice
+// that reads the maximum last, which makes them from the weights once more.
+// All accesses to the words are agent-scope atomics, and no other memory is
+// exchanged.  A slice's wait ends because the workgroups of a group have
+// consecutive ids, are started in order of their ids and fit the chip several
+// times over; should it last longer than the polls it is given, the workgroup
+// reads the whole group for the maximum itself, so that the result never
+// depends on it.
+//
+// Larger groups: clear, absmax (integer atomic max on the fp32 bit pattern,
+// exact and order independent), quantize, and turn absmax into the scale in
+// place; the weights are read twice.  s_w is the scratch here.
 // ---------------------------------------------------------------------------
+
+constexpr int kWqThreads = 256;
+constexpr int kWqVecs = 16;                             // 16-byte vectors of a slice per thread
+constexpr int kWqMaxSlices = 255;                       // eight bits of the exchange word
+constexpr int kWqPolls = 1 << 16;                       // some 90 ms
+constexpr int kWqSleep = 12;                            // 768 cycles between polls (4: more traffic, 32: later, both 3 % behind)
+constexpr int kWqLine = 128;
+// Where the line of a group's exchange word begins in its codes.
+__device__ __forceinline__ int wq_line_offset(const void *codes) {
+    return (int)(-reinterpret_cast<uintptr_t>(codes) & (kWqLine - 1));
+}
+
+__global__ void wq_clear_line_kernel(uint8_t *wq, long group_bytes, int groups) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= groups) return;
+    uint8_t *codes = wq + i * group_bytes;
+    *reinterpret_cast<uint32_t *>(codes + wq_line_offset(codes)) = 0u;
+}
+
+// The largest |fp16| pattern of a vector, merged into the two halves of m.
+typedef uint16_t ushort2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ ushort2_t absmax_pattern(ushort2_t m, uint32x4_t v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        m = __builtin_elementwise_max(m, __builtin_bit_cast(ushort2_t, v[e] & 0x7fff7fffu));
+    return m;
+}
+// ... of the workgroup, in every thread.
+__device__ __forceinline__ uint32_t block_max_pattern(ushort2_t m, uint32_t *lds) {
+    const uint32_t w = wave_max_u32(m[0] > m[1] ? m[0] : m[1]);
+    __syncthreads();
+    if ((threadIdx.x % kWave) == 0) lds[threadIdx.x / kWave] = w;
+    __syncthreads();
+    uint32_t r = 0;
+#pragma unroll
+    for (int i = 0; i < kWqThreads / kWave; ++i) r = lds[i] > r ? lds[i] : r;
+    return r;
+}
+__device__ __forceinline__ float pattern_to_float(uint32_t p) { return (float)__builtin_bit_cast(half_t, (uint16_t)p); }
+
+template <int BITS>
+__device__ __forceinline__ void store_codes(void *wq, long i, uint32x4_t v, float inv) {
+    const half8 h = __builtin_bit_cast(half8, v);
+    uint32_t q[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = quant_code_bits((float)h[e], inv);
+    if (BITS == 8) {
+        reinterpret_cast<uint2 *>(wq)[i] =
+            make_uint2(pack4_code_bits(q[0], q[1], q[2], q[3]), pack4_code_bits(q[4], q[5], q[6], q[7]));
+    } else {
+        uint32_t p = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p |= (q[e] & 0xfu) << (4 * e);   // even k in the low nibble
+        reinterpret_cast<uint32_t *>(wq)[i] = p;
+    }
+}
+
+template <int BITS, int VPT>
+__global__ __launch_bounds__(kWqThreads) void wq_group_kernel(const uint32x4_t *__restrict__ w, long chunk_vecs,
+                                                              int slices, int slice_vecs, int polls,
+                                                              void *wq, float *__restrict__ s_w) {
+    __shared__ uint32_t lds[kWqThreads / kWave], lds_max;
+    const int g = blockIdx.x / slices;
+    const long first = (long)(blockIdx.x % slices) * slice_vecs;
+    const int n = (int)(chunk_vecs - first < slice_vecs ? chunk_vecs - first : slice_vecs);   // at least 1
+    const long base = g * chunk_vecs + first;
+
+    // Vectors past the end of the slice read its first one again, so that no branch separates the loads.  Streaming
+    // loads: no later access finds the weights in a cache (24576x6144 109 -> 98 us).
+    uint32x4_t raw[VPT];
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        const int idx = i * kWqThreads + (int)threadIdx.x;
+        raw[i] = __builtin_nontemporal_load(w + base + (idx < n ? idx : 0));
+    }
+    ushort2_t mv = {0, 0};
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) mv = absmax_pattern(mv, raw[i]);
+    uint32_t m = block_max_pattern(mv, lds);
+
+    const float qmax = (BITS == 8) ? 127.0f : 7.0f;
+    constexpr int CB = BITS;                                // bytes of eight codes
+    uint8_t *codes = static_cast<uint8_t *>(wq) + g * chunk_vecs * CB;
+    const int line = wq_line_offset(codes);
+    uint32_t *word = reinterpret_cast<uint32_t *>(codes + line);
+    int skip = INT_MAX;                                     // the first of the vectors whose codes the line will hold
+    if (slices > 1) {
+        constexpr uint32_t kExpired = ~0u;
+        if (first == 0) skip = line / CB;
+        if (threadIdx.x == 0) {
+            uint32_t cur = 0;
+            for (;;) {                                      // a failed swap means that another slice arrived
+                const uint32_t want = (m << 16) | ((cur & 0xffffu) + 0x100u);
+                if (__hip_atomic_compare_exchange_strong(word, &cur, want, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)) {
+                    cur = want;
+                    break;
+                }
+                if ((cur >> 16) >= m) {
+                    cur = __hip_atomic_fetch_add(word, 0x100u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 0x100u;
+                    break;
+                }
+            }
+            while (((cur >> 8) & 0xffu) != (uint32_t)slices && polls-- > 0) {
+                __builtin_amdgcn_s_sleep(kWqSleep);
+                cur = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            lds_max = ((cur >> 8) & 0xffu) == (uint32_t)slices ? cur >> 16 : kExpired;
+        }
+        __syncthreads();
+        m = lds_max;
+        if (m == kExpired) {
+            ushort2_t all = {0, 0};
+            for (long i = threadIdx.x; i < chunk_vecs; i += kWqThreads) all = absmax_pattern(all, w[g * chunk_vecs + i]);
+            m = block_max_pattern(all, lds);
+        }
+    }
+    float scale, inv;
+    quant_scales(pattern_to_float(m), qmax, scale, inv);
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        const int idx = i * kWqThreads + (int)threadIdx.x;
+        if (idx < n && (unsigned)(idx - skip) >= (unsigned)(kWqLine / CB)) store_codes<BITS>(wq, base + idx, raw[i], inv);
+    }
+    if (threadIdx.x >= kWave) return;
+    uint32_t read = (uint32_t)slices - 1u;                  // slices that have read the maximum before this one
+    if (slices > 1 && threadIdx.x == 0)
+        read = __hip_atomic_fetch_add(word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffu;
+    if (__builtin_amdgcn_readfirstlane(read) != (uint32_t)slices - 1u) return;
+    if (threadIdx.x == 0) s_w[g] = scale;
+    if (slices > 1 && threadIdx.x < kWqLine / CB) {
+        const long i = g * chunk_vecs + line / CB + threadIdx.x;
+        store_codes<BITS>(wq, i, w[i], inv);
+    }
+}
 
 __global__ void wq_clear_kernel(uint32_t *amax_bits, int groups) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < groups) amax_bits[i] = 0u;
 }
 
-__global__ __launch_bounds__(256) void wq_absmax_kernel(const uint4 *__restrict__ w, long chunk_vecs, long slice_vecs,
-                                                        uint32_t *__restrict__ amax_bits) {
-    __shared__ uint32_t lds[4];
+__global__ __launch_bounds__(kWqThreads) void wq_absmax_kernel(const uint32x4_t *__restrict__ w, long chunk_vecs,
+                                                               long slice_vecs, uint32_t *__restrict__ amax_bits) {
+    __shared__ uint32_t lds[kWqThreads / kWave];
     const int g = blockIdx.y;
     const long lo = (long)blockIdx.x * slice_vecs;
     long hi = lo + slice_vecs;
     if (hi > chunk_vecs) hi = chunk_vecs;
-    const uint4 *base = w + (long)g * chunk_vecs;
-    // |fp16| compares like its 15-bit pattern; keep the maximum pattern.
-    uint32_t m = 0;
-    for (long i = lo + threadIdx.x; i < hi; i += 256) {
-        uint4 u = base[i];
-        uint32_t d[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            uint32_t a0 = d[e] & 0x7fffu, a1 = (d[e] >> 16) & 0x7fffu;
-            m = a0 > m ? a0 : m;
-            m = a1 > m ? a1 : m;
-        }
-    }
-    m = wave_max_u32(m);
-    if ((threadIdx.x % kWave) == 0) lds[threadIdx.x / kWave] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t r = lds[0];
-        r = lds[1] > r ? lds[1] : r;
-        r = lds[2] > r ? lds[2] : r;
-        r = lds[3] > r ? lds[3] : r;
-        union { uint16_t u; half_t h; } cv;
-        cv.u = (uint16_t)r;
-        const float a = (float)cv.h;
-        atomicMax(amax_bits + g, __float_as_uint(a));   // non-negative floats order like their bits
-    }
+    ushort2_t m = {0, 0};
+    for (long i = lo + threadIdx.x; i < hi; i += kWqThreads) m = absmax_pattern(m, w[g * chunk_vecs + i]);
+    const uint32_t r = block_max_pattern(m, lds);
+    if (threadIdx.x == 0) atomicMax(amax_bits + g, __float_as_uint(pattern_to_float(r)));   // non-negative floats order like their bits
 }
 
 template <int BITS>
-__global__ __launch_bounds__(256) void wq_quant_kernel(const half8 *__restrict__ w, long chunk_vecs, long slice_vecs,
-                                                       const float *__restrict__ amax, void *__restrict__ wq) {
+__global__ __launch_bounds__(kWqThreads) void wq_quant_kernel(const uint32x4_t *__restrict__ w, long chunk_vecs,
+                                                              long slice_vecs, const float *__restrict__ amax,
+                                                              void *__restrict__ wq) {
     const int g = blockIdx.y;
     const long lo = (long)blockIdx.x * slice_vecs;
     long hi = lo + slice_vecs;
@@ -327,21 +473,7 @@ __global__ __launch_bounds__(256) void wq_quant_kernel(const half8 *__restrict__
     float scale, inv;
     quant_scales(amax[g], qmax, scale, inv);
     const long gbase = (long)g * chunk_vecs;
-    for (long i = lo + threadIdx.x; i < hi; i += 256) {
-        half8 h = w[gbase + i];
-        uint32_t q[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) q[e] = quant_code_bits((float)h[e], inv);
-        if (BITS == 8) {
-            reinterpret_cast<uint2 *>(wq)[gbase + i] =
-                make_uint2(pack4_code_bits(q[0], q[1], q[2], q[3]), pack4_code_bits(q[4], q[5], q[6], q[7]));
-        } else {
-            uint32_t p = 0;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) p |= (q[e] & 0xfu) << (4 * e);   // even k in the low nibble
-            reinterpret_cast<uint32_t *>(wq)[gbase + i] = p;
-        }
-    }
+    for (long i = lo + threadIdx.x; i < hi; i += kWqThreads) store_codes<BITS>(wq, gbase + i, w[gbase + i], inv);
 }
 
 __global__ void wq_finalize_kernel(float *s_w, int groups, float qmax) {
@@ -353,28 +485,52 @@ __global__ void wq_finalize_kernel(float *s_w, int groups, float qmax) {
     }
 }
 
-hipError_t launch_weight_quant(const void *w, int N, int K, int groups, int bits, void *wq, float *s_w,
-                               hipStream_t st) {
+template <int BITS, int VPT>
+static hipError_t launch_wq_group(const void *w, long chunk_vecs, int groups, int polls, void *wq, float *s_w,
+                                  hipStream_t st) {
+    const int most = kWqThreads * VPT;
+    const int p = (int)((chunk_vecs + most - 1) / most);
+    const int slice_vecs = (int)((chunk_vecs + p - 1) / p);
+    const int slices = (int)((chunk_vecs + slice_vecs - 1) / slice_vecs);       // every slice holds a vector
+    if (slices > 1)
+        hipLaunchKernelGGL(wq_clear_line_kernel, dim3((groups + 255) / 256), dim3(256), 0, st, static_cast<uint8_t *>(wq),
+                           chunk_vecs * BITS, groups);
+    hipLaunchKernelGGL((wq_group_kernel<BITS, VPT>), dim3((unsigned)(groups * slices)), dim3(kWqThreads), 0, st,
+                       reinterpret_cast<const uint32x4_t *>(w), chunk_vecs, slices, slice_vecs, polls, wq, s_w);
+    return hipGetLastError();
+}
+
+template <int BITS>
+static hipError_t launch_wq(const void *w, int N, int K, int groups, bool wait, void *wq, float *s_w, hipStream_t st) {
     const long chunk_vecs = (long)(N / groups) * K / 8;
+    // the slices of a group have to run at once: each needs a fifth of a compute unit's registers, so one per compute
+    // unit always fits
+    const int cus = compute_units();
+    if (chunk_vecs <= (long)kWqThreads * kWqVecs * (cus < kWqMaxSlices ? cus : kWqMaxSlices)) {
+        const int polls = wait ? kWqPolls : 0;
+        if (chunk_vecs <= kWqThreads * 4) return launch_wq_group<BITS, 4>(w, chunk_vecs, groups, polls, wq, s_w, st);
+        if (chunk_vecs <= kWqThreads * 8) return launch_wq_group<BITS, 8>(w, chunk_vecs, groups, polls, wq, s_w, st);
+        return launch_wq_group<BITS, kWqVecs>(w, chunk_vecs, groups, polls, wq, s_w, st);
+    }
     // enough slices per group to put a few thousand workgroups in flight
     long P = (4096 + groups - 1) / groups;
     const long max_p = (chunk_vecs + 255) / 256;
     if (P > max_p) P = max_p;
-    if (P < 1) P = 1;
     const long slice_vecs = (chunk_vecs + P - 1) / P;
     const dim3 grid((unsigned)P, (unsigned)groups);
     const int cb = (groups + 255) / 256;
+    const uint32x4_t *wv = reinterpret_cast<const uint32x4_t *>(w);
     hipLaunchKernelGGL(wq_clear_kernel, dim3(cb), dim3(256), 0, st, reinterpret_cast<uint32_t *>(s_w), groups);
-    hipLaunchKernelGGL(wq_absmax_kernel, grid, dim3(256), 0, st, reinterpret_cast<const uint4 *>(w), chunk_vecs,
-                       slice_vecs, reinterpret_cast<uint32_t *>(s_w));
-    if (bits == 8)
-        hipLaunchKernelGGL(wq_quant_kernel<8>, grid, dim3(256), 0, st, reinterpret_cast<const half8 *>(w), chunk_vecs,
-                           slice_vecs, s_w, wq);
-    else
-        hipLaunchKernelGGL(wq_quant_kernel<4>, grid, dim3(256), 0, st, reinterpret_cast<const half8 *>(w), chunk_vecs,
-                           slice_vecs, s_w, wq);
-    hipLaunchKernelGGL(wq_finalize_kernel, dim3(cb), dim3(256), 0, st, s_w, groups, bits == 8 ? 127.0f : 7.0f);
+    hipLaunchKernelGGL(wq_absmax_kernel, grid, dim3(kWqThreads), 0, st, wv, chunk_vecs, slice_vecs,
+                       reinterpret_cast<uint32_t *>(s_w));
+    hipLaunchKernelGGL(wq_quant_kernel<BITS>, grid, dim3(kWqThreads), 0, st, wv, chunk_vecs, slice_vecs, s_w, wq);
+    hipLaunchKernelGGL(wq_finalize_kernel, dim3(cb), dim3(256), 0, st, s_w, groups, BITS == 8 ? 127.0f : 7.0f);
     return hipGetLastError();
+}
+
+hipError_t launch_weight_quant(const void *w, int N, int K, int groups, int bits, bool wait, void *wq, float *s_w,
+                               hipStream_t st) {
+    return bits == 8 ? launch_wq<8>(w, N, K, groups, wait, wq, s_w, st) : launch_wq<4>(w, N, K, groups, wait, wq, s_w, st);
 }
 
 }  // namespace zq
