@@ -100,9 +100,9 @@ __device__ __forceinline__ void stage_wait(Stage<RT, MT, LW, LX> &s) {
 // wave keeps in flight, NW: waves.  rows: weight rows of a workgroup, even, at most 16 * RT.
 template <int MT, int RT, int WBITS, int XB, int D, int NW>
 __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void gemm_direct_kernel(
-    const uint8_t *__restrict__ xq, const float *__restrict__ s_tok, const uint8_t *__restrict__ wq,
-    const float *__restrict__ s_w, int gs, const half_t *__restrict__ bias, int M, int N, int K, int rows,
-    half_t *__restrict__ out, int32_t *__restrict__ acc_out, int act) {
+    const uint8_t *__restrict__ xq, const uint8_t *__restrict__ wq, int M, int N, int K, int rows, int gs, int act,
+    const float *__restrict__ s_tok, const float *__restrict__ s_w, const half_t *__restrict__ bias,
+    half_t *__restrict__ out, int32_t *__restrict__ acc_out) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     static_assert(XB == 1 || WBITS == 8, "FP16 activations go with INT8 weights");
     static_assert(D <= 2, "the drain is written out for two stages");
@@ -339,9 +339,9 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
 // MT, RT: 16-token tiles, 16-row strips; D: stages a wave keeps in flight; NW: waves.
 template <int MT, int RT, int WBITS, int XB, int D, int NW>
 __global__ __launch_bounds__(64 * NW, (MT * RT <= 8) ? 2 : 1) void gemm_mid_kernel(
-    const uint8_t *__restrict__ xq, const float *__restrict__ s_tok, const uint8_t *__restrict__ wq,
-    const float *__restrict__ s_w, int gs, const half_t *__restrict__ bias, int M, int N, int K, int tiles_m,
-    half_t *__restrict__ out, int32_t *__restrict__ acc_out, int act) {
+    const uint8_t *__restrict__ xq, const uint8_t *__restrict__ wq, int M, int N, int K, int tiles_m, int gs, int act,
+    const float *__restrict__ s_tok, const float *__restrict__ s_w, const half_t *__restrict__ bias,
+    half_t *__restrict__ out, int32_t *__restrict__ acc_out) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     constexpr int LW = kMidStageK * WBITS / 512;            // 16-byte loads per lane and stage: of a strip ...
     constexpr int LX = kMidStageK * XB / 64;                // ... and of 16 tokens
@@ -552,8 +552,8 @@ hipError_t launch_mid_t(const void *x, const float *s_tok, const void *wq, const
     if (hipError_t e = ensure_dynamic_lds(kernel, lds, configured); e != hipSuccess) return e;
     const int tiles_m = (M + 16 * MT - 1) / (16 * MT), tiles_n = (N + 16 * RT - 1) / (16 * RT);
     hipLaunchKernelGGL((gemm_mid_kernel<MT, RT, WBITS, XB, D, NW>), dim3(tiles_m * tiles_n), dim3(64 * NW), lds, st,
-                       static_cast<const uint8_t *>(x), s_tok, static_cast<const uint8_t *>(wq), s_w, N / groups,
-                       static_cast<const half_t *>(bias), M, N, K, tiles_m, static_cast<half_t *>(out), acc_out, act);
+                       static_cast<const uint8_t *>(x), static_cast<const uint8_t *>(wq), M, N, K, tiles_m, N / groups, act, s_tok,
+                       s_w, static_cast<const half_t *>(bias), static_cast<half_t *>(out), acc_out);
     return hipGetLastError();
 }
 
@@ -599,8 +599,8 @@ hipError_t launch_direct_t(const void *x, const float *s_tok, const void *wq, co
                            hipStream_t st) {
     hipLaunchKernelGGL((gemm_direct_kernel<MT, RT, WBITS, XB, D, NW>),
                        dim3((N + rows - 1) / rows, (M + 16 * MT - 1) / (16 * MT)), dim3(64 * NW), 0, st,
-                       static_cast<const uint8_t *>(x), s_tok, static_cast<const uint8_t *>(wq), s_w, N / groups,
-                       static_cast<const half_t *>(bias), M, N, K, rows, static_cast<half_t *>(out), acc_out, act);
+                       static_cast<const uint8_t *>(x), static_cast<const uint8_t *>(wq), M, N, K, rows, N / groups, act, s_tok,
+                       s_w, static_cast<const half_t *>(bias), static_cast<half_t *>(out), acc_out);
     return hipGetLastError();
 }
 

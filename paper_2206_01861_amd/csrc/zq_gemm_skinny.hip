@@ -163,10 +163,11 @@ struct StreamPlan {
 
 template <int MT, int WBITS, int DW, int R, int QSH = 0>
 __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_kernel(
-    const int8_t *__restrict__ xq, const float *__restrict__ s_tok, const uint8_t *__restrict__ wq,
-    const float *__restrict__ s_w, int gs, const half_t *__restrict__ bias, int M, int N, int K,
-    half_t *__restrict__ out, int32_t *__restrict__ acc_out, int32_t *__restrict__ partial,
-    unsigned *__restrict__ arrivals, StreamPlan plan, int act) {
+    const int8_t *__restrict__ xq, const uint8_t *__restrict__ wq, int M, int N, int K, int strips_per_block,
+    int strips_rem, int stages_per_split, int stages_rem, int gs, const float *__restrict__ s_tok,
+    const float *__restrict__ s_w, const half_t *__restrict__ bias, half_t *__restrict__ out,
+    int32_t *__restrict__ acc_out, int32_t *__restrict__ partial, unsigned *__restrict__ arrivals, int strips,
+    int k_splits, int act) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     constexpr int LW = (WBITS == 8) ? 4 : 2;          // 16-byte weight loads per lane per stage
@@ -182,10 +183,10 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_kernel(
     // strip / stage (the quotients come from the host: no integer division at the head of the kernel)
     const int rb = (int)blockIdx.x;
     const int ks = (int)blockIdx.y;
-    const int s_lo = rb * plan.strips_per_block + (rb < plan.strips_rem ? rb : plan.strips_rem);
-    const int s_hi = s_lo + plan.strips_per_block + (rb < plan.strips_rem ? 1 : 0);
-    const int k_lo = ks * plan.stages_per_split + (ks < plan.stages_rem ? ks : plan.stages_rem);
-    const int k_hi = k_lo + plan.stages_per_split + (ks < plan.stages_rem ? 1 : 0);
+    const int s_lo = rb * strips_per_block + (rb < strips_rem ? rb : strips_rem);
+    const int s_hi = s_lo + strips_per_block + (rb < strips_rem ? 1 : 0);
+    const int k_lo = ks * stages_per_split + (ks < stages_rem ? ks : stages_rem);
+    const int k_hi = k_lo + stages_per_split + (ks < stages_rem ? 1 : 0);
     const int n = k_hi - k_lo;                        // stages of this workgroup (>= 1: k_splits <= stages)
     constexpr int Q = 1 << QSH;                       // K ranges per strip (1, or 2 with QSH = 1)
     const int nq = (n + Q - 1) >> QSH;                // stages per range = steps of this workgroup
@@ -393,11 +394,11 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_kernel(
     }
 
     // ---- K split: park the partial strip, count the arrival, last arrival adds the others -----
-    if (plan.k_splits > 1) {
-        const int nseg = plan.k_splits;
+    if (k_splits > 1) {
+        const int nseg = k_splits;
         const size_t slot_ints = (size_t)M * 16;      // one strip of one split
         const __amdgpu_buffer_rsrc_t rs_p = __builtin_amdgcn_make_buffer_rsrc(
-            partial, 0, (int)((size_t)plan.strips * nseg * slot_ints * sizeof(int32_t)), kRsrcFlags);
+            partial, 0, (int)((size_t)strips * nseg * slot_ints * sizeof(int32_t)), kRsrcFlags);
         constexpr int kNowhere = 0x7ffffff0;          // past the end of the buffer: stores dropped, loads 0
         // byte offset of this lane's 16 bytes of row m in the slot of split o
         auto slot_off = [&](int o, int m) __attribute__((always_inline)) {
@@ -477,9 +478,10 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_kernel(
 // arrival order.  Epilogue: acc * s_w[group] + bias (there is no activation scale).
 template <int MT, int DW, int R>
 __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_a16_kernel(
-    const half_t *__restrict__ x, const uint8_t *__restrict__ wq, const float *__restrict__ s_w, int gs,
-    const half_t *__restrict__ bias, int M, int N, int K, half_t *__restrict__ out, float *__restrict__ partial,
-    unsigned *__restrict__ arrivals, StreamPlan plan) {
+    const half_t *__restrict__ x, const uint8_t *__restrict__ wq, int M, int N, int K, int strips_per_block,
+    int strips_rem, int stages_per_split, int stages_rem, int gs, const float *__restrict__ s_w,
+    const half_t *__restrict__ bias, half_t *__restrict__ out, float *__restrict__ partial,
+    unsigned *__restrict__ arrivals, int strips, int k_splits) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     constexpr int LW = 4;                             // 16-byte weight loads per lane per stage
@@ -496,10 +498,10 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_a16_kern
     // strip / stage (the quotients come from the host: no integer division at the head of the kernel)
     const int rb = (int)blockIdx.x;
     const int ks = (int)blockIdx.y;
-    const int s_lo = rb * plan.strips_per_block + (rb < plan.strips_rem ? rb : plan.strips_rem);
-    const int s_hi = s_lo + plan.strips_per_block + (rb < plan.strips_rem ? 1 : 0);
-    const int k_lo = ks * plan.stages_per_split + (ks < plan.stages_rem ? ks : plan.stages_rem);
-    const int k_hi = k_lo + plan.stages_per_split + (ks < plan.stages_rem ? 1 : 0);
+    const int s_lo = rb * strips_per_block + (rb < strips_rem ? rb : strips_rem);
+    const int s_hi = s_lo + strips_per_block + (rb < strips_rem ? 1 : 0);
+    const int k_lo = ks * stages_per_split + (ks < stages_rem ? ks : stages_rem);
+    const int k_hi = k_lo + stages_per_split + (ks < stages_rem ? 1 : 0);
     const int n = k_hi - k_lo;
     const int npad = (n + DW - 1) / DW * DW;
 
@@ -624,11 +626,11 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_a16_kern
     const float sw = __uint_as_float(sw_bits);
 
     // ---- K split: park the fp32 partial strip, count the arrival, last arrival adds all in order --
-    if (plan.k_splits > 1) {
-        const int nseg = plan.k_splits;
+    if (k_splits > 1) {
+        const int nseg = k_splits;
         const size_t slot_words = (size_t)M * 16;
         const __amdgpu_buffer_rsrc_t rs_p = __builtin_amdgcn_make_buffer_rsrc(
-            partial, 0, (int)((size_t)plan.strips * nseg * slot_words * sizeof(float)), kRsrcFlags);
+            partial, 0, (int)((size_t)strips * nseg * slot_words * sizeof(float)), kRsrcFlags);
         constexpr int kNowhere = 0x7ffffff0;          // past the end of the buffer: stores dropped, loads 0
         auto slot_off = [&](int o, int m) __attribute__((always_inline)) {
             return (int)((((size_t)strip * nseg + o) * slot_words + (size_t)m * 16 + 4 * j) * 4);
@@ -794,11 +796,12 @@ hipError_t launch_stream_q(const GemmArgs &a, const StreamPlan &plan, hipStream_
                   a.workspace_bytes < kWsFixedBytes + (size_t)plan.k_splits * a.M * a.N * sizeof(int32_t)))
         return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemm_stream_kernel<MT, WBITS, DW, R, QSH>), dim3(plan.row_blocks, plan.k_splits),
-                       dim3(64 * ((plan.consumers << QSH) + 1)), lds, st, a.xq, a.s_tok,
-                       reinterpret_cast<const uint8_t *>(a.wq), a.s_w, a.N / a.groups,
-                       reinterpret_cast<const half_t *>(a.bias), a.M, a.N, a.K, reinterpret_cast<half_t *>(a.out),
-                       a.acc_out, split ? reinterpret_cast<int32_t *>(ws_partials(a.workspace)) : nullptr,
-                       split ? ws_counters(a.workspace) : nullptr, plan, a.act);
+                       dim3(64 * ((plan.consumers << QSH) + 1)), lds, st, a.xq,
+                       reinterpret_cast<const uint8_t *>(a.wq), a.M, a.N, a.K, plan.strips_per_block, plan.strips_rem,
+                       plan.stages_per_split, plan.stages_rem, a.N / a.groups, a.s_tok, a.s_w,
+                       reinterpret_cast<const half_t *>(a.bias), reinterpret_cast<half_t *>(a.out), a.acc_out,
+                       split ? reinterpret_cast<int32_t *>(ws_partials(a.workspace)) : nullptr,
+                       split ? ws_counters(a.workspace) : nullptr, plan.strips, plan.k_splits, a.act);
     return hipGetLastError();
 }
 template <int MT, int WBITS>
@@ -844,10 +847,11 @@ hipError_t launch_stream_a16_t(const A16Args &a, const StreamPlan &plan, hipStre
         return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemm_stream_a16_kernel<MT, DW, R>), dim3(plan.row_blocks, plan.k_splits),
                        dim3(64 * (plan.consumers + 1)), lds, st, reinterpret_cast<const half_t *>(a.x),
-                       reinterpret_cast<const uint8_t *>(a.wq), a.s_w, a.N / a.groups,
-                       reinterpret_cast<const half_t *>(a.bias), a.M, a.N, a.K, reinterpret_cast<half_t *>(a.out),
+                       reinterpret_cast<const uint8_t *>(a.wq), a.M, a.N, a.K, plan.strips_per_block, plan.strips_rem,
+                       plan.stages_per_split, plan.stages_rem, a.N / a.groups, a.s_w,
+                       reinterpret_cast<const half_t *>(a.bias), reinterpret_cast<half_t *>(a.out),
                        split ? reinterpret_cast<float *>(ws_partials(a.workspace)) : nullptr,
-                       split ? ws_counters(a.workspace) : nullptr, plan);
+                       split ? ws_counters(a.workspace) : nullptr, plan.strips, plan.k_splits);
     return hipGetLastError();
 }
 }  // namespace

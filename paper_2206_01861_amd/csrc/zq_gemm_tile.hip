@@ -118,10 +118,10 @@ struct TileCfg {
 template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NSTAGE, int WBITS, int XT = 0, int QOUT = 0,
           int KSPLIT = 0, int KT = 1>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * KT >= 8) ? 1 : 2) void gemm_tile_kernel(
-    const int8_t *__restrict__ xq, const float *__restrict__ s_tok, const uint8_t *__restrict__ wq,
-    const float *__restrict__ s_w, int gs, const half_t *__restrict__ bias, int M, int N, int K,
-    half_t *__restrict__ out, int32_t *__restrict__ acc_out, int tiles_m, int tiles_n, int act,
-    int8_t *__restrict__ q_out, float *__restrict__ q_scale_out, int k_splits, int32_t *__restrict__ partial,
+    const int8_t *__restrict__ xq, const uint8_t *__restrict__ wq, int M, int N, int K, int tiles_m, int tiles_n,
+    int k_splits, int gs, int act, const float *__restrict__ s_tok, const float *__restrict__ s_w,
+    const half_t *__restrict__ bias, half_t *__restrict__ out, int32_t *__restrict__ acc_out,
+    int8_t *__restrict__ q_out, float *__restrict__ q_scale_out, int32_t *__restrict__ partial,
     unsigned long long *__restrict__ q_slots, unsigned *__restrict__ q_ctl) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     using Cfg = TileCfg<BM, BN, WAVES_M, WAVES_N, BK, NSTAGE, KT, XT>;
@@ -981,10 +981,10 @@ hipError_t launch_tile_t(const GemmArgs &a, hipStream_t st, int k_splits = 1) {
     const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
     if (KSPLIT == 0 && k_splits != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WAVES_M, WAVES_N, BK, NSTAGE, WBITS, XT, QOUT, KSPLIT, KT>),
-                       dim3(tiles_m * tiles_n * k_splits), dim3(Cfg::kThreads), lds, st, a.xq, a.s_tok,
-                       reinterpret_cast<const uint8_t *>(a.wq), a.s_w, a.N / a.groups,
-                       reinterpret_cast<const half_t *>(a.bias), a.M, a.N, a.K, reinterpret_cast<half_t *>(a.out),
-                       a.acc_out, tiles_m, tiles_n, a.act, a.q_out, a.q_scale_out, k_splits,
+                       dim3(tiles_m * tiles_n * k_splits), dim3(Cfg::kThreads), lds, st, a.xq,
+                       reinterpret_cast<const uint8_t *>(a.wq), a.M, a.N, a.K, tiles_m, tiles_n, k_splits,
+                       a.N / a.groups, a.act, a.s_tok, a.s_w, reinterpret_cast<const half_t *>(a.bias),
+                       reinterpret_cast<half_t *>(a.out), a.acc_out, a.q_out, a.q_scale_out,
                        KSPLIT ? reinterpret_cast<int32_t *>(ws_partials(a.workspace)) : nullptr,
                        QOUT ? ws_slots(a.workspace) : nullptr, QOUT ? ws_control(a.workspace) : nullptr);
     return hipGetLastError();
