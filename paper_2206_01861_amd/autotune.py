@@ -88,8 +88,8 @@ def tune_shape(M, N, K, bits, m_lo=None, m_hi=None, verbose=False):
     for v in range(v_count):
         if v in (SKINNY, SKINNY_SPLITK):
             continue
-        if zq.gemm_variant_name(v) == "simple" and M * N * K > (1 << 31):
-            continue                                  # the fallback schedule is never competitive at size
+        if zq.gemm_variant_name(v) == "simple" and M > 32 and M * N > (1 << 20):
+            continue                                  # more than one round of 64 x 64 tiles: never competitive
         candidates.append((v, 0, 0))
     if M <= 128 and K % 256 == 0:
         for rb, ks in _cuts(M, N, K, bits):
