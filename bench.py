@@ -632,7 +632,7 @@ def time_gemm(zq, name, M, min_launches=50, repeats=5, comparators=True, oracle=
             except Exception:                       # not every build routes _int_mm to a library kernel
                 lib_int8 = None
     bytes_min = M * K + wbytes + 4 * M + 4 * g + 2 * N + 2 * M * N
-    variant = zq.gemm_variant_name(zq.gemm_choose_variant(M, N, K, bits, nws))
+    variant = zq.gemm_schedule(M, N, K, bits, nws)
     row = {"linear": name, "M": M, "N": N, "K": K, "w_bits": bits, "groups": g, "schedule": variant,
            "us": best * 1e3, "TOPS": ops / (best * 1e-3) / 1e12, "GBs": bytes_min / (best * 1e-3) / 1e9,
            "frac_int8_peak": ops / (best * 1e-3) / 1e12 / PEAK_INT8_TOPS,
@@ -691,7 +691,7 @@ def time_gemm_a16(zq, name, M, reps_target=40):
     ops = 2.0 * M * N * K
     bytes_min = 2 * M * K + wbytes + 4 * g + 2 * N + 2 * M * N
     return {"linear": name + "/w8a16", "M": M, "N": N, "K": K, "w_bits": 8, "groups": g,
-            "schedule": "stream_a16" if (M <= 64 and K % 256 == 0) else ("tile_a16" if K % 64 == 0 else "simple_a16"),
+            "schedule": zq.gemm_schedule(M, N, K, 8, nws, x_bits=16),
             "us": best * 1e3, "TOPS": ops / (best * 1e-3) / 1e12, "GBs": bytes_min / (best * 1e-3) / 1e9,
             "frac_int8_peak": None, "frac_fp16_peak": ops / (best * 1e-3) / 1e12 / 2500.0,
             "frac_hbm_peak": bytes_min / (best * 1e-3) / 1e9 / PEAK_HBM_GBS,

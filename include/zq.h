@@ -324,10 +324,28 @@ int zq_gemm_quantizes_in_kernel(int M, int N, int K, int w_bits, size_t workspac
 int zq_debug_set_in_kernel_quant(int on);
 zq_status zq_quant_wait_expired(void *workspace, int *count_out);
 
-/* Name of schedule `variant` (NULL when out of range), and the schedule the
- * dispatcher would choose for a shape. */
+/*
+ * Name of schedule `variant` (NULL when out of range), and the class of schedules
+ * of a shape: what its workspace is sized for, a table entry can name and decides
+ * whether its output is quantized in the kernel.  A call runs that class unless
+ * the direct or small-tile kernels are ahead of it for the shape; then it runs
+ * those (the class "simple") whatever zq_gemm_choose_variant says.
+ */
 const char *zq_gemm_variant_name(int variant);
 int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t workspace_bytes);
+
+/*
+ * What a GeMM call without a quantized output launches for a shape, a forced
+ * schedule included: "direct", "small32x32", "small64x32", "small64x64" (tokens x
+ * columns of a tile), "stream", "stream_splitk", "tile128x64", "tile128x128",
+ * "tile192x128", "tile256x128", "tile256x192", "tile256x256", "tile128x128_splitk".
+ * x_bits 8: zq_gemm_i8_dequant (w_bits 8) and zq_gemm_w4a8_dequant (w_bits 4);
+ * x_bits 16: zq_gemm_w8a16_dequant, whose streaming launches over two halves of 65 to
+ * 128 token rows are "stream_halves" and "stream_splitk_halves".  workspace_bytes:
+ * what the call is given, 0 without a workspace.  Host-only; launches nothing.
+ * Returns NULL for a shape or bit widths that no call takes.
+ */
+const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t workspace_bytes);
 
 /*
  * Measured schedule table (App. D ranks schedules by measuring them offline

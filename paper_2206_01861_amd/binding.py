@@ -20,7 +20,7 @@ SYMBOLS = [
     "zq_tune_set", "zq_tune_clear", "zq_tune_count", "zq_gemm_w8a16_dequant", "zq_gemm_w8a16_workspace_bytes",
     "zq_gemm_w8a16_stream_plan",
     "zq_gemm_quantizes_in_kernel", "zq_debug_set_in_kernel_quant", "zq_quant_wait_expired",
-    "zq_workspace_init", "zq_gemm_quant_workspace_bytes", "zq_gemm_i8_dequant_static",
+    "zq_workspace_init", "zq_gemm_quant_workspace_bytes", "zq_gemm_i8_dequant_static", "zq_gemm_schedule",
 ]
 PROBE_SYMBOLS = ["zq_probe_read_stream", "zq_probe_mfma_i8", "zq_probe_mfma_i8_tile_traffic"]      # include/zq_probe.h
 
@@ -94,6 +94,8 @@ def lib():
     L.zq_gemm_variant_name.argtypes = [ci]
     L.zq_gemm_choose_variant.restype = ci
     L.zq_gemm_choose_variant.argtypes = [ci, ci, ci, ci, sz]
+    L.zq_gemm_schedule.restype = ctypes.c_char_p
+    L.zq_gemm_schedule.argtypes = [ci, ci, ci, ci, ci, sz]
     L.zq_gemm_stream_plan.restype = ci
     L.zq_gemm_stream_plan.argtypes = [ci, ci, ci, ci, sz] + [ctypes.POINTER(ci)] * 3
     L.zq_gemm_stream_k_ranges.restype = ci
@@ -176,6 +178,12 @@ def gemm_variant_name(variant):
 
 def gemm_choose_variant(M, N, K, w_bits=8, workspace_bytes=0):
     return lib().zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes)
+
+
+def gemm_schedule(M, N, K, w_bits=8, workspace_bytes=0, x_bits=8):
+    """Name of what a GeMM call launches (x_bits 16: zq_gemm_w8a16_dequant); None for a shape no call takes."""
+    s = lib().zq_gemm_schedule(M, N, K, w_bits, x_bits, workspace_bytes)
+    return None if s is None else s.decode()
 
 
 def gemm_quantizes_in_kernel(M, N, K, w_bits=8, workspace_bytes=0):

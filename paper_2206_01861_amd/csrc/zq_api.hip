@@ -32,6 +32,23 @@ zq_status check_rowquant(const void *in, const void *p0, const void *p1, int M, 
     return ZQ_OK;
 }
 
+bool good_shape(int M, int N, int K, int w_bits, int x_bytes) {
+    if (M <= 0 || N <= 0 || K <= 0) return false;
+    if ((K % (w_bits == 4 ? 32 : 16)) != 0 || K > (w_bits == 4 ? ZQ_MAX_K_W4 : ZQ_MAX_K)) return false;
+    // the kernels address both operands through 32-bit buffer offsets
+    return (uint64_t)M * K * x_bytes < kMaxOperandBytes && (uint64_t)N * K * w_bits / 8 < kMaxOperandBytes;
+}
+
+// The schedule that is forced, else the class chosen for the shape; and what a call of that class runs.
+int class_of_call(int M, int N, int K, int w_bits, size_t workspace_bytes, bool *forced) {
+    const int variant = g_forced_variant.load();
+    *forced = variant >= 0;
+    return *forced ? variant : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
+}
+int variant_of_call(int variant, bool forced, int M, int N, int K, int w_bits) {
+    return !forced && zq::gemm_goes_direct(M, N, K, w_bits) ? zq::kGemmSimple : variant;
+}
+
 zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, const float *s_w, int groups,
                       const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int8_t *out_q,
                       float *out_s_tok, void *workspace, size_t workspace_bytes, int w_bits, int act,
@@ -39,11 +56,8 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
     if (xq == nullptr || s_tok == nullptr || wq == nullptr || s_w == nullptr) return ZQ_ERR_NULL;
     if (out == nullptr && !(out_optional && out_q != nullptr)) return ZQ_ERR_NULL;
     if ((out_q == nullptr) != (out_s_tok == nullptr)) return ZQ_ERR_NULL;
-    if (M <= 0 || N <= 0 || K <= 0 || groups <= 0) return ZQ_ERR_SHAPE;
-    if ((N % groups) != 0 || ((N / groups) % 16) != 0) return ZQ_ERR_SHAPE;
-    if ((K % (w_bits == 4 ? 32 : 16)) != 0 || K > (w_bits == 4 ? ZQ_MAX_K_W4 : ZQ_MAX_K)) return ZQ_ERR_SHAPE;
-    // the kernels address both operands through 32-bit buffer offsets
-    if ((uint64_t)M * K >= kMaxOperandBytes || (uint64_t)N * K * w_bits / 8 >= kMaxOperandBytes) return ZQ_ERR_SHAPE;
+    if (groups <= 0 || (N % groups) != 0 || ((N / groups) % 16) != 0) return ZQ_ERR_SHAPE;
+    if (!good_shape(M, N, K, w_bits, 1)) return ZQ_ERR_SHAPE;
     if (out_q != nullptr && N > kMaxRow) return ZQ_ERR_SHAPE;
     if (misaligned(xq) || misaligned(s_tok) || misaligned(wq) || misaligned(s_w) || misaligned(bias) ||
         misaligned(out) || misaligned(acc_out) || misaligned(out_q) || misaligned(out_s_tok) ||
@@ -51,13 +65,9 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         return ZQ_ERR_ALIGN;
     if (workspace == nullptr) workspace_bytes = 0;
 
-    int variant = g_forced_variant.load();
-    const bool forced = variant >= 0;
-    if (forced) {
-        if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
-    } else {
-        variant = zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
-    }
+    bool forced;
+    const int variant = class_of_call(M, N, K, w_bits, workspace_bytes, &forced);
+    if (forced && !zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
     // On the tiled schedules the output rows are quantized inside the GeMM kernel.
     const bool in_kernel = out_q != nullptr && g_in_kernel_quant.load() != 0 && is_tile_variant(variant) &&
                            zq::gemm_tile_quant_supported(M, N, workspace_bytes);
@@ -71,8 +81,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         a.q_out = out_q; a.q_scale_out = out_s_tok;
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
-    if (!forced && zq::gemm_goes_direct(M, N, K, w_bits)) variant = zq::kGemmSimple;
-    if (zq::launch_gemm(variant, a, st) != hipSuccess) return ZQ_ERR_HIP;
+    if (zq::launch_gemm(variant_of_call(variant, forced, M, N, K, w_bits), a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
         if (zq::launch_rowquant(zq::kOpIdentity, out, nullptr, nullptr, 0.0f, M, N, out_q, out_s_tok, nullptr, 0,
@@ -224,6 +233,19 @@ static bool a16_tiles_with_split(int M, int N, int K) {
     return ks >= ((M <= kA16StreamTokens && (K % 256) == 0) ? 3 : 2);
 }
 
+enum A16Route { kA16Direct, kA16Stream, kA16Tile };
+static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
+    if ((M <= 64 && (K % 256) != 0) || zq::direct_pays(M, N, K, 8, 2)) return kA16Direct;
+    if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16Tile;
+    if (M <= kA16StreamTokens && (K % 256) == 0) return kA16Stream;
+    return (long)M * N * K > (1L << 27) ? kA16Tile : kA16Direct;
+}
+// The K split of the streaming launches is taken only when the workspace holds its fp32 partials.
+static bool a16_stream_splits(int M, int N, int K, size_t workspace_bytes) {
+    const size_t need = zq::stream_a16_workspace_bytes(M, N, K);
+    return need > 0 && workspace_bytes >= need;
+}
+
 size_t zq_gemm_w8a16_workspace_bytes(int M, int N, int K) {
     if (M <= 0 || N <= 0 || K <= 0 || (N % 16) != 0 || (K % 16) != 0) return 0;
     size_t need = 0;
@@ -248,10 +270,8 @@ zq_status zq_gemm_w8a16_dequant(const void *x_fp16, const int8_t *wq, const floa
                                 const void *bias_fp16, int M, int N, int K, void *out_fp16, void *workspace,
                                 size_t workspace_bytes, zq_stream stream) {
     if (x_fp16 == nullptr || wq == nullptr || s_w == nullptr || out_fp16 == nullptr) return ZQ_ERR_NULL;
-    if (M <= 0 || N <= 0 || K <= 0 || groups <= 0) return ZQ_ERR_SHAPE;
-    if ((N % groups) != 0 || ((N / groups) % 16) != 0) return ZQ_ERR_SHAPE;
-    if ((K % 16) != 0 || K > ZQ_MAX_K) return ZQ_ERR_SHAPE;
-    if ((uint64_t)M * K * 2 >= kMaxOperandBytes || (uint64_t)N * K >= kMaxOperandBytes) return ZQ_ERR_SHAPE;
+    if (groups <= 0 || (N % groups) != 0 || ((N / groups) % 16) != 0) return ZQ_ERR_SHAPE;
+    if (!good_shape(M, N, K, 8, 2)) return ZQ_ERR_SHAPE;
     if (misaligned(x_fp16) || misaligned(wq) || misaligned(s_w) || misaligned(bias_fp16) || misaligned(out_fp16) ||
         misaligned(workspace))
         return ZQ_ERR_ALIGN;
@@ -260,30 +280,22 @@ zq_status zq_gemm_w8a16_dequant(const void *x_fp16, const int8_t *wq, const floa
     a.x = x_fp16; a.wq = wq; a.s_w = s_w; a.groups = groups; a.bias = bias_fp16;
     a.M = M; a.N = N; a.K = K; a.out = out_fp16; a.workspace = workspace; a.workspace_bytes = workspace_bytes;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    hipError_t e;
-    const bool tile_split = a16_tiles_with_split(M, N, K) &&
-                            workspace_bytes >= zq::gemm_a16_tile_split_workspace(M, N, K);
-    if ((M <= 64 && (K % 256) != 0) || zq::direct_pays(M, N, K, 8, 2)) {
-        e = zq::launch_gemm_a16_direct(a, st);
-    } else if (tile_split) {
-        e = zq::launch_gemm_a16_tile(a, st);
-    } else if (M <= kA16StreamTokens && (K % 256) == 0) {
-        // Weight streaming holds up to 64 tokens per launch; 65..128 tokens run as two launches over
-        // row halves (the weights are read twice, which is still well ahead of the tiled schedule on
-        // so few rows).  The K split is taken only when the workspace holds its fp32 partials.
-        e = hipSuccess;
-        for (int m0 = 0; m0 < M && e == hipSuccess; m0 += 64) {
-            zq::A16Args h = a;
-            h.M = (M - m0) < 64 ? (M - m0) : 64;
-            h.x = static_cast<const uint16_t *>(x_fp16) + (size_t)m0 * K;
-            h.out = static_cast<uint16_t *>(out_fp16) + (size_t)m0 * N;
-            const size_t need = zq::stream_a16_workspace_bytes(h.M, N, K);
-            e = zq::launch_gemm_a16_stream(h, need > 0 && workspace_bytes >= need, st);
-        }
-    } else if ((long)M * N * K > (1L << 27)) {
-        e = zq::launch_gemm_a16_tile(a, st);
-    } else {
-        e = zq::launch_gemm_a16_direct(a, st);
+    hipError_t e = hipSuccess;
+    switch (a16_route(M, N, K, workspace_bytes)) {
+        case kA16Direct: e = zq::launch_gemm_a16_direct(a, st); break;
+        case kA16Tile: e = zq::launch_gemm_a16_tile(a, st); break;
+        case kA16Stream:
+            // Weight streaming holds up to 64 tokens per launch; 65..128 tokens run as two launches over
+            // row halves (the weights are read twice, which is still well ahead of the tiled schedule on
+            // so few rows).
+            for (int m0 = 0; m0 < M && e == hipSuccess; m0 += 64) {
+                zq::A16Args h = a;
+                h.M = (M - m0) < 64 ? (M - m0) : 64;
+                h.x = static_cast<const uint16_t *>(x_fp16) + (size_t)m0 * K;
+                h.out = static_cast<uint16_t *>(out_fp16) + (size_t)m0 * N;
+                e = zq::launch_gemm_a16_stream(h, a16_stream_splits(h.M, N, K, workspace_bytes), st);
+            }
+            break;
     }
     return e == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
 }
@@ -360,6 +372,26 @@ zq_status zq_quant_wait_expired(void *workspace, int *count_out) {
     if (hipMemcpy(word, &zero, sizeof(unsigned), hipMemcpyHostToDevice) != hipSuccess) return ZQ_ERR_HIP;
     *count_out = (int)c;
     return ZQ_OK;
+}
+
+const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t workspace_bytes) {
+    if ((w_bits != 8 && w_bits != 4) || (x_bits != 8 && (x_bits != 16 || w_bits != 8))) return nullptr;
+    if (!good_shape(M, N, K, w_bits, x_bits / 8) || (N % 16) != 0) return nullptr;
+    if (x_bits == 8) {
+        bool forced;
+        const int variant = class_of_call(M, N, K, w_bits, workspace_bytes, &forced);
+        if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return nullptr;
+        return zq::gemm_schedule_name(variant_of_call(variant, forced, M, N, K, w_bits), M, N, K, w_bits);
+    }
+    switch (a16_route(M, N, K, workspace_bytes)) {
+        case kA16Direct: return zq::gemm_direct_name(M, N, K, 8, 2);
+        case kA16Stream:
+            if (M > 64) return a16_stream_splits(64, N, K, workspace_bytes) ? "stream_splitk_halves" : "stream_halves";
+            return a16_stream_splits(M, N, K, workspace_bytes) ? "stream_splitk" : "stream";
+        default:
+            if (zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return "tile128x128_splitk";
+            return zq::tile_shape_name(zq::choose_tile(zq::kTileA16, M, N, K, zq::kAllTileShapes, nullptr));
+    }
 }
 
 const char *zq_gemm_variant_name(int variant) {

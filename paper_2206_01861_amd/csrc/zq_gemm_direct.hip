@@ -756,16 +756,29 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
 }
 
 namespace {
+// The tile of gemm_mid_kernel that a launch takes, kMidShapes: gemm_direct_kernel.
+MidShape small_shape(int M, int N, int K, int w_bits, int xb) {
+    return M <= 32 || short_problem(M, N, K, xb) ? kMidShapes : choose_mid(M, N, K, w_bits, xb, nullptr);
+}
+
 template <int WBITS, int XB>
 hipError_t launch_small(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
                         const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int act, hipStream_t st) {
-    const MidShape shape =
-        M <= 32 || short_problem(M, N, K, XB) ? kMidShapes : choose_mid(M, N, K, WBITS, XB, nullptr);
+    const MidShape shape = small_shape(M, N, K, WBITS, XB);
     if (shape != kMidShapes)
         return launch_mid<WBITS, XB>(shape, x, s_tok, wq, s_w, groups, bias, M, N, K, out, acc_out, act, st);
     return launch_direct<WBITS, XB>(x, s_tok, wq, s_w, groups, bias, M, N, K, out, acc_out, act, st);
 }
 }  // namespace
+
+const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb) {
+    switch (small_shape(M, N, K, w_bits, xb)) {
+        case kMid32x32: return "small32x32";
+        case kMid64x32: return "small64x32";
+        case kMid64x64: return "small64x64";
+        default: return "direct";
+    }
+}
 
 hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st) {
     if (a.w_bits == 8)

@@ -117,6 +117,16 @@ hipError_t launch_gemm(int variant, const GemmArgs &a, hipStream_t st) {
     return hipErrorInvalidValue;
 }
 
+const char *gemm_schedule_name(int variant, int M, int N, int K, int w_bits) {
+    switch (variant) {
+        case kGemmSimple: return gemm_direct_name(M, N, K, w_bits, 1);
+        case kGemmTileSplitK: return "tile128x128_splitk";
+        case kGemmSkinny: return "stream";
+        case kGemmSkinnySplitK: return "stream_splitk";
+    }
+    return tile_shape_name(choose_tile(tile_kind(w_bits), M, N, K, shapes_of(variant), nullptr));
+}
+
 }  // namespace zq
 
 extern "C" int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t workspace_bytes) {

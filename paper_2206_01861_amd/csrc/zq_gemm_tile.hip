@@ -1268,6 +1268,22 @@ size_t gemm_a16_tile_split_workspace(int M, int N, int K) {
     return ks > 1 ? kWsFixedBytes + (size_t)ks * M * N * sizeof(float) : 0;
 }
 
+const char *tile_shape_name(TileShape shape) {
+    switch (shape) {
+        case kTile128x64: return "tile128x64";
+        case kTile128x128: return "tile128x128";
+        case kTile192x128: return "tile192x128";
+        case kTile256x128: return "tile256x128";
+        case kTile256x192: return "tile256x192";
+        default: return "tile256x256";
+    }
+}
+
+bool gemm_a16_tile_splits_here(int M, int N, int K, size_t workspace_bytes) {
+    const size_t need = gemm_a16_tile_split_workspace(M, N, K);
+    return need > 0 && workspace_bytes >= need;
+}
+
 // FP16 activations x INT8 weights on the tiled schedules.  The argument block is the
 // INT8 one with xq pointing at the FP16 activations and no token scales.
 hipError_t launch_gemm_a16_tile(const A16Args &a16, hipStream_t st) {
@@ -1278,9 +1294,8 @@ hipError_t launch_gemm_a16_tile(const A16Args &a16, hipStream_t st) {
     a.M = a16.M; a.N = a16.N; a.K = a16.K; a.out = a16.out; a.acc_out = nullptr;
     a.workspace = a16.workspace; a.workspace_bytes = a16.workspace_bytes; a.w_bits = 8; a.act = 0;
     // few tiles against a long K: split K (fp32 partials, added in split order by the second kernel)
-    const int ks = tile_splits(a.M, a.N, a.K, 2);
-    if (ks > 1 && a.workspace != nullptr &&
-        a.workspace_bytes >= kWsFixedBytes + (size_t)ks * a.M * a.N * sizeof(float)) {
+    if (gemm_a16_tile_splits_here(a.M, a.N, a.K, a.workspace_bytes)) {
+        const int ks = tile_splits(a.M, a.N, a.K, 2);
         if (hipError_t e = launch_tile_t<128, 128, 2, 4, 128, 4, 8, 1, 0, 1>(a, st, ks); e != hipSuccess) return e;
         return launch_splitk_finish<1>(a, ks, st);
     }

@@ -105,6 +105,7 @@ enum TileShape { kTile128x64, kTile128x128, kTile192x128, kTile256x128, kTile256
 constexpr unsigned kAllTileShapes = (1u << kTileShapes) - 1u;
 enum TileKind { kTileI8, kTileI4, kTileA16 };
 TileShape choose_tile(TileKind kind, int M, int N, int K, unsigned shapes, double *us);
+const char *tile_shape_name(TileShape shape);
 hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st);
 
 // 128x128 tiles with a K split: how many splits pay for a shape (1 = none), the workspace they
@@ -122,6 +123,10 @@ hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st);
 // gemm_goes_direct: the same for INT8 activations, unless a schedule is registered for the shape.
 bool direct_pays(int M, int N, int K, int w_bits, int xb);
 bool gemm_goes_direct(int M, int N, int K, int w_bits);
+const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb);    // of the kernel that launch takes
+
+// Name of what launch_gemm runs for a variant (see zq_gemm_schedule).
+const char *gemm_schedule_name(int variant, int M, int N, int K, int w_bits);
 
 // A caller-supplied cut of the streaming schedules for this shape, if one was registered.
 bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_splits);
@@ -145,6 +150,7 @@ void stream_a16_plan(int M, int N, int K, bool allow_split, int *row_blocks, int
 hipError_t launch_gemm_a16_tile(const A16Args &a, hipStream_t st);                       // any K the ABI accepts
 int gemm_a16_tile_splits(int M, int N, int K);                                          // K splits that pay on tiles, 1 = none
 size_t gemm_a16_tile_split_workspace(int M, int N, int K);                              // of its K split, 0 if none
+bool gemm_a16_tile_splits_here(int M, int N, int K, size_t workspace_bytes);            // what launch_gemm_a16_tile does
 
 bool gemm_variant_supports(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes);
 size_t gemm_variant_workspace(int variant, int M, int N, int K, int w_bits);

@@ -1,0 +1,52 @@
+"""zq_gemm_schedule says what a call launches (host only): the kernels that take a shape from the class that
+zq_gemm_choose_variant names, the tile of a tiled call, forced schedules, the FP16-activation call."""
+import pytest
+
+import paper_2206_01861_amd as zq
+
+NAMES = ("direct", "small32x32", "small64x32", "small64x64", "stream", "stream_splitk", "tile128x64", "tile128x128",
+         "tile192x128", "tile256x128", "tile256x192", "tile256x256", "tile128x128_splitk")
+
+
+@pytest.mark.parametrize("M,N,K,bits,want", [
+    (1, 2048, 2048, 8, "direct"), (1, 16384, 4096, 4, "direct"),                # class "skinny"
+    (128, 2048, 2048, 8, "small"), (64, 6144, 6144, 4, "small"),                # a streaming class, small tiles
+    (32, 12288, 4096, 8, "stream"), (4096, 4096, 1024, 8, "tile256x256"), (333, 4096, 4096, 8, "tile"),
+    (128, 768, 784, 8, "direct"),
+])
+def test_schedule_is_what_runs(M, N, K, bits, want):
+    name = zq.gemm_schedule(M, N, K, bits)
+    assert name.startswith(want) and name in NAMES
+
+
+def test_schedule_uses_the_workspace():
+    M, N, K = 64, 6144, 24576
+    ws = zq.gemm_workspace_bytes(M, N, K)
+    assert zq.gemm_schedule(M, N, K, 8, ws) == "stream_splitk"
+    assert zq.gemm_schedule(M, N, K, 8, ws - 1) == "stream"
+    ws = zq.gemm_workspace_bytes(256, 4096, 16384, 4)
+    assert zq.gemm_schedule(256, 4096, 16384, 4, ws) == "tile128x128_splitk"
+    assert zq.gemm_schedule(256, 4096, 16384, 4, 0).startswith("tile")
+
+
+def test_schedule_of_fp16_activations():
+    assert zq.gemm_schedule(1, 6144, 2048, 8, x_bits=16) == "direct"
+    assert zq.gemm_schedule(64, 18432, 6144, 8, x_bits=16) == "stream"
+    assert zq.gemm_schedule(128, 18432, 6144, 8, x_bits=16) == "stream_halves"
+    assert zq.gemm_schedule(16384, 18432, 6144, 8, x_bits=16) == "tile256x256"
+    ws = zq.gemm_w8a16_workspace_bytes(256, 2064, 8000)
+    assert zq.gemm_schedule(256, 2064, 8000, 8, ws, x_bits=16) == "tile128x128_splitk"
+
+
+def test_forced_schedule_and_shapes_no_call_takes():
+    before = zq.force_gemm_variant(1)
+    try:
+        assert zq.gemm_schedule(1, 2048, 2048) in ("tile128x64", "tile128x128")
+        zq.force_gemm_variant(3)
+        assert zq.gemm_schedule(1, 2048, 2048) == "stream"
+        assert zq.gemm_schedule(1, 2048, 2064) is None          # streaming needs K % 256 == 0
+    finally:
+        zq.force_gemm_variant(before)
+    for bad in [(0, 16, 16, 8, 0, 8), (1, 24, 16, 8, 0, 8), (1, 16, 24, 8, 0, 8), (1, 16, 16, 4, 0, 8), (1, 16, 32, 4, 0, 16),
+                (1, 16, 16, 8, 0, 4), (1 << 20, 1 << 20, 1 << 20, 8, 0, 8)]:
+        assert zq.gemm_schedule(*bad) is None, bad
