@@ -236,8 +236,8 @@ zq_status zq_dequantize_acc(const int32_t *acc, const float *s_tok, const float 
  *   xq, s_tok, s_w, groups, bias_fp16, M, N, K, workspace: as zq_gemm_i8_dequant
  *   wq        w_bits = 8: int8 [N,K];  w_bits = 4: packed uint8 [N,K/2]   (device)
  *   g_fp16    out, fp16 [M,N]: the activated tensor (device); may be NULL
- *             when zq_gemm_quantizes_in_kernel() says 1 for the shape (the
- *             tensor is then never written), otherwise ZQ_ERR_UNSUPPORTED
+ *             when zq_gemm_quantizes_in_kernel() says 1 for the shape, otherwise
+ *             ZQ_ERR_UNSUPPORTED
  *   gq_out    out, int8 [M,N];  s_tok_out  out, fp32 [M]                  (device, required)
  * N <= 32768 (a row of g is quantized from registers).  Errors as the GeMM calls.
  *
@@ -248,7 +248,10 @@ zq_status zq_dequantize_acc(const int32_t *acc, const float *s_tok, const float 
  * registers, so g is not read back (and not written at all when g_fp16 is
  * NULL).  The same holds for out_q / out_s_tok of zq_gemm_i8_dequant and
  * zq_gemm_w4a8_dequant.  Elsewhere, and without a workspace, a second kernel
- * quantizes the FP16 rows just written.  Both ways give the same bits.  It
+ * quantizes the FP16 rows just written.  That also holds for up to 64 tokens
+ * against a K that is no multiple of 256 wherever the direct kernels are ahead of
+ * the tiles; without g_fp16 the rows are then kept in the workspace, and one that
+ * is too small for them takes the tiles.  Both ways give the same bits.  It
  * needs a band of tiles to fit a quarter of the device's compute units (N <=
  * 16384 on 256 of them) and (M rounded up to the tile edge) * (tiles along N)
  * <= 2^19 exchange slots; beyond that the second kernel is used.
@@ -306,8 +309,9 @@ int zq_gemm_w8a16_stream_plan(int M, int N, int K, size_t workspace_bytes, int *
 int zq_debug_force_gemm_variant(int variant);
 
 /*
- * 1 if a GeMM call with out_q / gq_out on this shape quantizes its output
- * inside the GeMM kernel (see zq_gemm_gelu_quant_tokenwise), else 0.
+ * 1 if a GeMM call with out_q / gq_out on this shape can quantize its output
+ * inside the GeMM kernel, so that it needs no FP16 tensor from the caller (see
+ * zq_gemm_gelu_quant_tokenwise), else 0.
  *
  * zq_debug_set_in_kernel_quant: test and ablation hook; on = 0 makes every
  * call use the second kernel, and no workgroup of the weight quantizer wait

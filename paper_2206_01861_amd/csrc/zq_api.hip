@@ -49,6 +49,13 @@ int variant_of_call(int variant, bool forced, int M, int N, int K, int w_bits) {
     return !forced && zq::gemm_goes_direct(M, N, K, w_bits) ? zq::kGemmSimple : variant;
 }
 
+// Up to 64 tokens of a tiled class (K no multiple of 256) that the direct kernels are ahead of: the output rows are
+// quantized by the second kernel, from FP16 rows that stand in the workspace if the caller has no use for them.
+bool rows_beside_tiles(int M, int N, int K, int w_bits, bool forced) {
+    return M <= 64 && !forced && zq::gemm_goes_direct(M, N, K, w_bits);
+}
+size_t row_bytes(int M, int N) { return (size_t)M * N * sizeof(uint16_t); }
+
 zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, const float *s_w, int groups,
                       const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int8_t *out_q,
                       float *out_s_tok, void *workspace, size_t workspace_bytes, int w_bits, int act,
@@ -69,9 +76,16 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
     const int variant = class_of_call(M, N, K, w_bits, workspace_bytes, &forced);
     if (forced && !zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
     // On the tiled schedules the output rows are quantized inside the GeMM kernel.
-    const bool in_kernel = out_q != nullptr && g_in_kernel_quant.load() != 0 && is_tile_variant(variant) &&
-                           zq::gemm_tile_quant_supported(M, N, workspace_bytes);
+    bool in_kernel = out_q != nullptr && g_in_kernel_quant.load() != 0 && is_tile_variant(variant) &&
+                     zq::gemm_tile_quant_supported(M, N, workspace_bytes);
     if (out == nullptr && !in_kernel) return ZQ_ERR_UNSUPPORTED;
+    // ... except for few tokens, where the direct kernels and the row quantizer together are faster (GeLU and quantizer,
+    // weights from memory, us: 27x6400x1600 15.7 -> 7.6, INT4 17.6 -> 7.2; 60x8192x2080 21.9 -> 14.4); a call that wants
+    // no FP16 rows has them in the workspace.
+    if (in_kernel && rows_beside_tiles(M, N, K, w_bits, forced)) {
+        if (out == nullptr && workspace_bytes >= zq::kWsFixedBytes + row_bytes(M, N)) out = zq::ws_partials(workspace);
+        in_kernel = out == nullptr;
+    }
     zq::GemmArgs a;
     a.xq = xq; a.s_tok = s_tok; a.wq = wq; a.s_w = s_w; a.groups = groups; a.bias = bias;
     a.M = M; a.N = N; a.K = K; a.out = out; a.acc_out = acc_out;
@@ -181,8 +195,10 @@ size_t zq_gemm_quant_workspace_bytes(int M, int N, int K, int w_bits) {
     size_t need = zq_gemm_workspace_bytes(M, N, K, w_bits);
     // the schedule of a caller who offers exactly `need` (a larger offer changes nothing)
     const int variant = zq_gemm_choose_variant(M, N, K, w_bits, need);
-    if (is_tile_variant(variant) && zq::gemm_tile_quant_supported(M, N, zq::kWsFixedBytes) && need < zq::kWsFixedBytes)
-        need = zq::kWsFixedBytes;
+    if (is_tile_variant(variant) && zq::gemm_tile_quant_supported(M, N, zq::kWsFixedBytes)) {
+        const size_t rows = rows_beside_tiles(M, N, K, w_bits, false) ? row_bytes(M, N) : 0;
+        if (need < zq::kWsFixedBytes + rows) need = zq::kWsFixedBytes + rows;
+    }
     return need;
 }
 
@@ -235,7 +251,7 @@ static bool a16_tiles_with_split(int M, int N, int K) {
 
 enum A16Route { kA16Direct, kA16Stream, kA16Tile };
 static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
-    if ((M <= 64 && (K % 256) != 0) || zq::direct_pays(M, N, K, 8, 2)) return kA16Direct;
+    if (zq::direct_pays(M, N, K, 8, 2)) return kA16Direct;
     if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16Tile;
     if (M <= kA16StreamTokens && (K % 256) == 0) return kA16Stream;
     return (long)M * N * K > (1L << 27) ? kA16Tile : kA16Direct;

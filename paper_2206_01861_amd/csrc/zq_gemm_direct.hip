@@ -730,6 +730,9 @@ bool short_problem(int M, int N, int K, int xb) {
 //   W8A16  6144x2048 at 64 10.6 / 8.6, at 128 18.7 / 10.5; 4800x1600 at 192 17.4 / 10.8; beyond: 7680x2560 at 64 12.6 /
 //          17.8, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
+    // K no multiple of 256: the streaming kernel does not take it (6400x1600 at 27 tokens 6.0 us, 12.2 on 128x128
+    // tiles), except where many tokens meet more rows than 64 x 64 tiles cover in one round.
+    if ((K % 256) != 0 && (M <= 32 || (M <= 64 && (N <= 16384 || xb == 2)))) return true;
     if (M > 32) {
         double us, tile_us;
         if (short_problem(M, N, K, xb)) return true;

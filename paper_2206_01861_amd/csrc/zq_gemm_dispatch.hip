@@ -147,9 +147,6 @@ extern "C" int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t wo
             return kGemmSkinnySplitK;
         if (gemm_variant_supports(kGemmSkinny, M, N, K, w_bits, 0)) return kGemmSkinny;
     }
-    // Up to 64 tokens and K not a multiple of 256: the direct kernels, which take any K (6400x1600 at 27 tokens
-    // 6.0 us, 12.2 on 128x128 tiles), except where many tokens meet more rows than 64 x 64 tiles cover in one round.
-    if (M <= 32 || (M <= 64 && N <= 16384)) return kGemmSimple;
     // Tiny problems (a BERT-base layer at 128 tokens) are all latency: the direct kernel starts and finishes
     // sooner than a handful of LDS-tiled workgroups (768x768 at 128 tokens 3.3 us, 6.8 on tiles).
     if ((long)M * N * K <= (1L << 27)) return kGemmSimple;

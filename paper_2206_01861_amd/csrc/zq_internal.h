@@ -29,7 +29,7 @@ inline hipError_t ensure_dynamic_lds(const void *kernel, size_t bytes, std::atom
 //                       [2] threads whose bounded wait ran out
 //   [256, +32 KB)       arrival counters of the strips a streaming schedule splits along K
 //   [.., +4 MB)         exchange slots of the in-kernel output quantization (8 bytes per tile and row)
-//   [kWsFixedBytes, ..) partial sums of the K-split schedules
+//   [kWsFixedBytes, ..) partial sums of the K-split schedules, or FP16 output rows that no caller wants
 // Every kernel leaves the first three parts ready for the next call; the parts never overlap, so
 // calls of any kind and shape can share a workspace as long as they are ordered on one stream.
 constexpr size_t kWsControlBytes = 256;

@@ -370,3 +370,17 @@ def test_missing_library_is_an_error(tmp_path, monkeypatch):
     monkeypatch.setattr(binding, "_LIB_PATH", str(tmp_path / "libzq.so"))
     with pytest.raises(ImportError):
         binding.lib()
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_few_tokens_with_ragged_k_need_no_fp16_output(bits):
+    """Up to 64 tokens against a K that is no multiple of 256 belong to a tiled class, so the call may be made without
+    an FP16 tensor; the workspace that is asked for also holds its rows, for the direct kernels."""
+    for M, N, K in [(27, 6400, 1600), (64, 4096, 2080), (5, 8192, 4000), (33, 8192, 1056)]:
+        assert zq.gemm_quantizes_in_kernel(M, N, K, bits, FIXED)
+        assert not zq.gemm_quantizes_in_kernel(M, N, K, bits, FIXED - 1)
+        assert zq.gemm_quant_workspace_bytes(M, N, K, bits) >= FIXED + 2 * M * N
+        assert zq.gemm_quant_workspace_bytes(M, N, K, bits) <= zq.STATIC_SCRATCH_BYTES
+    assert not zq.gemm_quantizes_in_kernel(27, 6400, 1536, bits, FIXED)            # the streaming kernel's
+    assert not zq.gemm_quantizes_in_kernel(27, 8192 + 128, 1600, bits, FIXED)      # the band that must be resident
+    assert not zq.gemm_quantizes_in_kernel(5, 1600, 1600, bits, FIXED)             # tiny: direct kernel and row quantizer

@@ -248,3 +248,35 @@ def test_in_kernel_quantization_while_another_stream_keeps_the_chip_busy(zq, orc
     for i, (_, q, s) in enumerate(outs):
         assert_bit_equal(host(s), host(s_ref), "call %d s_tok" % i)
         assert_bit_equal(host(q), host(q_ref), "call %d codes" % i)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("M,N,K,g", [(27, 6400, 1600, 100), (64, 4096, 2080, 16), (20, 8192, 1056, 4), (33, 4112, 1056, 257)])
+def test_few_tokens_ragged_k_without_fp16_output(zq, orc, M, N, K, g, bits):
+    """A tiled class that the direct kernels take: the FP16 rows come from the caller, stand in the workspace, or, where
+    it is too small, the tiles quantize in the kernel; the same bits each time, also for the plain call's out_q."""
+    print("ragged fused", bits, M, N, K, g, flush=True)
+    rng = zq_inputs.rng_for(7, M + N + K + bits)
+    xq, s_tok, s_w, bias, codes, wq = _case(rng, M, N, K, g, bits)
+    s_tok = (s_tok * (3.0 / max(1e-9, float(np.sqrt(K)) * 40.0 * float(s_tok.mean()) * float(s_w.mean())))).astype(np.float32)
+    args = (dev(xq), dev(s_tok), dev(wq), dev(s_w), dev(bias))
+    gemm = zq.zq_gemm_i8_dequant if bits == 8 else zq.zq_gemm_w4a8_dequant
+    ws = zq.new_workspace(zq.gemm_quant_workspace_bytes(M, N, K, bits))
+    small = zq.new_workspace(0)
+    assert zq.gemm_quantizes_in_kernel(M, N, K, bits, small.numel())
+    g0, q0, s0 = zq.zq_gemm_gelu_quant_tokenwise(*args)
+    _, oq0, os0 = gemm(*args, requant=True)[1:]
+    for rep in range(2):
+        for w in (ws, small):
+            for keep in (True, False):
+                g1, q1, s1 = zq.zq_gemm_gelu_quant_tokenwise(*args, keep_g=keep, workspace=w)
+                assert (g1 is not None) == keep
+                if keep:
+                    assert_bit_equal(host(g1), host(g0), "g")
+                assert_bit_equal(host(s1), host(s0), "s_tok")
+                assert_bit_equal(host(q1), host(q0), "codes")
+            _, _, oq, os_ = gemm(*args, requant=True, workspace=w)
+            assert_bit_equal(host(os_), host(os0), "out_s_tok")
+            assert_bit_equal(host(oq), host(oq0), "out_q")
+    assert zq.quant_wait_expired(ws) == 0 and zq.quant_wait_expired(small) == 0
+    _check_fused(orc, host(g0), host(q0), host(s0), xq, s_tok, codes, s_w, bias, False, "ragged %d-bit %dx%dx%d" % (bits, M, N, K))
