@@ -45,14 +45,14 @@ int class_of_call(int M, int N, int K, int w_bits, size_t workspace_bytes, bool 
     *forced = variant >= 0;
     return *forced ? variant : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
 }
-int variant_of_call(int variant, bool forced, int M, int N, int K, int w_bits) {
-    return !forced && zq::gemm_goes_direct(M, N, K, w_bits) ? zq::kGemmSimple : variant;
+int variant_of_call(int variant, bool forced, int M, int N, int K, int w_bits, size_t workspace_bytes) {
+    return !forced && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes) ? zq::kGemmSimple : variant;
 }
 
 // Up to 64 tokens of a tiled class (K no multiple of 256) that the direct kernels are ahead of: the output rows are
 // quantized by the second kernel, from FP16 rows that stand in the workspace if the caller has no use for them.
-bool rows_beside_tiles(int M, int N, int K, int w_bits, bool forced) {
-    return M <= 64 && !forced && zq::gemm_goes_direct(M, N, K, w_bits);
+bool rows_beside_tiles(int M, int N, int K, int w_bits, size_t workspace_bytes, bool forced) {
+    return M <= 64 && !forced && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes);
 }
 size_t row_bytes(int M, int N) { return (size_t)M * N * sizeof(uint16_t); }
 
@@ -82,7 +82,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
     // ... except for few tokens, where the direct kernels and the row quantizer together are faster (GeLU and quantizer,
     // weights from memory, us: 27x6400x1600 15.7 -> 7.6, INT4 17.6 -> 7.2; 60x8192x2080 21.9 -> 14.4); a call that wants
     // no FP16 rows has them in the workspace.
-    if (in_kernel && rows_beside_tiles(M, N, K, w_bits, forced)) {
+    if (in_kernel && rows_beside_tiles(M, N, K, w_bits, workspace_bytes, forced)) {
         if (out == nullptr && workspace_bytes >= zq::kWsFixedBytes + row_bytes(M, N)) out = zq::ws_partials(workspace);
         in_kernel = out == nullptr;
     }
@@ -95,7 +95,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         a.q_out = out_q; a.q_scale_out = out_s_tok;
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
-    if (zq::launch_gemm(variant_of_call(variant, forced, M, N, K, w_bits), a, st) != hipSuccess) return ZQ_ERR_HIP;
+    if (zq::launch_gemm(variant_of_call(variant, forced, M, N, K, w_bits, workspace_bytes), a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
         if (zq::launch_rowquant(zq::kOpIdentity, out, nullptr, nullptr, 0.0f, M, N, out_q, out_s_tok, nullptr, 0,
@@ -196,7 +196,7 @@ size_t zq_gemm_quant_workspace_bytes(int M, int N, int K, int w_bits) {
     // the schedule of a caller who offers exactly `need` (a larger offer changes nothing)
     const int variant = zq_gemm_choose_variant(M, N, K, w_bits, need);
     if (is_tile_variant(variant) && zq::gemm_tile_quant_supported(M, N, zq::kWsFixedBytes)) {
-        const size_t rows = rows_beside_tiles(M, N, K, w_bits, false) ? row_bytes(M, N) : 0;
+        const size_t rows = rows_beside_tiles(M, N, K, w_bits, need, false) ? row_bytes(M, N) : 0;
         if (need < zq::kWsFixedBytes + rows) need = zq::kWsFixedBytes + rows;
     }
     return need;
@@ -249,9 +249,18 @@ static bool a16_tiles_with_split(int M, int N, int K) {
     return ks >= ((M <= kA16StreamTokens && (K % 256) == 0) ? 3 : 2);
 }
 
+// A cut of the streaming schedules that is registered for the shape, and whose K split the workspace can hold, goes
+// before the direct kernels.
+static bool a16_cut_registered(int M, int N, int K, size_t workspace_bytes) {
+    const int m = M < 64 ? M : 64;                // tokens of a streaming launch
+    int row_blocks = 0, k_splits = 0;
+    if (M > kA16StreamTokens || (K % 256) != 0 || !zq::tuned_stream_plan(m, N, K, 8, &row_blocks, &k_splits)) return false;
+    return k_splits == 1 || workspace_bytes >= zq::kWsFixedBytes + (size_t)k_splits * m * N * sizeof(float);
+}
+
 enum A16Route { kA16Direct, kA16Stream, kA16Tile };
 static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
-    if (zq::direct_pays(M, N, K, 8, 2)) return kA16Direct;
+    if (zq::direct_pays(M, N, K, 8, 2) && !a16_cut_registered(M, N, K, workspace_bytes)) return kA16Direct;
     if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16Tile;
     if (M <= kA16StreamTokens && (K % 256) == 0) return kA16Stream;
     return (long)M * N * K > (1L << 27) ? kA16Tile : kA16Direct;
@@ -397,7 +406,7 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
         bool forced;
         const int variant = class_of_call(M, N, K, w_bits, workspace_bytes, &forced);
         if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return nullptr;
-        return zq::gemm_schedule_name(variant_of_call(variant, forced, M, N, K, w_bits), M, N, K, w_bits);
+        return zq::gemm_schedule_name(variant_of_call(variant, forced, M, N, K, w_bits, workspace_bytes), M, N, K, w_bits);
     }
     switch (a16_route(M, N, K, workspace_bytes)) {
         case kA16Direct: return zq::gemm_direct_name(M, N, K, 8, 2);

@@ -47,10 +47,6 @@ bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_
     return true;
 }
 
-bool gemm_goes_direct(int M, int N, int K, int w_bits) {
-    TuneEntry e;
-    return direct_pays(M, N, K, w_bits, 1) && !tune_lookup(M, N, K, w_bits, &e);
-}
 
 size_t gemm_variant_workspace(int variant, int M, int N, int K, int w_bits) {
     if (variant == kGemmTileSplitK) return gemm_tile_split_workspace(M, N, K);
@@ -76,6 +72,12 @@ bool gemm_variant_supports(int variant, int M, int N, int K, int w_bits, size_t 
                    workspace_bytes >= gemm_variant_workspace(variant, M, N, K, w_bits);
     }
     return false;
+}
+
+bool gemm_goes_direct(int M, int N, int K, int w_bits, size_t workspace_bytes) {
+    TuneEntry e;
+    return direct_pays(M, N, K, w_bits, 1) &&
+           !(tune_lookup(M, N, K, w_bits, &e) && gemm_variant_supports(e.variant, M, N, K, w_bits, workspace_bytes));
 }
 
 namespace {

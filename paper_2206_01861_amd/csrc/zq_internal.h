@@ -120,9 +120,9 @@ bool gemm_tile_quant_supported(int M, int N, size_t workspace_bytes);
 hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st);
 
 // Whether the small-tile kernels of zq_gemm_direct.hip beat the streaming and the tiled ones; xb: bytes of an activation.
-// gemm_goes_direct: the same for INT8 activations, unless a schedule is registered for the shape.
+// gemm_goes_direct: the same for INT8 activations, unless a schedule is registered for the shape that the call can run.
 bool direct_pays(int M, int N, int K, int w_bits, int xb);
-bool gemm_goes_direct(int M, int N, int K, int w_bits);
+bool gemm_goes_direct(int M, int N, int K, int w_bits, size_t workspace_bytes);
 const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb);    // of the kernel that launch takes
 
 // Name of what launch_gemm runs for a variant (see zq_gemm_schedule).

@@ -50,3 +50,23 @@ def test_forced_schedule_and_shapes_no_call_takes():
     for bad in [(0, 16, 16, 8, 0, 8), (1, 24, 16, 8, 0, 8), (1, 16, 24, 8, 0, 8), (1, 16, 16, 4, 0, 8), (1, 16, 32, 4, 0, 16),
                 (1, 16, 16, 8, 0, 4), (1 << 20, 1 << 20, 1 << 20, 8, 0, 8)]:
         assert zq.gemm_schedule(*bad) is None, bad
+
+
+def test_a_table_entry_that_cannot_run_changes_nothing():
+    M, N, K = 1, 2048, 8192
+    for x_bits in (8, 16):
+        assert zq.gemm_schedule(M, N, K, 8, 0, x_bits=x_bits) == "direct"
+    zq.tune_set(1, 8, N, K, 8, 4, 64, 4)                         # a streaming cut with a K split
+    try:
+        need = {8: zq.gemm_workspace_bytes(M, N, K), 16: zq.gemm_w8a16_workspace_bytes(M, N, K)}
+        for x_bits in (8, 16):
+            assert zq.gemm_schedule(M, N, K, 8, need[x_bits], x_bits=x_bits) == "stream_splitk"
+            assert zq.gemm_schedule(M, N, K, 8, need[x_bits] - 1, x_bits=x_bits) == "direct"
+            assert zq.gemm_schedule(M, N, K, 8, 0, x_bits=x_bits) == "direct"
+        assert zq.gemm_schedule(9, N, K, 8, 0) == zq.gemm_schedule(9, N, K, 8, 1)       # outside the entry
+        zq.tune_set(1, 8, N, K, 8, 3, 64, 1)                     # a cut without one
+        for x_bits in (8, 16):
+            assert zq.gemm_schedule(M, N, K, 8, 0, x_bits=x_bits) == "stream"
+    finally:
+        zq.tune_clear()
+    assert zq.gemm_schedule(M, N, K, 8, 0, x_bits=16) == "direct"
