@@ -701,6 +701,29 @@ bool short_problem(int M, int N, int K, int xb) {
 
 }  // namespace
 
+// Up to 64 tokens and K no multiple of 256, which the streaming kernel does not take: against the LDS tiles, which split
+// K over workgroups for few rows where the workspace holds it.  The direct kernels are ahead nearly everywhere up to
+// 32 tokens; every workgroup of theirs goes through all of K, and with more tokens or rows their second round loses.  The
+// lines follow 43000 random shapes (256 to 32768 rows, K 256 to 28000); in microseconds, weights from memory, tiles /
+// direct kernels:
+//   INT8   6400x1600 at 27 tokens 7.4 / 4.8, 1600x6400 at 48 9.2 / 8.6; beyond: 4704x18816 at 57 24.2 / 45.3, 3200x9280
+//          at 64 16.0 / 17.9, 5600x5600 at 64 16.7 / 18.8, 5920x23680 at 30 31.2 / 36.2
+//   INT4   2400x9600 at 48 13.6 / 13.3; beyond: 4672x17632 at 63 23.8 / 47.3, 8000x8032 at 64 19.8 / 23.2, 5920x23680 at
+//          30 27.1 / 28.8
+//   W8A16  4800x1600 at 27 14.4 / 6.6, 16320x5440 at 64 43.4 / 34.4; beyond: 18240x6080 at 60 49.5 / 74.9, 22784x5696 at
+//          56 47.1 / 84.3
+bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
+    if (M <= 24) return xb == 2 || M <= 16 || K <= 16384 || N > 3072;
+    if (M <= 32) {
+        if (N > 20480 && K > 1024) return false;
+        return xb == 2 || K <= 12288 || (N > 2560 && K <= 16384);
+    }
+    if (N > 16384) return false;                        // more rows than 64 x 64 tiles cover in one round
+    if (xb == 2) return true;                           // (its tiles do not split K at so few tokens)
+    if (w_bits == 4) return K <= (N <= 1024 ? 9216 : N <= 4096 ? 10240 : N <= 10240 ? 6144 : 8192);
+    return K <= (N <= 4096 ? 9216 : N <= 10240 ? 4096 : 6144);
+}
+
 // Whether the kernels of this file beat the streaming and the tiled ones.
 //
 // Up to 32 tokens: the direct kernel against streaming (K a multiple of 256).  Its
@@ -730,9 +753,7 @@ bool short_problem(int M, int N, int K, int xb) {
 //   W8A16  6144x2048 at 64 10.6 / 8.6, at 128 18.7 / 10.5; 4800x1600 at 192 17.4 / 10.8; beyond: 7680x2560 at 64 12.6 /
 //          17.8, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
-    // K no multiple of 256: the streaming kernel does not take it (6400x1600 at 27 tokens 6.0 us, 12.2 on 128x128
-    // tiles), except where many tokens meet more rows than 64 x 64 tiles cover in one round.
-    if ((K % 256) != 0 && (M <= 32 || (M <= 64 && (N <= 16384 || xb == 2)))) return true;
+    if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
     if (M > 32) {
         double us, tile_us;
         if (short_problem(M, N, K, xb)) return true;

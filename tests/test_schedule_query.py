@@ -70,3 +70,18 @@ def test_a_table_entry_that_cannot_run_changes_nothing():
     finally:
         zq.tune_clear()
     assert zq.gemm_schedule(M, N, K, 8, 0, x_bits=16) == "direct"
+
+
+@pytest.mark.parametrize("M,N,K,bits,x_bits,direct", [
+    # the direct and small-tile kernels keep a ragged K where they are ahead ...
+    (27, 6400, 1600, 8, 8, True), (5, 1600, 6400, 8, 8, True), (48, 2400, 8224, 8, 8, True), (48, 2400, 9600, 4, 8, True),
+    (16, 5920, 23680, 8, 8, True), (24, 4704, 18816, 4, 8, True), (64, 16320, 5440, 8, 16, True), (24, 24000, 6000, 8, 16, True),
+    # ... and leave it to the tiles where K or the rows are too long for one round of them
+    (57, 4704, 18816, 8, 8, False), (64, 3200, 9280, 8, 8, False), (64, 5600, 5600, 8, 8, False), (30, 5920, 23680, 8, 8, False),
+    (24, 2400, 18816, 8, 8, False), (63, 4672, 17632, 4, 8, False), (64, 8000, 8032, 4, 8, False), (30, 5920, 23680, 4, 8, False),
+    (60, 18240, 6080, 8, 16, False), (56, 22784, 5696, 8, 16, False), (30, 24000, 6000, 8, 16, False),
+])
+def test_ragged_k_up_to_64_tokens(M, N, K, bits, x_bits, direct):
+    for ws in (0, 1 << 30):
+        name = zq.gemm_schedule(M, N, K, bits, ws, x_bits=x_bits)
+        assert name.startswith(("direct", "small") if direct else "tile"), name
