@@ -733,12 +733,17 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // splits K.  The lines below follow 130 shapes (1536 to 24576 rows, K 1024 to 24576) at 1 to 32 tokens; in
 // microseconds, streaming / direct:
 //   INT4   2048x8192 at 16 tokens 10.7 / 7.0, 8192x8192 at 32 (262 KB) 17.4 / 13.4, 16384x4096 at 8 11.1 / 9.9; beyond:
-//          4096x16384 at 24 (393 KB) 14.2 / 16.1, 16384x4096 at 32 (262 KB) 12.3 / 13.3
-//   W8A16  3072x4096 at 8 8.5 / 6.5, 6144x4096 at 16 (131 KB) 10.4 / 9.8; beyond: 12288x2048 at 12 (98 KB) 8.8 / 9.7
+//          4096x16384 at 24 (393 KB) 14.2 / 16.1, and more than 16 tokens against a second workgroup per compute unit:
+//          9216x2304 at 30 6.8 / 9.2, 16384x4096 at 32 12.3 / 13.3 (8192x2304 at 30 6.4 / 5.8)
+//   W8A16  3072x4096 at 8 8.5 / 6.5, 6144x4096 at 16 (131 KB) 10.4 / 9.8, 5120x4352 at 2 9.6 / 8.1, 12288x6144 at 2
+//          17.3 / 15.7; beyond: 12288x2048 at 12 (98 KB) 8.8 / 9.7, and with stages that do not fill the waves
+//          13824x4608 at 1 14.8 / 17.6, 9216x2304 at 2 7.8 / 9.3, 7680x2560 at 16 7.3 / 8.7
 //   INT8   2048x2048 at 1 4.2 / 3.6, 2560x10240 at 4 9.6 / 8.4, 16384x4096 at 1 16.8 / 13.7, 3072x6144 at 16 8.4 / 7.2,
 //          4096x2048 at 24 5.5 / 5.0; beyond: 4096x4096 at 16 5.9 / 6.4, 12288x4096 at 8 12.1 / 12.9, 24576x6144 at 64
 //          31.8 / 47.5.  Where the stages do not fill the waves (ten stages on eight), the second round is mostly empty:
 //          10240x2560 at 1 8.0 / 9.0.
+// A K of one or two stages leaves most of the waves without work (12144x256 at 39 3.9 / 4.8, 11632x512 at 30 3.9 / 5.0,
+// INT4 12304x256 at 36 4.0 / 5.0, W8A16 9184x256 at 35 5.0 / 6.6).
 //
 // More tokens, as long as one round of small tiles covers the output (choose_mid): streaming was built for a weight
 // stream that 128 tokens no longer are, and the LDS tiles leave most compute units idle or split K through memory.  The
@@ -746,37 +751,42 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // time, and, up to 64 tokens, where the matrix is large enough to keep the streaming kernel busy.  Microseconds,
 // what ran before / small tiles:
 //   INT8   2048x2048 at 64 tokens 6.5 / 4.9, at 128 10.7 / 5.7, at 256 9.2 / 6.6; 768x3072 at 128 12.8 / 5.9; 1600x6400
-//          at 128 14.3 / 10.0; 4096x4096 at 192 17.4 / 14.4; beyond: 7680x2560 at 64 9.5 / 11.4, 2048x8192 at 64 10.5 /
-//          12.2, 2560x10240 at 128 18.8 / 24.8, 2048x2048 at 512 (K tiles as good) 9.3 / 9.9
+//          at 128 14.3 / 10.0; 4096x4096 at 192 17.4 / 14.4; beyond: 7680x2560 at 64 9.5 / 11.4, 6912x2304 at 40 7.7 / 9.7,
+//          1792x6656 at 54 8.8 / 10.4, 2048x8192 at 64 10.5 / 12.2, 2560x10240 at 128 18.8 / 24.8, 2048x2048 at 512 (K tiles as good) 9.3 / 9.9
 //   INT4   2048x2048 at 128 10.7 / 5.3, 1024x4096 at 1024 18.4 / 10.7, 16384x4096 at 64 15.9 / 11.5, 6144x6144 at 64
-//          19.3 / 11.8, 2560x10240 at 256 26.6 / 21.1; beyond: 4096x16384 at 128 21.6 / 23.6
+//          19.3 / 11.8, 2560x10240 at 256 26.6 / 21.1; beyond: 4096x16384 at 128 21.6 / 23.6, 3072x12288 at 48 14.8 / 16.4,
+//          4096x11872 at 65 17.6 / 24.2, 4000x11584 at 200 23.3 / 27.0
 //   W8A16  6144x2048 at 64 10.6 / 8.6, at 128 18.7 / 10.5; 4800x1600 at 192 17.4 / 10.8; beyond: 7680x2560 at 64 12.6 /
-//          17.8, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
+//          17.8, 6912x2304 at 40 11.2 / 12.4, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
+    if (M <= 64 && ((K <= 256 && (w_bits == 8 || N > 4096)) || (K <= 512 && M > 16 && N > 4096))) return false;
     if (M > 32) {
         double us, tile_us;
         if (short_problem(M, N, K, xb)) return true;
         const MidShape shape = choose_mid(M, N, K, w_bits, xb, &us);
         if (shape == kMidShapes) return false;
         const bool int8 = w_bits == 8 && xb == 1;
-        if (K > (xb == 2 ? 4096 : w_bits == 4 ? 12288 : shape == kMid64x64 ? 5120 : M <= 64 || shape == kMid64x32 ? 6656 : 8192))
+        if (M <= 64) {
+            if (w_bits == 4) return K <= (N <= 1024 ? 8192 : 10240);
+            if ((long)N * K > (1L << 24) || (K > 1024 && N > (K <= 2048 ? 8192 : 4096))) return false;
+            return K <= (xb == 2 ? 3072 : shape == kMid64x64 ? 5120 : 6144);
+        }
+        if (K > (xb == 2 ? 4096 : w_bits == 4 ? (N <= 2560 ? 10240 : 8192) : shape == kMid64x64 ? 5120 :
+                 shape == kMid64x32 ? 6656 : 8192))
             return false;
-        if (M <= 64) return w_bits == 4 || (K % 256) != 0 || ((long)N * K <= (1L << 24) && (int8 || K <= 3072));
         choose_tile(xb == 2 ? kTileA16 : int8 ? kTileI8 : kTileI4, M, N, K, kAllTileShapes, &tile_us);
         return us < (int8 ? 0.94 : 1.0) * tile_us;
     }
     const long load = (long)M * K * xb * ((N + 32 * kCUs - 1) / (32 * kCUs));
     const bool one_round = N <= 32 * kCUs;
-    if (xb == 2) return load <= (one_round ? 131072 : 65536);
-    if (w_bits == 4) return load <= (one_round ? 270000 : 200000);
     const int stages = (K + kStageK - 1) / kStageK, last = stages % 8;
-    if (M <= 8) {
-        const bool filled = stages <= 8 || last == 0 || last > 4;
-        return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);
-    }
-    if (M <= 16) return K <= 2560 ? N <= 4096 : (K >= 5120 && N >= 2560 && one_round && load <= 131072);
-    return K <= 2048 && N <= 4096;
+    const bool filled = stages <= 8 || last == 0 || last > 4;
+    if (xb == 2) return load <= (one_round ? 131072 : 65536) && (filled || N <= (M <= 8 ? 6144 : 5120));
+    if (w_bits == 4) return load <= (one_round ? 270000 : 200000) && (one_round || M <= 16);
+    if (M <= 8) return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);
+    if (M <= 16) return K > 512 && (K <= 2560 ? N <= 4096 : (K >= 5120 && N >= 2560 && one_round && load <= 131072));
+    return K >= 1024 && K <= 2048 && N <= 4096;
 }
 
 namespace {

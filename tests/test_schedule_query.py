@@ -85,3 +85,20 @@ def test_ragged_k_up_to_64_tokens(M, N, K, bits, x_bits, direct):
     for ws in (0, 1 << 30):
         name = zq.gemm_schedule(M, N, K, bits, ws, x_bits=x_bits)
         assert name.startswith(("direct", "small") if direct else "tile"), name
+
+
+@pytest.mark.parametrize("M,N,K,bits,x_bits,want", [
+    # K a multiple of 256: the direct and small-tile kernels on one side of each line, streaming or the tiles on the other
+    (2, 5120, 4352, 8, 16, "direct"), (2, 12288, 6144, 8, 16, "direct"), (8, 6144, 2304, 8, 16, "direct"),
+    (1, 13824, 4608, 8, 16, "stream"), (2, 9216, 2304, 8, 16, "stream"), (16, 7680, 2560, 8, 16, "stream"),
+    (30, 8192, 2304, 4, 8, "direct"), (30, 9216, 2304, 4, 8, "stream"), (16, 9216, 2304, 4, 8, "direct"),
+    (48, 4096, 3072, 8, 8, "small"), (40, 6912, 2304, 8, 8, "stream"), (48, 6912, 2048, 8, 8, "small"),
+    (54, 1792, 6656, 8, 8, "stream"), (40, 6912, 2304, 8, 16, "stream"), (40, 4096, 2304, 8, 16, "small"),
+    (48, 2560, 10240, 4, 8, "small"), (48, 3072, 12288, 4, 8, "stream"), (100, 2560, 10240, 4, 8, "small"),
+    (65, 4096, 11872, 4, 8, "tile"), (200, 4000, 11584, 4, 8, "tile"),
+    (39, 12144, 256, 8, 8, "stream"), (30, 11632, 512, 8, 8, "stream"), (35, 9184, 256, 8, 16, "stream"),
+    (8, 4096, 256, 4, 8, "direct"), (8, 4096, 256, 8, 8, "stream"), (24, 2048, 1024, 8, 8, "direct"), (24, 2304, 768, 8, 8, "stream"),
+])
+def test_lines_between_the_direct_kernels_and_the_others(M, N, K, bits, x_bits, want):
+    name = zq.gemm_schedule(M, N, K, bits, 0, x_bits=x_bits)
+    assert name.startswith(want), name
