@@ -741,7 +741,8 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 //   INT8   2048x2048 at 1 4.2 / 3.6, 2560x10240 at 4 9.6 / 8.4, 16384x4096 at 1 16.8 / 13.7, 3072x6144 at 16 8.4 / 7.2,
 //          4096x2048 at 24 5.5 / 5.0; beyond: 4096x4096 at 16 5.9 / 6.4, 12288x4096 at 8 12.1 / 12.9, 24576x6144 at 64
 //          31.8 / 47.5.  Where the stages do not fill the waves (ten stages on eight), the second round is mostly empty:
-//          10240x2560 at 1 8.0 / 9.0.
+//          10240x2560 at 1 8.0 / 9.0.  Three strips per compute unit whose rows lie 4 KB apart meet on the same memory
+//          channels: 12288x4096 at 1 to 4 11.3 / 13.2 to 13.5 (12256x4608 13.0 / 12.4, 11520x3840 10.1 / 9.7).
 // A K of one or two stages leaves most of the waves without work (12144x256 at 39 3.9 / 4.8, 11632x512 at 30 3.9 / 5.0,
 // INT4 12304x256 at 36 4.0 / 5.0, W8A16 9184x256 at 35 5.0 / 6.6).
 //
@@ -784,7 +785,10 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     const bool filled = stages <= 8 || last == 0 || last > 4;
     if (xb == 2) return load <= (one_round ? 131072 : 65536) && (filled || N <= (M <= 8 ? 6144 : 5120));
     if (w_bits == 4) return load <= (one_round ? 270000 : 200000) && (one_round || M <= 16);
-    if (M <= 8) return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);
+    if (M <= 8) {
+        if (K % 4096 == 0 && N > 8192 && N <= 12288) return false;      // three strips per compute unit, rows 4 KB apart
+        return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);
+    }
     if (M <= 16) return K > 512 && (K <= 2560 ? N <= 4096 : (K >= 5120 && N >= 2560 && one_round && load <= 131072));
     return K >= 1024 && K <= 2048 && N <= 4096;
 }

@@ -97,6 +97,7 @@ def test_ragged_k_up_to_64_tokens(M, N, K, bits, x_bits, direct):
     (48, 2560, 10240, 4, 8, "small"), (48, 3072, 12288, 4, 8, "stream"), (100, 2560, 10240, 4, 8, "small"),
     (65, 4096, 11872, 4, 8, "tile"), (200, 4000, 11584, 4, 8, "tile"),
     (39, 12144, 256, 8, 8, "stream"), (30, 11632, 512, 8, 8, "stream"), (35, 9184, 256, 8, 16, "stream"),
+    (2, 12288, 4096, 8, 8, "stream"), (2, 12288, 3584, 8, 8, "direct"), (2, 16384, 4096, 8, 8, "direct"),
     (8, 4096, 256, 4, 8, "direct"), (8, 4096, 256, 8, 8, "stream"), (24, 2048, 1024, 8, 8, "direct"), (24, 2304, 768, 8, 8, "stream"),
 ])
 def test_lines_between_the_direct_kernels_and_the_others(M, N, K, bits, x_bits, want):
