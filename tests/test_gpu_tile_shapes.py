@@ -1,6 +1,6 @@
 """GPU parity of every tile shape of the tiled GeMM, at edges in M, N and K, in one round of workgroups and in several.
-The shape a call takes follows from its sizes; the sizes below reach all of them (128x64, 128x128, 192x128, 256x128,
-256x192, 256x256) for INT8 and INT4 weights and for FP16 activations."""
+The shape a call takes follows from its sizes; the cases of REACHED name the one they are for and ask the library
+whether they reach it (128x64, 128x128, 192x128, 256x128, 256x192, 256x256; INT8 and INT4 weights, FP16 activations)."""
 import pytest
 import torch
 
@@ -11,36 +11,77 @@ from test_gpu_gemm_a16 import _check as _check_a16
 
 pytestmark = pytest.mark.gpu
 
-# (variant, M, N, K, groups)
+# (variant, M, N, K, groups): one or a few tiles, K of a part of a stage to many
 SHAPES = [
-    (TILE128, 129, 80, 1056, 5), (TILE128, 333, 1040, 2080, 65), (TILE128, 200, 64, 32, 4),      # 128x64
-    (TILE128, 1300, 3088, 544, 193),                                                             # 128x128
-    (TILE256X128, 193, 144, 672, 9), (TILE256X128, 333, 1040, 2080, 65), (TILE256X128, 192, 128, 96, 8),   # 192x128
-    (TILE256X128, 2060, 4112, 160, 257),                                                         # 256x128, two rounds
-    (TILE256X128, 2048, 4096, 544, 64),                                                          # 256x128, one round
+    (TILE128, 129, 80, 1056, 5), (TILE128, 333, 1040, 2080, 65), (TILE128, 200, 64, 32, 4),
+    (TILE128, 1300, 3088, 544, 193),
+    (TILE256X128, 193, 144, 672, 9), (TILE256X128, 333, 1040, 2080, 65), (TILE256X128, 192, 128, 96, 8),
+    (TILE256X128, 2060, 4112, 160, 257),
+    (TILE256X128, 2048, 4096, 544, 64),
     (TILE256X192, 257, 208, 416, 13), (TILE256, 513, 272, 416, 17),
 ]
+VARIANT = {"tile128x64": TILE128, "tile128x128": TILE128, "tile192x128": TILE256X128, "tile256x128": TILE256X128,
+           "tile256x192": TILE256X192, "tile256x256": TILE256}
+# (tile, M, N, K, groups) per weight bits; 16: FP16 activations.  For each shape a case of one round and one of several
+# (more tiles than the 256 compute units), with a short last tile in M and N and a short last stage in K in most of them.
+REACHED = {
+    8: [("tile128x64", 165, 16, 80, 1), ("tile128x64", 2961, 1296, 160, 81), ("tile128x128", 137, 8304, 144, 519),
+        ("tile128x128", 1497, 4944, 112, 3), ("tile192x128", 333, 1040, 2080, 65), ("tile192x128", 2671, 4192, 80, 2),
+        ("tile256x128", 2990, 2080, 112, 130), ("tile256x128", 1550, 7392, 80, 7), ("tile256x192", 257, 208, 416, 13),
+        ("tile256x192", 1886, 6800, 96, 25), ("tile256x256", 513, 272, 416, 17), ("tile256x256", 2853, 6288, 80, 3)],
+    4: [("tile128x64", 412, 3248, 672, 29), ("tile128x64", 1703, 784, 672, 49), ("tile128x64", 2961, 1296, 160, 81),
+        ("tile128x128", 129, 80, 1056, 5), ("tile128x128", 2553, 3136, 96, 7), ("tile192x128", 193, 144, 672, 9),
+        ("tile192x128", 2803, 4240, 96, 5), ("tile256x128", 807, 7856, 96, 491), ("tile256x128", 2758, 4432, 96, 277),
+        ("tile256x192", 257, 208, 416, 13), ("tile256x192", 4016, 4368, 96, 3), ("tile256x256", 513, 272, 416, 17),
+        ("tile256x256", 2398, 8208, 96, 27)],
+    16: [("tile128x64", 4240, 400, 832, 25), ("tile128x64", 129, 7440, 1616, 5), ("tile128x128", 191, 4000, 176, 2),
+         ("tile128x128", 2321, 6608, 80, 7), ("tile192x128", 822, 5424, 144, 3), ("tile192x128", 2534, 6624, 80, 9),
+         ("tile256x128", 2385, 2608, 112, 163), ("tile256x128", 3249, 4880, 64, 5), ("tile256x192", 1982, 5184, 80, 4),
+         ("tile256x192", 3838, 5712, 64, 3), ("tile256x256", 4840, 2672, 80, 167), ("tile256x256", 3474, 7856, 64, 491)],
+}
 
 
-@pytest.mark.parametrize("bits", [8, 4])
-@pytest.mark.parametrize("variant,M,N,K,g", SHAPES)
-def test_tile_shape_against_oracle(zq, orc, bits, variant, M, N, K, g):
-    print("tile shape", variant, bits, M, N, K, g, flush=True)
-    xq, s_tok, s_w, bias, codes, wq = _case(zq_inputs.rng_for(4, 6000 + M + N + K + bits), M, N, K, g, bits)
+def _integers(zq, orc, variant, bits, M, N, K, g, seed):
+    xq, s_tok, s_w, bias, codes, wq = _case(zq_inputs.rng_for(4, seed + M + N + K + bits), M, N, K, g, bits)
     res = _run(zq, bits, variant, xq, s_tok, wq, s_w, bias)
     _check(orc, res, xq, s_tok, codes, s_w, bias, "tile %d %d-bit %dx%dx%d" % (variant, bits, M, N, K))
 
 
-# FP16 activations choose among the same shapes (above 64 tokens, K no multiple of 256): 128x64, 192x128, 128x128,
-# 256x128, 256x192, 256x256
-@pytest.mark.parametrize("M,N,K,g", [(129, 1040, 1040, 65), (333, 8208, 528, 27), (1025, 3088, 272, 193),
-                                     (2040, 4112, 400, 257), (2048, 6144, 208, 128), (4080, 4112, 208, 257)])
-def test_tile_shape_a16_against_oracle(zq, orc, M, N, K, g):
-    print("tile shape a16", M, N, K, g, flush=True)
-    rng = zq_inputs.rng_for(9, 6000 + M + N + K)
+def _fp16(zq, orc, M, N, K, g, seed):
+    rng = zq_inputs.rng_for(9, seed + M + N + K)
     x = zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=15.0)
     codes = zq_inputs.random_codes(rng, (N, K))
     s_w, bias = zq_inputs.random_scales(rng, g, 1e-4, 1e-2), zq_inputs.bias(rng, N)
     out = zq.zq_gemm_w8a16_dequant(dev(x), dev(codes), dev(s_w), dev(bias))
     torch.cuda.synchronize()
     _check_a16(orc, host(out), x, codes, s_w, bias, "tile a16 %dx%dx%d" % (M, N, K))
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("variant,M,N,K,g", SHAPES)
+def test_tile_shape_against_oracle(zq, orc, bits, variant, M, N, K, g):
+    print("tile shape", variant, bits, M, N, K, g, flush=True)
+    _integers(zq, orc, variant, bits, M, N, K, g, 6000)
+
+
+# FP16 activations over the limits between the shapes (K no multiple of 256)
+@pytest.mark.parametrize("M,N,K,g", [(129, 1040, 1040, 65), (333, 8208, 528, 27), (1025, 3088, 272, 193),
+                                     (2040, 4112, 400, 257), (2048, 6144, 208, 128), (4080, 4112, 208, 257)])
+def test_tile_shape_a16_against_oracle(zq, orc, M, N, K, g):
+    print("tile shape a16", M, N, K, g, flush=True)
+    _fp16(zq, orc, M, N, K, g, 6000)
+
+
+@pytest.mark.parametrize("bits,tile,M,N,K,g", [(b,) + c for b in sorted(REACHED) for c in REACHED[b]])
+def test_every_tile_shape_is_reached(zq, orc, bits, tile, M, N, K, g):
+    print("reached", bits, tile, M, N, K, g, flush=True)
+    if bits == 16:
+        assert zq.gemm_schedule(M, N, K, 8, 0, x_bits=16) == tile
+        _fp16(zq, orc, M, N, K, g, 6100)
+        return
+    before = zq.force_gemm_variant(VARIANT[tile])
+    try:
+        assert zq.gemm_schedule(M, N, K, bits, 0) == tile
+    finally:
+        zq.force_gemm_variant(before)
+    _integers(zq, orc, VARIANT[tile], bits, M, N, K, g, 6100)
