@@ -30,33 +30,58 @@ def _check(orc, out16, x, codes, s_w, bias, what, rows=None):
 
 
 SHAPES = [
-    # (M, N, K, groups): the untiled schedule (ragged K, M > 128) ...
+    # (M, N, K, groups): few tokens or few rows, K of one load to many stages ...
     (1, 16, 16, 1), (17, 768, 784, 48), (129, 96, 1024, 2), (70, 272, 208, 17),
-    # ... the streaming schedule, one to four token tiles, uneven strips ...
     (1, 64, 256, 4), (8, 6144, 2048, 128), (33, 144, 1792, 9), (64, 1024, 1536, 64), (16, 33040, 512, 5),
     (50, 16, 256, 1),
-    # ... the tiled schedules (128x128 and 256x256 tiles, ragged edges) ...
+    # ... some hundred tokens and more, ragged edges, K not a multiple of the stage depth ...
     (300, 400, 384, 25), (515, 1024, 1024, 64), (129, 272, 2048, 17), (2500, 4112, 512, 257),
-    (515, 1024, 400, 64), (300, 1040, 1008, 65),       # K not a multiple of the stage depth
+    (515, 1024, 400, 64), (300, 1040, 1008, 65),
     (2300, 7152, 336, 3),                              # 256x256 tiles (one round of 252), ragged in M, N and K
-    # ... and with a K split
+    # ... a long K
     (32, 2048, 8192, 128), (7, 528, 24576, 11), (64, 4112, 16384, 1), (1, 2048, 8192, 128),
-    # above 128 tokens with few tiles and a long K: the tiled schedule splits K (fp32 partials, second kernel)
     (130, 1024, 4096, 64), (300, 400, 2048, 25), (256, 2064, 2000, 3), (129, 272, 8192, 17),
-    # 65 to 128 tokens: two streaming launches over row halves (second half ragged, one row, full), also with a K split
+    # 65 to 128 tokens
     (65, 1024, 1536, 64), (100, 6144, 2048, 128), (128, 2064, 512, 3), (90, 2048, 8192, 128), (128, 528, 24576, 11),
+]
+# (schedule, workspace, M, N, K, groups); the workspace is the one that is asked for, none, or the streaming K split's only
+ROUTES = [
+    # the streaming schedule, one to four token tiles, uneven strips ...
+    ("stream", "asked", 2, 6576, 2816, 137), ("stream", "asked", 12, 544, 5632, 2), ("stream", "asked", 31, 528, 4352, 11),
+    ("stream", "asked", 60, 1040, 3584, 13), ("stream", "asked", 50, 4112, 2304, 1), ("stream", "none", 24, 144, 9728, 9),
+    # ... and with a K split (fp32 partials, added in the order of K)
+    ("stream_splitk", "asked", 11, 272, 9728, 17), ("stream_splitk", "asked", 27, 272, 5888, 1),
+    ("stream_splitk", "asked", 44, 528, 12032, 11),
+    # 65 to 128 tokens: two streaming launches over row halves (second half one row, ragged, full), also with a K split
+    ("stream_halves", "asked", 65, 19088, 768, 1193), ("stream_halves", "asked", 98, 12384, 768, 3),
+    ("stream_halves", "none", 128, 528, 9728, 33), ("stream_splitk_halves", "stream", 90, 2048, 8192, 128),
+    ("stream_splitk_halves", "stream", 65, 528, 24576, 11),
+    # the tiled schedule that splits K over workgroups (fp32 partials, second kernel)
+    ("tile128x128_splitk", "asked", 101, 528, 9728, 11), ("tile128x128_splitk", "asked", 245, 400, 5728, 25),
+    ("tile128x128_splitk", "asked", 129, 2064, 8192, 3), ("tile128x128_splitk", "asked", 300, 1024, 6000, 64),
 ]
 
 
 @pytest.mark.parametrize("M,N,K,g", SHAPES)
 def test_w8a16_against_oracle(zq, orc, M, N, K, g):
-    print("w8a16", M, N, K, g, flush=True)
+    _against_oracle(zq, orc, M, N, K, g, zq.gemm_w8a16_workspace_bytes(M, N, K))
+
+
+@pytest.mark.parametrize("name,workspace,M,N,K,g", ROUTES)
+def test_w8a16_reaches(zq, orc, name, workspace, M, N, K, g):
+    nbytes = {"asked": zq.gemm_w8a16_workspace_bytes(M, N, K), "none": 0,
+              "stream": zq.gemm_w8a16_workspace_bytes(64, N, K)}[workspace]
+    assert zq.gemm_schedule(M, N, K, 8, nbytes, x_bits=16) == name
+    _against_oracle(zq, orc, M, N, K, g, nbytes)
+
+
+def _against_oracle(zq, orc, M, N, K, g, nbytes):
+    print("w8a16", M, N, K, g, zq.gemm_schedule(M, N, K, 8, nbytes, x_bits=16), flush=True)
     rng = zq_inputs.rng_for(9, M + N + K)
     x = zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=15.0)
     codes = zq_inputs.random_codes(rng, (N, K))
     s_w = zq_inputs.random_scales(rng, g, 1e-4, 1e-2)
     bias = zq_inputs.bias(rng, N)
-    nbytes = zq.gemm_w8a16_workspace_bytes(M, N, K)
     ws = zq.new_workspace(nbytes)
     out = zq.zq_gemm_w8a16_dequant(dev(x), dev(codes), dev(s_w), dev(bias), workspace=ws)
     out2 = zq.zq_gemm_w8a16_dequant(dev(x), dev(codes), dev(s_w), dev(bias), workspace=ws)

@@ -32,10 +32,11 @@ def _capture(fn):
 def _eager_noise(zq):
     """Unrelated eager work between replays: a K-split GeMM and a front-end call of other shapes."""
     rng = zq_inputs.rng_for(3, 1)
-    xq = dev(zq_inputs.random_codes(rng, (8, 8192)))
+    xq = dev(zq_inputs.random_codes(rng, (16, 8192)))
     wq = dev(zq_inputs.random_codes(rng, (512, 8192)))
-    ws = zq.new_workspace(zq.gemm_workspace_bytes(8, 512, 8192, 8))
-    zq.zq_gemm_i8_dequant(xq, torch.ones(8, device="cuda"), wq, torch.ones(32, device="cuda"), workspace=ws)
+    ws = zq.new_workspace(zq.gemm_workspace_bytes(16, 512, 8192, 8))
+    assert zq.gemm_schedule(16, 512, 8192, 8, ws.numel()) == "stream_splitk"
+    zq.zq_gemm_i8_dequant(xq, torch.ones(16, device="cuda"), wq, torch.ones(32, device="cuda"), workspace=ws)
     zq.zq_quantize_tokenwise(torch.randn((33, 1024), device="cuda").half())
     torch.cuda.synchronize()
 

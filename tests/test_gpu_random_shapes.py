@@ -1,7 +1,7 @@
-"""GPU parity on seeded random shapes through the default dispatch: whatever schedule the library
-picks for a shape (streaming with or without K ranges and K splits, tiles, tiles with a K split,
-untiled), the INT32 accumulators equal the oracle's bit for bit and the FP16 output is within the
-tolerance, for INT8 and INT4 weights; the W8A16 call within its own tolerance."""
+"""GPU parity through the default dispatch: whatever schedule the library picks for a shape, the INT32 accumulators equal
+the oracle's bit for bit and the FP16 output is within the tolerance, for INT8 and INT4 weights; the W8A16 call within
+its own tolerance.  Seeded random shapes, most of which run the direct and small-tile kernels, and shapes that are known
+to reach each of the other schedules (ROUTES, whose names are asserted)."""
 import numpy as np
 import pytest
 import torch
@@ -43,12 +43,36 @@ def _shapes(seed, count):
 SHAPES = _shapes(20220601, 36)
 
 
+# (schedule, M, N, K, groups): streaming with one, two, four and eight token tiles, uneven strips, one and two K ranges;
+# its K split; tiles, and their K split with a ragged K, some hundred tokens and less than a tile of them
+ROUTES = {
+    8: [("stream", 1, 6336, 2304, 3), ("stream", 12, 64, 5376, 4), ("stream", 29, 64, 4608, 1), ("stream", 24, 4336, 2816, 271),
+        ("stream", 54, 4688, 2816, 293), ("stream", 93, 5792, 2560, 2), ("stream_splitk", 14, 96, 6656, 6),
+        ("stream_splitk", 27, 272, 11776, 17), ("stream_splitk", 60, 528, 11776, 3), ("tile128x64", 211, 3008, 1280, 47),
+        ("tile128x128", 135, 9584, 768, 599), ("tile192x128", 268, 5552, 288, 347), ("tile256x128", 240, 16832, 288, 263),
+        ("tile128x128_splitk", 29, 544, 12384, 17), ("tile128x128_splitk", 52, 528, 12512, 3),
+        ("tile128x128_splitk", 102, 528, 11264, 33), ("tile128x128_splitk", 157, 400, 10336, 5)],
+    4: [("stream", 7, 17824, 9984, 557), ("stream", 22, 11408, 1792, 23), ("stream", 48, 17536, 1280, 4),
+        ("stream", 87, 9472, 2304, 37), ("stream_splitk", 11, 9728, 12032, 4), ("stream_splitk", 27, 272, 11264, 17),
+        ("stream_splitk", 46, 528, 10752, 3), ("tile128x64", 335, 3888, 1024, 3), ("tile128x128", 381, 5328, 288, 9),
+        ("tile192x128", 312, 11056, 288, 691), ("tile256x128", 240, 16832, 288, 263),
+        ("tile128x128_splitk", 29, 544, 12384, 17), ("tile128x128_splitk", 62, 416, 11168, 13),
+        ("tile128x128_splitk", 92, 528, 10496, 3), ("tile128x128_splitk", 319, 400, 11424, 5)],
+}
+
+
+@pytest.mark.parametrize("bits,name,M,N,K,g", [(b,) + r for b in (8, 4) for r in ROUTES[b]])
+def test_default_dispatch_reaches(zq, orc, bits, name, M, N, K, g):
+    assert zq.gemm_schedule(M, N, K, bits, zq.gemm_workspace_bytes(M, N, K, bits)) == name
+    test_default_dispatch_against_oracle(zq, orc, bits, M, N, K, g)
+
+
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("M,N,K,g", SHAPES)
 def test_default_dispatch_against_oracle(zq, orc, bits, M, N, K, g):
     nbytes = zq.gemm_workspace_bytes(M, N, K, bits)
-    name = zq.gemm_variant_name(zq.gemm_choose_variant(M, N, K, bits, nbytes))
-    print("random", bits, M, N, K, g, name, flush=True)
+    name = zq.gemm_schedule(M, N, K, bits, nbytes)
+    print("default", bits, M, N, K, g, name, flush=True)
     rng = zq_inputs.rng_for(11, M + N + K + bits)
     xq = zq_inputs.random_codes(rng, (M, K))
     s_tok = zq_inputs.random_scales(rng, M, 5e-3, 0.3)
