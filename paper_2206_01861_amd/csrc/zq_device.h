@@ -162,6 +162,41 @@ __device__ __forceinline__ half8 cvt8_i8_f16(uint32_t lo, uint32_t hi) {
     return h - half8{bias, bias, bias, bias, bias, bias, bias, bias};
 }
 
+// Eight nibbles -> two words of int8 (value x16) in natural k order.
+__device__ __forceinline__ void unpack8_nat(uint32_t p, uint32_t &d0, uint32_t &d1) {
+    const uint32_t lo = (p << 4) & 0xf0f0f0f0u;   // k 0,2,4,6
+    const uint32_t hi = p & 0xf0f0f0f0u;          // k 1,3,5,7
+    d0 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);   // lo0 hi0 lo1 hi1
+    d1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);   // lo2 hi2 lo3 hi3
+}
+
+// Loads that are issued and awaited with explicit instructions.  The compiler's automatic wait insertion cannot count
+// loads that stay in flight across a loop back-edge and falls back to draining the whole queue (vmcnt(0)) at every use.  A
+// load written as an asm statement is not tracked by the compiler; the wait that covers it has to name the destination
+// registers as in/out operands (landed() does for a dword), so that no use of the data is scheduled above it, and
+// everything that touches them in between has to be unconditional, so that none of them is copied or merged in flight.
+constexpr uint32_t kRsrcFlags = 0x00020000u;      // raw 32-bit buffer, gfx9 encoding
+
+__device__ __forceinline__ uint32x4_t make_srd(const void *p, uint32_t bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    uint32x4_t d;
+    d[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
+    d[2] = __builtin_amdgcn_readfirstlane(bytes);    // bounds: reads past the matrix return 0, never fault
+    d[3] = kRsrcFlags;
+    return d;
+}
+template <int IMM>
+__device__ __forceinline__ void async_load16(int32x4 &dst, int voff, uint32x4_t srd, int soff) {
+    asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen offset:%4"
+                 : "=&v"(dst)
+                 : "v"(voff), "s"(srd), "s"(soff), "n"(IMM));
+}
+__device__ __forceinline__ void async_load_dword(uint32_t &dst, const void *p) {
+    asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p));
+}
+__device__ __forceinline__ void landed(uint32_t &v) { asm volatile("" : "+v"(v)); }
+
 // Activation fused into a GeMM epilogue: 0 none, 1 GeLU (erf form), 2 GeLU (tanh form).
 __device__ __forceinline__ float apply_activation(float f, int act) {
     if (act == 1) return gelu_erf(f);

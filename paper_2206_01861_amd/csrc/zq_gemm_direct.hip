@@ -34,45 +34,10 @@ namespace zq {
 
 namespace {
 
-constexpr uint32_t kRsrcFlags = 0x00020000u;   // raw 32-bit buffer, gfx9 encoding
 constexpr int kStageK = 256;                   // values of K per stage
 constexpr int kMidStageK = 128;                // ... and in gemm_mid_kernel
 constexpr int kCUs = 256;
 [[maybe_unused]] constexpr int kTileInts = 384;  // a 16x16 accumulator tile in LDS: four groups of columns, 96 ints apart
-
-typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32x4 make_srd(const void *p, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    uint32x4 d;
-    d[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
-    d[2] = __builtin_amdgcn_readfirstlane(bytes);    // bounds: reads past the matrix return 0, never fault
-    d[3] = kRsrcFlags;
-    return d;
-}
-
-// The loads are asm statements, so that they stay in flight across the loop's back-edge (the
-// compiler's own waits drain the queue there); the wait names the registers, so no use of the data can
-// be scheduled above it.
-template <int IMM>
-__device__ __forceinline__ void load16(int32x4 &dst, int voff, uint32x4 srd, int soff) {
-    asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen offset:%4"
-                 : "=&v"(dst)
-                 : "v"(voff), "s"(srd), "s"(soff), "n"(IMM));
-}
-__device__ __forceinline__ void load_dword(uint32_t &dst, const void *p) {
-    asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p));
-}
-__device__ __forceinline__ void landed(uint32_t &v) { asm volatile("" : "+v"(v)); }
-
-// Eight nibbles -> two words of int8 (value x16) in natural k order.
-__device__ __forceinline__ void unpack8_nat(uint32_t p, uint32_t &d0, uint32_t &d1) {
-    const uint32_t lo = (p << 4) & 0xf0f0f0f0u;   // k 0,2,4,6
-    const uint32_t hi = p & 0xf0f0f0f0u;          // k 1,3,5,7
-    d0 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);
-    d1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);
-}
 
 // One stage of one wave: LW weight loads per strip of 16 rows, LX activation loads per 16 tokens.
 template <int RT, int MT, int LW, int LX>
@@ -120,8 +85,8 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
     const int m_base = (int)blockIdx.y * 16 * MT;
 
     const int wrow = (WBITS == 8) ? K : K / 2;              // bytes of a weight row
-    const uint32x4 rs_w = make_srd(wq, (uint32_t)((size_t)N * wrow));
-    const uint32x4 rs_x = make_srd(xq, (uint32_t)((size_t)M * K * XB));
+    const uint32x4_t rs_w = make_srd(wq, (uint32_t)((size_t)N * wrow));
+    const uint32x4_t rs_x = make_srd(xq, (uint32_t)((size_t)M * K * XB));
     constexpr int kNowhere = 0x7ffffff0;                    // past the end of either buffer: loads give 0
     // Weight loads run chunk-fastest (lane = 4 * row + 16-byte chunk), so that four consecutive lanes read 64
     // contiguous bytes; one cross-lane permutation per register restores the operand layout (lane = row + 16
@@ -156,11 +121,11 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
         const int so_x = lim > 0 ? b * (8 / WBITS) * XB : 0;
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
-            load16<0>(s.w[t][0], wc < lim ? voff_w[t] : kNowhere, rs_w, so_w);
-            load16<64>(s.w[t][1], wc + 64 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+            async_load16<0>(s.w[t][0], wc < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+            async_load16<64>(s.w[t][1], wc + 64 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
             if constexpr (LW == 4) {
-                load16<128>(s.w[t][2], wc + 128 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
-                load16<192>(s.w[t][3], wc + 192 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+                async_load16<128>(s.w[t][2], wc + 128 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+                async_load16<192>(s.w[t][3], wc + 192 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
             }
         }
         // INT8 activations past the end of a row (less than a load) are whatever follows: their weights are zero.
@@ -170,26 +135,26 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
             const int xl = lim - (XB == 2 ? 16 * j : 0);
             const int v0 = 0 < xl ? voff_x[t] : kNowhere, v1 = 64 < xl ? voff_x[t] : kNowhere;
             if constexpr (WBITS == 4) {
-                load16<0>(s.x[t][0], v0, rs_x, so_x);
-                load16<16>(s.x[t][1], v0, rs_x, so_x);
-                load16<128>(s.x[t][2], v1, rs_x, so_x);
-                load16<144>(s.x[t][3], v1, rs_x, so_x);
+                async_load16<0>(s.x[t][0], v0, rs_x, so_x);
+                async_load16<16>(s.x[t][1], v0, rs_x, so_x);
+                async_load16<128>(s.x[t][2], v1, rs_x, so_x);
+                async_load16<144>(s.x[t][3], v1, rs_x, so_x);
             } else {
                 const int v2 = 128 < xl ? voff_x[t] : kNowhere, v3 = 192 < xl ? voff_x[t] : kNowhere;
                 if constexpr (XB == 1) {
-                    load16<0>(s.x[t][0], v0, rs_x, so_x);
-                    load16<64>(s.x[t][1], v1, rs_x, so_x);
-                    load16<128>(s.x[t][2], v2, rs_x, so_x);
-                    load16<192>(s.x[t][3], v3, rs_x, so_x);
+                    async_load16<0>(s.x[t][0], v0, rs_x, so_x);
+                    async_load16<64>(s.x[t][1], v1, rs_x, so_x);
+                    async_load16<128>(s.x[t][2], v2, rs_x, so_x);
+                    async_load16<192>(s.x[t][3], v3, rs_x, so_x);
                 } else {
-                    load16<0>(s.x[t][0], v0, rs_x, so_x);
-                    load16<16>(s.x[t][1], v0, rs_x, so_x);
-                    load16<128>(s.x[t][2], v1, rs_x, so_x);
-                    load16<144>(s.x[t][3], v1, rs_x, so_x);
-                    load16<256>(s.x[t][4], v2, rs_x, so_x);
-                    load16<272>(s.x[t][5], v2, rs_x, so_x);
-                    load16<384>(s.x[t][6], v3, rs_x, so_x);
-                    load16<400>(s.x[t][7], v3, rs_x, so_x);
+                    async_load16<0>(s.x[t][0], v0, rs_x, so_x);
+                    async_load16<16>(s.x[t][1], v0, rs_x, so_x);
+                    async_load16<128>(s.x[t][2], v1, rs_x, so_x);
+                    async_load16<144>(s.x[t][3], v1, rs_x, so_x);
+                    async_load16<256>(s.x[t][4], v2, rs_x, so_x);
+                    async_load16<272>(s.x[t][5], v2, rs_x, so_x);
+                    async_load16<384>(s.x[t][6], v3, rs_x, so_x);
+                    async_load16<400>(s.x[t][7], v3, rs_x, so_x);
                 }
             }
         }
@@ -263,9 +228,9 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
         int n = n_base + (t / MT) * 16 + 2 * (q % 8), m = m_base + (t % MT) * 16 + q / 8;
         if (n > N - 2) n = N - 2;
         if (m > M - 1) m = M - 1;
-        load_dword(e_sw[it], s_w + n / gs);
-        if constexpr (XB == 1) load_dword(e_st[it], s_tok + m);
-        load_dword(e_b[it], bias != nullptr ? static_cast<const void *>(bias + n) : s_w);
+        async_load_dword(e_sw[it], s_w + n / gs);
+        if constexpr (XB == 1) async_load_dword(e_st[it], s_tok + m);
+        async_load_dword(e_b[it], bias != nullptr ? static_cast<const void *>(bias + n) : s_w);
     }
     if constexpr (D == 2) {
         stage_wait<L>(st[0]);                               // (stricter than needed: the operands above are younger)

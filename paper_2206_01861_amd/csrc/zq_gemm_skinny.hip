@@ -46,7 +46,6 @@ namespace zq {
 
 namespace {
 
-constexpr uint32_t kRsrcFlags = 0x00020000u;   // raw 32-bit buffer, gfx9 encoding
 constexpr int kStageK = 256;                   // values of K per stage
 [[maybe_unused]] constexpr int kAuxDeviceCoherent = 0x10;        // sc1: coherent across the XCDs of the device
 constexpr int kMaxConsumers = 8;               // consumer waves per workgroup
@@ -77,31 +76,6 @@ __device__ __forceinline__ int32x4 permute_x4(int32x4 x) {
     return b;
 }
 
-// The weight stream is issued and awaited with explicit instructions.  The compiler's automatic
-// wait insertion cannot count loads that stay in flight across a loop back-edge and falls back
-// to draining the whole queue (vmcnt(0)) at every use, which would leave one stage in flight
-// instead of DW.  A load written as an asm statement is not tracked by the compiler; the
-// matching wait names the destination registers as in/out operands, so no use of the data can
-// be scheduled above it.
-typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32x4 make_srd(const void *p, uint32_t bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    uint32x4 d;
-    d[0] = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    d[1] = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32) & 0xffffu);
-    d[2] = __builtin_amdgcn_readfirstlane(bytes);    // bounds: reads past the matrix return 0, never fault
-    d[3] = kRsrcFlags;
-    return d;
-}
-
-template <int IMM>
-__device__ __forceinline__ void stream_load16(int32x4 &dst, int voff, uint32x4 srd, int soff) {
-    asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen offset:%4"
-                 : "=&v"(dst)
-                 : "v"(voff), "s"(srd), "s"(soff), "n"(IMM));
-}
-
 // Weight loads of a 16-row strip, 64 bytes of each row per load.  The vector cache works through a
 // load four lanes at a time and is fastest when those four lanes are contiguous in memory; in the
 // matrix-core operand layout (lane = row a of 16, 16-byte chunk b of 4: consecutive lanes are
@@ -109,12 +83,12 @@ __device__ __forceinline__ void stream_load16(int32x4 &dst, int voff, uint32x4 s
 // once the activation tile shares the cache (64 tokens).  So the loads run chunk-fastest (lane =
 // 4a + b) and one cross-lane permutation per register turns the result into the operand layout.
 template <int LW>
-__device__ __forceinline__ void issue_strip(int32x4 (&dst)[LW], int voff, uint32x4 srd, int soff) {
-    stream_load16<0>(dst[0], voff, srd, soff);
-    stream_load16<64>(dst[1], voff, srd, soff);
+__device__ __forceinline__ void issue_strip(int32x4 (&dst)[LW], int voff, uint32x4_t srd, int soff) {
+    async_load16<0>(dst[0], voff, srd, soff);
+    async_load16<64>(dst[1], voff, srd, soff);
     if (LW == 4) {
-        stream_load16<128>(dst[2], voff, srd, soff);
-        stream_load16<192>(dst[3], voff, srd, soff);
+        async_load16<128>(dst[2], voff, srd, soff);
+        async_load16<192>(dst[3], voff, srd, soff);
     }
 }
 // pull = 4 * (4 * (lane % 16) + lane / 16): byte address of the lane that holds (row lane%16, chunk lane/16).
@@ -126,14 +100,7 @@ __device__ __forceinline__ void strip_operands(const int32x4 (&w)[LW], int32x4 (
         for (int e = 0; e < 4; ++e) t[i][e] = __builtin_amdgcn_ds_bpermute(pull, w[i][e]);
 }
 
-// One dword fetched the same way (used for the operands of the epilogue): issued here, not tracked
-// by the compiler, usable only after a wait followed by landed().
-__device__ __forceinline__ void async_load_dword(uint32_t &dst, const void *p) {
-    asm volatile("global_load_dword %0, %1, off" : "=&v"(dst) : "v"(p));
-}
-// After a wait that covers it: from here on the register holds the loaded value.
-__device__ __forceinline__ void landed(uint32_t &v) { asm volatile("" : "+v"(v)); }
-
+// The weight stream's wait: DW stages stay in flight (zq_device.h, async_load16).
 template <int N, int LW>
 __device__ __forceinline__ void stream_wait(int32x4 (&w)[LW]) {
     if (LW == 4)
@@ -253,7 +220,7 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_kernel(
 
     // ---- consumers: weight strip through registers ------------------------
     const int wrow_bytes = (WBITS == 8) ? K : K / 2;
-    const uint32x4 rs_w = make_srd(wq, (uint32_t)((size_t)N * wrow_bytes));
+    const uint32x4_t rs_w = make_srd(wq, (uint32_t)((size_t)N * wrow_bytes));
     constexpr int W_STAGE_BYTES = (WBITS == 8) ? kStageK : kStageK / 2;   // bytes of a row per stage
     const int voff_w = (int)((uint32_t)(strip * 16 + lane / 4) * (uint32_t)wrow_bytes + (uint32_t)((lane % 4) * 16));
     const int pull = 4 * (4 * r + j);
@@ -549,7 +516,7 @@ __global__ __launch_bounds__(64 * (kMaxConsumers + 1)) void gemm_stream_a16_kern
     }
 
     // ---- consumers: INT8 weight strip through registers ----------------------
-    const uint32x4 rs_w = make_srd(wq, (uint32_t)((size_t)N * K));
+    const uint32x4_t rs_w = make_srd(wq, (uint32_t)((size_t)N * K));
     // Operand layout straight from memory (lane = row r, chunk j).  The chunk-fastest loads of the
     // INT8 kernel measured 5-10 % slower here: the conversion and the twice as large activation
     // fragments already load the vector and LDS pipes that the extra permutations would use.

@@ -55,7 +55,6 @@ namespace zq {
 
 namespace {
 
-constexpr uint32_t kRsrcFlags = 0x00020000u;
 typedef __attribute__((address_space(3))) void lds_void;
 
 // Chunk swizzle: 16 consecutive rows reading the same logical chunk hit 16 different bank groups.
@@ -67,14 +66,6 @@ __device__ __forceinline__ int swz(int row) {
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0f70 | (N & 15) | ((N >> 4) << 14));
-}
-
-// Eight nibbles -> two words of int8 (value x16) in natural k order.
-__device__ __forceinline__ void unpack8_nat(uint32_t p, uint32_t &d0, uint32_t &d1) {
-    const uint32_t lo = (p << 4) & 0xf0f0f0f0u;   // k 0,2,4,6
-    const uint32_t hi = p & 0xf0f0f0f0u;          // k 1,3,5,7
-    d0 = __builtin_amdgcn_perm(hi, lo, 0x05010400u);   // lo0 hi0 lo1 hi1
-    d1 = __builtin_amdgcn_perm(hi, lo, 0x07030602u);   // lo2 hi2 lo3 hi3
 }
 
 // In-kernel output quantization (QOUT = 1).  The tiles that share a band of token rows publish
