@@ -121,14 +121,19 @@ def _check(code):
 
 # A call at the smallest sizes is host time (LayerNorm+quant and a 768x768 GeMM at 128 tokens: 23.9 us issued call by
 # call, 18.3 with the three points below; replayed as a graph 5.6): addresses go to ctypes as plain numbers (the argument
-# types convert them), the current stream is read without building a Stream object, and what was allocated here is not
-# checked again.
+# types convert them), the current stream is read without building a Stream object (by a function that torch does not
+# document; the public call does where a torch has none), and what was allocated here is not checked again.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev(t, dtype, name):
