@@ -277,7 +277,7 @@ hipError_t launch_dequant(const int32_t *acc, const float *s_tok, const float *s
 // Group-wise weight quantization.  A group is a contiguous chunk of gs*K fp16
 // values.
 //
-// Groups of up to 16 MB: wq_group_kernel, one pass over the weights.  A group
+// Groups of up to 16 MB, as a rule (one_pass_pays): wq_group_kernel, one pass over the weights.  A group
 // is cut into slices of at most 64 KB, one workgroup each, which keeps its
 // slice in registers while the workgroups of the group agree on their maximum.
 // Bound: HBM, 2 + bits/8 bytes per weight.  Up to five workgroups on a compute
@@ -303,7 +303,7 @@ hipError_t launch_dequant(const int32_t *acc, const float *s_tok, const float *s
 // reads the whole group for the maximum itself, so that the result never
 // depends on it.
 //
-// Larger groups: clear, absmax (integer atomic max on the fp32 bit pattern,
+// Else: clear, absmax (integer atomic max on the fp32 bit pattern,
 // exact and order independent), quantize, and turn absmax into the scale in
 // place; the weights are read twice.  s_w is the scratch here.
 // ---------------------------------------------------------------------------
@@ -500,13 +500,28 @@ static hipError_t launch_wq_group(const void *w, long chunk_vecs, int groups, in
     return hipGetLastError();
 }
 
+// One pass where it is faster than two, measured over 3700 sizes (1 to 300 groups of 0.2 to 255 slices, weights from HBM).
+// The time of two passes over time of one:  slices 8, 32, 64, 96, 128, 192, 255
+//     1 group     0.9  1.0  1.1  1.2  1.3  1.3  1.4         12 groups   2.0  3.1  2.1  1.5  1.2  0.7  0.6
+//     4 groups    1.2  1.8  2.4  2.0  1.7  1.2  0.9         48 groups   2.6  1.9  1.2  0.9  0.8  0.6  0.5
+// A few slices in all are too little work for the exchange.  A group of many slices leaves the chip together when its last
+// one has arrived, and the next groups' loads start together: some 5 workgroups per compute unit hold the loads of later
+// groups only while a group is a small part of them (INT8 12800x12640 in 25 groups 182 us in two passes, 360 in one; INT4
+// 16x14336 in one group 8.2 and 10.0).
+static bool one_pass_pays(int groups, long slices, int cus) {
+    if (slices > (cus < kWqMaxSlices ? cus : kWqMaxSlices)) return false;
+    if (slices == 1) return true;
+    if (groups <= 3 && groups * slices < 32) return false;
+    return slices <= 80 || groups * slices <= (2500 - 7 * slices) * cus / 256;
+}
+
 template <int BITS>
 static hipError_t launch_wq(const void *w, int N, int K, int groups, bool wait, void *wq, float *s_w, hipStream_t st) {
     const long chunk_vecs = (long)(N / groups) * K / 8;
     // the slices of a group have to run at once: each needs a fifth of a compute unit's registers, so one per compute
     // unit always fits
     const int cus = compute_units();
-    if (chunk_vecs <= (long)kWqThreads * kWqVecs * (cus < kWqMaxSlices ? cus : kWqMaxSlices)) {
+    if (one_pass_pays(groups, (chunk_vecs + kWqThreads * kWqVecs - 1) / (kWqThreads * kWqVecs), cus)) {
         const int polls = wait ? kWqPolls : 0;
         if (chunk_vecs <= kWqThreads * 4) return launch_wq_group<BITS, 4>(w, chunk_vecs, groups, polls, wq, s_w, st);
         if (chunk_vecs <= kWqThreads * 8) return launch_wq_group<BITS, 8>(w, chunk_vecs, groups, polls, wq, s_w, st);
