@@ -1063,8 +1063,9 @@ int tile_splits(int M, int N, int K, int x_bytes) {
 // tiles) x (time of a tile): a + rounds * stages * b + (rounds - 1) * c microseconds, with a stage of 128 bytes of an
 // activation row.  b grows from b0, with few compute units at work, to b1 with all of them (power, L2 and memory shared):
 // the last, partly filled round is charged in between.  Fitted to 317 shapes each (72 to 8192 tokens, 768 to 24576
-// columns, K 768 to 24576; 70 for FP16 activations): within 3 to 9 % rms, and the choice by it costs 0.1 to 0.4 % on
-// average over the best shape.
+// columns, K 768 to 24576; 70 for FP16 activations).  Against 7151 random shapes its error is 5 to 15 % rms (most where
+// weights from memory meet few tokens); the choice by it costs 0.1 % (INT8), 0.5 % (INT4) and 2.9 % (FP16 activations) on
+// average over the best shape, 4, 5 and 20 % in one of a hundred.
 // What the smaller shapes are for, INT8, in microseconds: 128x64 and 128x128 fill the chip at some hundred tokens
 // (4096x4096 at 333 tokens: 15.6 on 128x64 tiles, 20.2 on 128x128, 41 on 256x192), 192x128 and 256x128 carry a third
 // stage in flight, which tiles of 256x192 have no LDS for and weights that come from HBM need (12288x4096 at 333: 28.2 on
