@@ -500,18 +500,17 @@ static hipError_t launch_wq_group(const void *w, long chunk_vecs, int groups, in
     return hipGetLastError();
 }
 
-// One pass where it is faster than two, measured over 4000 sizes (1 to 300 groups of 0.2 to 255 slices, weights from HBM).
-// The time of two passes over time of one:  slices 8, 32, 64, 96, 128, 192, 255
+// One pass where it is faster than two, measured over 4000 sizes (1 to 300 groups of 0.2 to 255 slices, weights from HBM,
+// replayed graphs).  The time of two passes over time of one:  slices 8, 32, 64, 96, 128, 192, 255
 //     1 group     0.9  1.0  1.1  1.2  1.3  1.3  1.4         12 groups   2.0  3.1  2.1  1.5  1.2  0.7  0.6
 //     4 groups    1.2  1.8  2.4  2.0  1.7  1.2  0.9         48 groups   2.6  1.9  1.2  0.9  0.8  0.6  0.5
-// A few slices in all are too little work for the exchange.  A group of many slices leaves the chip together when its last
-// one has arrived, and the next groups' loads start together: some 5 workgroups per compute unit hold the loads of later
-// groups only while a group is a small part of them (INT8 12800x12640 in 25 groups 182 us in two passes, 360 in one; INT4
-// one group of 229376 weights 8.2 and 10.0).
+// A group of many slices leaves the chip together when its last one has arrived, and the next groups' loads start together:
+// some 5 workgroups per compute unit hold the loads of later groups only while a group is a small part of them (INT8
+// 12800x12640 in 25 groups 182 us in two passes, 360 in one).  A few slices in all are too little work for the exchange (one
+// group of 229376 INT4 weights 8.2 us in two passes, 10.0 in one), but issued as a call of its own, as weights are, that is
+// two launches instead of four: 12.1 and 7.9.
 static bool one_pass_pays(int groups, long slices, int cus) {
     if (slices > (cus < kWqMaxSlices ? cus : kWqMaxSlices)) return false;
-    if (slices == 1) return true;
-    if (groups <= 3 && groups * slices < 32) return false;
     return slices <= 80 || groups * slices <= (2500 - 7 * slices) * cus / 256;
 }
 
