@@ -39,21 +39,10 @@ bool good_shape(int M, int N, int K, int w_bits, int x_bytes) {
     return (uint64_t)M * K * x_bytes < kMaxOperandBytes && (uint64_t)N * K * w_bits / 8 < kMaxOperandBytes;
 }
 
-// The schedule that is forced, else the class chosen for the shape; and what a call of that class runs.
-int class_of_call(int M, int N, int K, int w_bits, size_t workspace_bytes, bool *forced) {
-    const int variant = g_forced_variant.load();
-    *forced = variant >= 0;
-    return *forced ? variant : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
-}
-int variant_of_call(int variant, bool forced, int M, int N, int K, int w_bits, size_t workspace_bytes) {
-    return !forced && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes) ? zq::kGemmSimple : variant;
-}
-
-// Up to 64 tokens of a tiled class (K no multiple of 256) that the direct kernels are ahead of: the output rows are
-// quantized by the second kernel, from FP16 rows that stand in the workspace if the caller has no use for them.
-bool rows_beside_tiles(int M, int N, int K, int w_bits, size_t workspace_bytes, bool forced) {
-    return M <= 64 && !forced && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes);
-}
+// Few tokens of a tiled class (K no multiple of 256) that the direct kernels are ahead of: these and the row quantizer
+// together are faster than tiles that quantize in the kernel (GeLU and quantizer, weights from memory, us: 27x6400x1600
+// 15.7 -> 7.6, INT4 17.6 -> 7.2; 60x8192x2080 21.9 -> 14.4); a call that wants no FP16 rows has them in the workspace.
+bool rows_beside_tiles(int M) { return M <= 64; }
 size_t row_bytes(int M, int N) { return (size_t)M * N * sizeof(uint16_t); }
 
 zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, const float *s_w, int groups,
@@ -72,19 +61,22 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         return ZQ_ERR_ALIGN;
     if (workspace == nullptr) workspace_bytes = 0;
 
-    bool forced;
-    const int variant = class_of_call(M, N, K, w_bits, workspace_bytes, &forced);
-    if (forced && !zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
-    // On the tiled schedules the output rows are quantized inside the GeMM kernel.
-    bool in_kernel = out_q != nullptr && g_in_kernel_quant.load() != 0 && is_tile_variant(variant) &&
+    const int forced = g_forced_variant.load();
+    if (forced >= 0 && !zq::gemm_variant_supports(forced, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
+    const bool direct = forced < 0 && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes);
+    // The class of the shape says whether the output rows are quantized inside the GeMM kernel (the tiled schedules do
+    // that), also where the direct kernels would be ahead of the plain call; other direct calls have no use for it.
+    const bool beside = direct && rows_beside_tiles(M);
+    const int cls = forced >= 0 ? forced
+                    : direct && (out_q == nullptr || (beside && out != nullptr))
+                        ? (int)zq::kGemmSimple
+                        : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
+    bool in_kernel = out_q != nullptr && g_in_kernel_quant.load() != 0 && is_tile_variant(cls) &&
                      zq::gemm_tile_quant_supported(M, N, workspace_bytes);
     if (out == nullptr && !in_kernel) return ZQ_ERR_UNSUPPORTED;
-    // ... except for few tokens, where the direct kernels and the row quantizer together are faster (GeLU and quantizer,
-    // weights from memory, us: 27x6400x1600 15.7 -> 7.6, INT4 17.6 -> 7.2; 60x8192x2080 21.9 -> 14.4); a call that wants
-    // no FP16 rows has them in the workspace.
-    if (in_kernel && rows_beside_tiles(M, N, K, w_bits, workspace_bytes, forced)) {
-        if (out == nullptr && workspace_bytes >= zq::kWsFixedBytes + row_bytes(M, N)) out = zq::ws_partials(workspace);
-        in_kernel = out == nullptr;
+    if (in_kernel && beside && workspace_bytes >= zq::kWsFixedBytes + row_bytes(M, N)) {
+        out = zq::ws_partials(workspace);
+        in_kernel = false;
     }
     zq::GemmArgs a;
     a.xq = xq; a.s_tok = s_tok; a.wq = wq; a.s_w = s_w; a.groups = groups; a.bias = bias;
@@ -95,7 +87,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         a.q_out = out_q; a.q_scale_out = out_s_tok;
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
-    if (zq::launch_gemm(variant_of_call(variant, forced, M, N, K, w_bits, workspace_bytes), a, st) != hipSuccess) return ZQ_ERR_HIP;
+    if (zq::launch_gemm(direct ? (int)zq::kGemmSimple : cls, a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
         if (zq::launch_rowquant(zq::kOpIdentity, out, nullptr, nullptr, 0.0f, M, N, out_q, out_s_tok, nullptr, 0,
@@ -196,7 +188,8 @@ size_t zq_gemm_quant_workspace_bytes(int M, int N, int K, int w_bits) {
     // the schedule of a caller who offers exactly `need` (a larger offer changes nothing)
     const int variant = zq_gemm_choose_variant(M, N, K, w_bits, need);
     if (is_tile_variant(variant) && zq::gemm_tile_quant_supported(M, N, zq::kWsFixedBytes)) {
-        const size_t rows = rows_beside_tiles(M, N, K, w_bits, need, false) ? row_bytes(M, N) : 0;
+        const bool beside = rows_beside_tiles(M) && zq::gemm_goes_direct(M, N, K, w_bits, need);
+        const size_t rows = beside ? row_bytes(M, N) : 0;
         if (need < zq::kWsFixedBytes + rows) need = zq::kWsFixedBytes + rows;
     }
     return need;
@@ -403,10 +396,13 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
     if ((w_bits != 8 && w_bits != 4) || (x_bits != 8 && (x_bits != 16 || w_bits != 8))) return nullptr;
     if (!good_shape(M, N, K, w_bits, x_bits / 8) || (N % 16) != 0) return nullptr;
     if (x_bits == 8) {
-        bool forced;
-        const int variant = class_of_call(M, N, K, w_bits, workspace_bytes, &forced);
+        int variant = g_forced_variant.load();
+        if (variant < 0)
+            variant = zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes)
+                          ? (int)zq::kGemmSimple
+                          : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
         if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return nullptr;
-        return zq::gemm_schedule_name(variant_of_call(variant, forced, M, N, K, w_bits, workspace_bytes), M, N, K, w_bits);
+        return zq::gemm_schedule_name(variant, M, N, K, w_bits);
     }
     switch (a16_route(M, N, K, workspace_bytes)) {
         case kA16Direct: return zq::gemm_direct_name(M, N, K, 8, 2);

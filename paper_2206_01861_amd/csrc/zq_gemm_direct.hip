@@ -673,22 +673,19 @@ bool short_problem(int M, int N, int K, int xb) {
 // 32 tokens; every workgroup of theirs goes through all of K, and with more tokens or rows their second round loses.  The
 // lines follow 43000 random shapes (256 to 32768 rows, K 256 to 28000); in microseconds, weights from memory, tiles /
 // direct kernels:
-//   INT8   6400x1600 at 27 tokens 7.4 / 4.8, 1600x6400 at 48 9.2 / 8.6; beyond: 4704x18816 at 57 24.2 / 45.3, 3200x9280
-//          at 64 16.0 / 17.9, 5600x5600 at 64 16.7 / 18.8, 5920x23680 at 30 31.2 / 36.2
-//   INT4   2400x9600 at 48 13.6 / 13.3; beyond: 4672x17632 at 63 23.8 / 47.3, 8000x8032 at 64 19.8 / 23.2, 5920x23680 at
-//          30 27.1 / 28.8
+//   INT8   6400x1600 at 27 tokens 7.4 / 4.8, 1600x6400 at 48 9.2 / 8.6; beyond: 4704x18816 at 57 24.2 / 45.3, 3008x12000
+//          at 64 17.5 / 23.7, 5920x23680 at 30 31.2 / 36.2
+//   INT4   2400x9600 at 48 13.6 / 13.3; beyond: 4672x17632 at 63 23.8 / 47.3, 5920x23680 at 30 27.1 / 28.8
 //   W8A16  4800x1600 at 27 14.4 / 6.6, 16320x5440 at 64 43.4 / 34.4; beyond: 18240x6080 at 60 49.5 / 74.9, 22784x5696 at
 //          56 47.1 / 84.3
+// A K split is a second launch, some 4 us of host time in a program that issues its calls one by one (a 5600x5600 linear
+// with quantized output at 64 tokens: 24.1 us a pass direct, 28.1 split; in a graph 18.8 and 16.7), so it has to win by more.
 bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
-    if (M <= 24) return xb == 2 || M <= 16 || K <= 16384 || N > 3072;
-    if (M <= 32) {
-        if (N > 20480 && K > 1024) return false;
-        return xb == 2 || K <= 12288 || (N > 2560 && K <= 16384);
-    }
+    if (M <= 24) return true;
+    if (M <= 32) return (N <= 20480 || K <= 1024) && (xb == 2 || K <= 16384);
     if (N > 16384) return false;                        // more rows than 64 x 64 tiles cover in one round
     if (xb == 2) return true;                           // (its tiles do not split K at so few tokens)
-    if (w_bits == 4) return K <= (N <= 1024 ? 9216 : N <= 4096 ? 10240 : N <= 10240 ? 6144 : 8192);
-    return K <= (N <= 4096 ? 9216 : N <= 10240 ? 4096 : 6144);
+    return K <= (w_bits == 4 ? (N <= 4096 ? 12288 : 8192) : (N <= 4096 ? 10240 : 6144));
 }
 
 // Whether the kernels of this file beat the streaming and the tiled ones.
@@ -740,7 +737,7 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
             if ((long)N * K > (1L << 24) || (K > 1024 && N > (K <= 2048 ? 8192 : 4096))) return false;
             return K <= (xb == 2 ? 3072 : shape == kMid64x64 ? 5120 : 6144);
         }
-        if (K > (xb == 2 ? 4096 : w_bits == 4 ? (N <= 2560 ? 10240 : 8192) : shape == kMid64x64 ? 5120 :
+        if (K > (xb == 2 ? 4096 : w_bits == 4 ? (N <= 3072 ? 12288 : 9216) : shape == kMid64x64 ? 5120 :
                  shape == kMid64x32 ? 6656 : 8192))
             return false;
         choose_tile(xb == 2 ? kTileA16 : int8 ? kTileI8 : kTileI4, M, N, K, kAllTileShapes, &tile_us);

@@ -50,14 +50,14 @@ ROUTES = {
         ("stream", 54, 4688, 2816, 293), ("stream", 93, 5792, 2560, 2), ("stream_splitk", 14, 96, 6656, 6),
         ("stream_splitk", 27, 272, 11776, 17), ("stream_splitk", 60, 528, 11776, 3), ("tile128x64", 211, 3008, 1280, 47),
         ("tile128x128", 135, 9584, 768, 599), ("tile192x128", 268, 5552, 288, 347), ("tile256x128", 240, 16832, 288, 263),
-        ("tile128x128_splitk", 29, 544, 12384, 17), ("tile128x128_splitk", 52, 528, 12512, 3),
+        ("tile128x128_splitk", 29, 544, 16992, 17), ("tile128x128_splitk", 52, 528, 12512, 3),
         ("tile128x128_splitk", 102, 528, 11264, 33), ("tile128x128_splitk", 157, 400, 10336, 5)],
     4: [("stream", 7, 17824, 9984, 557), ("stream", 22, 11408, 1792, 23), ("stream", 48, 17536, 1280, 4),
         ("stream", 87, 9472, 2304, 37), ("stream_splitk", 11, 9728, 12032, 4), ("stream_splitk", 27, 272, 11264, 17),
         ("stream_splitk", 46, 528, 10752, 3), ("tile128x64", 335, 3888, 1024, 3), ("tile128x128", 381, 5328, 288, 9),
         ("tile192x128", 312, 11056, 288, 691), ("tile256x128", 240, 16832, 288, 263),
-        ("tile128x128_splitk", 29, 544, 12384, 17), ("tile128x128_splitk", 62, 416, 11168, 13),
-        ("tile128x128_splitk", 92, 528, 10496, 3), ("tile128x128_splitk", 319, 400, 11424, 5)],
+        ("tile128x128_splitk", 29, 544, 16992, 17), ("tile128x128_splitk", 62, 416, 12704, 13),
+        ("tile128x128_splitk", 92, 528, 12800, 3), ("tile128x128_splitk", 319, 400, 12640, 5)],
 }
 
 
