@@ -676,13 +676,16 @@ bool short_problem(int M, int N, int K, int xb) {
 //   INT8   6400x1600 at 27 tokens 7.4 / 4.8, 1600x6400 at 48 9.2 / 8.6; beyond: 4704x18816 at 57 24.2 / 45.3, 3008x12000
 //          at 64 17.5 / 23.7, 5920x23680 at 30 31.2 / 36.2
 //   INT4   2400x9600 at 48 13.6 / 13.3; beyond: 4672x17632 at 63 23.8 / 47.3, 5920x23680 at 30 27.1 / 28.8
-//   W8A16  4800x1600 at 27 14.4 / 6.6, 16320x5440 at 64 43.4 / 34.4; beyond: 18240x6080 at 60 49.5 / 74.9, 22784x5696 at
-//          56 47.1 / 84.3
+//   W8A16  4800x1600 at 27 14.4 / 6.6, 24000x6000 at 30 52.7 / 49.8, 16320x5440 at 64 43.4 / 34.4; beyond: 18240x6080 at 60
+//          49.5 / 74.9, 22784x5696 at 56 47.1 / 84.3
 // A K split is a second launch, some 4 us of host time in a program that issues its calls one by one (a 5600x5600 linear
 // with quantized output at 64 tokens: 24.1 us a pass direct, 28.1 split; in a graph 18.8 and 16.7), so it has to win by more.
 bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
     if (M <= 24) return true;
-    if (M <= 32) return (N <= 20480 || K <= 1024) && (xb == 2 || K <= 16384);
+    if (M <= 32) {
+        if (N > 24576 && K > 1024) return false;        // the fourth workgroup of a compute unit
+        return xb == 2 ? N <= 16384 || K <= 1024 || K > 4096 : K <= 16384;
+    }
     if (N > 16384) return false;                        // more rows than 64 x 64 tiles cover in one round
     if (xb == 2) return true;                           // (its tiles do not split K at so few tokens)
     return K <= (w_bits == 4 ? (N <= 4096 ? 12288 : 8192) : (N <= 4096 ? 10240 : 6144));
@@ -698,15 +701,16 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // microseconds, streaming / direct:
 //   INT4   2048x8192 at 16 tokens 10.7 / 7.0, 8192x8192 at 32 (262 KB) 17.4 / 13.4, 16384x4096 at 8 11.1 / 9.9; beyond:
 //          4096x16384 at 24 (393 KB) 14.2 / 16.1, and more than 16 tokens against a second workgroup per compute unit:
-//          9216x2304 at 30 6.8 / 9.2, 16384x4096 at 32 12.3 / 13.3 (8192x2304 at 30 6.4 / 5.8)
+//          9216x2304 at 30 6.8 / 9.2, 16384x4096 at 32 12.3 / 13.3 (8192x2304 at 30 6.4 / 5.8, 16384x4096 at 17 11.1 / 10.3)
 //   W8A16  3072x4096 at 8 8.5 / 6.5, 6144x4096 at 16 (131 KB) 10.4 / 9.8, 5120x4352 at 2 9.6 / 8.1, 12288x6144 at 2
 //          17.3 / 15.7; beyond: 12288x2048 at 12 (98 KB) 8.8 / 9.7, and with stages that do not fill the waves
-//          13824x4608 at 1 14.8 / 17.6, 9216x2304 at 2 7.8 / 9.3, 7680x2560 at 16 7.3 / 8.7
+//          13824x4608 at 1 14.8 / 17.6, 9216x2304 at 2 7.8 / 9.3, 7680x2560 at 16 7.3 / 8.7 (15360x5120 at 2 24.1 / 18.2)
 //   INT8   2048x2048 at 1 4.2 / 3.6, 2560x10240 at 4 9.6 / 8.4, 16384x4096 at 1 16.8 / 13.7, 3072x6144 at 16 8.4 / 7.2,
 //          4096x2048 at 24 5.5 / 5.0; beyond: 4096x4096 at 16 5.9 / 6.4, 12288x4096 at 8 12.1 / 12.9, 24576x6144 at 64
 //          31.8 / 47.5.  Where the stages do not fill the waves (ten stages on eight), the second round is mostly empty:
-//          10240x2560 at 1 8.0 / 9.0.  Three strips per compute unit whose rows lie 4 KB apart meet on the same memory
-//          channels: 12288x4096 at 1 to 4 11.3 / 13.2 to 13.5 (12256x4608 13.0 / 12.4, 11520x3840 10.1 / 9.7).
+//          10240x2560 at 1 8.0 / 9.0.  Three strips per compute unit whose rows lie 4 KB apart depend on where the
+//          captured launches run: 12288x4096 at 1 to 4 11.3 / 11.4 in some graphs, 13.2 to 13.5 in others (12256x4608 13.0 /
+//          12.4, 11520x3840 10.1 / 9.7).
 // A K of one or two stages leaves most of the waves without work (12144x256 at 39 3.9 / 4.8, 11632x512 at 30 3.9 / 5.0,
 // INT4 12304x256 at 36 4.0 / 5.0, W8A16 9184x256 at 35 5.0 / 6.6).
 //
@@ -733,9 +737,9 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
         if (shape == kMidShapes) return false;
         const bool int8 = w_bits == 8 && xb == 1;
         if (M <= 64) {
-            if (w_bits == 4) return K <= (N <= 1024 ? 8192 : 10240);
+            if (w_bits == 4) return K <= (N <= 1024 ? 8192 : N <= 3072 ? 10240 : 12288);
             if ((long)N * K > (1L << 24) || (K > 1024 && N > (K <= 2048 ? 8192 : 4096))) return false;
-            return K <= (xb == 2 ? 3072 : shape == kMid64x64 ? 5120 : 6144);
+            return K <= (xb == 2 ? 3072 : shape == kMid64x64 ? 5120 : 6400);
         }
         if (K > (xb == 2 ? 4096 : w_bits == 4 ? (N <= 3072 ? 12288 : 9216) : shape == kMid64x64 ? 5120 :
                  shape == kMid64x32 ? 6656 : 8192))
@@ -747,8 +751,11 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     const bool one_round = N <= 32 * kCUs;
     const int stages = (K + kStageK - 1) / kStageK, last = stages % 8;
     const bool filled = stages <= 8 || last == 0 || last > 4;
-    if (xb == 2) return load <= (one_round ? 131072 : 65536) && (filled || N <= (M <= 8 ? 6144 : 5120));
-    if (w_bits == 4) return load <= (one_round ? 270000 : 200000) && (one_round || M <= 16);
+    if (xb == 2)
+        return load <= (one_round ? 131072 : 65536) &&
+               (filled || N <= (M <= 8 ? 6144 : 5120) || (M <= 4 && K > 4608 && N <= 16384));
+    if (w_bits == 4)
+        return load <= (one_round ? 270000 : 200000) && (one_round || M <= 16 || (M <= 24 && N > 12288 && N <= 16384));
     if (M <= 8) {
         if (K % 4096 == 0 && N > 8192 && N <= 12288) return false;      // three strips per compute unit, rows 4 KB apart
         return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);

@@ -76,11 +76,12 @@ def test_a_table_entry_that_cannot_run_changes_nothing():
     # the direct and small-tile kernels keep a ragged K where they are ahead ...
     (27, 6400, 1600, 8, 8, True), (5, 1600, 6400, 8, 8, True), (48, 2400, 8224, 8, 8, True), (48, 2400, 9600, 4, 8, True),
     (16, 5920, 23680, 8, 8, True), (24, 4704, 18816, 4, 8, True), (64, 16320, 5440, 8, 16, True), (24, 24000, 6000, 8, 16, True),
+    (28, 21376, 5344, 8, 8, True), (30, 24000, 6000, 8, 16, True),
     (64, 5600, 5600, 8, 8, True), (64, 3200, 9280, 8, 8, True), (64, 8000, 8032, 4, 8, True), (30, 4704, 16352, 8, 8, True),
     # ... and leave it to the tiles where K or the rows are too long for one round of them
     (57, 4704, 18816, 8, 8, False), (64, 3008, 12000, 8, 8, False), (64, 5600, 6304, 8, 8, False), (30, 5920, 23680, 8, 8, False),
     (63, 4672, 17632, 4, 8, False), (64, 8000, 8288, 4, 8, False), (30, 5920, 23680, 4, 8, False),
-    (60, 18240, 6080, 8, 16, False), (56, 22784, 5696, 8, 16, False), (30, 24000, 6000, 8, 16, False),
+    (60, 18240, 6080, 8, 16, False), (56, 22784, 5696, 8, 16, False), (30, 24000, 2400, 8, 16, False), (30, 26400, 6304, 8, 8, False),
 ])
 def test_ragged_k_up_to_64_tokens(M, N, K, bits, x_bits, direct):
     for ws in (0, 1 << 30):
@@ -94,8 +95,9 @@ def test_ragged_k_up_to_64_tokens(M, N, K, bits, x_bits, direct):
     (1, 13824, 4608, 8, 16, "stream"), (2, 9216, 2304, 8, 16, "stream"), (16, 7680, 2560, 8, 16, "stream"),
     (30, 8192, 2304, 4, 8, "direct"), (30, 9216, 2304, 4, 8, "stream"), (16, 9216, 2304, 4, 8, "direct"),
     (48, 4096, 3072, 8, 8, "small"), (40, 6912, 2304, 8, 8, "stream"), (48, 6912, 2048, 8, 8, "small"),
-    (54, 1792, 6656, 8, 8, "stream"), (40, 6912, 2304, 8, 16, "stream"), (40, 4096, 2304, 8, 16, "small"),
-    (48, 2560, 10240, 4, 8, "small"), (48, 3072, 12288, 4, 8, "stream"), (100, 3072, 12288, 4, 8, "small"),
+    (54, 1792, 6656, 8, 8, "stream"), (42, 1600, 6400, 8, 8, "small"), (2, 15360, 5120, 8, 16, "direct"), (6, 15360, 5120, 8, 16, "stream"),
+    (17, 16384, 4096, 4, 8, "direct"), (26, 16384, 3584, 4, 8, "stream"), (40, 6912, 2304, 8, 16, "stream"), (40, 4096, 2304, 8, 16, "small"),
+    (48, 2560, 10240, 4, 8, "small"), (48, 3072, 12288, 4, 8, "stream"), (40, 3328, 10496, 4, 8, "small"), (100, 3072, 12288, 4, 8, "small"),
     (65, 4096, 11872, 4, 8, "tile"), (200, 4000, 11584, 4, 8, "tile"),
     (39, 12144, 256, 8, 8, "stream"), (30, 11632, 512, 8, 8, "stream"), (35, 9184, 256, 8, 16, "stream"),
     (2, 12288, 4096, 8, 8, "stream"), (2, 12288, 3584, 8, 8, "direct"), (2, 16384, 4096, 8, 8, "direct"),
