@@ -139,8 +139,9 @@ zq_status zq_gelu_quant_tokenwise(const void *h_fp16, const void *bias_fp16, int
  *
  * zq_gemm_quant_workspace_bytes: the same for a call that also asks for the
  * token-wise quantization of its output (out_q / gq_out): at least
- * ZQ_WORKSPACE_FIXED_BYTES where the GeMM kernel itself would quantize (see
- * zq_gemm_gelu_quant_tokenwise), so never less than zq_gemm_workspace_bytes.
+ * ZQ_WORKSPACE_FIXED_BYTES where the GeMM kernel itself would quantize, and
+ * 2 M N bytes more where up to 64 tokens keep FP16 rows that no caller wants there
+ * (see zq_gemm_gelu_quant_tokenwise), so never less than zq_gemm_workspace_bytes.
  */
 size_t zq_gemm_workspace_bytes(int M, int N, int K, int w_bits);
 size_t zq_gemm_quant_workspace_bytes(int M, int N, int K, int w_bits);

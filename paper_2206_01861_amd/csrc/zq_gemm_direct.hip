@@ -671,7 +671,7 @@ bool short_problem(int M, int N, int K, int xb) {
 // Up to 64 tokens and K no multiple of 256, which the streaming kernel does not take: against the LDS tiles, which split
 // K over workgroups for few rows where the workspace holds it.  The direct kernels are ahead nearly everywhere up to
 // 32 tokens; every workgroup of theirs goes through all of K, and with more tokens or rows their second round loses.  The
-// lines follow 43000 random shapes (256 to 32768 rows, K 256 to 28000); in microseconds, weights from memory, tiles /
+// lines follow 46000 random shapes (256 to 32768 rows, K 256 to 28000); in microseconds, weights from memory, tiles /
 // direct kernels:
 //   INT8   6400x1600 at 27 tokens 7.4 / 4.8, 1600x6400 at 48 9.2 / 8.6; beyond: 4704x18816 at 57 24.2 / 45.3, 3008x12000
 //          at 64 17.5 / 23.7, 5920x23680 at 30 31.2 / 36.2
@@ -697,7 +697,7 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // workgroups read M x K activation bytes each, from L2, which stays hidden behind the weights only up to some 130 to
 // 270 KB per compute unit; the streaming kernel shares one activation tile among up to 128 rows.  On the other side the
 // streaming kernel leaves compute units idle on matrices of few rows, or pays for an exchange between workgroups where it
-// splits K.  The lines below follow 130 shapes (1536 to 24576 rows, K 1024 to 24576) at 1 to 32 tokens; in
+// splits K.  The lines below follow 57000 random shapes (256 to 32768 rows, K 256 to 28000); in
 // microseconds, streaming / direct:
 //   INT4   2048x8192 at 16 tokens 10.7 / 7.0, 8192x8192 at 32 (262 KB) 17.4 / 13.4, 16384x4096 at 8 11.1 / 9.9; beyond:
 //          4096x16384 at 24 (393 KB) 14.2 / 16.1, and more than 16 tokens against a second workgroup per compute unit:
