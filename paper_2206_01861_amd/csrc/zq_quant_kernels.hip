@@ -16,8 +16,8 @@ namespace zq {
 int compute_units();                                    // of the current device
 
 // ---------------------------------------------------------------------------
-// Row front-ends.  A row is handled by TPR threads (one wave, or the whole
-// 256-thread workgroup), each holding VPT vectors of 8 elements in registers.
+// Row front-ends.  A row is handled by TPR threads (one wave, or a whole
+// workgroup of 256 or more), each holding VPT vectors of 8 elements in registers.
 // ---------------------------------------------------------------------------
 
 template <int TPR>
@@ -29,6 +29,8 @@ __device__ __forceinline__ float row_sum(float v, float *lds) {
         if ((threadIdx.x % kWave) == 0) lds[w] = v;
         __syncthreads();
         v = lds[0] + lds[1] + lds[2] + lds[3];
+#pragma unroll
+        for (int i = 4; i < TPR / kWave; ++i) v += lds[i];
     }
     return v;
 }
@@ -42,17 +44,43 @@ __device__ __forceinline__ float row_max(float v, float *lds) {
         if ((threadIdx.x % kWave) == 0) lds[w] = v;
         __syncthreads();
         v = fmaxf(fmaxf(lds[0], lds[1]), fmaxf(lds[2], lds[3]));
+#pragma unroll
+        for (int i = 4; i < TPR / kWave; ++i) v = fmaxf(v, lds[i]);
     }
     return v;
 }
 
+// Vector idx of a row: y where it is wanted, and the codes.
+__device__ __forceinline__ void store_row_vector(const float (&v)[8], float inv, int row, int K, int idx,
+                                                 int8_t *__restrict__ xq, void *__restrict__ y_out, int y_dtype) {
+    if (y_out != nullptr) {
+        if (y_dtype == 1) {
+            float4 *yo = reinterpret_cast<float4 *>(reinterpret_cast<float *>(y_out) + (size_t)row * K) + 2 * idx;
+            yo[0] = make_float4(v[0], v[1], v[2], v[3]);
+            yo[1] = make_float4(v[4], v[5], v[6], v[7]);
+        } else {
+            half8 h;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] = (half_t)v[e];
+            reinterpret_cast<half8 *>(reinterpret_cast<half_t *>(y_out) + (size_t)row * K)[idx] = h;
+        }
+    }
+    uint32_t q[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = quant_code_bits(v[e], inv);
+    reinterpret_cast<uint2 *>(xq + (size_t)row * K)[idx] =
+        make_uint2(pack4_code_bits(q[0], q[1], q[2], q[3]), pack4_code_bits(q[4], q[5], q[6], q[7]));
+}
+
+constexpr int row_block(int tpr) { return tpr > 256 ? tpr : 256; }      // threads of a workgroup
+
 template <int OP, int TPR, int VPT>
-__global__ __launch_bounds__(256) void rowquant_kernel(const half8 *__restrict__ in, const half8 *__restrict__ p0,
+__global__ __launch_bounds__(row_block(TPR)) void rowquant_kernel(const half8 *__restrict__ in, const half8 *__restrict__ p0,
                                                        const half8 *__restrict__ p1, float eps, int M, int K,
                                                        int8_t *__restrict__ xq, float *__restrict__ s_tok,
                                                        void *__restrict__ y_out, int y_dtype) {
-    __shared__ float lds[4];
-    constexpr int RPB = 256 / TPR;
+    __shared__ float lds[row_block(TPR) / kWave];
+    constexpr int RPB = row_block(TPR) / TPR;
     const int t = threadIdx.x % TPR;
     const int row = blockIdx.x * RPB + threadIdx.x / TPR;
     if (TPR <= kWave && row >= M) return;   // whole waves leave together; no block barrier is used
@@ -166,27 +194,81 @@ __global__ __launch_bounds__(256) void rowquant_kernel(const half8 *__restrict__
     quant_scales(a, 127.0f, scale, inv);
     if (t == 0) s_tok[row] = scale;
 
-    uint2 *rq = reinterpret_cast<uint2 *>(xq + (size_t)row * K);
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
         const int idx = i * TPR + t;
-        if (ok[i]) {
-            if (y_out != nullptr) {
-                if (y_dtype == 1) {
-                    float4 *yo = reinterpret_cast<float4 *>(reinterpret_cast<float *>(y_out) + (size_t)row * K) + 2 * idx;
-                    yo[0] = make_float4(v[i][0], v[i][1], v[i][2], v[i][3]);
-                    yo[1] = make_float4(v[i][4], v[i][5], v[i][6], v[i][7]);
-                } else {
-                    half8 h;
+        if (ok[i]) store_row_vector(v[i], inv, row, K, idx, xq, y_out, y_dtype);
+    }
+}
+
+// GeLU without a bias for up to as many rows as there are compute units: a row is cut into gridDim.x parts, one workgroup
+// each.  One compute unit works 18 VALU instructions an element off at 64 a cycle, 0.96 us for 8192 elements, while the
+// others idle.  The parts of a row agree on its scale without exchanging anything, because each of them reads the whole row:
+// GeLU of an FP16 input rises from where it passes kGeluNegMax on, and below zero it stays under kGeluNegMax in size, so the
+// row's absmax is the GeLU of its largest input (two elements per instruction) once that is above kGeluNegMax.  A row of
+// smaller inputs is worked off whole by each part.  The computed functions have both properties over every finite FP16
+// value, so the scale has the bits that the maximum over all results has; with a bias the argument is any fp32 value,
+// where neighbours may round the other way.  us per call, a workgroup per row / parts: 1x8192 3.3 / 2.6, 27x8192 3.7 / 2.6,
+// 16x16384 5.0 / 2.7, 64x24576 6.9 / 4.6, 5x6400 3.5 / 2.6, 256x16384 6.8 / 5.5.
+constexpr float kGeluNegMax = 0.1702f;               // erf form: 0.16997, tanh form: 0.17004
+
+template <int OP>
+__device__ __forceinline__ float gelu_op(float u) {
+    return OP == kOpGeluErf ? gelu_erf(u) : gelu_tanh(u);
+}
+
+template <int OP, int NT, int VPT>
+__global__ __launch_bounds__(NT) void gelu_parts_kernel(const uint32x4_t *__restrict__ in, int K, int own,
+                                                        int8_t *__restrict__ xq, float *__restrict__ s_tok,
+                                                        void *__restrict__ y_out, int y_dtype) {
+    __shared__ float lds[NT / kWave];
+    const int t = threadIdx.x;
+    const int row = blockIdx.y;
+    const int nvec = K >> 3;
+    const uint32x4_t *rin = in + (size_t)row * nvec;
+    // This part's vectors, the first `own` of a thread, then the others'.  Vectors past the end read vector 0.
+    const int first = (int)blockIdx.x * own;
+    uint32x4_t raw[VPT];
+    int idx[VPT];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) h[e] = (half_t)v[i][e];
-                    reinterpret_cast<half8 *>(reinterpret_cast<half_t *>(y_out) + (size_t)row * K)[idx] = h;
-                }
-            }
-            uint32_t q[8];
+    for (int i = 0; i < VPT; ++i) {
+        const int slot = first + i < VPT ? first + i : first + i - VPT;
+        idx[i] = slot * NT + t;
+        raw[i] = rin[idx[i] < nvec ? idx[i] : 0];
+    }
+    // The bits of non-negative FP16 numbers order like 16-bit integers, those of negative ones are below all of them.
+    typedef int16_t short2_t __attribute__((ext_vector_type(2)));
+    short2_t m2 = {0, 0};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) q[e] = quant_code_bits(v[i][e], inv);
-            rq[idx] = make_uint2(pack4_code_bits(q[0], q[1], q[2], q[3]), pack4_code_bits(q[4], q[5], q[6], q[7]));
+    for (int i = 0; i < VPT; ++i)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const uint32_t two = raw[i][d];              // (a bit cast of the element itself reads element 0)
+            m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(short2_t, two));
+        }
+    const half_t top = __builtin_bit_cast(half_t, m2[0] > m2[1] ? m2[0] : m2[1]);
+    float a = gelu_op<OP>(row_max<NT>((float)top, lds));
+    if (!(a > kGeluNegMax)) {
+        a = 0.0f;
+        for (int i = t; i < nvec; i += NT) {
+            const half8 h = __builtin_bit_cast(half8, rin[i]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(gelu_op<OP>((float)h[e])));
+        }
+        a = row_max<NT>(a, lds);
+    }
+    float scale, inv;
+    quant_scales(a, 127.0f, scale, inv);
+    if (t == 0 && blockIdx.x == 0) s_tok[row] = scale;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        if (i >= own) break;
+        if (idx[i] < nvec) {
+            const half8 h = __builtin_bit_cast(half8, raw[i]);
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = gelu_op<OP>((float)h[e]);
+            store_row_vector(v, inv, row, K, idx[i], xq, y_out, y_dtype);
         }
     }
 }
@@ -194,9 +276,9 @@ __global__ __launch_bounds__(256) void rowquant_kernel(const half8 *__restrict__
 template <int OP, int TPR, int VPT>
 static hipError_t launch_rq(const void *in, const void *p0, const void *p1, float eps, int M, int K, int8_t *xq,
                             float *s_tok, void *y_out, int y_dtype, hipStream_t st) {
-    constexpr int RPB = 256 / TPR;
+    constexpr int RPB = row_block(TPR) / TPR;
     const int blocks = (M + RPB - 1) / RPB;
-    hipLaunchKernelGGL((rowquant_kernel<OP, TPR, VPT>), dim3(blocks), dim3(256), 0, st,
+    hipLaunchKernelGGL((rowquant_kernel<OP, TPR, VPT>), dim3(blocks), dim3(row_block(TPR)), 0, st,
                        reinterpret_cast<const half8 *>(in), reinterpret_cast<const half8 *>(p0),
                        reinterpret_cast<const half8 *>(p1), eps, M, K, xq, s_tok, y_out, y_dtype);
     return hipGetLastError();
@@ -207,24 +289,66 @@ static hipError_t launch_rq_op(const void *in, const void *p0, const void *p1, f
                                float *s_tok, void *y_out, int y_dtype, hipStream_t st) {
     const int nvec = K / 8;
 #define ZQ_RQ(TPR, VPT) return launch_rq<OP, TPR, VPT>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st)
-    // Short rows: one wave per row, four rows per workgroup.
+    // Short rows: one wave per row, four rows per workgroup.  Up to 2048 values where a workgroup per row would be many
+    // rounds of them: no barrier in the three reductions (LayerNorm 2048x2048 5.9 -> 5.1 us, 2048x1280 5.3 -> 4.2,
+    // 8192x2048 16.4 -> 14.0; at 512 rows level, at 5 rows 2.7 -> 2.9; 4096 values are 25 % slower that way).  The
+    // arithmetic of GeLU wants more waves: 2100x1920 5.2 -> 5.6.
     if (nvec <= 64 * 1) ZQ_RQ(64, 1);
     if (nvec <= 64 * 2) ZQ_RQ(64, 2);
-    // Longer rows: the whole workgroup shares one row.
+    if (M > 512 && (OP == kOpLayerNorm || OP == kOpIdentity)) {
+        if (nvec <= 64 * 3) ZQ_RQ(64, 3);
+        if (nvec <= 64 * 4) ZQ_RQ(64, 4);
+    }
+    // Longer rows: a workgroup shares one row, with up to four vectors per thread: six to sixteen of 256 threads are too few
+    // waves for the arithmetic of GeLU (300x16384 7.8 -> 6.5 us, 300x24576 10.9 -> 8.4, 2048x24576 33.5 -> 31.9).
     if (nvec <= 256 * 1) ZQ_RQ(256, 1);
     if (nvec <= 256 * 2) ZQ_RQ(256, 2);
     if (nvec <= 256 * 3) ZQ_RQ(256, 3);
     if (nvec <= 256 * 4) ZQ_RQ(256, 4);
-    if (nvec <= 256 * 6) ZQ_RQ(256, 6);
-    if (nvec <= 256 * 8) ZQ_RQ(256, 8);
-    if (nvec <= 256 * 12) ZQ_RQ(256, 12);
-    if (nvec <= 256 * 16) ZQ_RQ(256, 16);
+    if (nvec <= 512 * 3) ZQ_RQ(512, 3);
+    if (nvec <= 512 * 4) ZQ_RQ(512, 4);
+    if (nvec <= 1024 * 3) ZQ_RQ(1024, 3);
+    if (nvec <= 1024 * 4) ZQ_RQ(1024, 4);
 #undef ZQ_RQ
+    return hipErrorInvalidValue;
+}
+
+template <int OP, int NT, int VPT>
+static hipError_t launch_gelu_parts_t(const void *in, int M, int K, int parts, int8_t *xq, float *s_tok, void *y_out,
+                                      int y_dtype, hipStream_t st) {
+    const int own = (VPT + parts - 1) / parts;          // vectors of a thread
+    hipLaunchKernelGGL((gelu_parts_kernel<OP, NT, VPT>), dim3((VPT + own - 1) / own, M), dim3(NT), 0, st,
+                       reinterpret_cast<const uint32x4_t *>(in), K, own, xq, s_tok, y_out, y_dtype);
+    return hipGetLastError();
+}
+
+// Parts: as many as a compute unit each holds, one vector per thread at least.  Rows of up to 4096 values leave something to
+// part with 256 threads only (64x3072 2.5 us, with 512 2.7), longer ones have fewer parts that read the row with 512
+// (64x24576 4.6 us, with 256 threads 7.1, with 1024 4.9).
+template <int OP>
+static hipError_t launch_gelu_parts(const void *in, int M, int K, int cus, int8_t *xq, float *s_tok, void *y_out,
+                                    int y_dtype, hipStream_t st) {
+    const int nvec = K / 8;
+#define ZQ_GP(NT, VPT) return launch_gelu_parts_t<OP, NT, VPT>(in, M, K, cus / M, xq, s_tok, y_out, y_dtype, st)
+    if (nvec <= 256 * 1) ZQ_GP(256, 1);
+    if (nvec <= 256 * 2) ZQ_GP(256, 2);
+    if (nvec <= 512 * 2) ZQ_GP(512, 2);
+    if (nvec <= 512 * 3) ZQ_GP(512, 3);
+    if (nvec <= 512 * 4) ZQ_GP(512, 4);
+    if (nvec <= 512 * 6) ZQ_GP(512, 6);
+    if (nvec <= 512 * 8) ZQ_GP(512, 8);
+#undef ZQ_GP
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_rowquant(RowOp op, const void *in, const void *p0, const void *p1, float eps, int M, int K,
                            int8_t *xq, float *s_tok, void *y_out, int y_dtype, hipStream_t st) {
+    if ((op == kOpGeluErf || op == kOpGeluTanh) && p0 == nullptr) {
+        const int cus = compute_units();
+        if (M <= cus)
+            return op == kOpGeluErf ? launch_gelu_parts<kOpGeluErf>(in, M, K, cus, xq, s_tok, y_out, y_dtype, st)
+                                    : launch_gelu_parts<kOpGeluTanh>(in, M, K, cus, xq, s_tok, y_out, y_dtype, st);
+    }
     switch (op) {
         case kOpLayerNorm: return launch_rq_op<kOpLayerNorm>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st);
         case kOpGeluErf: return launch_rq_op<kOpGeluErf>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st);

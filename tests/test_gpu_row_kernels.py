@@ -1,0 +1,80 @@
+"""GPU parity of the row kernels' mappings: GeLU rows cut into parts (up to 256 rows, no bias) and rows of one wave or of 512
+and 1024 threads, at the edges of each; and what the parts rely on, that the computed GeLU of FP16 inputs never falls as
+its input grows."""
+import numpy as np
+import pytest
+import torch
+
+import zq_inputs
+from helpers import assert_bit_equal, check_fused_codes, dev, host
+from test_gpu_quant import orc, zq  # noqa: F401 (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+NEG_MAX = 0.1702            # kGeluNegMax of zq_quant_kernels.hip
+
+
+@pytest.mark.parametrize("approx", [False, True])
+def test_gelu_rises_over_the_fp16_inputs(zq, approx):
+    h = np.arange(65536, dtype=np.uint32).astype(np.uint16).view(np.float16)
+    h = np.sort(h[np.isfinite(h)])
+    pad = (-h.size) % 4096
+    x = np.concatenate([h, np.full(pad, h[-1])]).reshape(-1, 4096)
+    _, _, y = zq.zq_gelu_quant_tokenwise(dev(x), None, approx_tanh=approx, y_dtype=torch.float32)
+    y = host(y).ravel()[: h.size]
+    assert np.abs(y[h <= 0]).max() < NEG_MAX
+    up = y[h > 0]
+    up = up[up > NEG_MAX]
+    assert (np.diff(up) >= 0).all()
+
+
+# rows x width: one vector, parts that are full, short and empty, the widest row, the last count of rows with parts and the
+# first without, more parts than compute units hold
+PARTS = [(1, 16), (2, 2048), (9, 2064), (3, 4096), (3, 4112), (100, 8192), (5, 8208), (60, 12304), (17, 16400), (2, 24592),
+         (3, 32768), (256, 4096), (257, 4096), (200, 1040)]
+
+
+@pytest.mark.parametrize("approx", [False, True])
+@pytest.mark.parametrize("M,K", PARTS)
+def test_gelu_parts(zq, orc, approx, M, K):
+    print("gelu parts", approx, M, K, flush=True)
+    rng = zq_inputs.rng_for(3, 7000 + M + K)
+    h = (zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=6.0).astype(np.float32) * 1.5).astype(np.float16)
+    h[0] = -np.abs(h[0])                                    # no positive input
+    if M > 1:
+        h[1] *= np.float16(0.01)                            # the largest GeLU is below that of some negative input
+    if M > 2:
+        h[2] = 0
+    xq, s_tok, y = zq.zq_gelu_quant_tokenwise(dev(h), None, approx_tanh=approx, y_dtype=torch.float32)
+    xq2, s2, y16 = zq.zq_gelu_quant_tokenwise(dev(h), None, approx_tanh=approx, y_dtype=torch.float16)
+    assert torch.equal(xq, xq2) and torch.equal(s_tok, s2) and torch.equal(y16, y.half())
+    y64, _ = orc.gelu(h, None, approx_tanh=approx)
+    xq, s_tok, y = host(xq), host(s_tok), host(y)
+    xq_o, s_o = orc.quant_tokenwise(y)
+    assert_bit_equal(s_tok, s_o, "s_tok")
+    assert_bit_equal(xq, xq_o, "xq")
+    check_fused_codes(xq, s_tok, y, y64, "gelu %dx%d" % (M, K))
+
+
+# one wave per row with three and four vectors a lane, at the first count of rows; 512 and 1024 threads a row
+@pytest.mark.parametrize("M,K", [(513, 1040), (513, 1536), (515, 1552), (514, 2048), (512, 2048), (2, 8208), (3, 12304),
+                                 (2, 16400), (2, 24592)])
+def test_row_mappings(zq, orc, M, K):
+    print("rows", M, K, flush=True)
+    rng = zq_inputs.rng_for(3, 8000 + M + K)
+    x = zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=15.0, token_spread=True)
+    gamma, beta = zq_inputs.layernorm_params(rng, K)
+    bias = zq_inputs.bias(rng, K, std=0.2)
+    xd = dev(x)
+    y64, _ = orc.layernorm(x, gamma, beta, 1e-5)
+    for res, ref in ((zq.zq_layernorm_quant_tokenwise(xd, dev(gamma), dev(beta), 1e-5, y_dtype=torch.float32), y64),
+                     (zq.zq_gelu_quant_tokenwise(xd, dev(bias), y_dtype=torch.float32), orc.gelu(x, bias)[0])):
+        xq, s_tok, y = (host(t) for t in res)
+        xq_o, s_o = orc.quant_tokenwise(y)
+        assert_bit_equal(s_tok, s_o, "s_tok")
+        assert_bit_equal(xq, xq_o, "xq")
+        check_fused_codes(xq, s_tok, y, ref, "rows %dx%d" % (M, K))
+    xq, s_tok = zq.zq_quantize_tokenwise(xd)
+    xq_o, s_o = orc.quant_tokenwise(x.astype(np.float32))
+    assert_bit_equal(host(s_tok), s_o, "s_tok")
+    assert_bit_equal(host(xq), xq_o, "xq")
