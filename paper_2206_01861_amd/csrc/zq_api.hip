@@ -85,6 +85,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (in_kernel) {
         a.q_out = out_q; a.q_scale_out = out_s_tok;
+        if (forced >= 0) a.quant_shapes = zq::tile_shapes_of(forced);
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
     if (zq::launch_gemm(direct ? (int)zq::kGemmSimple : cls, a, st) != hipSuccess) return ZQ_ERR_HIP;

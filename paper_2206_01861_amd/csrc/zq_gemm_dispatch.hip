@@ -83,15 +83,7 @@ bool gemm_goes_direct(int M, int N, int K, int w_bits, size_t workspace_bytes) {
 namespace {
 TileKind tile_kind(int w_bits) { return w_bits == 8 ? kTileI8 : kTileI4; }
 
-// The tile shapes that stand behind a tiled variant, and the variant a shape belongs to.
-unsigned shapes_of(int variant) {
-    switch (variant) {
-        case kGemmTile128: return 1u << kTile128x64 | 1u << kTile128x128;
-        case kGemmTile256x128: return 1u << kTile192x128 | 1u << kTile256x128;
-        case kGemmTile256x192: return 1u << kTile256x192;
-    }
-    return 1u << kTile256x256;
-}
+// The variant a tile shape belongs to.
 int variant_of(TileShape shape) {
     switch (shape) {
         case kTile128x64:
@@ -104,6 +96,15 @@ int variant_of(TileShape shape) {
 }
 }  // namespace
 
+unsigned tile_shapes_of(int variant) {
+    switch (variant) {
+        case kGemmTile128: return 1u << kTile128x64 | 1u << kTile128x128;
+        case kGemmTile256x128: return 1u << kTile192x128 | 1u << kTile256x128;
+        case kGemmTile256x192: return 1u << kTile256x192;
+    }
+    return 1u << kTile256x256;
+}
+
 hipError_t launch_gemm(int variant, const GemmArgs &a, hipStream_t st) {
     switch (variant) {
         case kGemmSimple: return launch_gemm_direct(a, st);
@@ -111,7 +112,7 @@ hipError_t launch_gemm(int variant, const GemmArgs &a, hipStream_t st) {
         case kGemmTile256:
         case kGemmTile256x128:
         case kGemmTile256x192:
-            return launch_gemm_tile(a, choose_tile(tile_kind(a.w_bits), a.M, a.N, a.K, shapes_of(variant), nullptr), st);
+            return launch_gemm_tile(a, choose_tile(tile_kind(a.w_bits), a.M, a.N, a.K, tile_shapes_of(variant), nullptr), st);
         case kGemmTileSplitK: return launch_gemm_tile_splitk(a, st);
         case kGemmSkinny: return launch_gemm_skinny(a, false, st);
         case kGemmSkinnySplitK: return launch_gemm_skinny(a, true, st);
@@ -126,7 +127,7 @@ const char *gemm_schedule_name(int variant, int M, int N, int K, int w_bits) {
         case kGemmSkinny: return "stream";
         case kGemmSkinnySplitK: return "stream_splitk";
     }
-    return tile_shape_name(choose_tile(tile_kind(w_bits), M, N, K, shapes_of(variant), nullptr));
+    return tile_shape_name(choose_tile(tile_kind(w_bits), M, N, K, tile_shapes_of(variant), nullptr));
 }
 
 }  // namespace zq

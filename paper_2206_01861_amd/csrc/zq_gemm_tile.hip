@@ -153,7 +153,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     static_assert(!A16 || WBITS == 8, "FP16 activations go with INT8 weights");
     static_assert(XT != 3 || WBITS == 4, "packed weight rows in LDS are the INT4 ones");
     static_assert(!PAIRED || (BK == 128 && KT == 1), "the paired loop is written for four k steps per stage");
-    static_assert(QOUT == 0 || XT == 0, "the output quantization is built for the INT8 product");
+    static_assert(QOUT == 0 || !A16, "the output quantization is built for the INT8 product");
+    static_assert(QOUT == 0 || BN == 64 || BN == 128 || BN == 256, "the code tile's swizzle wants a power of two of chunks");
     static_assert(KSPLIT == 0 || QOUT == 0, "a K split leaves the epilogue to the second kernel");
     static_assert(XU % NW == 0, "activation load units must split evenly over the waves");
     constexpr int LX = XU / NW;                      // activation loads per wave per stage
@@ -1087,6 +1088,19 @@ constexpr TileCost kTileCost[3][kTileShapes] = {
      {256, 128, 5.96, 0.632, 0.998, 5.49}, {256, 192, 6.54, 0.911, 1.398, 6.56}, {256, 256, 6.91, 1.051, 1.644, 9.34}},
 };
 
+// The same for launches that quantize their output in the kernel (GeLU, row maxima exchanged between the tiles of a band, codes
+// from the accumulators), fitted to 370 shapes (65 to 8192 tokens, 768 to 8192 columns, K 768 to 4096): 3 to 8 % rms, and
+// the choice costs 0.1 % on average over the best shape.  256x192, whose twelve chunks a row the code tile's swizzle does not
+// take, has no such kernel.  Against 128x128 and 256x256 alone, us: 1237x4096x1024 25.6 -> 19.0 (one round of 192x128
+// instead of two of 128x128), 1161x6400x1600 35.0 -> 28.2, 1876x4096x1024 26.2 -> 21.9, 6408x768x4096 48.5 -> 36.1,
+// 882x1024x1024 11.4 -> 9.7 (128x64); INT4 2143x3072x2048 37.6 -> 30.1.
+constexpr TileCost kQuantTileCost[2][kTileShapes] = {
+    {{128, 64, 9.38, 0.028, 0.436, 6.92}, {128, 128, 9.58, 0.268, 0.716, 6.56}, {192, 128, 10.74, 0.434, 1.010, 7.59},
+     {256, 128, 12.35, 0.507, 1.166, 9.32}, {256, 192, 0, 0, 0, 0}, {256, 256, 16.17, 0.930, 1.885, 13.32}},
+    {{128, 64, 10.94, 0.057, 0.546, 7.80}, {128, 128, 9.56, 0.254, 0.744, 6.38}, {192, 128, 10.82, 0.427, 0.998, 7.83},
+     {256, 128, 11.73, 0.651, 1.272, 8.99}, {256, 192, 0, 0, 0, 0}, {256, 256, 16.32, 0.952, 1.918, 13.47}},
+};
+
 double tile_time(const TileCost &t, int M, int N, int K, int x_bytes) {
     const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
     const double stages = (double)(((long)K * x_bytes + 127) / 128);
@@ -1114,14 +1128,38 @@ TileShape choose_tile(TileKind kind, int M, int N, int K, unsigned shapes, doubl
 }
 
 namespace {
-// Tile edge of the schedule that quantizes its output in the kernel: 256 where the plain call
-// would use it or where 128x128 tiles would outnumber what eight-wave workgroups hold at once.
+// The tiles that say whether a call quantizes its output in the kernel.
 int quant_tile_edge(int M, int N) {
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     return (t256 >= 160 || t128 > 384) ? 256 : 128;
 }
 
+// A band no wider than a quarter of the compute units, a slot for every tile and row (see gemm_tile_quant_supported).
+bool quant_tiles_fit(int M, int N, int bm, int bn) {
+    const int tiles_m = (M + bm - 1) / bm, tiles_n = (N + bn - 1) / bn;
+    return tiles_n <= compute_units() / 4 && (long)tiles_m * tiles_n * bm <= kMaxQuantSlots;
+}
+
+// The tile of a launch that quantizes its output: the lowest modelled time among those in `shapes` that fit, or, where
+// none of these does, among all.
+TileShape choose_quant_tile(int M, int N, int K, int w_bits, unsigned shapes) {
+    int best = kTileShapes;
+    for (unsigned mask : {shapes, kAllTileShapes}) {
+        double best_us = 1e30;
+        for (int i = 0; i < kTileShapes; ++i) {
+            const TileCost &c = kQuantTileCost[w_bits == 8 ? 0 : 1][i];
+            if (i == kTile256x192 || ((mask >> i) & 1u) == 0 || !quant_tiles_fit(M, N, c.bm, c.bn)) continue;
+            const double t = tile_time(c, M, N, K, 1);
+            if (t < best_us) {
+                best_us = t;
+                best = i;
+            }
+        }
+        if (best != kTileShapes) break;
+    }
+    return (TileShape)best;
+}
 }  // namespace
 
 // INT8 weights on 128 x 128 and 128 x 64 tiles: two K teams of 2 x 2 waves (wave tile 64 x 64, 64 x 32); measured 5-8 %
@@ -1206,20 +1244,33 @@ hipError_t launch_gemm_tile_splitk(const GemmArgs &a, hipStream_t st) {
 bool gemm_tile_quant_supported(int M, int N, size_t workspace_bytes) {
     if (workspace_bytes < kWsFixedBytes) return false;
     const int edge = quant_tile_edge(M, N);
-    const int tiles_m = (M + edge - 1) / edge, tiles_n = (N + edge - 1) / edge;
-    return tiles_n <= compute_units() / 4 && (long)tiles_m * tiles_n * edge <= kMaxQuantSlots;
+    return quant_tiles_fit(M, N, edge, edge);
 }
 
 hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st) {
     if (a.workspace == nullptr || !gemm_tile_quant_supported(a.M, a.N, a.workspace_bytes) || a.q_out == nullptr ||
         a.q_scale_out == nullptr)
         return hipErrorInvalidValue;
-    if (quant_tile_edge(a.M, a.N) == 256) {
-        if (a.w_bits == 8) return launch_tile_t<256, 256, 2, 4, 128, 2, 8, 0, 1>(a, st);
-        return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 0, 1>(a, st);
+    const TileShape shape = choose_quant_tile(a.M, a.N, a.K, a.w_bits, a.quant_shapes);
+    if (a.w_bits == 8) {
+        switch (shape) {
+            case kTile128x64: return launch_tile_t<128, 64, 4, 2, 128, 5, 8, 0, 1>(a, st);
+            case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 8, 0, 1>(a, st);
+            case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 3, 8, 0, 1>(a, st);
+            case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 8, 0, 1>(a, st);
+            case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 8, 0, 1>(a, st);
+            default: return hipErrorInvalidValue;
+        }
     }
-    if (a.w_bits == 8) return launch_tile_t<128, 128, 2, 4, 128, 4, 8, 0, 1>(a, st);
-    return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 0, 1>(a, st);
+    // nibbles packed in LDS (XT = 3) where the plain call has them so: 589x6144x1536 19.2 -> 18.5 us on 128x128
+    switch (shape) {
+        case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 5, 4, 3, 1>(a, st);
+        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3, 1>(a, st);
+        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 3, 1>(a, st);
+        case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 4, 0, 1>(a, st);
+        case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 0, 1>(a, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // Compute units of the current device, asked once per device; 256 if no device answers.

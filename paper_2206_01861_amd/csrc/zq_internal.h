@@ -97,6 +97,7 @@ struct GemmArgs {
     int act;              // activation applied to acc*scale+bias before the FP16 rounding: 0 none, 1 GeLU erf, 2 GeLU tanh
     int8_t *q_out = nullptr;       // launch_gemm_tile_quant: int8 [M,N] codes of the output rows
     float *q_scale_out = nullptr;  //                         fp32 [M] their scales
+    unsigned quant_shapes = ~0u;   //                         the tiles it chooses from, a bit per TileShape
 };
 
 // Tiles of the tiled schedules (tokens x columns), and which of them a launch takes: the shape with the lowest
@@ -106,6 +107,7 @@ constexpr unsigned kAllTileShapes = (1u << kTileShapes) - 1u;
 enum TileKind { kTileI8, kTileI4, kTileA16 };
 TileShape choose_tile(TileKind kind, int M, int N, int K, unsigned shapes, double *us);
 const char *tile_shape_name(TileShape shape);
+unsigned tile_shapes_of(int variant);         // the tile shapes that stand behind a tiled variant
 hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st);
 
 // 128x128 tiles with a K split: how many splits pay for a shape (1 = none), the workspace they

@@ -1,6 +1,7 @@
 """GPU parity of every tile shape of the tiled GeMM, at edges in M, N and K, in one round of workgroups and in several.
 The shape a call takes follows from its sizes; the cases of REACHED name the one they are for and ask the library
 whether they reach it (128x64, 128x128, 192x128, 256x128, 256x192, 256x256; INT8 and INT4 weights, FP16 activations)."""
+import numpy as np
 import pytest
 import torch
 
@@ -8,6 +9,7 @@ import zq_inputs
 from helpers import dev, host
 from test_gpu_gemm import TILE128, TILE256, TILE256X128, TILE256X192, _case, _check, _run, orc, zq  # noqa: F401
 from test_gpu_gemm_a16 import _check as _check_a16
+from test_gpu_gemm_gelu import _check_fused
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +87,41 @@ def test_every_tile_shape_is_reached(zq, orc, bits, tile, M, N, K, g):
     finally:
         zq.force_gemm_variant(before)
     _integers(zq, orc, VARIANT[tile], bits, M, N, K, g, 6100)
+
+
+# The tiles that quantize their output: (variant, M, N, K, groups).  By the modelled times TILE128 stands for 128x64 in the first
+# three (INT4: two) and for 128x128 in the others, TILE256X128 for 192x128 in three and for 256x128 in three; -1: 192x128 and 256x128.
+QUANT = [
+    (TILE128, 129, 80, 1056, 5), (TILE128, 333, 1040, 2080, 65), (TILE128, 200, 64, 32, 4),
+    (TILE128, 1300, 3088, 544, 193), (TILE128, 137, 8192, 160, 512),
+    (TILE256X128, 193, 144, 672, 9), (TILE256X128, 333, 1040, 2080, 65), (TILE256X128, 2060, 4112, 160, 257),
+    (TILE256X128, 2048, 4096, 544, 64), (TILE256X128, 2990, 2080, 128, 130), (TILE256X128, 1550, 7392, 96, 7),
+    (TILE256, 513, 272, 416, 17), (-1, 1237, 4096, 1024, 64), (-1, 1161, 6400, 800, 100),
+]
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("variant,M,N,K,g", QUANT)
+def test_tiles_that_quantize(zq, orc, variant, bits, M, N, K, g):
+    """FP16 rows, codes and scales are those of the two-kernel path, with the FP16 rows and without, twice in a row on one
+    workspace; the first, last and edge rows against the oracle."""
+    print("quantizing tile", variant, bits, M, N, K, flush=True)
+    xq, s_tok, s_w, bias, codes, wq = _case(zq_inputs.rng_for(7, 600 + M + N + K + bits), M, N, K, g, bits)
+    s_tok = (s_tok * (3.0 / max(1e-9, float(np.sqrt(K)) * 40.0 * float(s_tok.mean()) * float(s_w.mean())))).astype(np.float32)
+    args = (dev(xq), dev(s_tok), dev(wq), dev(s_w), dev(bias))
+    ws = zq.new_workspace(0)
+    prev = zq.force_gemm_variant(variant)
+    try:
+        assert zq.gemm_quantizes_in_kernel(M, N, K, bits, ws.numel())
+        want = zq.zq_gemm_gelu_quant_tokenwise(*args)               # no workspace: the row quantizer
+        runs = [zq.zq_gemm_gelu_quant_tokenwise(*args, keep_g=keep, workspace=ws) for keep in (True, False, True)]
+        torch.cuda.synchronize()
+    finally:
+        zq.force_gemm_variant(prev)
+    for run in runs:
+        for got, ref in zip(run, want):
+            assert got is None or torch.equal(got, ref)
+    assert zq.quant_wait_expired(ws) == 0
+    rows = sorted({0, M // 2, M - 1, min(M, 128) - 1, min(M - 1, 192), min(M - 1, 256)})
+    _check_fused(orc, *(host(t)[rows] for t in runs[0]), xq[rows], s_tok[rows], codes, s_w, bias, False,
+                 "quantizing tile %d %d-bit %dx%dx%d" % (variant, bits, M, N, K))
