@@ -14,6 +14,7 @@ SOURCES = [
     "zq_quant_kernels.hip",
     "zq_gemm_dispatch.hip",
     "zq_gemm_direct.hip",
+    "zq_gemm_vector.hip",
     "zq_gemm_skinny.hip",
     "zq_gemm_tile.hip",
     "zq_probe.hip",

@@ -728,6 +728,7 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 //   W8A16  6144x2048 at 64 10.6 / 8.6, at 128 18.7 / 10.5; 4800x1600 at 192 17.4 / 10.8; beyond: 7680x2560 at 64 12.6 /
 //          17.8, 6912x2304 at 40 11.2 / 12.4, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
+    if (xb == 1 && vector_pays(M, N, K, w_bits)) return true;
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
     if (M <= 64 && ((K <= 256 && (w_bits == 8 || N > 4096)) || (K <= 512 && M > 16 && N > 4096))) return false;
     if (M > 32) {
@@ -790,6 +791,7 @@ const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb) {
 }
 
 hipError_t launch_gemm_direct(const GemmArgs &a, hipStream_t st) {
+    if (vector_pays(a.M, a.N, a.K, a.w_bits)) return launch_gemm_vector(a, st);
     if (a.w_bits == 8)
         return launch_small<8, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out, a.act, st);
     return launch_small<4, 1>(a.xq, a.s_tok, a.wq, a.s_w, a.groups, a.bias, a.M, a.N, a.K, a.out, a.acc_out, a.act, st);

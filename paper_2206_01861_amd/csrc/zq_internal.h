@@ -127,6 +127,10 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb);
 bool gemm_goes_direct(int M, int N, int K, int w_bits, size_t workspace_bytes);
 const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb);    // of the kernel that launch takes
 
+// Of the direct kernels, the one on the vector ALUs: whether it is ahead of the others (up to four tokens), and its launch.
+bool vector_pays(int M, int N, int K, int w_bits);
+hipError_t launch_gemm_vector(const GemmArgs &a, hipStream_t st);
+
 // Name of what launch_gemm runs for a variant (see zq_gemm_schedule).
 const char *gemm_schedule_name(int variant, int M, int N, int K, int w_bits);
 
