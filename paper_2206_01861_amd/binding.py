@@ -1,4 +1,5 @@
-"""ctypes binding of libzq.so: argument marshalling only.
+"""Binding of libzq.so: argument marshalling only.  Calls on plain tensors without given outputs go through the native
+module _zq_host (csrc/zq_host.cpp), everything else through ctypes.
 
 Functions carry the names of the C entry points (include/zq.h) and take torch
 CUDA tensors; outputs are allocated here with torch and returned.  The work is
@@ -11,7 +12,9 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libzq.so")
+_HOST_PATH = os.path.join(_HERE, "_zq_host.so")
 _lib = None
+_host = None                # _zq_host, once lib() has loaded it
 
 SYMBOLS = [
     "zq_status_string", "zq_version", "zq_quantize_weight_groupwise", "zq_layernorm_quant_tokenwise",
@@ -37,11 +40,11 @@ def lib_path():
 
 def lib():
     """Load libzq.so (built in-tree by paper_2206_01861_amd/build.py)."""
-    global _lib
+    global _lib, _host
     if _lib is not None:
         return _lib
-    if not os.path.exists(_LIB_PATH):
-        raise ImportError("libzq.so is not built; run `python -m paper_2206_01861_amd.build` "
+    if not (os.path.exists(_LIB_PATH) and os.path.exists(_HOST_PATH)):
+        raise ImportError("libzq.so or _zq_host.so is not built; run `python -m paper_2206_01861_amd.build` "
                           "(there is no fallback implementation)")
     L = ctypes.CDLL(_LIB_PATH)
     vp, ci, cf, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
@@ -110,7 +113,11 @@ def lib():
     L.zq_probe_mfma_i8.argtypes = [vp, ci, ci, vp, vp]
     L.zq_probe_mfma_i8_tile_traffic.restype = ci
     L.zq_probe_mfma_i8_tile_traffic.argtypes = [vp, sz, ci, ci, vp, vp]
-    _lib = L
+    from . import _zq_host
+    _zq_host.init(_check, *(ctypes.cast(f, vp).value for f in (
+        L.zq_layernorm_quant_tokenwise, L.zq_gelu_quant_tokenwise, L.zq_quantize_tokenwise, L.zq_gemm_i8_dequant,
+        L.zq_gemm_w4a8_dequant, L.zq_gemm_gelu_quant_tokenwise, L.zq_gemm_w8a16_dequant, L.zq_quantize_weight_groupwise)))
+    _lib, _host = L, _zq_host
     return L
 
 
@@ -119,10 +126,11 @@ def _check(code):
         raise ZQError(code, lib().zq_status_string(code).decode())
 
 
-# A call at the smallest sizes is host time (LayerNorm+quant and a 768x768 GeMM at 128 tokens: 23.9 us issued call by
-# call, 18.3 with the three points below; replayed as a graph 5.6): addresses go to ctypes as plain numbers (the argument
-# types convert them), the current stream is read without building a Stream object (by a function that torch does not
-# document; the public call does where a torch has none), and what was allocated here is not checked again.
+# A call at the smallest sizes is host time, which is what _zq_host is for (LayerNorm+quant and a 768x768 GeMM at 128 tokens:
+# 18.6 us issued call by call through ctypes, 9.4 through _zq_host; replayed as a graph 5.6).  On the ctypes path addresses go
+# over as plain numbers (the argument types convert them), the current stream is read without building a Stream object (by a
+# function that torch does not document; the public call does where a torch has none), and what was allocated here is not
+# checked again.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
@@ -279,6 +287,10 @@ def zq_probe_mfma_i8_tile_traffic(source, blocks, iters, sink):
 
 def zq_quantize_weight_groupwise(w_fp16, groups, bits):
     """w fp16 [N,K] -> (wq int8 [N,K] | uint8 [N,K/2], s_w fp32 [groups])."""
+    if _host is not None:
+        done = _host.weight(w_fp16, groups, bits)
+        if done is not None:
+            return done
     _dev(w_fp16, torch.float16, "w_fp16")
     N, K = w_fp16.shape
     if bits == 4:
@@ -302,6 +314,10 @@ def _y_buf(M, K, y_dtype, device):
 
 def zq_layernorm_quant_tokenwise(x_fp16, gamma_fp16, beta_fp16, eps, y_dtype=None, out=None):
     """x fp16 [M,K] -> (xq int8 [M,K], s_tok fp32 [M], y or None)."""
+    if out is None and _host is not None:
+        done = _host.layernorm(x_fp16, gamma_fp16, beta_fp16, eps, y_dtype)
+        if done is not None:
+            return done
     _dev(x_fp16, torch.float16, "x_fp16")
     _dev(gamma_fp16, torch.float16, "gamma_fp16")
     if beta_fp16 is not None:
@@ -318,6 +334,10 @@ def zq_layernorm_quant_tokenwise(x_fp16, gamma_fp16, beta_fp16, eps, y_dtype=Non
 
 def zq_gelu_quant_tokenwise(h_fp16, bias_fp16=None, approx_tanh=False, y_dtype=None, out=None):
     """h fp16 [M,N] -> (xq int8 [M,N], s_tok fp32 [M], y or None)."""
+    if out is None and _host is not None:
+        done = _host.gelu(h_fp16, bias_fp16, approx_tanh, y_dtype)
+        if done is not None:
+            return done
     _dev(h_fp16, torch.float16, "h_fp16")
     if bias_fp16 is not None:
         _dev(bias_fp16, torch.float16, "bias_fp16")
@@ -384,6 +404,10 @@ def _gemm(fn, wdtype, xq, s_tok, wq, s_w, bias_fp16, want_acc, requant, workspac
 def zq_gemm_i8_dequant(xq, s_tok, wq, s_w, bias_fp16=None, want_acc=False, requant=False, workspace=None,
                        out=None, acc_out=None):
     """-> (out fp16 [M,N], acc int32 | None, out_q int8 | None, out_s_tok fp32 | None)."""
+    if out is None and acc_out is None and not want_acc and _host is not None:
+        done = _host.gemm(8, xq, s_tok, wq, s_w, bias_fp16, requant, workspace)
+        if done is not None:
+            return done
     return _gemm(lib().zq_gemm_i8_dequant, torch.int8, xq, s_tok, wq, s_w, bias_fp16, want_acc, requant,
                  workspace, out, acc_out)
 
@@ -426,6 +450,10 @@ def zq_gemm_i8_dequant_static(xq, s_tok, wq, s_w, bias_fp16=None, requant=False,
 def zq_gemm_w4a8_dequant(xq, s_tok, wq4, s_w, bias_fp16=None, want_acc=False, requant=False, workspace=None,
                          out=None, acc_out=None):
     """INT4-packed weights uint8 [N,K/2]; otherwise as zq_gemm_i8_dequant."""
+    if out is None and acc_out is None and not want_acc and _host is not None:
+        done = _host.gemm(4, xq, s_tok, wq4, s_w, bias_fp16, requant, workspace)
+        if done is not None:
+            return done
     return _gemm(lib().zq_gemm_w4a8_dequant, torch.uint8, xq, s_tok, wq4, s_w, bias_fp16, want_acc, requant,
                  workspace, out, acc_out)
 
@@ -438,6 +466,11 @@ def zq_gemm_gelu_quant_tokenwise(xq, s_tok, wq, s_w, bias_fp16=None, approx_tanh
     `out` = (g, gq, s) reuses caller tensors.  keep_g=False passes no g buffer (g comes back None):
     allowed where gemm_quantizes_in_kernel() holds, an error elsewhere.
     """
+    if out is None and _host is not None and isinstance(wq, torch.Tensor):
+        done = _host.gemm_gelu(8 if wq.dtype == torch.int8 else 4, xq, s_tok, wq, s_w, bias_fp16, approx_tanh, workspace,
+                               keep_g)
+        if done is not None:
+            return done
     _dev(xq, torch.int8, "xq")
     _dev(s_tok, torch.float32, "s_tok")
     _dev(s_w, torch.float32, "s_w")
@@ -478,6 +511,10 @@ def zq_gemm_gelu_quant_tokenwise(xq, s_tok, wq, s_w, bias_fp16=None, approx_tanh
 
 def zq_quantize_tokenwise(x_fp16, out=None):
     """x fp16 [M,K] -> (xq int8 [M,K], s_tok fp32 [M])."""
+    if out is None and _host is not None:
+        done = _host.quantize(x_fp16)
+        if done is not None:
+            return done
     _dev(x_fp16, torch.float16, "x_fp16")
     M, K = x_fp16.shape
     xq, s_tok = out if out is not None else (
@@ -504,6 +541,10 @@ def zq_dequantize_acc(acc, s_tok, s_w, bias_fp16=None, out=None):
 
 def zq_gemm_w8a16_dequant(x_fp16, wq, s_w, bias_fp16=None, workspace=None, out=None):
     """x fp16 [M,K] x wq int8 [N,K] -> out fp16 [M,N] = (x @ wq^T) * s_w[group] + bias."""
+    if out is None and _host is not None:
+        done = _host.gemm_a16(x_fp16, wq, s_w, bias_fp16, workspace)
+        if done is not None:
+            return done
     _dev(x_fp16, torch.float16, "x_fp16")
     _dev(wq, torch.int8, "wq")
     _dev(s_w, torch.float32, "s_w")

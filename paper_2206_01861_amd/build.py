@@ -1,4 +1,5 @@
-"""Build libzq.so in-tree with hipcc for gfx950 (cross-compiles without a GPU)."""
+"""Build libzq.so with hipcc for gfx950 (cross-compiles without a GPU) and _zq_host.so, the binding's native calls, with g++
+against the installed torch; both in-tree."""
 import os
 import subprocess
 import sys
@@ -8,6 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libzq.so")
+HOST = os.path.join(HERE, "_zq_host.so")
 
 SOURCES = [
     "zq_api.hip",
@@ -47,11 +49,30 @@ def _compile(src):
     return obj
 
 
+def _build_host():
+    import sysconfig
+
+    import torch
+    at = torch.__path__[0]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-I" + sysconfig.get_paths()["include"]]
+    for inc in (os.path.join(at, "include"), os.path.join(at, "include", "torch", "csrc", "api", "include"),
+                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")):
+        cmd += ["-isystem", inc]
+    cmd += [os.path.join(CSRC, "zq_host.cpp"), "-o", HOST, "-L" + os.path.join(at, "lib"),
+            "-lc10", "-lc10_hip", "-ltorch", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("the native binding failed to build:\n%s\n%s" % (r.stdout, r.stderr))
+
+
 def build(verbose=False, jobs=6):
-    """Compile every source and link libzq.so; always rebuilds."""
+    """Compile every source and link libzq.so and _zq_host.so; always rebuilds."""
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        host = ex.submit(_build_host)
         objs = list(ex.map(_compile, SOURCES))
+        host.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:

@@ -25,6 +25,7 @@ struct TuneEntry {
 };
 std::mutex g_tune_mutex;
 std::vector<TuneEntry> g_tune;
+std::atomic<unsigned> g_tune_generation{1};
 
 bool tune_lookup(int M, int N, int K, int w_bits, TuneEntry *out) {
     std::lock_guard<std::mutex> lock(g_tune_mutex);
@@ -37,6 +38,8 @@ bool tune_lookup(int M, int N, int K, int w_bits, TuneEntry *out) {
     return false;
 }
 }  // namespace
+
+unsigned tune_generation() { return g_tune_generation.load(std::memory_order_acquire); }
 
 bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_splits) {
     TuneEntry e;
@@ -196,12 +199,14 @@ extern "C" int zq_tune_set(int m_lo, int m_hi, int N, int K, int w_bits, int var
     }
     std::lock_guard<std::mutex> lock(g_tune_mutex);
     g_tune.push_back(TuneEntry{m_lo, m_hi, N, K, w_bits, variant, row_blocks, k_splits});
+    g_tune_generation.fetch_add(1, std::memory_order_release);
     return ZQ_OK;
 }
 
 extern "C" void zq_tune_clear(void) {
     std::lock_guard<std::mutex> lock(zq::g_tune_mutex);
     zq::g_tune.clear();
+    zq::g_tune_generation.fetch_add(1, std::memory_order_release);
 }
 
 extern "C" int zq_tune_count(void) {

@@ -116,13 +116,13 @@ __device__ __forceinline__ void stream_wait(int32x4 (&w)[LW]) {
 // (the wave that completes a strip resets its counter), so no launch is spent clearing them.
 
 struct StreamPlan {
-    int strips;       // 16-row strips of the weight matrix (N / 16)
-    int stages;       // stages of 256 K-values (K / 256)
-    int row_blocks;   // workgroups along N; the strips are dealt out as evenly as whole strips allow
-    int k_splits;     // workgroups along K; the stages likewise
-    int consumers;    // consumer waves per workgroup = most strips in a row block
+    int strips = 0;   // 16-row strips of the weight matrix (N / 16)
+    int stages = 0;   // stages of 256 K-values (K / 256)
+    int row_blocks = 0;   // workgroups along N; the strips are dealt out as evenly as whole strips allow
+    int k_splits = 1; // workgroups along K; the stages likewise
+    int consumers = 1;    // consumer waves per workgroup = most strips in a row block
     // filled by finish_plan(): strips / row_blocks, strips % row_blocks, stages / k_splits, stages % k_splits
-    int strips_per_block, strips_rem, stages_per_split, stages_rem;
+    int strips_per_block = 0, strips_rem = 0, stages_per_split = 0, stages_rem = 0;
     // 1: every strip of a row block is streamed by two waves, each over half of the block's K
     // range, and their accumulators are added through LDS at the end (see plan_stream)
     int range_shift = 0;
@@ -673,7 +673,7 @@ int stream_depth(int w_bits) { return w_bits == 8 ? 4 : 8; }   // a stage of a s
 // at most kCuRate bytes per microsecond, and no more than its consumers keep in flight over one
 // memory latency; the CU with the most bytes sets the time; activation loads share the CU's load
 // path in proportion to token tiles per consumer; a K split costs the exchange round trips.
-StreamPlan plan_stream(int M, int N, int K, int w_bits, bool allow_split, bool allow_ranges = true) {
+StreamPlan search_stream_plan(int M, int N, int K, int w_bits, bool allow_split, bool allow_ranges) {
     const int S = N / 16, St = K / kStageK, mt = token_tiles(M);
     const double kCuRate = 24e3, kStart = 4.0, kExchange = 4.5, kExchangeRate = 3e6;
     // memory latency in microseconds: about 1 on a quiet chip, 2 with 32 MB streaming, 4 beyond 80 MB
@@ -747,6 +747,26 @@ StreamPlan plan_stream(int M, int N, int K, int w_bits, bool allow_split, bool a
     best.stages_rem = St % best.k_splits;
     best.range_shift = (allow_ranges && best.k_splits == 1) ? range_rule(best.consumers, best.stages_per_split) : 0;
     return best;
+}
+
+// The search weighs some 300 cuts, 3 us of host time, and a call asks for the same plan up to four times (which schedule,
+// whether it splits, how much workspace, the launch): each thread remembers its last plans.  A plan follows from its
+// arguments and the schedule table alone.
+StreamPlan plan_stream(int M, int N, int K, int w_bits, bool allow_split, bool allow_ranges = true) {
+    struct Entry {
+        int M = 0, N = 0, K = 0, w_bits = 0, flags = 0;
+        unsigned table = 0;
+        StreamPlan plan;
+    };
+    constexpr unsigned kEntries = 64;
+    static thread_local Entry memo[kEntries];
+    const int flags = (allow_split ? 1 : 0) | (allow_ranges ? 2 : 0);
+    const unsigned table = tune_generation();
+    const unsigned h = ((unsigned)M * 73856093u ^ (unsigned)N * 19349663u ^ (unsigned)K * 83492791u ^ (unsigned)(w_bits + flags)) >> 4;
+    Entry &e = memo[(h ^ h >> 8) % kEntries];
+    if (e.M != M || e.N != N || e.K != K || e.w_bits != w_bits || e.flags != flags || e.table != table)
+        e = Entry{M, N, K, w_bits, flags, table, search_stream_plan(M, N, K, w_bits, allow_split, allow_ranges)};
+    return e.plan;
 }
 
 template <int MT, int WBITS, int QSH>

@@ -135,6 +135,7 @@ hipError_t launch_gemm_vector(const GemmArgs &a, hipStream_t st);
 const char *gemm_schedule_name(int variant, int M, int N, int K, int w_bits);
 
 // A caller-supplied cut of the streaming schedules for this shape, if one was registered.
+unsigned tune_generation();                   // changes with every change of the table
 bool tuned_stream_plan(int M, int N, int K, int w_bits, int *row_blocks, int *k_splits);
 
 // FP16 activations x INT8 weights (W8A16).
