@@ -63,7 +63,13 @@ __device__ __forceinline__ void stage_wait(Stage<RT, MT, LW, LX> &s) {
 
 // MT: 16-token tiles, RT: 16-row strips of the weights, XB: bytes of an activation (1 INT8, 2 FP16), D: stages a
 // wave keeps in flight, NW: waves.  rows: weight rows of a workgroup, even, at most 16 * RT.
-template <int MT, int RT, int WBITS, int XB, int D, int NW>
+//
+// HALF: up to eight tokens and eight weight rows fill a 16 x 16 matrix instruction twice, operand rows 0 to 7 with one half of a
+// stage that is then 512 values of K, rows 8 to 15 with the other; the two diagonal quarters of the result belong together.
+// Loads without idle lanes, half as many of them, and of permutations and products (pairs_pay says where).
+//
+// XP: activations are loaded like weights, 64 contiguous bytes per four lanes, and permuted (permuted_pays).
+template <int MT, int RT, int WBITS, int XB, int D, int NW, int HALF = 0, int XP = 0>
 __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void gemm_direct_kernel(
     const uint8_t *__restrict__ xq, const uint8_t *__restrict__ wq, int M, int N, int K, int rows, int gs, int act,
     const float *__restrict__ s_tok, const float *__restrict__ s_w, const half_t *__restrict__ bias,
@@ -71,6 +77,7 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     static_assert(XB == 1 || WBITS == 8, "FP16 activations go with INT8 weights");
     static_assert(D <= 2, "the drain is written out for two stages");
+    static_assert(HALF == 0 || (MT == 1 && RT == 1), "eight tokens and eight rows");
     constexpr int LW = (WBITS == 8) ? 4 : 2;
     constexpr int LX = (XB == 1) ? 4 : 8;
     constexpr int NT = 64 * NW;
@@ -90,22 +97,25 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
     constexpr int kNowhere = 0x7ffffff0;                    // past the end of either buffer: loads give 0
     // Weight loads run chunk-fastest (lane = 4 * row + 16-byte chunk), so that four consecutive lanes read 64
     // contiguous bytes; one cross-lane permutation per register restores the operand layout (lane = row + 16
-    // * chunk).  Activations are loaded in operand layout: with few tokens most lanes have no row to read.
+    // * chunk).  Activations are loaded in operand layout, unless XP: with few tokens most lanes have no row to read.
     const int wc = (lane % 4) * 16;
+    const int w_half = HALF ? lane / 32 * (64 * LW) : 0;    // second half of a stage: where it lies in a weight row
     int voff_w[RT], voff_x[MT];
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        const int n = n_base + 16 * t + lane / 4;
-        voff_w[t] = n < n_end ? n * wrow + wc : kNowhere;
+        const int n = n_base + 16 * t + (HALF ? lane / 4 % 8 : lane / 4);
+        voff_w[t] = n < n_end ? n * wrow + wc + w_half : kNowhere;
     }
     // The sixteen values of K that a lane multiplies in a step: INT8 weights, step i: 64i + 16j ..; INT4, step
     // 2i + h: 128i + 32j + 16h .. (16 packed bytes serve two steps); W8A16, eight values, step 2i + h: 64i +
     // 16j + 8h ...  Both operands use the same order, and a sum over K does not depend on it.
     constexpr int XJ = (XB == 1 && WBITS == 8) ? 16 : 32;   // bytes between the activations of neighbouring j
+    const int xr = XP ? lane / 4 : r, xj = XP ? lane % 4 : j;
+    const int x_half = HALF ? xr / 8 * (kStageK * XB) : 0;   // ... and in a row of activations
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-        const int m = m_base + 16 * t + r;
-        voff_x[t] = m < M ? m * K * XB + j * XJ : kNowhere;
+        const int m = m_base + 16 * t + (HALF ? xr % 8 : xr);
+        voff_x[t] = m < M ? m * K * XB + xj * XJ + x_half : kNowhere;
     }
     const int pull = 4 * (4 * r + j);
 
@@ -113,26 +123,28 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
     // Stage s of K belongs to wave s % NW: the workgroup reads its rows front to back.  (A contiguous range of K per
     // wave, which deals K out more evenly, measured 3-7 % slower: 6144x6144 at one token 9.4 -> 10.1 us.)  Past the end
     // of K nothing is read and the operands are zeros.
-    const int stages = (wrow + 64 * LW - 1) / (64 * LW);
+    constexpr int SB = 64 * LW * (1 + HALF);                // bytes of a weight row in a stage
+    const int stages = (wrow + SB - 1) / SB;
     auto issue = [&](int i, Stage<RT, MT, LW, LX> &s) __attribute__((always_inline)) {
-        const int b = (wave + i * NW) * (64 * LW);
+        const int b = (wave + i * NW) * SB;
         const int lim = wrow - b;                           // bytes of the row that are left
+        const int wlim = lim - w_half;
         const int so_w = lim > 0 ? b : 0;
         const int so_x = lim > 0 ? b * (8 / WBITS) * XB : 0;
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
-            async_load16<0>(s.w[t][0], wc < lim ? voff_w[t] : kNowhere, rs_w, so_w);
-            async_load16<64>(s.w[t][1], wc + 64 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+            async_load16<0>(s.w[t][0], wc < wlim ? voff_w[t] : kNowhere, rs_w, so_w);
+            async_load16<64>(s.w[t][1], wc + 64 < wlim ? voff_w[t] : kNowhere, rs_w, so_w);
             if constexpr (LW == 4) {
-                async_load16<128>(s.w[t][2], wc + 128 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
-                async_load16<192>(s.w[t][3], wc + 192 < lim ? voff_w[t] : kNowhere, rs_w, so_w);
+                async_load16<128>(s.w[t][2], wc + 128 < wlim ? voff_w[t] : kNowhere, rs_w, so_w);
+                async_load16<192>(s.w[t][3], wc + 192 < wlim ? voff_w[t] : kNowhere, rs_w, so_w);
             }
         }
         // INT8 activations past the end of a row (less than a load) are whatever follows: their weights are zero.
         // FP16 ones have to be zero themselves (0 * NaN is not 0), so the test is made per lane.
 #pragma unroll
         for (int t = 0; t < MT; ++t) {
-            const int xl = lim - (XB == 2 ? 16 * j : 0);
+            const int xl = lim - (HALF ? xr / 8 * (64 * LW) : 0) - (XB == 2 ? 16 * xj : 0);
             const int v0 = 0 < xl ? voff_x[t] : kNowhere, v1 = 64 < xl ? voff_x[t] : kNowhere;
             if constexpr (WBITS == 4) {
                 async_load16<0>(s.x[t][0], v0, rs_x, so_x);
@@ -168,6 +180,14 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[t][m][e] = 0;
     auto compute = [&](const Stage<RT, MT, LW, LX> &s) __attribute__((always_inline)) {
+        int32x4 xf[MT][LX];
+#pragma unroll
+        for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int i = 0; i < LX; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    xf[m][i][e] = XP ? __builtin_amdgcn_ds_bpermute(pull, s.x[m][i][e]) : s.x[m][i][e];
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
@@ -178,7 +198,7 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
                 if constexpr (XB == 1 && WBITS == 8) {
 #pragma unroll
                     for (int m = 0; m < MT; ++m)
-                        acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, s.x[m][i], acc[t][m], 0, 0, 0);
+                        acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w, xf[m][i], acc[t][m], 0, 0, 0);
                 } else {
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
@@ -189,13 +209,13 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
                             const int32x4 a = {(int)d0, (int)d1, (int)d2, (int)d3};
 #pragma unroll
                             for (int m = 0; m < MT; ++m)
-                                acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, s.x[m][2 * i + h], acc[t][m], 0, 0, 0);
+                                acc[t][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, xf[m][2 * i + h], acc[t][m], 0, 0, 0);
                         } else {
                             const half8 a = cvt8_i8_f16((uint32_t)w[2 * h], (uint32_t)w[2 * h + 1]);
 #pragma unroll
                             for (int m = 0; m < MT; ++m)
                                 acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                                    a, __builtin_bit_cast(half8, s.x[m][2 * i + h]), acc[t][m], 0, 0, 0);
+                                    a, __builtin_bit_cast(half8, xf[m][2 * i + h]), acc[t][m], 0, 0, 0);
                         }
                     }
                 }
@@ -219,13 +239,14 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
     // Operands of the epilogue, fetched under the last stages.  Thread t of an output tile finishes columns 2 *
     // (t % 8), + 1 of token t / 8 (an even column and the next lie in one weight group); indices past the edge are
     // clamped, loaded and not used; without a bias its load reads a valid dummy.
-    constexpr int ITEMS = RT * MT * 128, IT = (ITEMS + NT - 1) / NT;
+    constexpr int PAIRS = HALF ? 4 : 8;
+    constexpr int ITEMS = HALF ? 32 : RT * MT * 128, IT = (ITEMS + NT - 1) / NT;
     uint32_t e_sw[IT], e_st[IT], e_b[IT];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
         const int idx = (int)threadIdx.x + it * NT;
         const int t = idx / 128, q = idx % 128;
-        int n = n_base + (t / MT) * 16 + 2 * (q % 8), m = m_base + (t % MT) * 16 + q / 8;
+        int n = n_base + (t / MT) * 16 + 2 * (q % PAIRS), m = m_base + (t % MT) * 16 + q / PAIRS;
         if (n > N - 2) n = N - 2;
         if (m > M - 1) m = M - 1;
         async_load_dword(e_sw[it], s_w + n / gs);
@@ -254,7 +275,7 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
         const int idx = (int)threadIdx.x + it * NT;
         if (idx >= ITEMS) break;
         const int t = idx / 128, q = idx % 128;
-        const int nl = 2 * (q % 8), ml = q / 8;
+        const int nl = 2 * (q % PAIRS), ml = q / PAIRS;
         const int n = n_base + (t / MT) * 16 + nl, m = m_base + (t % MT) * 16 + ml;
         const int32_t *p = part + t * kTileInts + (nl / 4) * 96 + ml * 4 + nl % 4;
         // the waves in order: the fp32 sums are the same in every call
@@ -262,6 +283,16 @@ __global__ __launch_bounds__(64 * NW, (MT * RT == 1 && XB == 1) ? 4 : 2) void ge
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const int2 v = *reinterpret_cast<const int2 *>(p + w * RT * MT * kTileInts);
+            if constexpr (HALF) {                           // rows 8 to 15, tokens 8 to 15
+                const int2 u = *reinterpret_cast<const int2 *>(p + w * kTileInts + 2 * 96 + 8 * 4);
+                if constexpr (XB == 2) {
+                    a0 += __int_as_float(u.x);
+                    a1 += __int_as_float(u.y);
+                } else {
+                    a0 += u.x;
+                    a1 += u.y;
+                }
+            }
             if constexpr (XB == 2) {
                 a0 += __int_as_float(v.x);
                 a1 += __int_as_float(v.y);
@@ -558,11 +589,27 @@ DirectPlan plan_direct(int M, int N, int w_bits, int xb) {
     return p;
 }
 
-template <int MT, int RT, int WBITS, int XB, int D, int NW>
+// Up to eight tokens against so few rows that a workgroup has eight of them: both halves of the matrix instruction (HALF).
+// us, before / so: INT8 1600x6400 at 5 tokens 6.1 / 5.2, 2048x8192 at 5 6.7 / 6.1, 1536x1536 at 6 3.2 / 2.9; INT4 1984x1984 at 8
+// 3.0 / 2.8, 2048x8192 at 5 5.3 / 4.6; W8A16 1600x1600 at 6 3.7 / 3.3.  More rows are more workgroups of eight, each of which
+// reads the activations (2400x2400 at 5 3.7 / 4.0, 3072x12288 at 8 10.0 / 14.1), and of four stages or fewer half the waves
+// are idle (1024x1024 at 5 2.5 / 2.7).
+bool pairs_pay(int M, int N, int K) { return M <= 8 && N <= 8 * kCUs && K > 4 * kStageK; }
+
+// In operand layout the vector cache delivers 38 GB/s a compute unit, a quarter of its rate (four neighbouring lanes read four
+// lines); the permutations that contiguous loads need instead pay from some twelve tokens on, where a compute unit has few
+// rows against its activations and their rows begin on cache lines.  us, operand layout / permuted: INT8 2048x2048 at 27 tokens
+// 4.5 / 4.0, 896x3584 at 16 4.4 / 3.8; INT4 2048x8192 at 27 9.7 / 7.5, 4096x16384 at 16 12.6 / 11.7; W8A16 2048x2048 at 27 6.2 / 5.0;
+// beyond: 3072x3072 at 9 4.6 / 4.7, 1600x1600 at 24 3.6 / 3.9, 1120x1120 at 20 3.3 / 3.6, 6144x2048 at 16 5.2 / 5.2.
+bool permuted_pays(int M, int N, int K) {
+    return M >= 12 && M <= 32 && N <= 16 * kCUs && (K % 256 == 0 || (K >= 2048 && K % 64 == 0));
+}
+
+template <int MT, int RT, int WBITS, int XB, int D, int NW, int HALF, int XP>
 hipError_t launch_direct_t(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
                            const void *bias, int M, int N, int K, int rows, void *out, int32_t *acc_out, int act,
                            hipStream_t st) {
-    hipLaunchKernelGGL((gemm_direct_kernel<MT, RT, WBITS, XB, D, NW>),
+    hipLaunchKernelGGL((gemm_direct_kernel<MT, RT, WBITS, XB, D, NW, HALF, XP>),
                        dim3((N + rows - 1) / rows, (M + 16 * MT - 1) / (16 * MT)), dim3(64 * NW), 0, st,
                        static_cast<const uint8_t *>(x), static_cast<const uint8_t *>(wq), M, N, K, rows, N / groups, act, s_tok,
                        s_w, static_cast<const half_t *>(bias), static_cast<half_t *>(out), acc_out);
@@ -575,32 +622,46 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
     const DirectPlan p = plan_direct(M, N, WBITS, XB);
     const int nst = (K + kStageK - 1) / kStageK;
     const int rt = p.rows > 16 ? 2 : 1;
+#define ZQ_DK(MT, RT, D, NW, HALF, XP)                                                                                     \
+    return launch_direct_t<MT, RT, WBITS, XB, D, NW, HALF, XP>(x, s_tok, wq, s_w, groups, bias, M, N, K, p.rows, out,      \
+                                                               acc_out, act, st)
+    if (pairs_pay(M, N, K)) {
+        const int pairs = (K + 2 * kStageK - 1) / (2 * kStageK);
+        if (pairs <= 4) ZQ_DK(1, 1, 1, 4, 1, 0);
+        if (pairs <= 8) ZQ_DK(1, 1, 1, 8, 1, 0);
+        ZQ_DK(1, 1, 2, 8, 1, 0);
+    }
     // Eight waves, four where K has no stage for more (768x768 at 64 tokens: 2.9 us against 3.2).  INT4 stages are half
     // as many bytes: with few tokens a wave keeps two in flight, unless that leaves one of them empty (2048x8192 at one
     // token 5.7 -> 5.3 us; for INT8 it measured level).
     const int nw = nst <= 4 ? 4 : 8;
     [[maybe_unused]] const bool two = M <= 8 && ((nst + nw - 1) / nw) % 2 == 0;
-#define ZQ_DK(MT, RT, D, NW)                                                                                         \
-    return launch_direct_t<MT, RT, WBITS, XB, D, NW>(x, s_tok, wq, s_w, groups, bias, M, N, K, p.rows, out, acc_out, \
-                                                     act, st)
+    if (permuted_pays(M, N, K)) {
+        if (p.mt == 1) {
+            if (nw == 4) ZQ_DK(1, 1, 1, 4, 0, 1);
+            ZQ_DK(1, 1, 1, 8, 0, 1);
+        }
+        if (nw == 4) ZQ_DK(2, 1, 1, 4, 0, 1);
+        ZQ_DK(2, 1, 1, 8, 0, 1);
+    }
     if (p.mt == 1) {
         if (nw == 4) {
-            if (rt == 1) ZQ_DK(1, 1, 1, 4);
-            ZQ_DK(1, 2, 1, 4);
+            if (rt == 1) ZQ_DK(1, 1, 1, 4, 0, 0);
+            ZQ_DK(1, 2, 1, 4, 0, 0);
         }
         if constexpr (WBITS == 4) {
-            if (two && rt == 1) ZQ_DK(1, 1, 2, 8);
-            if (two) ZQ_DK(1, 2, 2, 8);
+            if (two && rt == 1) ZQ_DK(1, 1, 2, 8, 0, 0);
+            if (two) ZQ_DK(1, 2, 2, 8, 0, 0);
         }
-        if (rt == 1) ZQ_DK(1, 1, 1, 8);
-        ZQ_DK(1, 2, 1, 8);
+        if (rt == 1) ZQ_DK(1, 1, 1, 8, 0, 0);
+        ZQ_DK(1, 2, 1, 8, 0, 0);
     }
     if (nw == 4) {
-        if (rt == 1) ZQ_DK(2, 1, 1, 4);
-        ZQ_DK(2, 2, 1, 4);
+        if (rt == 1) ZQ_DK(2, 1, 1, 4, 0, 0);
+        ZQ_DK(2, 2, 1, 4, 0, 0);
     }
-    if (rt == 1) ZQ_DK(2, 1, 1, 8);
-    ZQ_DK(2, 2, 1, 8);
+    if (rt == 1) ZQ_DK(2, 1, 1, 8, 0, 0);
+    ZQ_DK(2, 2, 1, 8, 0, 0);
 #undef ZQ_DK
 }
 
@@ -711,6 +772,11 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 //          10240x2560 at 1 8.0 / 9.0.  Three strips per compute unit whose rows lie 4 KB apart depend on where the
 //          captured launches run: 12288x4096 at 1 to 4 11.3 / 11.4 in some graphs, 13.2 to 13.5 in others (12256x4608 13.0 /
 //          12.4, 11520x3840 10.1 / 9.7).
+// With permuted activations (permuted_pays) some lines for up to 4096 rows lie further out; 150 shapes, us, streaming / direct:
+//   INT8   9 to 16 tokens, K 2816 to 6144: 3840x3840 at 12 7.4 / 5.5, 1008x3328 at 16 4.8 / 3.8, 832x6144 at 12 5.5 / 4.5, 1184x4864 at 16
+//          4.7 / 4.8; beyond: 4096x4096 at 16 5.7 / 6.1.  17 to 32, K 3072 to 4096: 1424x3840 at 24 6.1 / 4.8, 1888x3328 at 32 5.7 / 5.2;
+//          beyond: 3072x3072 at 32 6.2 / 6.5, 2144x4352 at 20 6.3 / 6.8, 2304x2304 at 24 4.7 / 4.9
+//   INT4   1904x10240 at 32 15.9 / 9.6, 2816x11264 at 32 18.8 / 10.9, 4400x11776 at 24 19.6 / 13.9; beyond: 1744x12544 at 24 9.7 / 10.7
 // A K of one or two stages leaves most of the waves without work (12144x256 at 39 3.9 / 4.8, 11632x512 at 30 3.9 / 5.0,
 // INT4 12304x256 at 36 4.0 / 5.0, W8A16 9184x256 at 35 5.0 / 6.6).
 //
@@ -755,13 +821,19 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     if (xb == 2)
         return load <= (one_round ? 131072 : 65536) &&
                (filled || N <= (M <= 8 ? 6144 : 5120) || (M <= 4 && K > 4608 && N <= 16384));
-    if (w_bits == 4)
+    if (w_bits == 4) {
+        if (N >= 1792 && N <= 4608 && K <= 11776 && load <= 362000) return true;
         return load <= (one_round ? 270000 : 200000) && (one_round || M <= 16 || (M <= 24 && N > 12288 && N <= 16384));
+    }
     if (M <= 8) {
         if (K % 4096 == 0 && N > 8192 && N <= 12288) return false;      // three strips per compute unit, rows 4 KB apart
         return load <= 200000 && (N <= 4096 || filled) && (one_round || M <= 4);
     }
-    if (M <= 16) return K > 512 && (K <= 2560 ? N <= 4096 : (K >= 5120 && N >= 2560 && one_round && load <= 131072));
+    if (M <= 16) {
+        if (K > 2560 && K <= 6144 && N >= 768 && N < 4096) return true;
+        return K > 512 && (K <= 2560 ? N <= 4096 : (K >= 5120 && N >= 2560 && one_round && load <= 131072));
+    }
+    if (K >= 3072 && K <= 4096 && N >= 768 && (N <= 2048 || (M <= 24 && N < 4096 && K < 4096))) return true;
     return K >= 1024 && K <= 2048 && N <= 4096;
 }
 
