@@ -341,8 +341,9 @@ __global__ __launch_bounds__(64 * NW, (MT * RT <= 8) ? 2 : 1) void gemm_mid_kern
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass only needs the launch stub
     constexpr int LW = kMidStageK * WBITS / 512;            // 16-byte loads per lane and stage: of a strip ...
     constexpr int LX = kMidStageK * XB / 64;                // ... and of 16 tokens
-    constexpr int T = RT * MT, TPW = T / NW;                // tiles of the workgroup; those that one wave finishes
-    static_assert(T % NW == 0 && LW >= 1, "");
+    // tiles of the workgroup; those that one wave finishes (with more waves than tiles only the first T finish any)
+    constexpr int T = RT * MT, TPW = T > NW ? T / NW : 1;
+    static_assert((T % NW == 0 || NW % T == 0) && LW >= 1, "");
     using AccT = typename std::conditional<XB == 2, float32x4, int32x4>::type;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     AccT *part = reinterpret_cast<AccT *>(smem);            // [wave][tile][lane]
@@ -379,7 +380,7 @@ __global__ __launch_bounds__(64 * NW, (MT * RT <= 8) ? 2 : 1) void gemm_mid_kern
     half4 e_b[TPW];
 #pragma unroll
     for (int q = 0; q < TPW; ++q) {
-        const int tile = wave * TPW + q;
+        const int tile = (wave * TPW + q) % T;
         int n = n_base + (tile / MT) * 16 + 4 * j, m = m_base + (tile % MT) * 16 + r;
         if (n > N - 4) n = N - 4;
         if (m > M - 1) m = M - 1;
@@ -491,7 +492,7 @@ __global__ __launch_bounds__(64 * NW, (MT * RT <= 8) ? 2 : 1) void gemm_mid_kern
     const int pull_out = 4 * ((lane % 4) * 16 + lane / 4);
     auto finish = [&](auto w_c) __attribute__((always_inline)) {
         constexpr int W = decltype(w_c)::value;
-        if constexpr (W < NW) {
+        if constexpr (W < NW && W < T) {
             if (wave != W) return;
 #pragma unroll
             for (int q = 0; q < TPW; ++q) {
@@ -665,23 +666,23 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
 #undef ZQ_DK
 }
 
-// The tile of gemm_mid_kernel for a shape: the one with the lowest modelled time among those whose workgroups all run at
-// once (one per compute unit; two of the 32 x 32 ones).  A second round of them loses to the LDS-tiled kernels.  The
-// model: a start, the rounds of stages that a wave goes through, the bytes a compute unit pulls through its vector cache
-// (in 115 KB, which take a microsecond) and the weights from memory (in 5 MB).  Fitted to 32 shapes (768 to 24576 rows, K
-// 768 to 24576) at 24 to 1024 tokens.  Against 4355 random ones its error is 10 to 20 % rms; the choice by it costs 0.3 % (INT8),
-// 0.4 % (INT4) and 4.2 % (W8A16) on average over the best tile: the W8A16 row of 64 x 32, whose start of 1.06 and stage of
-// 3.4 us are those of no launch, is 12 % too high in the median, and that tile is taken too rarely.
+// The tile of gemm_mid_kernel for a shape: the one with the lowest modelled time among those whose workgroups run at once (a
+// compute unit holds up to four of 32 x 32, two of 64 x 32, one of 64 x 64).  The model: a start, the rounds of stages that a
+// wave goes through, the bytes a compute unit pulls through its vector cache (in 115 KB, which take a microsecond) and the
+// weights from memory (in 5 MB); a compute unit's share of the tiles is taken between the fullest one's and the average, by
+// `full`.  Fitted to 577 shapes (33 to 900 tokens, 768 to 24576 rows, K 768 to 16384): 5 to 10 % rms, and the choice by it
+// costs 0.1 % (INT8), 0.3 % (INT4) and 0.2 % (W8A16) on average over the best tile.
 enum MidShape { kMid32x32, kMid64x32, kMid64x64, kMidShapes };
 struct MidCost {
-    int bm, bn, waves, depth;
-    double start, stage, cache, memory;
+    int bm, bn, waves;
+    double start, stage, cache, memory, full;
 };
 constexpr MidCost kMidCost[3][kMidShapes] = {
-    {{32, 32, 4, 2, 2.92, 0.374, 0.84, 0.22}, {64, 32, 8, 2, 2.88, 1.298, 0.92, 0.0}, {64, 64, 4, 1, 4.09, 0.875, 0.70, 0.23}},
-    {{32, 32, 4, 2, 3.00, 0.405, 0.04, 0.27}, {64, 32, 8, 2, 3.47, 0.910, 0.58, 0.0}, {64, 64, 8, 1, 4.13, 1.261, 0.64, 0.01}},
-    {{32, 32, 4, 2, 3.23, 0.597, 0.61, 0.26}, {64, 32, 8, 2, 1.06, 3.392, 0.30, 0.0}, {64, 64, 8, 1, 4.03, 2.807, 0.57, 0.0}},
+    {{32, 32, 8, 2.41, 0.601, 0.94, 0.40, 0.68}, {64, 32, 8, 2.37, 0.992, 0.84, 0.56, 0.71}, {64, 64, 4, 3.39, 0.968, 0.50, 0.47, 0.00}},
+    {{32, 32, 8, 2.51, 0.588, 0.50, 0.49, 0.90}, {64, 32, 8, 2.59, 1.169, 0.00, 0.65, 1.00}, {64, 64, 8, 3.35, 1.314, 0.63, 0.55, 0.00}},
+    {{32, 32, 8, 2.49, 1.011, 0.75, 0.20, 0.69}, {64, 32, 8, 2.21, 2.376, 0.21, 0.50, 0.99}, {64, 64, 8, 3.36, 2.159, 1.07, 0.44, 0.42}},
 };
+constexpr int kMidPerCU[kMidShapes] = {4, 2, 1};
 
 MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
     int best = kMidShapes;
@@ -689,11 +690,12 @@ MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
     for (int i = 0; i < kMidShapes; ++i) {
         const MidCost &c = kMidCost[xb == 2 ? kTileA16 : w_bits == 8 ? kTileI8 : kTileI4][i];
         const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        if (tiles > (i == kMid32x32 ? 2 : 1) * kCUs) continue;
-        const int per_wave = (K + kMidStageK * c.waves - 1) / (kMidStageK * c.waves);
-        const int stages = (per_wave + c.depth - 1) / c.depth * c.depth * (tiles > kCUs ? 2 : 1);
-        const double per_cu = (double)tiles / kCUs * K * (c.bm * xb + c.bn * w_bits / 8.0);
-        const double t = c.start + stages * c.stage + c.cache * per_cu / 115e3 + c.memory * N * K * (w_bits / 8.0) / 5e6;
+        if (tiles > kMidPerCU[i] * kCUs) continue;
+        const int stages = (K + kMidStageK * c.waves - 1) / (kMidStageK * c.waves);
+        const double load = c.full * ((tiles + kCUs - 1) / kCUs) + (1.0 - c.full) * tiles / kCUs;
+        const double bytes = (double)K * (c.bm * xb + c.bn * w_bits / 8.0);
+        const double t = c.start + stages * c.stage * (load > 1.0 ? load : 1.0) + c.cache * load * bytes / 115e3 +
+                         c.memory * N * K * (w_bits / 8.0) / 5e6;
         if (t < best_us) {
             best_us = t;
             best = i;
@@ -708,8 +710,25 @@ hipError_t launch_mid(MidShape shape, const void *x, const float *s_tok, const v
                       const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int act, hipStream_t st) {
 #define ZQ_MK(MT, RT, D, NW) \
     return launch_mid_t<MT, RT, WBITS, XB, D, NW>(x, s_tok, wq, s_w, groups, bias, M, N, K, out, acc_out, act, st)
-    if (shape == kMid32x32) ZQ_MK(2, 2, 2, 4);
-    if (shape == kMid64x32) ZQ_MK(4, 2, 2, 8);
+    // Eight waves with one stage in flight each: twice as many workgroups fit a compute unit as with two stages, and K is in more
+    // hands (four waves with two stages / eight with one, us: W8A16 2048x2048 at 128 tokens 7.2 / 5.9, INT4 1600x6400 at 64
+    // 9.0 / 7.4, INT8 2048x2048 at 48 4.35 / 4.10, 1600x6400 at 128 10.8 / 10.9; on 64 x 32, eight waves with two / one: W8A16 3072x1024
+    // at 100 7.6 / 5.2, INT8 3072x3072 at 128 10.9 / 9.5).  Two where a wave has many of them, one after the other: INT4, whose
+    // stages are half the bytes, from four on (2048x8192 at 40 8.8 against 10.1), INT8 on 64 x 32 from six (1536x6144 at 245
+    // 14.1 against 14.9).
+    [[maybe_unused]] const int per_wave = (K + 8 * kMidStageK - 1) / (8 * kMidStageK);
+    if (shape == kMid32x32) {
+        if constexpr (WBITS == 4) {
+            if (per_wave >= 4 && per_wave % 2 == 0) ZQ_MK(2, 2, 2, 8);
+        }
+        ZQ_MK(2, 2, 1, 8);
+    }
+    if (shape == kMid64x32) {
+        if constexpr (WBITS == 8 && XB == 1) {
+            if (per_wave >= 6) ZQ_MK(4, 2, 2, 8);
+        }
+        ZQ_MK(4, 2, 1, 8);
+    }
     // Eight waves on 64 x 64 where a stage is half or twice the bytes of an INT8 one (INT4: 2560x10240 at 256 tokens 21.1
     // us, 26.6 with four; W8A16: 6144x2048 at 128 tokens 10.5, 13.5), four for INT8 (1600x6400 at 450 18.8, 21.0)
     if constexpr (WBITS == 8 && XB == 1)
@@ -780,19 +799,20 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // A K of one or two stages leaves most of the waves without work (12144x256 at 39 3.9 / 4.8, 11632x512 at 30 3.9 / 5.0,
 // INT4 12304x256 at 36 4.0 / 5.0, W8A16 9184x256 at 35 5.0 / 6.6).
 //
-// More tokens, as long as one round of small tiles covers the output (choose_mid): streaming was built for a weight
+// More tokens, as long as the small tiles that cover the output run at once (choose_mid): streaming was built for a weight
 // stream that 128 tokens no longer are, and the LDS tiles leave most compute units idle or split K through memory.  The
 // small tiles lose where K is so long that their traffic per product, two to four times that of a 128 x 128 tile, is the
 // time, and, up to 64 tokens, where the matrix is large enough to keep the streaming kernel busy.  Microseconds,
 // what ran before / small tiles:
-//   INT8   2048x2048 at 64 tokens 6.5 / 4.9, at 128 10.7 / 5.7, at 256 9.2 / 6.6; 768x3072 at 128 12.8 / 5.9; 1600x6400
-//          at 128 14.3 / 10.0; 4096x4096 at 192 17.4 / 14.4; beyond: 7680x2560 at 64 9.5 / 11.4, 6912x2304 at 40 7.7 / 9.7,
-//          1792x6656 at 54 8.8 / 10.4, 2048x8192 at 64 10.5 / 12.2, 2560x10240 at 128 18.8 / 24.8, 2048x2048 at 512 (K tiles as good) 9.3 / 9.9
-//   INT4   2048x2048 at 128 10.7 / 5.3, 1024x4096 at 1024 18.4 / 10.7, 16384x4096 at 64 15.9 / 11.5, 6144x6144 at 64
-//          19.3 / 11.8, 2560x10240 at 256 26.6 / 21.1; beyond: 4096x16384 at 128 21.6 / 23.6, 3072x12288 at 48 14.8 / 16.4,
-//          4096x11872 at 65 17.6 / 24.2, 4000x11584 at 200 23.3 / 27.0
-//   W8A16  6144x2048 at 64 10.6 / 8.6, at 128 18.7 / 10.5; 4800x1600 at 192 17.4 / 10.8; beyond: 7680x2560 at 64 12.6 /
-//          17.8, 6912x2304 at 40 11.2 / 12.4, 1024x4096 at 64 8.9 / 10.6, 1600x6400 at 128 16.4 / 16.8
+//   INT8   2048x2048 at 64 tokens 6.5 / 4.2, at 128 10.7 / 5.2; 1600x6400 at 128 14.3 / 10.9; beyond: 7680x2560 at 64 9.5 / 11.4,
+//          6912x2304 at 40 7.7 / 9.7, 1664x6656 at 61 9.1 / 10.6, 2048x8192 at 64 9.9 / 12.1
+//   INT4   2048x2048 at 128 10.7 / 4.4, 6144x6144 at 64 19.3 / 11.8, 3392x13568 at 45 19.4 / 14.8, 3072x12288 at 128 21.8 / 19.4;
+//          beyond: 3072x12288 at 48 15.2 / 13.7 to 16.4, 4096x11872 at 65 17.6 / 24.2, 4000x11584 at 200 23.3 / 27.0
+//   W8A16  6144x2048 at 64 10.6 / 8.6, 3840x3840 at 39 15.8 / 9.4, 896x3584 at 40 13.4 / 7.5, 8064x2688 at 59 16.8 / 12.8; beyond:
+//          7680x2560 at 64 12.6 / 17.8, 1280x5120 at 52 10.0 / 10.3, 2752x11008 at 49 17.4 / 19.5
+// Above 64 tokens the modelled time decides, against those of the unsplit and the split LDS tiles; the factors are the ones
+// that lose least over 600 shapes (INT8 80x6144x2048 11.3 / 9.1 against streaming, whose time at K 2048 to 2304 is above that
+// of the tiles; W8A16 149x1280x5120 1.35 times as fast, 245x400x5728 and longer K left to the split).
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     if (xb == 1 && vector_pays(M, N, K, w_bits)) return true;
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
@@ -804,15 +824,17 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
         if (shape == kMidShapes) return false;
         const bool int8 = w_bits == 8 && xb == 1;
         if (M <= 64) {
-            if (w_bits == 4) return K <= (N <= 1024 ? 8192 : N <= 3072 ? 10240 : 12288);
+            if (w_bits == 4) return K <= (N <= 1024 ? 8192 : N <= 3072 ? 10240 : 16384);
             if ((long)N * K > (1L << 24) || (K > 1024 && N > (K <= 2048 ? 8192 : 4096))) return false;
-            return K <= (xb == 2 ? 3072 : shape == kMid64x64 ? 5120 : 6400);
+            return K <= (xb == 2 ? (M <= 48 ? 4608 : 3072) : shape == kMid64x64 ? 5120 : 6400);
         }
-        if (K > (xb == 2 ? 4096 : w_bits == 4 ? (N <= 3072 ? 12288 : 9216) : shape == kMid64x64 ? 5120 :
-                 shape == kMid64x32 ? 6656 : 8192))
-            return false;
         choose_tile(xb == 2 ? kTileA16 : int8 ? kTileI8 : kTileI4, M, N, K, kAllTileShapes, &tile_us);
-        return us < (int8 ? 0.94 : 1.0) * tile_us;
+        if (w_bits == 4) return K <= (N <= 3072 ? 12288 : 9216) && us < 0.96 * tile_us;
+        const double split_us = tile_split_time(M, N, K, xb);
+        if (split_us < tile_us) tile_us = split_us;
+        if (xb == 2 && K > 5120) return false;
+        const bool streams = M <= 128 && K >= 2048 && K < 2560;
+        return us < (xb == 2 ? 0.85 : streams ? 1.1 : 0.93) * tile_us;
     }
     const long load = (long)M * K * xb * ((N + 32 * kCUs - 1) / (32 * kCUs));
     const bool one_round = N <= 32 * kCUs;

@@ -1038,9 +1038,10 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const int32x4 *__res
 // measurements at 130 to 1024 tokens (microseconds): a tile over K takes 4.5 + u per 1024 bytes of
 // an activation row (u = 4.0 for INT8 activations, 5.2 for FP16 ones); the K split adds the second
 // kernel's launch, 3, and 0.5 per MB of partial products written and read back.
-int tile_splits(int M, int N, int K, int x_bytes) {
+int tile_splits(int M, int N, int K, int x_bytes, double *us = nullptr) {
     const long tiles = (long)((M + 127) / 128) * ((N + 127) / 128);
     const int nkt = (K * x_bytes + 127) / 128;
+    if (us != nullptr) *us = 1e30;
     if (tiles > 128 || nkt < 8) return 1;
     int ks_max = (int)(256 / tiles);
     if (ks_max > nkt / 4) ks_max = nkt / 4;
@@ -1055,6 +1056,7 @@ int tile_splits(int M, int N, int K, int x_bytes) {
         if (t < best_t) {
             best_t = t;
             best = ks;
+            if (us != nullptr) *us = t;
         }
     }
     return best;
@@ -1199,6 +1201,12 @@ int gemm_tile_splits(int M, int N, int K) {
     // tokens, K split against streaming: 4096x4096 15.2 vs 17 us, 1024x4096 11.3 vs 13 us, 2048x2048 a tie)
     if ((K % 256) == 0 && (M <= 64 || (M <= 128 && K < 4096))) return 1;
     return tile_splits(M, N, K, 1);
+}
+
+double tile_split_time(int M, int N, int K, int x_bytes) {
+    double us;
+    tile_splits(M, N, K, x_bytes, &us);
+    return us;
 }
 
 size_t gemm_tile_split_workspace(int M, int N, int K) {

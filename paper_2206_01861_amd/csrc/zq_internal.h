@@ -113,6 +113,7 @@ hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st);
 // 128x128 tiles with a K split: how many splits pay for a shape (1 = none), the workspace they
 // need, and the launch (two kernels).
 int gemm_tile_splits(int M, int N, int K);
+double tile_split_time(int M, int N, int K, int x_bytes);      // modelled, in microseconds; 1e30 where no split pays
 size_t gemm_tile_split_workspace(int M, int N, int K);
 hipError_t launch_gemm_tile_splitk(const GemmArgs &a, hipStream_t st);
 
