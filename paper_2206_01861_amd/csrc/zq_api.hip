@@ -88,7 +88,10 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
         if (forced >= 0) a.quant_shapes = zq::tile_shapes_of(forced);
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
-    if (zq::launch_gemm(direct ? (int)zq::kGemmSimple : cls, a, st) != hipSuccess) return ZQ_ERR_HIP;
+    const int launched = direct ? (int)zq::kGemmSimple
+                         : forced >= 0 ? cls
+                                       : zq::unsplit_if_faster(cls, M, N, K, w_bits, workspace_bytes);
+    if (zq::launch_gemm(launched, a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
         if (zq::launch_rowquant(zq::kOpIdentity, out, nullptr, nullptr, 0.0f, M, N, out_q, out_s_tok, nullptr, 0,
@@ -401,7 +404,8 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
         if (variant < 0)
             variant = zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes)
                           ? (int)zq::kGemmSimple
-                          : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
+                          : zq::unsplit_if_faster(zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes), M, N, K,
+                                                  w_bits, workspace_bytes);
         if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return nullptr;
         return zq::gemm_schedule_name(variant, M, N, K, w_bits);
     }

@@ -99,6 +99,20 @@ int variant_of(TileShape shape) {
 }
 }  // namespace
 
+// The K split of the tiles is a class by a model that knows 128x128 tiles only, and what a workspace is sized for.  A call
+// runs the best unsplit tile instead where that is faster by its own model, also without the second launch (INT8, 842x1024x4096
+// 15.9 -> 13.6 us, 1007x1600x6400 24.9 -> 21.2, 200x2560x3072 14.8 -> 12.3).  At five per cent 5 of 15 shapes of the class change over
+// and none loses; at equal times or above 512x2048x8192 would (25.3 -> 27.4).  INT4 weights and FP16 activations keep the
+// split: their models draw even only where it is ahead (INT4 784x1600x6400 24.4 against 27.2, W8A16 433x3072x3072 24.7, 26.9).
+int unsplit_if_faster(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes) {
+    TuneEntry e;
+    if (variant != kGemmTileSplitK || w_bits != 8) return variant;
+    if (tune_lookup(M, N, K, w_bits, &e) && gemm_variant_supports(e.variant, M, N, K, w_bits, workspace_bytes)) return variant;
+    double us;
+    const TileShape shape = choose_tile(kTileI8, M, N, K, kAllTileShapes, &us);
+    return us < 0.95 * tile_split_time(M, N, K, 1) ? variant_of(shape) : variant;
+}
+
 unsigned tile_shapes_of(int variant) {
     switch (variant) {
         case kGemmTile128: return 1u << kTile128x64 | 1u << kTile128x128;

@@ -125,3 +125,20 @@ def test_tiles_that_quantize(zq, orc, variant, bits, M, N, K, g):
     rows = sorted({0, M // 2, M - 1, min(M, 128) - 1, min(M - 1, 192), min(M - 1, 256)})
     _check_fused(orc, *(host(t)[rows] for t in runs[0]), xq[rows], s_tok[rows], codes, s_w, bias, False,
                  "quantizing tile %d %d-bit %dx%dx%d" % (variant, bits, M, N, K))
+
+
+@pytest.mark.parametrize("M,N,K,g", [(161, 2912, 2896, 91), (236, 2080, 2896, 65)])
+def test_split_class_that_runs_unsplit(zq, orc, M, N, K, g):
+    """The class is the K split, the workspace is sized for it, and the unsplit tiles run; forced, or with a table entry that names
+    it, the split does."""
+    nbytes = zq.gemm_workspace_bytes(M, N, K)
+    split = zq.gemm_choose_variant(M, N, K, 8, nbytes)
+    assert zq.gemm_variant_name(split) == "tile128_splitk" and zq.gemm_schedule(M, N, K, 8, nbytes) in VARIANT
+    xq, s_tok, s_w, bias, codes, wq = _case(zq_inputs.rng_for(4, 6400 + M + N + K), M, N, K, g, 8)
+    res = _run(zq, 8, -1, xq, s_tok, wq, s_w, bias, workspace=zq.new_workspace(nbytes))
+    _check(orc, res, xq, s_tok, codes, s_w, bias, "unsplit %dx%dx%d" % (M, N, K))
+    zq.tune_set(M, M, N, K, 8, split)
+    try:
+        assert zq.gemm_schedule(M, N, K, 8, nbytes) == "tile128x128_splitk"
+    finally:
+        zq.tune_clear()
