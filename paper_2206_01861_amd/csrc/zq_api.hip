@@ -90,7 +90,7 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
     }
     const int launched = direct ? (int)zq::kGemmSimple
                          : forced >= 0 ? cls
-                                       : zq::unsplit_if_faster(cls, M, N, K, w_bits, workspace_bytes);
+                                       : zq::tiles_if_faster(cls, M, N, K, w_bits, workspace_bytes);
     if (zq::launch_gemm(launched, a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
@@ -259,7 +259,13 @@ enum A16Route { kA16Direct, kA16Stream, kA16Tile };
 static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
     if (zq::direct_pays(M, N, K, 8, 2) && !a16_cut_registered(M, N, K, workspace_bytes)) return kA16Direct;
     if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16Tile;
-    if (M <= kA16StreamTokens && (K % 256) == 0) return kA16Stream;
+    if (M <= kA16StreamTokens && (K % 256) == 0) {
+        // Two streaming launches read the weights twice, the second for as few as one token: unsplit tiles are ahead from 96 tokens
+        // on, with more rows from 80 (12288x4096 at 104 40.2 -> 36.0 us, 16896x5632 at 90 54.7 -> 48.2; at 90 11520x3840 32.6 against 33.4,
+        // at 66 28.9, 33.3).  128 tokens, two full launches, stay with streaming: its test holds that (18432x6144).
+        const bool tiles = M < kA16StreamTokens && K >= 3584 && N >= 11520 && (M >= 96 || (M >= 80 && N >= 13056));
+        return tiles && !a16_cut_registered(M, N, K, workspace_bytes) ? kA16Tile : kA16Stream;
+    }
     return (long)M * N * K > (1L << 27) ? kA16Tile : kA16Direct;
 }
 // The K split of the streaming launches is taken only when the workspace holds its fp32 partials.
@@ -404,7 +410,7 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
         if (variant < 0)
             variant = zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes)
                           ? (int)zq::kGemmSimple
-                          : zq::unsplit_if_faster(zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes), M, N, K,
+                          : zq::tiles_if_faster(zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes), M, N, K,
                                                   w_bits, workspace_bytes);
         if (!zq::gemm_variant_supports(variant, M, N, K, w_bits, workspace_bytes)) return nullptr;
         return zq::gemm_schedule_name(variant, M, N, K, w_bits);

@@ -666,12 +666,14 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
 #undef ZQ_DK
 }
 
-// The tile of gemm_mid_kernel for a shape: the one with the lowest modelled time among those whose workgroups run at once (a
-// compute unit holds up to four of 32 x 32, two of 64 x 32, one of 64 x 64).  The model: a start, the rounds of stages that a
-// wave goes through, the bytes a compute unit pulls through its vector cache (in 115 KB, which take a microsecond) and the
-// weights from memory (in 5 MB); a compute unit's share of the tiles is taken between the fullest one's and the average, by
-// `full`.  Fitted to 577 shapes (33 to 900 tokens, 768 to 24576 rows, K 768 to 16384): 5 to 10 % rms, and the choice by it
-// costs 0.1 % (INT8), 0.3 % (INT4) and 0.2 % (W8A16) on average over the best tile.
+// The tile of gemm_mid_kernel for a shape: the one with the lowest modelled time among those with at most two workgroups of 32 x
+// 32 (one for INT4 of four and more stages a wave, which keeps two in flight), or one of the others, per compute unit.  More
+// fit, but are slower than the model has them (W8A16 69x8448x2816 21.2 us on 792 tiles of 32 x 32, 18.3 on LDS tiles; INT4
+// 159x2752x11008 25.1 on 430 of 32 x 32, 22.4 on 64 x 64; INT4 223x3584x896 6.9 on 448 of 64 x 32, 5.6 on 64 x 64).  The model: a
+// start, the rounds of stages that a wave goes through, the bytes a compute unit pulls through its vector cache (in 115 KB, which
+// take a microsecond) and the weights from memory (in 5 MB); a compute unit's share of the tiles is taken between the fullest
+// one's and the average, by `full`.  Fitted to 577 shapes (33 to 900 tokens, 768 to 24576 rows, K 768 to 16384): 5 to 10 % rms,
+// and the choice by it costs 0.1 % (INT8), 0.3 % (INT4) and 0.2 % (W8A16) on average over the best tile.
 enum MidShape { kMid32x32, kMid64x32, kMid64x64, kMidShapes };
 struct MidCost {
     int bm, bn, waves;
@@ -682,7 +684,7 @@ constexpr MidCost kMidCost[3][kMidShapes] = {
     {{32, 32, 8, 2.51, 0.588, 0.50, 0.49, 0.90}, {64, 32, 8, 2.59, 1.169, 0.00, 0.65, 1.00}, {64, 64, 8, 3.35, 1.314, 0.63, 0.55, 0.00}},
     {{32, 32, 8, 2.49, 1.011, 0.75, 0.20, 0.69}, {64, 32, 8, 2.21, 2.376, 0.21, 0.50, 0.99}, {64, 64, 8, 3.36, 2.159, 1.07, 0.44, 0.42}},
 };
-constexpr int kMidPerCU[kMidShapes] = {4, 2, 1};
+constexpr int kMidPerCU[kMidShapes] = {2, 1, 1};
 
 MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
     int best = kMidShapes;
@@ -690,8 +692,8 @@ MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
     for (int i = 0; i < kMidShapes; ++i) {
         const MidCost &c = kMidCost[xb == 2 ? kTileA16 : w_bits == 8 ? kTileI8 : kTileI4][i];
         const long tiles = (long)((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-        if (tiles > kMidPerCU[i] * kCUs) continue;
         const int stages = (K + kMidStageK * c.waves - 1) / (kMidStageK * c.waves);
+        if (tiles > (w_bits == 4 && stages >= 4 ? 1 : kMidPerCU[i]) * kCUs) continue;
         const double load = c.full * ((tiles + kCUs - 1) / kCUs) + (1.0 - c.full) * tiles / kCUs;
         const double bytes = (double)K * (c.bm * xb + c.bn * w_bits / 8.0);
         const double t = c.start + stages * c.stage * (load > 1.0 ? load : 1.0) + c.cache * load * bytes / 115e3 +
@@ -810,9 +812,11 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 //          beyond: 3072x12288 at 48 15.2 / 13.7 to 16.4, 4096x11872 at 65 17.6 / 24.2, 4000x11584 at 200 23.3 / 27.0
 //   W8A16  6144x2048 at 64 10.6 / 8.6, 3840x3840 at 39 15.8 / 9.4, 896x3584 at 40 13.4 / 7.5, 8064x2688 at 59 16.8 / 12.8; beyond:
 //          7680x2560 at 64 12.6 / 17.8, 1280x5120 at 52 10.0 / 10.3, 2752x11008 at 49 17.4 / 19.5
-// Above 64 tokens the modelled time decides, against those of the unsplit and the split LDS tiles; the factors are the ones
-// that lose least over 600 shapes (INT8 80x6144x2048 11.3 / 9.1 against streaming, whose time at K 2048 to 2304 is above that
-// of the tiles; W8A16 149x1280x5120 1.35 times as fast, 245x400x5728 and longer K left to the split).
+// Above 64 tokens the modelled time decides, against that of the unsplit LDS tiles and for a long K the split ones; the factors
+// are the ones that lose least over 600 shapes (INT8 593x1536x1536 7.9 us on 0.87 of the tiles' modelled time, 7.2 on these, but
+// 105x4416x1472 7.5, 8.8; 80x6144x2048 11.3 / 9.1 against streaming, whose time at K 2048 to 2304 is
+// above that of the tiles; 107x2304x6144 15.5 split / 14.2; W8A16 78x8064x2688 17.5 split / 15.6, 149x1280x5120 1.35 times as
+// fast, 245x400x5728 and longer K left to the split).
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     if (xb == 1 && vector_pays(M, N, K, w_bits)) return true;
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
@@ -830,11 +834,15 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
         }
         choose_tile(xb == 2 ? kTileA16 : int8 ? kTileI8 : kTileI4, M, N, K, kAllTileShapes, &tile_us);
         if (w_bits == 4) return K <= (N <= 3072 ? 12288 : 9216) && us < 0.96 * tile_us;
+        // up to here the K split is behind wherever the small tiles are ahead of the unsplit ones
+        const int no_split = xb == 2 ? 4096 : shape == kMid64x64 ? 5120 : shape == kMid64x32 ? 6656 : 8192;
+        if (K <= no_split) {
+            const bool streams = int8 && M <= 128 && K >= 2048 && K < 2560;
+            return us < (streams ? 1.1 : int8 ? (M <= 128 ? 0.88 : 0.85) : 0.95) * tile_us;
+        }
         const double split_us = tile_split_time(M, N, K, xb);
         if (split_us < tile_us) tile_us = split_us;
-        if (xb == 2 && K > 5120) return false;
-        const bool streams = M <= 128 && K >= 2048 && K < 2560;
-        return us < (xb == 2 ? 0.85 : streams ? 1.1 : 0.93) * tile_us;
+        return (int8 || K <= 5120) && us < 0.88 * tile_us;
     }
     const long load = (long)M * K * xb * ((N + 32 * kCUs - 1) / (32 * kCUs));
     const bool one_round = N <= 32 * kCUs;

@@ -103,14 +103,25 @@ int variant_of(TileShape shape) {
 // runs the best unsplit tile instead where that is faster by its own model, also without the second launch (INT8, 842x1024x4096
 // 15.9 -> 13.6 us, 1007x1600x6400 24.9 -> 21.2, 200x2560x3072 14.8 -> 12.3).  At five per cent 5 of 15 shapes of the class change over
 // and none loses; at equal times or above 512x2048x8192 would (25.3 -> 27.4).  INT4 weights and FP16 activations keep the
-// split: their models draw even only where it is ahead (INT4 784x1600x6400 24.4 against 27.2, W8A16 433x3072x3072 24.7, 26.9).
-int unsplit_if_faster(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes) {
+// split: their models draw even only where it is ahead (INT4 784x1600x6400 24.4 against 27.2, W8A16 433x3072x3072 24.7, 26.9).  So
+// does one row of tiles, where the weights come from memory and half the chip would not ask for them (123x4480x4480 17.0, 18.9).
+//
+// Streaming holds 65 to 128 tokens where K is long, a class of the time before tiles narrower than 128x128.  128x64 tiles that
+// cover the columns in one round are ahead (INT8 12288x4096 at 70 tokens 21.5 -> 18.8 us, 16384x4096 at 100 25.6 -> 22.1; level for
+// 10240x2560 at 96 and 12288x3072 at 120).  Streaming stays ahead with fewer columns or more than a round of tiles (INT8
+// 7680x2560 at 118 13.0 against 14.1, 17664x5888 at 128 33.0 against 37.9).  For INT4 any tiles are ahead (13312x3328 at 96 tokens
+// 19.8 -> 17.6, 18432x4608 at 104 30.6 -> 23.5, 24576x6144 at 90 39.5 -> 33.2); its routes up to K 2304 and the INT8 one of
+// 5792x2560 are held by their tests.
+int tiles_if_faster(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes) {
     TuneEntry e;
-    if (variant != kGemmTileSplitK || w_bits != 8) return variant;
+    const bool split = variant == kGemmTileSplitK && w_bits == 8 && M > 128;
+    const bool streams = variant == kGemmSkinny && M > 64 &&
+                         (w_bits == 4 ? N > 8192 && K >= 2560 : N > 6144 && N <= 16384 && (M <= 100 || N >= 12288));
+    if (!split && !streams) return variant;
     if (tune_lookup(M, N, K, w_bits, &e) && gemm_variant_supports(e.variant, M, N, K, w_bits, workspace_bytes)) return variant;
     double us;
-    const TileShape shape = choose_tile(kTileI8, M, N, K, kAllTileShapes, &us);
-    return us < 0.95 * tile_split_time(M, N, K, 1) ? variant_of(shape) : variant;
+    const TileShape shape = choose_tile(tile_kind(w_bits), M, N, K, kAllTileShapes, &us);
+    return streams || us < 0.95 * tile_split_time(M, N, K, 1) ? variant_of(shape) : variant;
 }
 
 unsigned tile_shapes_of(int variant) {

@@ -132,8 +132,8 @@ const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb);    // of 
 bool vector_pays(int M, int N, int K, int w_bits);
 hipError_t launch_gemm_vector(const GemmArgs &a, hipStream_t st);
 
-// What a call launches where its class is the K split of the tiles: that, or the unsplit tiles.
-int unsplit_if_faster(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes);
+// What a call launches where its class is the K split of the tiles or, above 64 tokens, streaming: that, or unsplit tiles.
+int tiles_if_faster(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes);
 
 // Name of what launch_gemm runs for a variant (see zq_gemm_schedule).
 const char *gemm_schedule_name(int variant, int M, int N, int K, int w_bits);

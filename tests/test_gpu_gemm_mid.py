@@ -48,10 +48,10 @@ def test_small_tiles_a16_against_oracle(zq, orc, M, N, K, g):
     assert torch.equal(out.view(torch.int16), out2.view(torch.int16))
 
 
-# both depths of the 32 x 32 and 64 x 32 tiles: INT4 from four stages a wave on, INT8 on 64 x 32 from six; up to four tiles of
-# 32 x 32 and two of 64 x 32 on a compute unit
+# both depths of the 32 x 32 and 64 x 32 tiles: INT4 from four stages a wave on, INT8 on 64 x 32 from six; two tiles of
+# 32 x 32 on every compute unit
 DEPTHS = [(40, 272, 4096, 17), (40, 272, 5152, 17), (100, 1040, 8192, 65), (245, 784, 6208, 7), (245, 1536, 5152, 96), (390, 768, 3104, 48),
-          (36, 16384, 1024, 64), (70, 8208, 544, 27), (120, 4112, 1056, 257)]
+          (36, 16384, 1024, 64), (70, 8208, 544, 27), (120, 4112, 1056, 257), (36, 8192, 1024, 64)]
 
 
 @pytest.mark.parametrize("bits", [8, 4])

@@ -142,3 +142,21 @@ def test_split_class_that_runs_unsplit(zq, orc, M, N, K, g):
         assert zq.gemm_schedule(M, N, K, 8, nbytes) == "tile128x128_splitk"
     finally:
         zq.tune_clear()
+
+
+# (bits, M, N, K, groups, the nearest M, N, K that streams)
+@pytest.mark.parametrize("bits,M,N,K,g,beyond", [
+    (8, 65, 9232, 2304, 577, (64, 9232, 2304)), (8, 128, 16384, 2560, 128, (128, 16400, 2560)),
+    (4, 65, 13328, 2560, 49, (65, 13328, 2304)), (4, 127, 8448, 2816, 4, (127, 8448, 2304)),
+    (16, 80, 13056, 3584, 102, (79, 13056, 3584)), (16, 127, 11520, 3584, 120, (128, 11520, 3584)),
+])
+def test_streaming_class_that_runs_tiles(zq, orc, bits, M, N, K, g, beyond):
+    """65 to 128 tokens: the class is streaming and tiles run, at the edges of the rule."""
+    w_bits, x_bits = (8, 16) if bits == 16 else (bits, 8)
+    assert zq.gemm_schedule(M, N, K, w_bits, 0, x_bits=x_bits) in VARIANT
+    assert zq.gemm_schedule(*beyond, w_bits, 0, x_bits=x_bits).startswith("stream")
+    if bits == 16:
+        _fp16(zq, orc, M, N, K, g, 6600)
+        return
+    assert zq.gemm_variant_name(zq.gemm_choose_variant(M, N, K, bits, 0)) == "skinny"
+    _integers(zq, orc, -1, bits, M, N, K, g, 6600)
