@@ -300,11 +300,23 @@ static hipError_t launch_rq_op(const void *in, const void *p0, const void *p1, f
         if (nvec <= 64 * 4) ZQ_RQ(64, 4);
     }
     // Longer rows: a workgroup shares one row, with up to four vectors per thread: six to sixteen of 256 threads are too few
-    // waves for the arithmetic of GeLU (300x16384 7.8 -> 6.5 us, 300x24576 10.9 -> 8.4, 2048x24576 33.5 -> 31.9).
+    // waves for the arithmetic of GeLU (300x16384 7.8 -> 6.5 us, 300x24576 10.9 -> 8.4, 2048x24576 33.5 -> 31.9; LayerNorm
+    // 2048x12288 21.2 -> 20.3, 1024x16384 16.3 -> 15.0).  With enough rows to keep the chip full either way the smaller
+    // workgroups are ahead, 256 threads / more (GeLU 16384x10240 93 / 97 us, 16384x24576 215 / 218, tanh form 220 / 229;
+    // LayerNorm 16384x10240 107.5 / 112), and for LayerNorm, whose parameters take registers too, everywhere on rows of more
+    // than 16384 values (4096x24576 68 / 98).  The plain quantizer gains (8192x24576 110 / 103), and so does GeLU with a bias,
+    // whose loads go out with the row's for up to four vectors only (16384x24576 252 / 220, 4096x10240 34.4 / 33.3).
     if (nvec <= 256 * 1) ZQ_RQ(256, 1);
     if (nvec <= 256 * 2) ZQ_RQ(256, 2);
     if (nvec <= 256 * 3) ZQ_RQ(256, 3);
     if (nvec <= 256 * 4) ZQ_RQ(256, 4);
+    const bool bias = OP != kOpLayerNorm && p0 != nullptr;
+    if (OP != kOpIdentity && !bias && (M > 2048 || (OP == kOpLayerNorm && nvec > 2048))) {
+        if (nvec <= 256 * 6) ZQ_RQ(256, 6);
+        if (nvec <= 256 * 8) ZQ_RQ(256, 8);
+        if (nvec <= 256 * 12) ZQ_RQ(256, 12);
+        if (nvec <= 256 * 16) ZQ_RQ(256, 16);
+    }
     if (nvec <= 512 * 3) ZQ_RQ(512, 3);
     if (nvec <= 512 * 4) ZQ_RQ(512, 4);
     if (nvec <= 1024 * 3) ZQ_RQ(1024, 3);

@@ -56,9 +56,10 @@ def test_gelu_parts(zq, orc, approx, M, K):
     check_fused_codes(xq, s_tok, y, y64, "gelu %dx%d" % (M, K))
 
 
-# one wave per row with three and four vectors a lane, at the first count of rows; 512 and 1024 threads a row
+# one wave per row with three and four vectors a lane, at the first count of rows; 512 and 1024 threads a row; many long rows on
+# 256 threads (LayerNorm; GeLU without its bias, below)
 @pytest.mark.parametrize("M,K", [(513, 1040), (513, 1536), (515, 1552), (514, 2048), (512, 2048), (2, 8208), (3, 12304),
-                                 (2, 16400), (2, 24592)])
+                                 (2, 16400), (2, 24592), (2049, 8208), (2051, 12304)])
 def test_row_mappings(zq, orc, M, K):
     print("rows", M, K, flush=True)
     rng = zq_inputs.rng_for(3, 8000 + M + K)
@@ -68,6 +69,7 @@ def test_row_mappings(zq, orc, M, K):
     xd = dev(x)
     y64, _ = orc.layernorm(x, gamma, beta, 1e-5)
     for res, ref in ((zq.zq_layernorm_quant_tokenwise(xd, dev(gamma), dev(beta), 1e-5, y_dtype=torch.float32), y64),
+                     (zq.zq_gelu_quant_tokenwise(xd, y_dtype=torch.float32), orc.gelu(x, None)[0]),
                      (zq.zq_gelu_quant_tokenwise(xd, dev(bias), y_dtype=torch.float32), orc.gelu(x, bias)[0])):
         xq, s_tok, y = (host(t) for t in res)
         xq_o, s_o = orc.quant_tokenwise(y)
