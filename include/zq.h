@@ -333,15 +333,16 @@ zq_status zq_quant_wait_expired(void *workspace, int *count_out);
  * Name of schedule `variant` (NULL when out of range), and the class of schedules
  * of a shape: what its workspace is sized for, a table entry can name and decides
  * whether its output is quantized in the kernel.  A call runs that class unless
- * the direct or small-tile kernels are ahead of it for the shape; then it runs
- * those (the class "simple") whatever zq_gemm_choose_variant says.
+ * the direct or small-tile kernels (the class "simple"), or tiles in place of a K
+ * split or of streaming, are ahead of it for the shape; then it runs those whatever
+ * zq_gemm_choose_variant says.
  */
 const char *zq_gemm_variant_name(int variant);
 int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t workspace_bytes);
 
 /*
  * What a GeMM call without a quantized output launches for a shape, a forced
- * schedule included: "direct", "small32x32", "small64x32", "small64x64" (tokens x
+ * schedule included: "direct" (on the vector ALUs too), "small32x32", "small64x32", "small64x64" (tokens x
  * columns of a tile), "stream", "stream_splitk", "tile128x64", "tile128x128",
  * "tile192x128", "tile256x128", "tile256x192", "tile256x256", "tile128x128_splitk".
  * x_bits 8: zq_gemm_i8_dequant (w_bits 8) and zq_gemm_w4a8_dequant (w_bits 4);

@@ -260,9 +260,10 @@ static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
     if (zq::direct_pays(M, N, K, 8, 2) && !a16_cut_registered(M, N, K, workspace_bytes)) return kA16Direct;
     if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16Tile;
     if (M <= kA16StreamTokens && (K % 256) == 0) {
-        // Two streaming launches read the weights twice, the second for as few as one token: unsplit tiles are ahead from 96 tokens
-        // on, with more rows from 80 (12288x4096 at 104 40.2 -> 36.0 us, 16896x5632 at 90 54.7 -> 48.2; at 90 11520x3840 32.6 against 33.4,
-        // at 66 28.9, 33.3).  128 tokens, two full launches, stay with streaming: its test holds that (18432x6144).
+        // Two streaming launches read the weights twice, the second for as few as one token: unsplit tiles are ahead from 96
+        // tokens on, with more rows from 80 (12288x4096 at 104 40.2 -> 36.0 us, 16896x5632 at 90 54.7 -> 48.2; at 90 11520x3840
+        // 32.6 against 33.4, at 66 28.9, 33.3).  128 tokens, two full launches, stay with streaming: its test holds that
+        // (18432x6144).
         const bool tiles = M < kA16StreamTokens && K >= 3584 && N >= 11520 && (M >= 96 || (M >= 80 && N >= 13056));
         return tiles && !a16_cut_registered(M, N, K, workspace_bytes) ? kA16Tile : kA16Stream;
     }

@@ -813,10 +813,10 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 //   W8A16  6144x2048 at 64 10.6 / 8.6, 3840x3840 at 39 15.8 / 9.4, 896x3584 at 40 13.4 / 7.5, 8064x2688 at 59 16.8 / 12.8; beyond:
 //          7680x2560 at 64 12.6 / 17.8, 1280x5120 at 52 10.0 / 10.3, 2752x11008 at 49 17.4 / 19.5
 // Above 64 tokens the modelled time decides, against that of the unsplit LDS tiles and for a long K the split ones; the factors
-// are the ones that lose least over 600 shapes (INT8 593x1536x1536 7.9 us on 0.87 of the tiles' modelled time, 7.2 on these, but
-// 105x4416x1472 7.5, 8.8; 80x6144x2048 11.3 / 9.1 against streaming, whose time at K 2048 to 2304 is
-// above that of the tiles; 107x2304x6144 15.5 split / 14.2; W8A16 78x8064x2688 17.5 split / 15.6, 149x1280x5120 1.35 times as
-// fast, 245x400x5728 and longer K left to the split).
+// are the ones that lose least over 600 shapes (INT8 593x1536x1536 7.9 us on 0.87 of the tiles' modelled time, 7.2 on these,
+// but 105x4416x1472 7.5, 8.8; 80x6144x2048 11.3 / 9.1 against streaming, whose time at K 2048 to 2304 is above that of the
+// tiles; 107x2304x6144 15.5 split / 14.2; W8A16 78x8064x2688 17.5 split / 15.6, 149x1280x5120 1.35 times as fast, 245x400x5728
+// and longer K left to the split).
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     if (xb == 1 && vector_pays(M, N, K, w_bits)) return true;
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);

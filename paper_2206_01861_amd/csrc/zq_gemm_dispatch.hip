@@ -99,12 +99,13 @@ int variant_of(TileShape shape) {
 }
 }  // namespace
 
-// The K split of the tiles is a class by a model that knows 128x128 tiles only, and what a workspace is sized for.  A call
-// runs the best unsplit tile instead where that is faster by its own model, also without the second launch (INT8, 842x1024x4096
-// 15.9 -> 13.6 us, 1007x1600x6400 24.9 -> 21.2, 200x2560x3072 14.8 -> 12.3).  At five per cent 5 of 15 shapes of the class change over
-// and none loses; at equal times or above 512x2048x8192 would (25.3 -> 27.4).  INT4 weights and FP16 activations keep the
-// split: their models draw even only where it is ahead (INT4 784x1600x6400 24.4 against 27.2, W8A16 433x3072x3072 24.7, 26.9).  So
-// does one row of tiles, where the weights come from memory and half the chip would not ask for them (123x4480x4480 17.0, 18.9).
+// The K split of the tiles is a class by a model that knows 128x128 tiles only, and what a workspace is sized for.  A call runs
+// the best unsplit tile instead where that is faster by its own model, also without the second launch (INT8, 842x1024x4096 15.9
+// -> 13.6 us, 1007x1600x6400 24.9 -> 21.2, 200x2560x3072 14.8 -> 12.3).  At five per cent 5 of 15 shapes of the class change
+// over and none loses; at equal times or above 512x2048x8192 would (25.3 -> 27.4).  INT4 weights and FP16 activations keep the
+// split: their models draw even only where it is ahead (INT4 784x1600x6400 24.4 against 27.2, W8A16 433x3072x3072 24.7, 26.9).
+// So does one row of tiles, where the weights come from memory and half the chip would not ask for them (123x4480x4480 17.0,
+// 18.9).
 //
 // Streaming holds 65 to 128 tokens where K is long, a class of the time before tiles narrower than 128x128.  128x64 tiles that
 // cover the columns in one round are ahead (INT8 12288x4096 at 70 tokens 21.5 -> 18.8 us, 16384x4096 at 100 25.6 -> 22.1; level for

@@ -187,9 +187,9 @@ hipError_t launch_vector(const GemmArgs &a, hipStream_t st) {
 }  // namespace
 
 // One token: everywhere but where nine pieces meet more than 4096 rows, which streaming keeps although this kernel is ahead
-// (6336x2304 5.8 / 4.7): the one-token route of the streaming schedule is held there by its test.  More tokens cost a 16-byte activation load each where the weights cost two, so the line is drawn
-// where the kernels with matrix cores pay more for something else, few rows against a long K above all.  us, before / this
-// kernel, over 110 random shapes:
+// (6336x2304 5.8 / 4.7): the one-token route of the streaming schedule is held there by its test.  More tokens cost a 16-byte
+// activation load each where the weights cost two, so the line is drawn where the kernels with matrix cores pay more for
+// something else, few rows against a long K above all.  us, before / this kernel, over 110 random shapes:
 //   2 tokens, INT8   1792x7168 6.5 / 4.7, 5664x1888 4.8 / 4.1, 8832x2944 9.0 / 7.6, 4736x18944 20.2 / 19.9; beyond: 2560x9216
 //                    7.5 / 8.2 (320 workgroups on 256 compute units); 12288x4096, see direct_pays
 //             INT4   896x3584 3.2 / 2.8, 6144x2048 3.7 / 3.5; beyond: 3072x768 2.6 / 2.8, 6016x6016 6.9 / 7.1, 13056x4352 9.5 / 11.3
