@@ -255,15 +255,17 @@ static bool a16_cut_registered(int M, int N, int K, size_t workspace_bytes) {
     return k_splits == 1 || workspace_bytes >= zq::kWsFixedBytes + (size_t)k_splits * m * N * sizeof(float);
 }
 
-enum A16Route { kA16Direct, kA16Stream, kA16Tile };
+enum A16Route { kA16Direct, kA16Stream, kA16Tile, kA16TileSplit };
 static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
     if (zq::direct_pays(M, N, K, 8, 2) && !a16_cut_registered(M, N, K, workspace_bytes)) return kA16Direct;
-    if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16Tile;
+    if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16TileSplit;
     if (M <= kA16StreamTokens && (K % 256) == 0) {
         // Two streaming launches read the weights twice, the second for as few as one token: unsplit tiles are ahead from 96
         // tokens on, with more rows from 80 (12288x4096 at 104 40.2 -> 36.0 us, 16896x5632 at 90 54.7 -> 48.2; at 90 11520x3840
         // 32.6 against 33.4, at 66 28.9, 33.3).  128 tokens, two full launches, stay with streaming: its test holds that
-        // (18432x6144).
+        // (18432x6144).  Unsplit whatever the workspace holds: a split by two is not among what a call may do here (see
+        // a16_tiles_with_split), and the workspace query names none.  130 shapes of 80 to 127 tokens, 11520 to 20000 rows, K 3584
+        // to 7000: streaming takes 1.25 times as long without a workspace, 1.26 with that of a model's other linears.
         const bool tiles = M < kA16StreamTokens && K >= 3584 && N >= 11520 && (M >= 96 || (M >= 80 && N >= 13056));
         return tiles && !a16_cut_registered(M, N, K, workspace_bytes) ? kA16Tile : kA16Stream;
     }
@@ -312,7 +314,8 @@ zq_status zq_gemm_w8a16_dequant(const void *x_fp16, const int8_t *wq, const floa
     hipError_t e = hipSuccess;
     switch (a16_route(M, N, K, workspace_bytes)) {
         case kA16Direct: e = zq::launch_gemm_a16_direct(a, st); break;
-        case kA16Tile: e = zq::launch_gemm_a16_tile(a, st); break;
+        case kA16Tile: e = zq::launch_gemm_a16_tile(a, false, st); break;
+        case kA16TileSplit: e = zq::launch_gemm_a16_tile(a, true, st); break;
         case kA16Stream:
             // Weight streaming holds up to 64 tokens per launch; 65..128 tokens run as two launches over
             // row halves (the weights are read twice, which is still well ahead of the tiled schedule on
@@ -421,8 +424,8 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
         case kA16Stream:
             if (M > 64) return a16_stream_splits(64, N, K, workspace_bytes) ? "stream_splitk_halves" : "stream_halves";
             return a16_stream_splits(M, N, K, workspace_bytes) ? "stream_splitk" : "stream";
+        case kA16TileSplit: return "tile128x128_splitk";
         default:
-            if (zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return "tile128x128_splitk";
             return zq::tile_shape_name(zq::choose_tile(zq::kTileA16, M, N, K, zq::kAllTileShapes, nullptr));
     }
 }

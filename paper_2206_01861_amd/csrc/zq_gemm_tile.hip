@@ -1336,8 +1336,9 @@ bool gemm_a16_tile_splits_here(int M, int N, int K, size_t workspace_bytes) {
 }
 
 // FP16 activations x INT8 weights on the tiled schedules.  The argument block is the
-// INT8 one with xq pointing at the FP16 activations and no token scales.
-hipError_t launch_gemm_a16_tile(const A16Args &a16, hipStream_t st) {
+// INT8 one with xq pointing at the FP16 activations and no token scales.  The caller says whether K is split: it knows
+// what the workspace query promised for the shape.
+hipError_t launch_gemm_a16_tile(const A16Args &a16, bool split, hipStream_t st) {
     GemmArgs a;
     a.xq = reinterpret_cast<const int8_t *>(a16.x);
     a.s_tok = nullptr;
@@ -1345,7 +1346,8 @@ hipError_t launch_gemm_a16_tile(const A16Args &a16, hipStream_t st) {
     a.M = a16.M; a.N = a16.N; a.K = a16.K; a.out = a16.out; a.acc_out = nullptr;
     a.workspace = a16.workspace; a.workspace_bytes = a16.workspace_bytes; a.w_bits = 8; a.act = 0;
     // few tiles against a long K: split K (fp32 partials, added in split order by the second kernel)
-    if (gemm_a16_tile_splits_here(a.M, a.N, a.K, a.workspace_bytes)) {
+    if (split) {
+        if (a.workspace == nullptr || !gemm_a16_tile_splits_here(a.M, a.N, a.K, a.workspace_bytes)) return hipErrorInvalidValue;
         const int ks = tile_splits(a.M, a.N, a.K, 2);
         if (hipError_t e = launch_tile_t<128, 128, 2, 4, 128, 4, 8, 1, 0, 1>(a, st, ks); e != hipSuccess) return e;
         return launch_splitk_finish<1>(a, ks, st);

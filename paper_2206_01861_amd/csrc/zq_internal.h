@@ -158,10 +158,10 @@ hipError_t launch_gemm_a16_direct(const A16Args &a, hipStream_t st);            
 hipError_t launch_gemm_a16_stream(const A16Args &a, bool allow_split, hipStream_t st);   // M <= 64, K % 256 == 0
 size_t stream_a16_workspace_bytes(int M, int N, int K);                                   // of that schedule's K split
 void stream_a16_plan(int M, int N, int K, bool allow_split, int *row_blocks, int *k_splits, int *consumers);
-hipError_t launch_gemm_a16_tile(const A16Args &a, hipStream_t st);                       // any K the ABI accepts
+hipError_t launch_gemm_a16_tile(const A16Args &a, bool split, hipStream_t st);           // any K the ABI accepts
 int gemm_a16_tile_splits(int M, int N, int K);                                          // K splits that pay on tiles, 1 = none
 size_t gemm_a16_tile_split_workspace(int M, int N, int K);                              // of its K split, 0 if none
-bool gemm_a16_tile_splits_here(int M, int N, int K, size_t workspace_bytes);            // what launch_gemm_a16_tile does
+bool gemm_a16_tile_splits_here(int M, int N, int K, size_t workspace_bytes);            // whether it could split K
 
 bool gemm_variant_supports(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes);
 size_t gemm_variant_workspace(int variant, int M, int N, int K, int w_bits);

@@ -144,6 +144,19 @@ def test_split_class_that_runs_unsplit(zq, orc, M, N, K, g):
         zq.tune_clear()
 
 
+def _fp16_with_room_to_split(zq, M, N, K, g):
+    """A workspace that holds partial sums (other linears need it) changes neither the schedule nor a bit of the result."""
+    rng = zq_inputs.rng_for(9, 6650 + M + N + K)
+    args = (dev(zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=15.0)),
+            dev(zq_inputs.random_codes(rng, (N, K))), dev(zq_inputs.random_scales(rng, g, 1e-4, 1e-2)), dev(zq_inputs.bias(rng, N)))
+    ws = zq.new_workspace(64 << 20)
+    assert zq.gemm_schedule(M, N, K, 8, ws.numel(), x_bits=16) == zq.gemm_schedule(M, N, K, 8, 0, x_bits=16)
+    want = zq.zq_gemm_w8a16_dequant(*args)
+    got = zq.zq_gemm_w8a16_dequant(*args, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+
+
 # (bits, M, N, K, groups, the nearest M, N, K that streams)
 @pytest.mark.parametrize("bits,M,N,K,g,beyond", [
     (8, 65, 9232, 2304, 577, (64, 9232, 2304)), (8, 128, 16384, 2560, 128, (128, 16400, 2560)),
@@ -157,6 +170,7 @@ def test_streaming_class_that_runs_tiles(zq, orc, bits, M, N, K, g, beyond):
     assert zq.gemm_schedule(*beyond, w_bits, 0, x_bits=x_bits).startswith("stream")
     if bits == 16:
         _fp16(zq, orc, M, N, K, g, 6600)
+        _fp16_with_room_to_split(zq, M, N, K, g)
         return
     assert zq.gemm_variant_name(zq.gemm_choose_variant(M, N, K, bits, 0)) == "skinny"
     _integers(zq, orc, -1, bits, M, N, K, g, 6600)

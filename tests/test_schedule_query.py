@@ -106,3 +106,28 @@ def test_ragged_k_up_to_64_tokens(M, N, K, bits, x_bits, direct):
 def test_lines_between_the_direct_kernels_and_the_others(M, N, K, bits, x_bits, want):
     name = zq.gemm_schedule(M, N, K, bits, 0, x_bits=x_bits)
     assert name.startswith(want), name
+
+
+# FP16 activations, 65 to 128 tokens, tiles in place of two streaming launches: no K split, however large the workspace (one that
+# other linears share)
+@pytest.mark.parametrize("M,N,K", [(104, 12288, 4096), (80, 13056, 3584), (90, 16384, 4096), (100, 16384, 8192)])
+def test_fp16_tiles_ahead_of_streaming_do_not_split(M, N, K):
+    own = zq.gemm_w8a16_workspace_bytes(M, N, K)
+    names = {zq.gemm_schedule(M, N, K, 8, ws, x_bits=16) for ws in (0, own, 64 << 20, 1 << 30)}
+    assert len(names) == 1 and names < {"tile128x64", "tile128x128", "tile192x128", "tile256x128"}, names
+
+
+def test_fp16_call_splits_k_only_where_the_workspace_query_says():
+    import random
+    rnd = random.Random(3)
+    asked = 0
+    for _ in range(3000):
+        M, N, K = rnd.choice([rnd.randint(1, 140), rnd.randint(1, 600)]), 16 * rnd.randint(1, 1600), 16 * rnd.randint(1, 1000)
+        if rnd.random() < 0.6:
+            K = K // 256 * 256 + 256
+        own = zq.gemm_w8a16_workspace_bytes(M, N, K)
+        name = zq.gemm_schedule(M, N, K, 8, 1 << 40, x_bits=16)
+        if name is not None and "splitk" in name:
+            assert own > 0, (M, N, K, name)
+            asked += 1
+    assert asked > 100
