@@ -211,6 +211,7 @@ __global__ __launch_bounds__(row_block(TPR)) void rowquant_kernel(const half8 *_
 // where neighbours may round the other way.  us per call, a workgroup per row / parts: 1x8192 3.3 / 2.6, 27x8192 3.7 / 2.6,
 // 16x16384 5.0 / 2.7, 64x24576 6.9 / 4.6, 5x6400 3.5 / 2.6, 256x16384 6.8 / 5.5.
 constexpr float kGeluNegMax = 0.1702f;               // erf form: 0.16997, tanh form: 0.17004
+constexpr int16_t kHalfInfBits = 0x7c00;
 
 template <int OP>
 __device__ __forceinline__ float gelu_op(float u) {
@@ -246,9 +247,11 @@ __global__ __launch_bounds__(NT) void gelu_parts_kernel(const uint32x4_t *__rest
             const uint32_t two = raw[i][d];              // (a bit cast of the element itself reads element 0)
             m2 = __builtin_elementwise_max(m2, __builtin_bit_cast(short2_t, two));
         }
-    const half_t top = __builtin_bit_cast(half_t, m2[0] > m2[1] ? m2[0] : m2[1]);
-    float a = gelu_op<OP>(row_max<NT>((float)top, lds));
-    if (!(a > kGeluNegMax)) {
+    // A positive NaN is above infinity and hides the other inputs of its thread: it counts as infinity here, and a row with
+    // either is worked off whole, where NaNs raise no maximum (the other values of such a row keep their codes).
+    const int16_t top = m2[0] > m2[1] ? m2[0] : m2[1];
+    float a = gelu_op<OP>(row_max<NT>(top > kHalfInfBits ? INFINITY : (float)__builtin_bit_cast(half_t, top), lds));
+    if (!(a > kGeluNegMax && a < INFINITY)) {
         a = 0.0f;
         for (int i = t; i < nvec; i += NT) {
             const half8 h = __builtin_bit_cast(half8, rin[i]);

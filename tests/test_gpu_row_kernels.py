@@ -56,6 +56,34 @@ def test_gelu_parts(zq, orc, approx, M, K):
     check_fused_codes(xq, s_tok, y, y64, "gelu %dx%d" % (M, K))
 
 
+# What is not finite: the same rows in a call of more rows than have parts.  NaNs of either sign in the thread and vector of the
+# row's largest value, alone in it, and infinities.
+@pytest.mark.parametrize("approx", [False, True])
+@pytest.mark.parametrize("K", [1024, 4096, 8192, 24592, 32768])
+def test_gelu_parts_beside_nan_and_infinity(zq, approx, K):
+    print("gelu parts, not finite", approx, K, flush=True)
+    rng = zq_inputs.rng_for(3, 7700 + K)
+    h = zq_inputs.activations(rng, 300, K, outlier_frac=0.01, outlier_scale=6.0)
+    for row, value in enumerate((np.nan, -np.nan, np.inf, -np.inf)):
+        at = int(np.argmax(h[4 * row + 1]))
+        h[4 * row, 5] = value
+        h[4 * row + 1, at ^ 1] = value                          # beside the largest
+        h[4 * row + 2, :: 97] = value
+        h[4 * row + 3] = value
+    h[16, 3], h[16, 700] = np.nan, np.inf
+    bits = h.view(np.uint16)
+    bits[4:8][np.isnan(h[4:8])] |= 0x8000                       # (numpy may drop the sign)
+    x = dev(h)
+    for y_dtype in (None, torch.float16):
+        want = zq.zq_gelu_quant_tokenwise(x, None, approx_tanh=approx, y_dtype=y_dtype)
+        for M in (17, 40, 128):
+            got = zq.zq_gelu_quant_tokenwise(x[:M], None, approx_tanh=approx, y_dtype=y_dtype)
+            assert torch.equal(got[1].view(torch.int32), want[1][:M].view(torch.int32))
+            assert torch.equal(got[0], want[0][:M])
+            # (the sign of a NaN that an operation makes is nobody's)
+            assert y_dtype is None or torch.equal(got[2].nan_to_num(nan=-1000.0), want[2][:M].nan_to_num(nan=-1000.0))
+
+
 # one wave per row with three and four vectors a lane, at the first count of rows; 512 and 1024 threads a row; many long rows on
 # 256 threads (LayerNorm; GeLU without its bias, below)
 @pytest.mark.parametrize("M,K", [(513, 1040), (513, 1536), (515, 1552), (514, 2048), (512, 2048), (2, 8208), (3, 12304),
