@@ -354,6 +354,14 @@ int zq_gemm_choose_variant(int M, int N, int K, int w_bits, size_t workspace_byt
 const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t workspace_bytes);
 
 /*
+ * Test hook: the kernel behind what zq_gemm_schedule names (same arguments).  "direct" is told apart into "vector"
+ * (vector ALUs), "direct_pairs" (both halves of the matrix instruction), "direct_permuted" (contiguous activation
+ * loads) and "direct"; with wants_codes 1 a call with out_q / gq_out and an FP16 output that quantizes in the GeMM
+ * kernel is "quant128x64", "quant128x128", "quant192x128", "quant256x128" or "quant256x256".
+ */
+const char *zq_debug_gemm_kernel(int M, int N, int K, int w_bits, int x_bits, int wants_codes, size_t workspace_bytes);
+
+/*
  * Measured schedule table (App. D ranks schedules by measuring them offline
  * and picks by batch x sequence length at run time).  zq_tune_set registers,
  * for the GeMM shape (N, K, w_bits) and token counts m_lo..m_hi, the schedule

@@ -4,6 +4,7 @@
 #include "zq_internal.h"
 
 #include <atomic>
+#include <cstring>
 
 namespace {
 
@@ -45,6 +46,35 @@ bool good_shape(int M, int N, int K, int w_bits, int x_bytes) {
 bool rows_beside_tiles(int M) { return M <= 64; }
 size_t row_bytes(int M, int N) { return (size_t)M * N * sizeof(uint16_t); }
 
+// What a GeMM call on codes launches: a variant (with the row quantizer behind it where codes are wanted), or the tiles that
+// quantize in the kernel.  Refused: no FP16 output, and nothing that could do without.
+struct GemmPlan {
+    int variant = 0;
+    bool in_kernel = false, rows_in_workspace = false, refused = false;
+};
+GemmPlan plan_gemm(int forced, int M, int N, int K, int w_bits, size_t workspace_bytes, bool wants_codes, bool has_out) {
+    const bool direct = forced < 0 && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes);
+    // The class of the shape says whether the output rows are quantized inside the GeMM kernel (the tiled schedules do
+    // that), also where the direct kernels would be ahead of the plain call; other direct calls have no use for it.
+    const bool beside = direct && rows_beside_tiles(M);
+    const int cls = forced >= 0 ? forced
+                    : direct && (!wants_codes || (beside && has_out))
+                        ? (int)zq::kGemmSimple
+                        : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
+    GemmPlan p;
+    p.in_kernel = wants_codes && g_in_kernel_quant.load() != 0 && is_tile_variant(cls) &&
+                  zq::gemm_tile_quant_supported(M, N, workspace_bytes);
+    p.refused = !has_out && !p.in_kernel;
+    if (!p.refused && p.in_kernel && beside && workspace_bytes >= zq::kWsFixedBytes + row_bytes(M, N)) {
+        p.rows_in_workspace = true;
+        p.in_kernel = false;
+    }
+    p.variant = direct ? (int)zq::kGemmSimple
+                : forced >= 0 || p.in_kernel ? cls
+                                             : zq::tiles_if_faster(cls, M, N, K, w_bits, workspace_bytes);
+    return p;
+}
+
 zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, const float *s_w, int groups,
                       const void *bias, int M, int N, int K, void *out, int32_t *acc_out, int8_t *out_q,
                       float *out_s_tok, void *workspace, size_t workspace_bytes, int w_bits, int act,
@@ -63,35 +93,20 @@ zq_status gemm_common(const int8_t *xq, const float *s_tok, const void *wq, cons
 
     const int forced = g_forced_variant.load();
     if (forced >= 0 && !zq::gemm_variant_supports(forced, M, N, K, w_bits, workspace_bytes)) return ZQ_ERR_UNSUPPORTED;
-    const bool direct = forced < 0 && zq::gemm_goes_direct(M, N, K, w_bits, workspace_bytes);
-    // The class of the shape says whether the output rows are quantized inside the GeMM kernel (the tiled schedules do
-    // that), also where the direct kernels would be ahead of the plain call; other direct calls have no use for it.
-    const bool beside = direct && rows_beside_tiles(M);
-    const int cls = forced >= 0 ? forced
-                    : direct && (out_q == nullptr || (beside && out != nullptr))
-                        ? (int)zq::kGemmSimple
-                        : zq_gemm_choose_variant(M, N, K, w_bits, workspace_bytes);
-    bool in_kernel = out_q != nullptr && g_in_kernel_quant.load() != 0 && is_tile_variant(cls) &&
-                     zq::gemm_tile_quant_supported(M, N, workspace_bytes);
-    if (out == nullptr && !in_kernel) return ZQ_ERR_UNSUPPORTED;
-    if (in_kernel && beside && workspace_bytes >= zq::kWsFixedBytes + row_bytes(M, N)) {
-        out = zq::ws_partials(workspace);
-        in_kernel = false;
-    }
+    const GemmPlan plan = plan_gemm(forced, M, N, K, w_bits, workspace_bytes, out_q != nullptr, out != nullptr);
+    if (plan.refused) return ZQ_ERR_UNSUPPORTED;
+    if (plan.rows_in_workspace) out = zq::ws_partials(workspace);
     zq::GemmArgs a;
     a.xq = xq; a.s_tok = s_tok; a.wq = wq; a.s_w = s_w; a.groups = groups; a.bias = bias;
     a.M = M; a.N = N; a.K = K; a.out = out; a.acc_out = acc_out;
     a.workspace = workspace; a.workspace_bytes = workspace_bytes; a.w_bits = w_bits; a.act = act;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (in_kernel) {
+    if (plan.in_kernel) {
         a.q_out = out_q; a.q_scale_out = out_s_tok;
         if (forced >= 0) a.quant_shapes = zq::tile_shapes_of(forced);
         return zq::launch_gemm_tile_quant(a, st) == hipSuccess ? ZQ_OK : ZQ_ERR_HIP;
     }
-    const int launched = direct ? (int)zq::kGemmSimple
-                         : forced >= 0 ? cls
-                                       : zq::tiles_if_faster(cls, M, N, K, w_bits, workspace_bytes);
-    if (zq::launch_gemm(launched, a, st) != hipSuccess) return ZQ_ERR_HIP;
+    if (zq::launch_gemm(plan.variant, a, st) != hipSuccess) return ZQ_ERR_HIP;
     if (out_q != nullptr) {
         // Re-quantization for the next GeMM: token-wise quantizer over the FP16 row just written.
         if (zq::launch_rowquant(zq::kOpIdentity, out, nullptr, nullptr, 0.0f, M, N, out_q, out_s_tok, nullptr, 0,
@@ -428,6 +443,18 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
         default:
             return zq::tile_shape_name(zq::choose_tile(zq::kTileA16, M, N, K, zq::kAllTileShapes, nullptr));
     }
+}
+
+const char *zq_debug_gemm_kernel(int M, int N, int K, int w_bits, int x_bits, int wants_codes, size_t workspace_bytes) {
+    const char *name = zq_gemm_schedule(M, N, K, w_bits, x_bits, workspace_bytes);
+    if (name == nullptr || (wants_codes != 0 && (x_bits != 8 || N > kMaxRow))) return nullptr;
+    if (wants_codes != 0) {
+        const int forced = g_forced_variant.load();
+        if (plan_gemm(forced, M, N, K, w_bits, workspace_bytes, true, true).in_kernel)
+            return zq::gemm_tile_quant_name(M, N, K, w_bits, forced >= 0 ? zq::tile_shapes_of(forced) : ~0u);
+    }
+    const bool direct = std::strcmp(name, "direct") == 0 || std::strncmp(name, "small", 5) == 0;
+    return direct ? zq::gemm_direct_kernel_name(M, N, K, w_bits, x_bits / 8) : name;
 }
 
 const char *zq_gemm_variant_name(int variant) {

@@ -606,6 +606,11 @@ bool permuted_pays(int M, int N, int K) {
     return M >= 12 && M <= 32 && N <= 16 * kCUs && (K % 256 == 0 || (K >= 2048 && K % 64 == 0));
 }
 
+enum DirectForm { kPlain, kPairs, kPermuted };
+DirectForm direct_form(int M, int N, int K) {
+    return pairs_pay(M, N, K) ? kPairs : permuted_pays(M, N, K) ? kPermuted : kPlain;
+}
+
 template <int MT, int RT, int WBITS, int XB, int D, int NW, int HALF, int XP>
 hipError_t launch_direct_t(const void *x, const float *s_tok, const void *wq, const float *s_w, int groups,
                            const void *bias, int M, int N, int K, int rows, void *out, int32_t *acc_out, int act,
@@ -626,7 +631,8 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
 #define ZQ_DK(MT, RT, D, NW, HALF, XP)                                                                                     \
     return launch_direct_t<MT, RT, WBITS, XB, D, NW, HALF, XP>(x, s_tok, wq, s_w, groups, bias, M, N, K, p.rows, out,      \
                                                                acc_out, act, st)
-    if (pairs_pay(M, N, K)) {
+    const DirectForm form = direct_form(M, N, K);
+    if (form == kPairs) {
         const int pairs = (K + 2 * kStageK - 1) / (2 * kStageK);
         if (pairs <= 4) ZQ_DK(1, 1, 1, 4, 1, 0);
         if (pairs <= 8) ZQ_DK(1, 1, 1, 8, 1, 0);
@@ -637,7 +643,7 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
     // token 5.7 -> 5.3 us; for INT8 it measured level).
     const int nw = nst <= 4 ? 4 : 8;
     [[maybe_unused]] const bool two = M <= 8 && ((nst + nw - 1) / nw) % 2 == 0;
-    if (permuted_pays(M, N, K)) {
+    if (form == kPermuted) {
         if (p.mt == 1) {
             if (nw == 4) ZQ_DK(1, 1, 1, 4, 0, 1);
             ZQ_DK(1, 1, 1, 8, 0, 1);
@@ -888,6 +894,16 @@ const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb) {
         case kMid32x32: return "small32x32";
         case kMid64x32: return "small64x32";
         case kMid64x64: return "small64x64";
+        default: return "direct";
+    }
+}
+
+const char *gemm_direct_kernel_name(int M, int N, int K, int w_bits, int xb) {
+    if (xb == 1 && vector_pays(M, N, K, w_bits)) return "vector";
+    if (small_shape(M, N, K, w_bits, xb) != kMidShapes) return gemm_direct_name(M, N, K, w_bits, xb);
+    switch (direct_form(M, N, K)) {
+        case kPairs: return "direct_pairs";
+        case kPermuted: return "direct_permuted";
         default: return "direct";
     }
 }

@@ -1255,6 +1255,16 @@ bool gemm_tile_quant_supported(int M, int N, size_t workspace_bytes) {
     return quant_tiles_fit(M, N, edge, edge);
 }
 
+const char *gemm_tile_quant_name(int M, int N, int K, int w_bits, unsigned shapes) {
+    switch (choose_quant_tile(M, N, K, w_bits, shapes)) {
+        case kTile128x64: return "quant128x64";
+        case kTile128x128: return "quant128x128";
+        case kTile192x128: return "quant192x128";
+        case kTile256x128: return "quant256x128";
+        default: return "quant256x256";
+    }
+}
+
 hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st) {
     if (a.workspace == nullptr || !gemm_tile_quant_supported(a.M, a.N, a.workspace_bytes) || a.q_out == nullptr ||
         a.q_scale_out == nullptr)

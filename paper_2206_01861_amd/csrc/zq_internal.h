@@ -121,12 +121,14 @@ hipError_t launch_gemm_tile_splitk(const GemmArgs &a, hipStream_t st);
 // needs a workspace of at least kWsFixedBytes.
 bool gemm_tile_quant_supported(int M, int N, size_t workspace_bytes);
 hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st);
+const char *gemm_tile_quant_name(int M, int N, int K, int w_bits, unsigned shapes);      // of the tile it takes
 
 // Whether the small-tile kernels of zq_gemm_direct.hip beat the streaming and the tiled ones; xb: bytes of an activation.
 // gemm_goes_direct: the same for INT8 activations, unless a schedule is registered for the shape that the call can run.
 bool direct_pays(int M, int N, int K, int w_bits, int xb);
 bool gemm_goes_direct(int M, int N, int K, int w_bits, size_t workspace_bytes);
-const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb);    // of the kernel that launch takes
+const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb);    // of the kernel that launch takes ...
+const char *gemm_direct_kernel_name(int M, int N, int K, int w_bits, int xb);     // ... and its form (zq_debug_gemm_kernel)
 
 // Of the direct kernels, the one on the vector ALUs: whether it is ahead of the others (up to four tokens), and its launch.
 bool vector_pays(int M, int N, int K, int w_bits);

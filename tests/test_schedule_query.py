@@ -131,3 +131,21 @@ def test_fp16_call_splits_k_only_where_the_workspace_query_says():
             assert own > 0, (M, N, K, name)
             asked += 1
     assert asked > 100
+
+
+@pytest.mark.parametrize("M,N,K,bits,x_bits,codes,want", [
+    (1, 2048, 2048, 8, 8, False, "vector"), (2, 1024, 2080, 4, 8, False, "vector"), (4, 2048, 2576, 8, 8, True, "vector"),
+    (5, 1536, 1536, 8, 8, False, "direct_pairs"), (5, 1536, 1536, 8, 16, False, "direct_pairs"), (27, 2048, 2048, 4, 8, False, "direct_permuted"),
+    (9, 2048, 2048, 8, 8, False, "direct"), (64, 2048, 2048, 8, 8, False, "small32x32"), (32, 12288, 4096, 8, 8, False, "stream"),
+    (4096, 4096, 1024, 8, 8, False, "tile256x256"), (1237, 4096, 1024, 8, 8, True, "quant192x128"),
+])
+def test_kernel_behind_the_schedule(M, N, K, bits, x_bits, codes, want):
+    ws = zq.WORKSPACE_FIXED_BYTES if codes else 0
+    assert zq.gemm_kernel(M, N, K, bits, ws, x_bits=x_bits, codes=codes) == want
+    name = zq.gemm_schedule(M, N, K, bits, ws, x_bits=x_bits)
+    assert name == ("direct" if want.startswith(("direct", "vector")) else name if codes else want)
+
+
+def test_kernel_of_shapes_no_call_takes():
+    assert zq.gemm_kernel(1, 24, 16) is None and zq.gemm_kernel(8, 16, 32, 8, 0, x_bits=16, codes=True) is None
+    assert zq.gemm_kernel(8, 32784, 32, codes=True) is None and zq.gemm_kernel(8, 32784, 32) is not None
