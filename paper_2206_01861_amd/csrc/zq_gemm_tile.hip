@@ -1091,8 +1091,7 @@ constexpr TileCost kTileCost[3][kTileShapes] = {
 };
 
 // The same for launches that quantize their output in the kernel (GeLU, row maxima exchanged between the tiles of a band, codes
-// from the accumulators), fitted to 370 shapes (65 to 8192 tokens, 768 to 8192 columns, K 768 to 4096): 3 to 8 % rms, and
-// the choice costs 0.1 % on average over the best shape.  256x192, whose twelve chunks a row the code tile's swizzle does not
+// from the accumulators), fitted to 370 shapes (65 to 8192 tokens, 768 to 8192 columns, K 768 to 4096).  256x192, whose twelve chunks a row the code tile's swizzle does not
 // take, has no such kernel.  Against 128x128 and 256x256 alone, us: 1237x4096x1024 25.6 -> 19.0 (one round of 192x128
 // instead of two of 128x128), 1161x6400x1600 35.0 -> 28.2, 1876x4096x1024 26.2 -> 21.9, 6408x768x4096 48.5 -> 36.1,
 // 882x1024x1024 11.4 -> 9.7 (128x64); INT4 2143x3072x2048 37.6 -> 30.1.
@@ -1102,6 +1101,25 @@ constexpr TileCost kQuantTileCost[2][kTileShapes] = {
     {{128, 64, 10.94, 0.057, 0.546, 7.80}, {128, 128, 9.56, 0.254, 0.744, 6.38}, {192, 128, 10.82, 0.427, 0.998, 7.83},
      {256, 128, 11.73, 0.651, 1.272, 8.99}, {256, 192, 0, 0, 0, 0}, {256, 256, 16.32, 0.952, 1.918, 13.47}},
 };
+
+// A tile that quantizes its rows waits for its band, so a band that the chip does not take in whole keeps the compute units of its
+// first tiles until its last ones are through: the rounds are dealt out in id order with those units taken away (INT8
+// 1318x5888x1472 on 128x128: 506 tiles are three rounds, 44.7 us, not two; 256x256 34.7).  And the maxima of a band come 16 at a
+// time, 0.6 us each (442x4096x1024, bands of 64 tiles of 128x64 14.7 us, of 32 of 128x128 13.7).  Against 2400 other shapes
+// (65 to 8192 tokens, 768 to 16384 columns, K 768 to 6144) 5 % rms; the choice costs 0.02 % on average over the best shape (0.27 %
+// without the two terms, 29 % at worst) and takes 0.962 of the time that 128x128 and 256x256 alone take.
+double quant_tile_time(const TileCost &t, int M, int N, int K) {
+    const long tiles_n = (N + t.bn - 1) / t.bn, tiles = (long)((M + t.bm - 1) / t.bm) * tiles_n;
+    const double stages = (double)((K + 127) / 128);
+    double us = t.a - t.c + 0.6 * (double)((tiles_n + 15) / 16 - 1);
+    for (long done = 0, held = 0; done < tiles;) {
+        const long take = tiles - done < 256 - held ? tiles - done : 256 - held;
+        us += t.c + stages * (t.b0 + (t.b1 - t.b0) * (double)take / 256.0);
+        done += take;
+        held = done % tiles_n;
+    }
+    return us;
+}
 
 double tile_time(const TileCost &t, int M, int N, int K, int x_bytes) {
     const long tiles = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
@@ -1152,7 +1170,7 @@ TileShape choose_quant_tile(int M, int N, int K, int w_bits, unsigned shapes) {
         for (int i = 0; i < kTileShapes; ++i) {
             const TileCost &c = kQuantTileCost[w_bits == 8 ? 0 : 1][i];
             if (i == kTile256x192 || ((mask >> i) & 1u) == 0 || !quant_tiles_fit(M, N, c.bm, c.bn)) continue;
-            const double t = tile_time(c, M, N, K, 1);
+            const double t = quant_tile_time(c, M, N, K);
             if (t < best_us) {
                 best_us = t;
                 best = i;

@@ -149,3 +149,16 @@ def test_kernel_behind_the_schedule(M, N, K, bits, x_bits, codes, want):
 def test_kernel_of_shapes_no_call_takes():
     assert zq.gemm_kernel(1, 24, 16) is None and zq.gemm_kernel(8, 16, 32, 8, 0, x_bits=16, codes=True) is None
     assert zq.gemm_kernel(8, 32784, 32, codes=True) is None and zq.gemm_kernel(8, 32784, 32) is not None
+
+
+# Tiles that quantize: a band that straddles a round of tiles holds its compute units (fewer, larger tiles are ahead although the
+# count of tiles alone says otherwise), a band of many tiles fetches its maxima in several goes
+@pytest.mark.parametrize("M,N,K,bits,want", [
+    (1318, 5888, 1472, 8, "quant256x256"), (1045, 7168, 3072, 8, "quant256x256"), (1848, 4288, 1056, 8, "quant256x256"),
+    (2306, 3328, 832, 8, "quant256x256"), (1854, 4352, 1088, 4, "quant256x256"), (1369, 5440, 2624, 4, "quant256x256"),
+    (442, 4096, 1024, 8, "quant128x128"), (76, 3328, 1792, 4, "quant128x128"),
+    (1237, 4096, 1024, 8, "quant192x128"), (882, 1024, 1024, 8, "quant128x64"), (1876, 4096, 1024, 8, "quant256x128"),
+    (4096, 4096, 1024, 8, "quant256x256"),
+])
+def test_tile_that_quantizes(M, N, K, bits, want):
+    assert zq.gemm_kernel(M, N, K, bits, zq.WORKSPACE_FIXED_BYTES, codes=True) == want
