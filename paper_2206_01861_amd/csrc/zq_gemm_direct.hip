@@ -601,14 +601,23 @@ bool pairs_pay(int M, int N, int K) { return M <= 8 && N <= 8 * kCUs && K > 4 * 
 // lines); the permutations that contiguous loads need instead pay from some twelve tokens on, where a compute unit has few
 // rows against its activations and their rows begin on cache lines.  us, operand layout / permuted: INT8 2048x2048 at 27 tokens
 // 4.5 / 4.0, 896x3584 at 16 4.4 / 3.8; INT4 2048x8192 at 27 9.7 / 7.5, 4096x16384 at 16 12.6 / 11.7; W8A16 2048x2048 at 27 6.2 / 5.0;
-// beyond: 3072x3072 at 9 4.6 / 4.7, 1600x1600 at 24 3.6 / 3.9, 1120x1120 at 20 3.3 / 3.6, 6144x2048 at 16 5.2 / 5.2.
-bool permuted_pays(int M, int N, int K) {
-    return M >= 12 && M <= 32 && N <= 16 * kCUs && (K % 256 == 0 || (K >= 2048 && K % 64 == 0));
+// beyond: 3072x3072 at 9 4.6 / 4.7, 1600x1600 at 24 3.6 / 3.9, 1120x1120 at 20 3.3 / 3.6, 6144x2048 at 16 5.2 / 5.2.  The lines
+// are 128 bytes: INT8 activations whose rows begin in the middle of one, K an odd multiple of 64, lose more often than not (1728x2240
+// at 19 4.2 / 4.7, 464x4928 at 17 5.3 / 5.9) and gain only where there are many of them for few stages a wave: over 900 shapes INT4
+// above 24 tokens and K 3072 1.07, INT8 up to 2048 rows K 3072 to 4096 1.07, above 24 tokens and K 5120 1.01; the others 0.96.  A
+// K of one or two stages is one round trip either way, with the permutations on top (INT4 1536x256 at 32 2.65 / 2.81, W8A16 2192x512
+// at 18 3.5 / 3.7).
+bool permuted_pays(int M, int N, int K, int w_bits, int xb) {
+    if (M < 12 || M > 32 || N > 16 * kCUs || K <= 2 * kStageK) return false;
+    if ((K * xb) % 128 == 0) return K % 256 == 0 || K >= 2048;
+    if ((K * xb) % 64 != 0) return false;
+    if (w_bits == 4) return M > 24 && K > 3072;
+    return xb == 1 && N <= 8 * kCUs && ((M >= 20 && K > 3072 && K <= 4096) || (M > 24 && K > 5120));
 }
 
 enum DirectForm { kPlain, kPairs, kPermuted };
-DirectForm direct_form(int M, int N, int K) {
-    return pairs_pay(M, N, K) ? kPairs : permuted_pays(M, N, K) ? kPermuted : kPlain;
+DirectForm direct_form(int M, int N, int K, int w_bits, int xb) {
+    return pairs_pay(M, N, K) ? kPairs : permuted_pays(M, N, K, w_bits, xb) ? kPermuted : kPlain;
 }
 
 template <int MT, int RT, int WBITS, int XB, int D, int NW, int HALF, int XP>
@@ -631,7 +640,7 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
 #define ZQ_DK(MT, RT, D, NW, HALF, XP)                                                                                     \
     return launch_direct_t<MT, RT, WBITS, XB, D, NW, HALF, XP>(x, s_tok, wq, s_w, groups, bias, M, N, K, p.rows, out,      \
                                                                acc_out, act, st)
-    const DirectForm form = direct_form(M, N, K);
+    const DirectForm form = direct_form(M, N, K, WBITS, XB);
     if (form == kPairs) {
         const int pairs = (K + 2 * kStageK - 1) / (2 * kStageK);
         if (pairs <= 4) ZQ_DK(1, 1, 1, 4, 1, 0);
@@ -901,7 +910,7 @@ const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb) {
 const char *gemm_direct_kernel_name(int M, int N, int K, int w_bits, int xb) {
     if (xb == 1 && vector_pays(M, N, K, w_bits)) return "vector";
     if (small_shape(M, N, K, w_bits, xb) != kMidShapes) return gemm_direct_name(M, N, K, w_bits, xb);
-    switch (direct_form(M, N, K)) {
+    switch (direct_form(M, N, K, w_bits, xb)) {
         case kPairs: return "direct_pairs";
         case kPermuted: return "direct_permuted";
         default: return "direct";

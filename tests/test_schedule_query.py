@@ -162,3 +162,15 @@ def test_kernel_of_shapes_no_call_takes():
 ])
 def test_tile_that_quantizes(M, N, K, bits, want):
     assert zq.gemm_kernel(M, N, K, bits, zq.WORKSPACE_FIXED_BYTES, codes=True) == want
+
+
+@pytest.mark.parametrize("M,N,K,bits,x_bits,want", [
+    # permuted activations: rows that begin on 128-byte lines, more than two stages
+    (19, 1728, 2240, 8, 8, "direct"), (19, 1728, 2304, 4, 8, "direct_permuted"), (19, 1728, 2176, 8, 8, "direct_permuted"),
+    (27, 512, 3904, 8, 8, "direct_permuted"), (27, 512, 4416, 8, 8, "direct"), (25, 512, 5184, 8, 8, "direct_permuted"),
+    (24, 512, 5184, 8, 8, "direct"), (27, 2064, 3904, 8, 8, "direct"), (25, 4096, 3136, 4, 8, "direct_permuted"), (24, 4096, 3136, 4, 8, "direct"),
+    (17, 464, 4928, 8, 8, "direct"), (12, 1888, 4288, 4, 8, "direct"), (27, 400, 2112, 8, 16, "direct_permuted"), (27, 400, 2080, 8, 16, "direct"),
+    (32, 1536, 256, 4, 8, "direct"), (19, 480, 512, 4, 8, "direct"), (18, 2192, 512, 8, 16, "direct"), (18, 2192, 768, 8, 16, "direct_permuted"),
+])
+def test_lines_between_the_forms_of_the_direct_kernel(M, N, K, bits, x_bits, want):
+    assert zq.gemm_kernel(M, N, K, bits, 0, x_bits=x_bits) == want
