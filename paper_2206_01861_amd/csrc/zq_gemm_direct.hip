@@ -594,8 +594,13 @@ DirectPlan plan_direct(int M, int N, int w_bits, int xb) {
 // us, before / so: INT8 1600x6400 at 5 tokens 6.1 / 5.2, 2048x8192 at 5 6.7 / 6.1, 1536x1536 at 6 3.2 / 2.9; INT4 1984x1984 at 8
 // 3.0 / 2.8, 2048x8192 at 5 5.3 / 4.6; W8A16 1600x1600 at 6 3.7 / 3.3.  More rows are more workgroups of eight, each of which
 // reads the activations (2400x2400 at 5 3.7 / 4.0, 3072x12288 at 8 10.0 / 14.1), and of four stages or fewer half the waves
-// are idle (1024x1024 at 5 2.5 / 2.7).
-bool pairs_pay(int M, int N, int K) { return M <= 8 && N <= 8 * kCUs && K > 4 * kStageK; }
+// are idle (1024x1024 at 5 2.5 / 2.7).  INT8 weights of 17 to 24 stages of 512 values are a third one for each of the eight waves
+// after two in flight, which more activations do not hide (at 8 tokens 1792x9536 W8A16 9.2 / 10.1, INT8 1360x9728 0.93; 90 shapes of
+// 7168 and more tokens x rows 0.96, 150 smaller ones 1.03).
+bool pairs_pay(int M, int N, int K, int w_bits) {
+    if (w_bits == 8 && K > 32 * kStageK && K <= 48 * kStageK && M * N >= 7168) return false;
+    return M <= 8 && N <= 8 * kCUs && K > 4 * kStageK;
+}
 
 // In operand layout the vector cache delivers 38 GB/s a compute unit, a quarter of its rate (four neighbouring lanes read four
 // lines); the permutations that contiguous loads need instead pay from some twelve tokens on, where a compute unit has few
@@ -617,7 +622,7 @@ bool permuted_pays(int M, int N, int K, int w_bits, int xb) {
 
 enum DirectForm { kPlain, kPairs, kPermuted };
 DirectForm direct_form(int M, int N, int K, int w_bits, int xb) {
-    return pairs_pay(M, N, K) ? kPairs : permuted_pays(M, N, K, w_bits, xb) ? kPermuted : kPlain;
+    return pairs_pay(M, N, K, w_bits) ? kPairs : permuted_pays(M, N, K, w_bits, xb) ? kPermuted : kPlain;
 }
 
 template <int MT, int RT, int WBITS, int XB, int D, int NW, int HALF, int XP>

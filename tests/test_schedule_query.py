@@ -171,6 +171,9 @@ def test_tile_that_quantizes(M, N, K, bits, want):
     (24, 512, 5184, 8, 8, "direct"), (27, 2064, 3904, 8, 8, "direct"), (25, 4096, 3136, 4, 8, "direct_permuted"), (24, 4096, 3136, 4, 8, "direct"),
     (17, 464, 4928, 8, 8, "direct"), (12, 1888, 4288, 4, 8, "direct"), (27, 400, 2112, 8, 16, "direct_permuted"), (27, 400, 2080, 8, 16, "direct"),
     (32, 1536, 256, 4, 8, "direct"), (19, 480, 512, 4, 8, "direct"), (18, 2192, 512, 8, 16, "direct"), (18, 2192, 768, 8, 16, "direct_permuted"),
+    # both halves of the matrix instruction: not where INT8 weights are a third stage for every wave and the activations many
+    (8, 1792, 9536, 8, 16, "direct"), (8, 1360, 9728, 8, 8, "direct"), (7, 1024, 12288, 8, 8, "direct"), (7, 1008, 9728, 8, 8, "direct_pairs"),
+    (8, 1792, 9536, 4, 8, "direct_pairs"), (8, 1360, 8192, 8, 8, "direct_pairs"), (8, 1360, 12304, 8, 8, "direct_pairs"),
 ])
 def test_lines_between_the_forms_of_the_direct_kernel(M, N, K, bits, x_bits, want):
     assert zq.gemm_kernel(M, N, K, bits, 0, x_bits=x_bits) == want
