@@ -195,11 +195,18 @@ hipError_t launch_vector(const GemmArgs &a, hipStream_t st) {
 //             INT4   896x3584 3.2 / 2.8, 6144x2048 3.7 / 3.5; beyond: 3072x768 2.6 / 2.8, 6016x6016 6.9 / 7.1, 13056x4352 9.5 / 11.3
 //   3, 4 tokens INT8 768x2560 3.4 / 3.1, 1696x6784 6.4 / 5.5; beyond: 6144x2048 4.9 / 4.9, 3840x3840 5.1 / 5.6
 //             INT4   none: 1536x6144 4.1 / 4.2, 18048x6016 13.2 / 23.2
+//
+// A K of a piece or two of 256 bytes leaves waves idle in every workgroup, which many rows make many of: not INT4 up to K 1024
+// above 16384 rows (1 token 31536x256 3.5 / 4.7, 26400x768 4.6 / 5.2, 29440x1024 4.9 / 5.6; 1152 and more 0.91 of the time), nor at 2
+// tokens up to K 1024 (3328x1024 2.5 / 2.7, 8192x1024 3.0 / 3.2), nor INT8 of one piece above 20480 rows at 2 tokens, 28672 at 1
+// (2 tokens 29024x256 4.2 / 4.9, 1 token 31424x256 4.2 / 4.5).
 bool vector_pays(int M, int N, int K, int w_bits) {
+    if (w_bits == 4 && M == 1 && N > 16384 && K <= 1024) return false;
+    if (w_bits == 8 && K <= kPiece && N > (M == 1 ? 28672 : 20480)) return false;
     if (M == 1) return !(w_bits == 8 && N > 4096 && K > 8 * kPiece && K <= 9 * kPiece && K % 256 == 0);
     if (M == 2) {
         if (w_bits == 8) return !(N > 2048 && N <= 3072 && K > 8192) && !(K % 4096 == 0 && N > 8192 && N <= 12288);
-        return N <= 2048 || (N <= 8192 && K >= 1024 && K <= 4096);
+        return N <= 2048 || (N <= 8192 && K > 1024 && K <= 4096);
     }
     return M <= 4 && w_bits == 8 && N <= 2048 && K >= 2560;
 }

@@ -177,3 +177,13 @@ def test_tile_that_quantizes(M, N, K, bits, want):
 ])
 def test_lines_between_the_forms_of_the_direct_kernel(M, N, K, bits, x_bits, want):
     assert zq.gemm_kernel(M, N, K, bits, 0, x_bits=x_bits) == want
+
+
+@pytest.mark.parametrize("M,N,K,bits,vector", [
+    # the vector kernel leaves a K of a piece or two to the others where the rows are many
+    (1, 31536, 256, 4, False), (1, 16400, 1024, 4, False), (1, 16384, 1024, 4, True), (1, 29440, 1056, 4, True), (1, 20672, 768, 4, False),
+    (2, 3328, 1024, 4, False), (2, 3328, 1056, 4, True), (2, 2048, 1024, 4, True), (2, 29024, 256, 8, False), (2, 20480, 256, 8, True),
+    (2, 29024, 272, 8, True), (1, 31424, 256, 8, False), (1, 28672, 256, 8, True),
+])
+def test_lines_of_the_vector_kernel(M, N, K, bits, vector):
+    assert (zq.gemm_kernel(M, N, K, bits) == "vector") == vector
