@@ -836,7 +836,9 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // are the ones that lose least over 600 shapes (INT8 593x1536x1536 7.9 us on 0.87 of the tiles' modelled time, 7.2 on these,
 // but 105x4416x1472 7.5, 8.8; 80x6144x2048 11.3 / 9.1 against streaming, whose time at K 2048 to 2304 is above that of the
 // tiles; 107x2304x6144 15.5 split / 14.2; W8A16 78x8064x2688 17.5 split / 15.6, 149x1280x5120 1.35 times as fast, 245x400x5728
-// and longer K left to the split).
+// and longer K left to the split).  64 x 64 tiles leave at least half their waves without a stage up to K 384, which the models,
+// fitted from K 768 on, do not see (tiles / small, us: W8A16 418x2080x256 5.6 / 7.1, 515x1024x320 5.9 / 6.9, INT4 509x1472x256 4.8 / 5.3,
+// INT8 318x3072x384 5.0 / 5.6).
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
     if (xb == 1 && vector_pays(M, N, K, w_bits)) return true;
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
@@ -852,6 +854,7 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
             if ((long)N * K > (1L << 24) || (K > 1024 && N > (K <= 2048 ? 8192 : 4096))) return false;
             return K <= (xb == 2 ? (M <= 48 ? 4608 : 3072) : shape == kMid64x64 ? 5120 : 6400);
         }
+        if (shape == kMid64x64 && K <= 3 * kMidStageK) return false;
         choose_tile(xb == 2 ? kTileA16 : int8 ? kTileI8 : kTileI4, M, N, K, kAllTileShapes, &tile_us);
         if (w_bits == 4) return K <= (N <= 3072 ? 12288 : 9216) && us < 0.96 * tile_us;
         // up to here the K split is behind wherever the small tiles are ahead of the unsplit ones

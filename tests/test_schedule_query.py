@@ -187,3 +187,12 @@ def test_lines_between_the_forms_of_the_direct_kernel(M, N, K, bits, x_bits, wan
 ])
 def test_lines_of_the_vector_kernel(M, N, K, bits, vector):
     assert (zq.gemm_kernel(M, N, K, bits) == "vector") == vector
+
+
+@pytest.mark.parametrize("M,N,K,bits,x_bits,want", [
+    # above 64 tokens 64 x 64 small tiles leave a K of up to three stages to the LDS tiles
+    (418, 2080, 256, 8, 16, "tile128x128"), (515, 1024, 320, 8, 16, "tile128x128"), (509, 1472, 256, 4, 8, "tile128x128"),
+    (318, 3072, 384, 8, 8, "tile128x64"), (69, 4384, 256, 8, 8, "small32x32"), (418, 2080, 512, 8, 16, "small64x64"),
+])
+def test_small_tiles_against_a_short_k(M, N, K, bits, x_bits, want):
+    assert zq.gemm_schedule(M, N, K, bits, 0, x_bits=x_bits) == want
