@@ -356,7 +356,7 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
 /*
  * Test hook: the kernel behind what zq_gemm_schedule names (same arguments).  "direct" is told apart into "vector"
  * (vector ALUs), "direct_pairs" (both halves of the matrix instruction), "direct_permuted" (contiguous activation
- * loads) and "direct"; with wants_codes 1 a call with out_q / gq_out and an FP16 output that quantizes in the GeMM
+ * loads) and "direct", "small32x32" on four waves is "small32x32_4waves"; with wants_codes 1 a call with out_q / gq_out and an FP16 output that quantizes in the GeMM
  * kernel is "quant128x64", "quant128x128", "quant192x128", "quant256x128" or "quant256x256".
  */
 const char *zq_debug_gemm_kernel(int M, int N, int K, int w_bits, int x_bits, int wants_codes, size_t workspace_bytes);

@@ -706,6 +706,15 @@ constexpr MidCost kMidCost[3][kMidShapes] = {
 };
 constexpr int kMidPerCU[kMidShapes] = {2, 1, 1};
 
+// INT4 on two 32 x 32 tiles a compute unit: four waves with two stages in flight hold half as many waves' partial sums for twice
+// the loads (eight with one / four with two, us: 80x5120x2816 8.3 / 7.6, 66x4736x2304 7.0 / 6.7, 72x4608x3072 8.2 / 7.65; 150 shapes
+// of 65 to 128 tokens, K 1024 to 3072 0.97), and stay ahead of one round of 64 x 64 up to K 5120 (79x4128x3136 10.0 / 9.2, 75x5344x4608
+// 11.7 / 11.1; 80 shapes 0.96).
+bool two_rounds(int M, int N) {
+    const long tiles = (long)((M + 31) / 32) * ((N + 31) / 32);
+    return tiles > kCUs && tiles <= 2 * kCUs;
+}
+
 MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
     int best = kMidShapes;
     double best_us = 1e30;
@@ -724,6 +733,7 @@ MidShape choose_mid(int M, int N, int K, int w_bits, int xb, double *us) {
         }
     }
     if (us != nullptr) *us = best_us;
+    if (best == kMid64x64 && w_bits == 4 && M > 64 && M <= 128 && K <= 5 * 8 * kMidStageK && two_rounds(M, N)) best = kMid32x32;
     return (MidShape)best;
 }
 
@@ -741,6 +751,7 @@ hipError_t launch_mid(MidShape shape, const void *x, const float *s_tok, const v
     [[maybe_unused]] const int per_wave = (K + 8 * kMidStageK - 1) / (8 * kMidStageK);
     if (shape == kMid32x32) {
         if constexpr (WBITS == 4) {
+            if (two_rounds(M, N)) ZQ_MK(2, 2, 2, 4);
             if (per_wave >= 4 && per_wave % 2 == 0) ZQ_MK(2, 2, 2, 8);
         }
         ZQ_MK(2, 2, 1, 8);
@@ -917,7 +928,9 @@ const char *gemm_direct_name(int M, int N, int K, int w_bits, int xb) {
 
 const char *gemm_direct_kernel_name(int M, int N, int K, int w_bits, int xb) {
     if (xb == 1 && vector_pays(M, N, K, w_bits)) return "vector";
-    if (small_shape(M, N, K, w_bits, xb) != kMidShapes) return gemm_direct_name(M, N, K, w_bits, xb);
+    const MidShape shape = small_shape(M, N, K, w_bits, xb);
+    if (shape == kMid32x32 && w_bits == 4 && two_rounds(M, N)) return "small32x32_4waves";
+    if (shape != kMidShapes) return gemm_direct_name(M, N, K, w_bits, xb);
     switch (direct_form(M, N, K, w_bits, xb)) {
         case kPairs: return "direct_pairs";
         case kPermuted: return "direct_permuted";

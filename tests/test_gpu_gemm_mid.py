@@ -58,3 +58,16 @@ DEPTHS = [(40, 272, 4096, 17), (40, 272, 5152, 17), (100, 1040, 8192, 65), (245,
 @pytest.mark.parametrize("M,N,K,g", DEPTHS)
 def test_small_tile_depths(zq, orc, bits, M, N, K, g):
     test_small_tiles_against_oracle(zq, orc, bits, M, N, K, g, SIMPLE)
+
+
+# INT4, more than one 32 x 32 tile per compute unit: four waves with two stages in flight; K of a stage, of fewer than waves, of
+# an odd and an even count of stages a wave, with a tail of 32 values
+@pytest.mark.parametrize("M,N,K,g", [(65, 2768, 32, 173), (80, 5136, 416, 107), (72, 4608, 1056, 96), (96, 4112, 1536, 257),
+                                     (70, 4112, 2080, 257), (80, 5440, 3104, 10), (66, 4112, 5120, 257)])
+def test_int4_on_four_waves(zq, orc, M, N, K, g):
+    before = zq.force_gemm_variant(SIMPLE)
+    try:
+        assert zq.gemm_kernel(M, N, K, 4) == "small32x32_4waves"
+    finally:
+        zq.force_gemm_variant(before)
+    test_small_tiles_against_oracle(zq, orc, 4, M, N, K, g, SIMPLE)

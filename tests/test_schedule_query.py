@@ -196,3 +196,13 @@ def test_lines_of_the_vector_kernel(M, N, K, bits, vector):
 ])
 def test_small_tiles_against_a_short_k(M, N, K, bits, x_bits, want):
     assert zq.gemm_schedule(M, N, K, bits, 0, x_bits=x_bits) == want
+
+
+@pytest.mark.parametrize("M,N,K,bits,want", [
+    # INT4, more than one 32 x 32 tile per compute unit: four waves, also in place of 64 x 64 tiles for 65 to 128 tokens up to K 5120
+    (80, 5120, 2816, 4, "small32x32_4waves"), (72, 4608, 3072, 4, "small32x32_4waves"), (79, 4128, 3136, 4, "small32x32_4waves"),
+    (75, 5344, 4608, 4, "small32x32_4waves"), (75, 5344, 5120, 4, "small32x32_4waves"), (75, 5344, 5376, 4, "small64x64"),
+    (96, 2720, 2816, 4, "small32x32"), (80, 5120, 2048, 8, "small32x32"),
+])
+def test_small_tiles_of_four_waves(M, N, K, bits, want):
+    assert zq.gemm_kernel(M, N, K, bits) == want
