@@ -362,6 +362,12 @@ const char *zq_gemm_schedule(int M, int N, int K, int w_bits, int x_bits, size_t
 const char *zq_debug_gemm_kernel(int M, int N, int K, int w_bits, int x_bits, int wants_codes, size_t workspace_bytes);
 
 /*
+ * Test hook: how a row kernel maps [M,K] (op 0 LayerNorm, 1 GeLU erf form, 2 GeLU tanh form, 3 the plain quantizer; bias: GeLU
+ * with one): "row64", "row256", "row512", "row1024" threads a row, or "parts", several workgroups a row.  Host-only.
+ */
+const char *zq_debug_row_kernel(int op, int M, int K, int bias);
+
+/*
  * Measured schedule table (App. D ranks schedules by measuring them offline
  * and picks by batch x sequence length at run time).  zq_tune_set registers,
  * for the GeMM shape (N, K, w_bits) and token counts m_lo..m_hi, the schedule

@@ -24,7 +24,7 @@ SYMBOLS = [
     "zq_gemm_w8a16_stream_plan",
     "zq_gemm_quantizes_in_kernel", "zq_debug_set_in_kernel_quant", "zq_quant_wait_expired",
     "zq_workspace_init", "zq_gemm_quant_workspace_bytes", "zq_gemm_i8_dequant_static", "zq_gemm_schedule",
-    "zq_debug_gemm_kernel",
+    "zq_debug_gemm_kernel", "zq_debug_row_kernel",
 ]
 PROBE_SYMBOLS = ["zq_probe_read_stream", "zq_probe_mfma_i8", "zq_probe_mfma_i8_tile_traffic"]      # include/zq_probe.h
 
@@ -100,6 +100,8 @@ def lib():
     L.zq_gemm_choose_variant.argtypes = [ci, ci, ci, ci, sz]
     L.zq_gemm_schedule.restype = ctypes.c_char_p
     L.zq_gemm_schedule.argtypes = [ci, ci, ci, ci, ci, sz]
+    L.zq_debug_row_kernel.restype = ctypes.c_char_p
+    L.zq_debug_row_kernel.argtypes = [ci, ci, ci, ci]
     L.zq_debug_gemm_kernel.restype = ctypes.c_char_p
     L.zq_debug_gemm_kernel.argtypes = [ci, ci, ci, ci, ci, ci, sz]
     L.zq_gemm_stream_plan.restype = ci
@@ -205,6 +207,15 @@ def gemm_schedule(M, N, K, w_bits=8, workspace_bytes=0, x_bits=8):
 def gemm_kernel(M, N, K, w_bits=8, workspace_bytes=0, x_bits=8, codes=False):
     """Test hook (zq_debug_gemm_kernel): the kernel behind gemm_schedule(); codes: a call that also quantizes its output."""
     s = lib().zq_debug_gemm_kernel(M, N, K, w_bits, x_bits, 1 if codes else 0, workspace_bytes)
+    return None if s is None else s.decode()
+
+
+ROW_OPS = ("layernorm", "gelu", "gelu_tanh", "quantize")
+
+
+def row_kernel(op, M, K, bias=False):
+    """Test hook (zq_debug_row_kernel): how the row kernel of `op` (one of ROW_OPS) maps [M, K]."""
+    s = lib().zq_debug_row_kernel(ROW_OPS.index(op), M, K, 1 if bias else 0)
     return None if s is None else s.decode()
 
 

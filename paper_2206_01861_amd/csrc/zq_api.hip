@@ -457,6 +457,18 @@ const char *zq_debug_gemm_kernel(int M, int N, int K, int w_bits, int x_bits, in
     return direct ? zq::gemm_direct_kernel_name(M, N, K, w_bits, x_bits / 8) : name;
 }
 
+const char *zq_debug_row_kernel(int op, int M, int K, int bias) {
+    if (op < 0 || op > zq::kOpIdentity || M <= 0 || K <= 0 || (K % 16) != 0 || K > kMaxRow) return nullptr;
+    const bool gelu = op == zq::kOpGeluErf || op == zq::kOpGeluTanh;
+    switch (zq::row_threads((zq::RowOp)op, M, K, gelu && bias != 0)) {
+        case 0: return "parts";
+        case 64: return "row64";
+        case 256: return "row256";
+        case 512: return "row512";
+        default: return "row1024";
+    }
+}
+
 const char *zq_gemm_variant_name(int variant) {
     switch (variant) {
         case zq::kGemmSimple: return "simple";

@@ -56,6 +56,7 @@ hipError_t launch_workspace_init(void *ws, hipStream_t st);
 enum RowOp { kOpLayerNorm = 0, kOpGeluErf = 1, kOpGeluTanh = 2, kOpIdentity = 3 };
 
 // in fp16 [M,K]; p0 = gamma (LayerNorm) or bias (GeLU, nullable); p1 = beta (nullable).
+int row_threads(RowOp op, int M, int K, bool bias);       // of a row, 0: several workgroups (GeLU in parts)
 hipError_t launch_rowquant(RowOp op, const void *in, const void *p0, const void *p1, float eps, int M, int K,
                            int8_t *xq, float *s_tok, void *y_out, int y_dtype, hipStream_t st);
 

@@ -287,43 +287,70 @@ static hipError_t launch_rq(const void *in, const void *p0, const void *p1, floa
     return hipGetLastError();
 }
 
+// Threads of a row, 0: GeLU in parts (gelu_parts_kernel).  bias: GeLU's.
+//
+// Short rows: one wave per row, four rows per workgroup.  Up to 2048 values where a workgroup per row would be many
+// rounds of them: no barrier in the three reductions (LayerNorm 2048x2048 5.9 -> 5.1 us, 2048x1280 5.3 -> 4.2,
+// 8192x2048 16.4 -> 14.0; at 512 rows level, at 5 rows 2.7 -> 2.9; 4096 values are 25 % slower that way).  The
+// arithmetic of GeLU wants more waves: 2100x1920 5.2 -> 5.6.
+//
+// Longer rows: a workgroup shares one row, with up to four vectors per thread: six to sixteen of 256 threads are too few
+// waves for the arithmetic of GeLU (300x16384 7.8 -> 6.5 us, 300x24576 10.9 -> 8.4, 2048x24576 33.5 -> 31.9; LayerNorm
+// 2048x12288 21.2 -> 20.3, 1024x16384 16.3 -> 15.0).  With enough rows to keep the chip full either way the smaller
+// workgroups are ahead, 256 threads / more (GeLU 16384x10240 93 / 97 us, 16384x24576 215 / 218, tanh form 220 / 229;
+// LayerNorm 16384x10240 107.5 / 112), and for LayerNorm, whose parameters take registers too, everywhere on rows of more
+// than 16384 values (4096x24576 68 / 98).  The plain quantizer gains (8192x24576 110 / 103), and so does GeLU with a bias,
+// whose loads go out with the row's for up to four vectors only (16384x24576 252 / 220, 4096x10240 34.4 / 33.3).
+int row_threads(RowOp op, int M, int K, bool bias) {
+    const int nvec = K / 8;
+    const bool gelu = op == kOpGeluErf || op == kOpGeluTanh;
+    if (gelu && !bias && M <= compute_units()) return 0;
+    if (nvec <= 64 * 2 || (M > 512 && !gelu && nvec <= 64 * 4)) return 64;
+    if (nvec <= 256 * 4) return 256;
+    if (op != kOpIdentity && !bias && (M > 2048 || (op == kOpLayerNorm && nvec > 2048))) return 256;
+    return nvec <= 512 * 4 ? 512 : 1024;
+}
+
+// The vectors a thread holds: the fewest of those built that cover the row.  Built is what row_threads can ask for.
 template <int OP>
 static hipError_t launch_rq_op(const void *in, const void *p0, const void *p1, float eps, int M, int K, int8_t *xq,
-                               float *s_tok, void *y_out, int y_dtype, hipStream_t st) {
+                               float *s_tok, void *y_out, int y_dtype, int threads, hipStream_t st) {
+    constexpr bool kGelu = OP == kOpGeluErf || OP == kOpGeluTanh;
     const int nvec = K / 8;
-#define ZQ_RQ(TPR, VPT) return launch_rq<OP, TPR, VPT>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st)
-    // Short rows: one wave per row, four rows per workgroup.  Up to 2048 values where a workgroup per row would be many
-    // rounds of them: no barrier in the three reductions (LayerNorm 2048x2048 5.9 -> 5.1 us, 2048x1280 5.3 -> 4.2,
-    // 8192x2048 16.4 -> 14.0; at 512 rows level, at 5 rows 2.7 -> 2.9; 4096 values are 25 % slower that way).  The
-    // arithmetic of GeLU wants more waves: 2100x1920 5.2 -> 5.6.
-    if (nvec <= 64 * 1) ZQ_RQ(64, 1);
-    if (nvec <= 64 * 2) ZQ_RQ(64, 2);
-    if (M > 512 && (OP == kOpLayerNorm || OP == kOpIdentity)) {
-        if (nvec <= 64 * 3) ZQ_RQ(64, 3);
-        if (nvec <= 64 * 4) ZQ_RQ(64, 4);
+#define ZQ_RQ(TPR, VPT) \
+    if (nvec <= (TPR) * (VPT)) return launch_rq<OP, TPR, VPT>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st)
+    switch (threads) {
+        case 64:
+            ZQ_RQ(64, 1);
+            ZQ_RQ(64, 2);
+            if constexpr (!kGelu) {
+                ZQ_RQ(64, 3);
+                ZQ_RQ(64, 4);
+            }
+            break;
+        case 256:
+            ZQ_RQ(256, 1);
+            ZQ_RQ(256, 2);
+            ZQ_RQ(256, 3);
+            ZQ_RQ(256, 4);
+            if constexpr (OP != kOpIdentity) {
+                ZQ_RQ(256, 6);
+                ZQ_RQ(256, 8);
+                ZQ_RQ(256, 12);
+                ZQ_RQ(256, 16);
+            }
+            break;
+        case 512:
+            ZQ_RQ(512, 3);
+            ZQ_RQ(512, 4);
+            break;
+        case 1024:
+            if constexpr (OP != kOpLayerNorm) {
+                ZQ_RQ(1024, 3);
+                ZQ_RQ(1024, 4);
+            }
+            break;
     }
-    // Longer rows: a workgroup shares one row, with up to four vectors per thread: six to sixteen of 256 threads are too few
-    // waves for the arithmetic of GeLU (300x16384 7.8 -> 6.5 us, 300x24576 10.9 -> 8.4, 2048x24576 33.5 -> 31.9; LayerNorm
-    // 2048x12288 21.2 -> 20.3, 1024x16384 16.3 -> 15.0).  With enough rows to keep the chip full either way the smaller
-    // workgroups are ahead, 256 threads / more (GeLU 16384x10240 93 / 97 us, 16384x24576 215 / 218, tanh form 220 / 229;
-    // LayerNorm 16384x10240 107.5 / 112), and for LayerNorm, whose parameters take registers too, everywhere on rows of more
-    // than 16384 values (4096x24576 68 / 98).  The plain quantizer gains (8192x24576 110 / 103), and so does GeLU with a bias,
-    // whose loads go out with the row's for up to four vectors only (16384x24576 252 / 220, 4096x10240 34.4 / 33.3).
-    if (nvec <= 256 * 1) ZQ_RQ(256, 1);
-    if (nvec <= 256 * 2) ZQ_RQ(256, 2);
-    if (nvec <= 256 * 3) ZQ_RQ(256, 3);
-    if (nvec <= 256 * 4) ZQ_RQ(256, 4);
-    const bool bias = OP != kOpLayerNorm && p0 != nullptr;
-    if (OP != kOpIdentity && !bias && (M > 2048 || (OP == kOpLayerNorm && nvec > 2048))) {
-        if (nvec <= 256 * 6) ZQ_RQ(256, 6);
-        if (nvec <= 256 * 8) ZQ_RQ(256, 8);
-        if (nvec <= 256 * 12) ZQ_RQ(256, 12);
-        if (nvec <= 256 * 16) ZQ_RQ(256, 16);
-    }
-    if (nvec <= 512 * 3) ZQ_RQ(512, 3);
-    if (nvec <= 512 * 4) ZQ_RQ(512, 4);
-    if (nvec <= 1024 * 3) ZQ_RQ(1024, 3);
-    if (nvec <= 1024 * 4) ZQ_RQ(1024, 4);
 #undef ZQ_RQ
     return hipErrorInvalidValue;
 }
@@ -358,17 +385,17 @@ static hipError_t launch_gelu_parts(const void *in, int M, int K, int cus, int8_
 
 hipError_t launch_rowquant(RowOp op, const void *in, const void *p0, const void *p1, float eps, int M, int K,
                            int8_t *xq, float *s_tok, void *y_out, int y_dtype, hipStream_t st) {
-    if ((op == kOpGeluErf || op == kOpGeluTanh) && p0 == nullptr) {
+    const int threads = row_threads(op, M, K, op != kOpLayerNorm && p0 != nullptr);
+    if (threads == 0) {
         const int cus = compute_units();
-        if (M <= cus)
-            return op == kOpGeluErf ? launch_gelu_parts<kOpGeluErf>(in, M, K, cus, xq, s_tok, y_out, y_dtype, st)
-                                    : launch_gelu_parts<kOpGeluTanh>(in, M, K, cus, xq, s_tok, y_out, y_dtype, st);
+        return op == kOpGeluErf ? launch_gelu_parts<kOpGeluErf>(in, M, K, cus, xq, s_tok, y_out, y_dtype, st)
+                                : launch_gelu_parts<kOpGeluTanh>(in, M, K, cus, xq, s_tok, y_out, y_dtype, st);
     }
     switch (op) {
-        case kOpLayerNorm: return launch_rq_op<kOpLayerNorm>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st);
-        case kOpGeluErf: return launch_rq_op<kOpGeluErf>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st);
-        case kOpGeluTanh: return launch_rq_op<kOpGeluTanh>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st);
-        case kOpIdentity: return launch_rq_op<kOpIdentity>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, st);
+        case kOpLayerNorm: return launch_rq_op<kOpLayerNorm>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, threads, st);
+        case kOpGeluErf: return launch_rq_op<kOpGeluErf>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, threads, st);
+        case kOpGeluTanh: return launch_rq_op<kOpGeluTanh>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, threads, st);
+        case kOpIdentity: return launch_rq_op<kOpIdentity>(in, p0, p1, eps, M, K, xq, s_tok, y_out, y_dtype, threads, st);
     }
     return hipErrorInvalidValue;
 }

@@ -206,3 +206,15 @@ def test_small_tiles_against_a_short_k(M, N, K, bits, x_bits, want):
 ])
 def test_small_tiles_of_four_waves(M, N, K, bits, want):
     assert zq.gemm_kernel(M, N, K, bits) == want
+
+
+@pytest.mark.parametrize("op,M,K,bias,want", [
+    ("layernorm", 513, 1040, False, "row64"), ("layernorm", 512, 1040, False, "row256"), ("quantize", 513, 2048, False, "row64"),
+    ("gelu", 513, 1040, False, "row256"), ("gelu", 513, 1024, False, "row64"), ("layernorm", 2, 8208, False, "row512"),
+    ("layernorm", 2, 16400, False, "row256"), ("quantize", 2, 16400, False, "row1024"), ("gelu", 257, 16400, False, "row1024"),
+    ("gelu", 2049, 16400, False, "row256"), ("gelu", 2049, 16400, True, "row1024"), ("gelu", 256, 4096, False, "parts"),
+    ("gelu_tanh", 1, 32768, False, "parts"), ("gelu", 256, 4096, True, "row256"), ("gelu", 257, 4096, False, "row256"),
+])
+def test_row_mapping(op, M, K, bias, want):
+    assert zq.row_kernel(op, M, K, bias) == want
+    assert zq.row_kernel(op, M, 32784, bias) is None and zq.row_kernel(op, 0, K, bias) is None
