@@ -299,7 +299,9 @@ static hipError_t launch_rq(const void *in, const void *p0, const void *p1, floa
 // 2048x12288 21.2 -> 20.3, 1024x16384 16.3 -> 15.0).  With enough rows to keep the chip full either way the smaller
 // workgroups are ahead, 256 threads / more (GeLU 16384x10240 93 / 97 us, 16384x24576 215 / 218, tanh form 220 / 229;
 // LayerNorm 16384x10240 107.5 / 112), and for LayerNorm, whose parameters take registers too, everywhere on rows of more
-// than 16384 values (4096x24576 68 / 98).  The plain quantizer gains (8192x24576 110 / 103), and so does GeLU with a bias,
+// than 16384 values (4096x24576 68 / 98).  Its rows of up to 16384 values fit the chip at once with 256 threads, four workgroups a compute unit,
+// where two of 512 do not: 513 to 1280 rows and, where the fourth vector of a thread is half empty, up to 2048 stay with 256
+// (571x12752 7.1 / 8.1, 900x12608 9.0 / 9.9, 1645x8496 11.2 / 11.8; 1480x16304 17.8 / 15.9).  The plain quantizer gains (8192x24576 110 / 103), and so does GeLU with a bias,
 // whose loads go out with the row's for up to four vectors only (16384x24576 252 / 220, 4096x10240 34.4 / 33.3).
 int row_threads(RowOp op, int M, int K, bool bias) {
     const int nvec = K / 8;
@@ -307,7 +309,8 @@ int row_threads(RowOp op, int M, int K, bool bias) {
     if (gelu && !bias && M <= compute_units()) return 0;
     if (nvec <= 64 * 2 || (M > 512 && !gelu && nvec <= 64 * 4)) return 64;
     if (nvec <= 256 * 4) return 256;
-    if (op != kOpIdentity && !bias && (M > 2048 || (op == kOpLayerNorm && nvec > 2048))) return 256;
+    if (op != kOpIdentity && !bias && M > 2048) return 256;
+    if (op == kOpLayerNorm && (nvec > 512 * 4 || (M > 512 && (M <= 1280 || K <= 11264)))) return 256;
     return nvec <= 512 * 4 ? 512 : 1024;
 }
 

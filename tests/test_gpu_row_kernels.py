@@ -87,7 +87,7 @@ def test_gelu_parts_beside_nan_and_infinity(zq, approx, K):
 # one wave per row with three and four vectors a lane, at the first count of rows; 512 and 1024 threads a row; many long rows on
 # 256 threads (LayerNorm; GeLU without its bias, below)
 @pytest.mark.parametrize("M,K", [(513, 1040), (513, 1536), (515, 1552), (514, 2048), (512, 2048), (2, 8208), (3, 12304),
-                                 (2, 16400), (2, 24592), (2049, 8208), (2051, 12304)])
+                                 (2, 16400), (2, 24592), (2049, 8208), (2051, 12304), (515, 12304), (1282, 12304)])
 def test_row_mappings(zq, orc, M, K):
     print("rows", M, K, flush=True)
     rng = zq_inputs.rng_for(3, 8000 + M + K)

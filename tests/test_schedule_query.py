@@ -212,6 +212,8 @@ def test_small_tiles_of_four_waves(M, N, K, bits, want):
     ("layernorm", 513, 1040, False, "row64"), ("layernorm", 512, 1040, False, "row256"), ("quantize", 513, 2048, False, "row64"),
     ("gelu", 513, 1040, False, "row256"), ("gelu", 513, 1024, False, "row64"), ("layernorm", 2, 8208, False, "row512"),
     ("layernorm", 2, 16400, False, "row256"), ("quantize", 2, 16400, False, "row1024"), ("gelu", 257, 16400, False, "row1024"),
+    ("layernorm", 512, 12752, False, "row512"), ("layernorm", 513, 12752, False, "row256"), ("layernorm", 1280, 16384, False, "row256"),
+    ("layernorm", 1281, 11280, False, "row512"), ("layernorm", 1281, 11264, False, "row256"), ("layernorm", 2048, 16384, False, "row512"),
     ("gelu", 2049, 16400, False, "row256"), ("gelu", 2049, 16400, True, "row1024"), ("gelu", 256, 4096, False, "parts"),
     ("gelu_tanh", 1, 32768, False, "parts"), ("gelu", 256, 4096, True, "row256"), ("gelu", 257, 4096, False, "row256"),
 ])
