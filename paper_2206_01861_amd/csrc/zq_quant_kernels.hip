@@ -296,12 +296,14 @@ static hipError_t launch_rq(const void *in, const void *p0, const void *p1, floa
 //
 // Longer rows: a workgroup shares one row, with up to four vectors per thread: six to sixteen of 256 threads are too few
 // waves for the arithmetic of GeLU (300x16384 7.8 -> 6.5 us, 300x24576 10.9 -> 8.4, 2048x24576 33.5 -> 31.9; LayerNorm
-// 2048x12288 21.2 -> 20.3, 1024x16384 16.3 -> 15.0).  With enough rows to keep the chip full either way the smaller
+// 2048x12288 21.2 -> 20.3).  With enough rows to keep the chip full either way the smaller
 // workgroups are ahead, 256 threads / more (GeLU 16384x10240 93 / 97 us, 16384x24576 215 / 218, tanh form 220 / 229;
 // LayerNorm 16384x10240 107.5 / 112), and for LayerNorm, whose parameters take registers too, everywhere on rows of more
 // than 16384 values (4096x24576 68 / 98).  Its rows of up to 16384 values fit the chip at once with 256 threads, four workgroups a compute unit,
 // where two of 512 do not: 513 to 1280 rows and, where the fourth vector of a thread is half empty, up to 2048 stay with 256
-// (571x12752 7.1 / 8.1, 900x12608 9.0 / 9.9, 1645x8496 11.2 / 11.8; 1480x16304 17.8 / 15.9).  The plain quantizer gains (8192x24576 110 / 103), and so does GeLU with a bias,
+// (571x12752 7.1 / 8.1, 900x12608 9.0 / 9.9, 1645x8496 11.2 / 11.8; 1480x16304 17.8 / 15.9).  The plain quantizer gains (8192x24576 110 / 103) but for
+// 257 to 512 rows of more than 16384 values, which 256 threads take at once (366x32256 6.7 / 7.4, 489x31456 7.8 / 8.9), and many of the
+// longest (3522x26208 44.7 / 49.5), and so does GeLU with a bias,
 // whose loads go out with the row's for up to four vectors only (16384x24576 252 / 220, 4096x10240 34.4 / 33.3).
 int row_threads(RowOp op, int M, int K, bool bias) {
     const int nvec = K / 8;
@@ -310,6 +312,7 @@ int row_threads(RowOp op, int M, int K, bool bias) {
     if (nvec <= 64 * 2 || (M > 512 && !gelu && nvec <= 64 * 4)) return 64;
     if (nvec <= 256 * 4) return 256;
     if (op != kOpIdentity && !bias && M > 2048) return 256;
+    if (op == kOpIdentity && nvec > 512 * 4 && ((M > 256 && M <= 512) || (M > 3072 && K > 24576))) return 256;
     if (op == kOpLayerNorm && (nvec > 512 * 4 || (M > 512 && (M <= 1280 || K <= 11264)))) return 256;
     return nvec <= 512 * 4 ? 512 : 1024;
 }
@@ -339,9 +342,9 @@ static hipError_t launch_rq_op(const void *in, const void *p0, const void *p1, f
             if constexpr (OP != kOpIdentity) {
                 ZQ_RQ(256, 6);
                 ZQ_RQ(256, 8);
-                ZQ_RQ(256, 12);
-                ZQ_RQ(256, 16);
             }
+            ZQ_RQ(256, 12);
+            ZQ_RQ(256, 16);
             break;
         case 512:
             ZQ_RQ(512, 3);

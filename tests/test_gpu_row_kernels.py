@@ -108,3 +108,16 @@ def test_row_mappings(zq, orc, M, K):
     xq_o, s_o = orc.quant_tokenwise(x.astype(np.float32))
     assert_bit_equal(host(s_tok), s_o, "s_tok")
     assert_bit_equal(host(xq), xq_o, "xq")
+
+
+# the plain quantizer on 256 threads a row with twelve and sixteen vectors each
+@pytest.mark.parametrize("M,K", [(257, 16400), (260, 24576), (258, 24592), (257, 32768)])
+def test_long_rows_of_the_quantizer(zq, orc, M, K):
+    print("long rows", M, K, flush=True)
+    assert zq.row_kernel("quantize", M, K) == "row256"
+    x = zq_inputs.activations(zq_inputs.rng_for(3, 8500 + M + K), M, K, outlier_frac=0.01, outlier_scale=15.0, token_spread=True)
+    x[1] = 0
+    xq, s_tok = zq.zq_quantize_tokenwise(dev(x))
+    xq_o, s_o = orc.quant_tokenwise(x.astype(np.float32))
+    assert_bit_equal(host(s_tok), s_o, "s_tok")
+    assert_bit_equal(host(xq), xq_o, "xq")

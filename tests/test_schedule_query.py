@@ -214,6 +214,9 @@ def test_small_tiles_of_four_waves(M, N, K, bits, want):
     ("layernorm", 2, 16400, False, "row256"), ("quantize", 2, 16400, False, "row1024"), ("gelu", 257, 16400, False, "row1024"),
     ("layernorm", 512, 12752, False, "row512"), ("layernorm", 513, 12752, False, "row256"), ("layernorm", 1280, 16384, False, "row256"),
     ("layernorm", 1281, 11280, False, "row512"), ("layernorm", 1281, 11264, False, "row256"), ("layernorm", 2048, 16384, False, "row512"),
+    ("quantize", 256, 32256, False, "row1024"), ("quantize", 257, 16400, False, "row256"), ("quantize", 257, 16384, False, "row512"),
+    ("quantize", 512, 32768, False, "row256"), ("quantize", 513, 32768, False, "row1024"), ("quantize", 3072, 26208, False, "row1024"),
+    ("quantize", 3073, 26208, False, "row256"), ("quantize", 8192, 24576, False, "row1024"),
     ("gelu", 2049, 16400, False, "row256"), ("gelu", 2049, 16400, True, "row1024"), ("gelu", 256, 4096, False, "parts"),
     ("gelu_tanh", 1, 32768, False, "parts"), ("gelu", 256, 4096, True, "row256"), ("gelu", 257, 4096, False, "row256"),
 ])
