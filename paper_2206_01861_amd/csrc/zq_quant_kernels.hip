@@ -289,6 +289,9 @@ static hipError_t launch_rq(const void *in, const void *p0, const void *p1, floa
 
 // Threads of a row, 0: GeLU in parts (gelu_parts_kernel).  bias: GeLU's.
 //
+// GeLU in parts: not rows that are one part of the same threads as here, with the search for the largest input on top (67x2000
+// 2.40 / 2.53, 12x512 2.2 / 2.4); from 528 to 1024 values one part has 256 threads for the one wave here (3 % ahead).
+//
 // Short rows: one wave per row, four rows per workgroup.  Up to 2048 values where a workgroup per row would be many
 // rounds of them: no barrier in the three reductions (LayerNorm 2048x2048 5.9 -> 5.1 us, 2048x1280 5.3 -> 4.2,
 // 8192x2048 16.4 -> 14.0; at 512 rows level, at 5 rows 2.7 -> 2.9; 4096 values are 25 % slower that way).  The
@@ -308,7 +311,8 @@ static hipError_t launch_rq(const void *in, const void *p0, const void *p1, floa
 int row_threads(RowOp op, int M, int K, bool bias) {
     const int nvec = K / 8;
     const bool gelu = op == kOpGeluErf || op == kOpGeluTanh;
-    if (gelu && !bias && M <= compute_units()) return 0;
+    const bool one_part = nvec <= 64 || (nvec > 64 * 2 && nvec <= 256);
+    if (gelu && !bias && !one_part && M <= compute_units()) return 0;
     if (nvec <= 64 * 2 || (M > 512 && !gelu && nvec <= 64 * 4)) return 64;
     if (nvec <= 256 * 4) return 256;
     if (op != kOpIdentity && !bias && M > 2048) return 256;

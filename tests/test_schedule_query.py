@@ -218,7 +218,9 @@ def test_small_tiles_of_four_waves(M, N, K, bits, want):
     ("quantize", 512, 32768, False, "row256"), ("quantize", 513, 32768, False, "row1024"), ("quantize", 3072, 26208, False, "row1024"),
     ("quantize", 3073, 26208, False, "row256"), ("quantize", 8192, 24576, False, "row1024"),
     ("gelu", 2049, 16400, False, "row256"), ("gelu", 2049, 16400, True, "row1024"), ("gelu", 256, 4096, False, "parts"),
-    ("gelu_tanh", 1, 32768, False, "parts"), ("gelu", 256, 4096, True, "row256"), ("gelu", 257, 4096, False, "row256"),
+    ("gelu_tanh", 1, 32768, False, "parts"), ("gelu", 256, 4096, True, "row256"), ("gelu", 67, 2000, False, "row256"),
+    ("gelu", 67, 2048, False, "row256"), ("gelu", 67, 2064, False, "parts"), ("gelu", 67, 1024, False, "parts"), ("gelu", 67, 528, False, "parts"),
+    ("gelu", 67, 512, False, "row64"), ("gelu_tanh", 67, 1040, False, "row256"), ("gelu", 257, 4096, False, "row256"),
 ])
 def test_row_mapping(op, M, K, bias, want):
     assert zq.row_kernel(op, M, K, bias) == want
