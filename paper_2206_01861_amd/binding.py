@@ -7,6 +7,7 @@ enqueued on torch's current stream.
 """
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -44,8 +45,8 @@ def lib():
     global _lib, _host
     if _lib is not None:
         return _lib
-    if not (os.path.exists(_LIB_PATH) and os.path.exists(_HOST_PATH)):
-        raise ImportError("libzq.so or _zq_host.so is not built; run `python -m paper_2206_01861_amd.build` "
+    if not os.path.exists(_LIB_PATH):
+        raise ImportError("libzq.so is not built; run `python -m paper_2206_01861_amd.build` "
                           "(there is no fallback implementation)")
     L = ctypes.CDLL(_LIB_PATH)
     vp, ci, cf, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_float, ctypes.c_size_t
@@ -118,12 +119,24 @@ def lib():
     L.zq_probe_mfma_i8.argtypes = [vp, ci, ci, vp, vp]
     L.zq_probe_mfma_i8_tile_traffic.restype = ci
     L.zq_probe_mfma_i8_tile_traffic.argtypes = [vp, sz, ci, ci, vp, vp]
-    from . import _zq_host
-    _zq_host.init(_check, *(ctypes.cast(f, vp).value for f in (
+    _lib, _host = L, _load_host(L)
+    return L
+
+
+def _load_host(L):
+    """_zq_host, or None with a warning where it is not there: every call then goes through ctypes, to the same library."""
+    try:
+        if not os.path.exists(_HOST_PATH):
+            raise ImportError("not built")
+        from . import _zq_host
+    except ImportError as e:
+        warnings.warn("_zq_host.so: %s; calls go through ctypes, some 5 to 10 us of host time more each "
+                      "(python -m paper_2206_01861_amd.build)" % e, RuntimeWarning, stacklevel=3)
+        return None
+    _zq_host.init(_check, *(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.zq_layernorm_quant_tokenwise, L.zq_gelu_quant_tokenwise, L.zq_quantize_tokenwise, L.zq_gemm_i8_dequant,
         L.zq_gemm_w4a8_dequant, L.zq_gemm_gelu_quant_tokenwise, L.zq_gemm_w8a16_dequant, L.zq_quantize_weight_groupwise)))
-    _lib, _host = L, _zq_host
-    return L
+    return _zq_host
 
 
 def _check(code):
