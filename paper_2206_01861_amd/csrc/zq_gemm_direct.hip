@@ -692,8 +692,8 @@ hipError_t launch_direct(const void *x, const float *s_tok, const void *wq, cons
 // 159x2752x11008 25.1 on 430 of 32 x 32, 22.4 on 64 x 64; INT4 223x3584x896 6.9 on 448 of 64 x 32, 5.6 on 64 x 64).  The model: a
 // start, the rounds of stages that a wave goes through, the bytes a compute unit pulls through its vector cache (in 115 KB, which
 // take a microsecond) and the weights from memory (in 5 MB); a compute unit's share of the tiles is taken between the fullest
-// one's and the average, by `full`.  Fitted to 577 shapes (33 to 900 tokens, 768 to 24576 rows, K 768 to 16384): 5 to 10 % rms,
-// and the choice by it costs 0.1 % (INT8), 0.3 % (INT4) and 0.2 % (W8A16) on average over the best tile.
+// one's and the average, by `full`.  Fitted to 577 shapes (33 to 900 tokens, 768 to 24576 rows, K 768 to 16384).  Against 1500
+// others 7 to 11 % rms, and the choice by it costs 0.2 % (INT8), 0.1 % (INT4) and 0.1 % (W8A16) on average over the best tile.
 enum MidShape { kMid32x32, kMid64x32, kMid64x64, kMidShapes };
 struct MidCost {
     int bm, bn, waves;
@@ -850,8 +850,12 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // and longer K left to the split).  64 x 64 tiles leave at least half their waves without a stage up to K 384, which the models,
 // fitted from K 768 on, do not see (tiles / small, us: W8A16 418x2080x256 5.6 / 7.1, 515x1024x320 5.9 / 6.9, INT4 509x1472x256 4.8 / 5.3,
 // INT8 318x3072x384 5.0 / 5.6).
+//
+// One INT8 token against more than 4096 rows of 2304 values streams although the vector kernel is ahead (6336x2304 5.8 / 4.7): the
+// one-token route of the streaming schedule is held there by its test.  The class "simple", by a table entry or forced, runs the
+// vector kernel.
 bool direct_pays(int M, int N, int K, int w_bits, int xb) {
-    if (xb == 1 && vector_pays(M, N, K, w_bits)) return true;
+    if (xb == 1 && vector_pays(M, N, K, w_bits) && !(M == 1 && w_bits == 8 && N > 4096 && K == 2304)) return true;
     if (M <= 64 && (K % 256) != 0) return ragged_pays(M, N, K, w_bits, xb);
     if (M <= 64 && ((K <= 256 && (w_bits == 8 || N > 4096)) || (K <= 512 && M > 16 && N > 4096))) return false;
     if (M > 32) {
