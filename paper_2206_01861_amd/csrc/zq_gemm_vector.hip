@@ -186,8 +186,7 @@ hipError_t launch_vector(const GemmArgs &a, hipStream_t st) {
 
 }  // namespace
 
-// One token: everywhere but where nine pieces meet more than 4096 rows, which streaming keeps although this kernel is ahead
-// (6336x2304 5.8 / 4.7): the one-token route of the streaming schedule is held there by its test.  More tokens cost a 16-byte
+// One token: everywhere (the route of a call leaves nine pieces against more than 4096 rows to streaming, see direct_pays).  More tokens cost a 16-byte
 // activation load each where the weights cost two, so the line is drawn where the kernels with matrix cores pay more for
 // something else, few rows against a long K above all.  us, before / this kernel, over 110 random shapes:
 //   2 tokens, INT8   1792x7168 6.5 / 4.7, 5664x1888 4.8 / 4.1, 8832x2944 9.0 / 7.6, 4736x18944 20.2 / 19.9; beyond: 2560x9216
@@ -203,7 +202,7 @@ hipError_t launch_vector(const GemmArgs &a, hipStream_t st) {
 bool vector_pays(int M, int N, int K, int w_bits) {
     if (w_bits == 4 && M == 1 && N > 16384 && K <= 1024) return false;
     if (w_bits == 8 && K <= kPiece && N > (M == 1 ? 28672 : 20480)) return false;
-    if (M == 1) return !(w_bits == 8 && N > 4096 && K > 8 * kPiece && K <= 9 * kPiece && K % 256 == 0);
+    if (M == 1) return true;
     if (M == 2) {
         if (w_bits == 8) return !(N > 2048 && N <= 3072 && K > 8192) && !(K % 4096 == 0 && N > 8192 && N <= 12288);
         return N <= 2048 || (N <= 8192 && K > 1024 && K <= 4096);

@@ -225,3 +225,19 @@ def test_small_tiles_of_four_waves(M, N, K, bits, want):
 def test_row_mapping(op, M, K, bias, want):
     assert zq.row_kernel(op, M, K, bias) == want
     assert zq.row_kernel(op, M, 32784, bias) is None and zq.row_kernel(op, 0, K, bias) is None
+
+
+def test_vector_kernel_by_table_where_the_route_streams():
+    M, N, K = 1, 6336, 2304
+    assert zq.gemm_kernel(M, N, K) == "stream"
+    zq.tune_set(M, M, N, K, 8, 0)                                # the class "simple"
+    try:
+        assert zq.gemm_schedule(M, N, K) == "direct" and zq.gemm_kernel(M, N, K) == "vector"
+    finally:
+        zq.tune_clear()
+    before = zq.force_gemm_variant(0)
+    try:
+        assert zq.gemm_kernel(M, N, K) == "vector"
+    finally:
+        zq.force_gemm_variant(before)
+    assert zq.gemm_kernel(M, 4096, K) == "vector" and zq.gemm_kernel(M, N, K + 16) == "vector"
