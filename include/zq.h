@@ -280,8 +280,8 @@ zq_status zq_gemm_gelu_quant_tokenwise(const int8_t *xq, const float *s_tok, con
  *             faster (fp32 partials; the result does not depend on the order in which workgroups finish)
  * K % 16 == 0, K <= ZQ_MAX_K, N % groups == 0, (N/groups) % 16 == 0 (the streaming
  * schedule, up to 128 tokens, needs K % 256 == 0, and 65 to 128 tokens run as two launches of it over row
- * halves unless tiles are the faster choice for the shape: with a K split where that wants three splits or more
- * and the workspace holds them, else without one; small shapes run the direct kernels, which take any K).  The codes are converted to
+ * halves unless tiles are the faster choice for the shape, with a K split if the workspace holds one and without
+ * where they are ahead all the same; small shapes run the direct kernels, which take any K).  The codes are converted to
  * FP16 exactly; the sum is accumulated in fp32 on the FP16 matrix cores, so unlike the INT8 calls
  * the result is reproducible but not bit-defined by the inputs alone (tolerance in the tests).
  * Errors: ZQ_ERR_NULL, ZQ_ERR_SHAPE, ZQ_ERR_ALIGN, ZQ_ERR_HIP.

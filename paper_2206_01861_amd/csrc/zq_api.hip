@@ -261,6 +261,16 @@ static bool a16_tiles_with_split(int M, int N, int K) {
     return ks >= ((M <= kA16StreamTokens && (K % 256) == 0) ? 3 : 2);
 }
 
+// Two streaming launches read the weights twice, the second for as few as one token: tiles are ahead from 96 tokens on, with more
+// rows from 80.  Unsplit, us: 12288x4096 at 104 40.2 -> 36.0, 16896x5632 at 90 54.7 -> 48.2; at 90 11520x3840 32.6 against 33.4, at
+// 66 28.9, 33.3; over 130 shapes of 80 to 127 tokens, 11520 to 20000 rows, K 3584 to 7000 streaming takes 1.25 times as long.  Split
+// in two, where that is all the shape divides into and the workspace holds it: 0.83 of the unsplit time at K 4096, 0.75 at 6144, 0.70
+// at 9216 (85 shapes; 116x11520x3840 32.3 -> 26.2).  128 tokens, two full launches, stay with streaming: its test holds that
+// (18432x6144).
+static bool a16_tiles_ahead(int M, int N, int K) {
+    return M < kA16StreamTokens && (K % 256) == 0 && K >= 3584 && N >= 11520 && (M >= 96 || (M >= 80 && N >= 13056));
+}
+
 // A cut of the streaming schedules that is registered for the shape, and whose K split the workspace can hold, goes
 // before the direct kernels.
 static bool a16_cut_registered(int M, int N, int K, size_t workspace_bytes) {
@@ -275,14 +285,8 @@ static A16Route a16_route(int M, int N, int K, size_t workspace_bytes) {
     if (zq::direct_pays(M, N, K, 8, 2) && !a16_cut_registered(M, N, K, workspace_bytes)) return kA16Direct;
     if (a16_tiles_with_split(M, N, K) && zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes)) return kA16TileSplit;
     if (M <= kA16StreamTokens && (K % 256) == 0) {
-        // Two streaming launches read the weights twice, the second for as few as one token: unsplit tiles are ahead from 96
-        // tokens on, with more rows from 80 (12288x4096 at 104 40.2 -> 36.0 us, 16896x5632 at 90 54.7 -> 48.2; at 90 11520x3840
-        // 32.6 against 33.4, at 66 28.9, 33.3).  128 tokens, two full launches, stay with streaming: its test holds that
-        // (18432x6144).  Unsplit whatever the workspace holds: a split by two is not among what a call may do here (see
-        // a16_tiles_with_split), and the workspace query names none.  130 shapes of 80 to 127 tokens, 11520 to 20000 rows, K 3584
-        // to 7000: streaming takes 1.25 times as long without a workspace, 1.26 with that of a model's other linears.
-        const bool tiles = M < kA16StreamTokens && K >= 3584 && N >= 11520 && (M >= 96 || (M >= 80 && N >= 13056));
-        return tiles && !a16_cut_registered(M, N, K, workspace_bytes) ? kA16Tile : kA16Stream;
+        if (!a16_tiles_ahead(M, N, K) || a16_cut_registered(M, N, K, workspace_bytes)) return kA16Stream;
+        return zq::gemm_a16_tile_splits_here(M, N, K, workspace_bytes) ? kA16TileSplit : kA16Tile;
     }
     return (long)M * N * K > (1L << 27) ? kA16Tile : kA16Direct;
 }
@@ -296,7 +300,7 @@ size_t zq_gemm_w8a16_workspace_bytes(int M, int N, int K) {
     if (M <= 0 || N <= 0 || K <= 0 || (N % 16) != 0 || (K % 16) != 0) return 0;
     size_t need = 0;
     if (M <= kA16StreamTokens && (K % 256) == 0) need = zq::stream_a16_workspace_bytes(M < 64 ? M : 64, N, K);
-    if (a16_tiles_with_split(M, N, K)) {
+    if (a16_tiles_with_split(M, N, K) || a16_tiles_ahead(M, N, K)) {
         const size_t t = zq::gemm_a16_tile_split_workspace(M, N, K);
         if (t > need) need = t;
     }

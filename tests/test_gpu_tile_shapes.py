@@ -144,17 +144,21 @@ def test_split_class_that_runs_unsplit(zq, orc, M, N, K, g):
         zq.tune_clear()
 
 
-def _fp16_with_room_to_split(zq, M, N, K, g):
-    """A workspace that holds partial sums (other linears need it) changes neither the schedule nor a bit of the result."""
+def _fp16_with_room_to_split(zq, orc, M, N, K, g):
+    """With the workspace that the query names the tiles split K; the same bits twice, and with more of it."""
+    own = zq.gemm_w8a16_workspace_bytes(M, N, K)
+    assert zq.gemm_schedule(M, N, K, 8, own, x_bits=16) == "tile128x128_splitk"
     rng = zq_inputs.rng_for(9, 6650 + M + N + K)
-    args = (dev(zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=15.0)),
-            dev(zq_inputs.random_codes(rng, (N, K))), dev(zq_inputs.random_scales(rng, g, 1e-4, 1e-2)), dev(zq_inputs.bias(rng, N)))
-    ws = zq.new_workspace(64 << 20)
-    assert zq.gemm_schedule(M, N, K, 8, ws.numel(), x_bits=16) == zq.gemm_schedule(M, N, K, 8, 0, x_bits=16)
-    want = zq.zq_gemm_w8a16_dequant(*args)
-    got = zq.zq_gemm_w8a16_dequant(*args, workspace=ws)
+    x = zq_inputs.activations(rng, M, K, outlier_frac=0.01, outlier_scale=15.0)
+    codes = zq_inputs.random_codes(rng, (N, K))
+    s_w, bias = zq_inputs.random_scales(rng, g, 1e-4, 1e-2), zq_inputs.bias(rng, N)
+    args = (dev(x), dev(codes), dev(s_w), dev(bias))
+    out = zq.zq_gemm_w8a16_dequant(*args, workspace=zq.new_workspace(own))
+    again = [zq.zq_gemm_w8a16_dequant(*args, workspace=zq.new_workspace(n)) for n in (own, 64 << 20)]
     torch.cuda.synchronize()
-    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    _check_a16(orc, host(out), x, codes, s_w, bias, "tile a16 split %dx%dx%d" % (M, N, K))
+    for t in again:
+        assert torch.equal(t.view(torch.int16), out.view(torch.int16))
 
 
 # (bits, M, N, K, groups, the nearest M, N, K that streams)
@@ -170,7 +174,7 @@ def test_streaming_class_that_runs_tiles(zq, orc, bits, M, N, K, g, beyond):
     assert zq.gemm_schedule(*beyond, w_bits, 0, x_bits=x_bits).startswith("stream")
     if bits == 16:
         _fp16(zq, orc, M, N, K, g, 6600)
-        _fp16_with_room_to_split(zq, M, N, K, g)
+        _fp16_with_room_to_split(zq, orc, M, N, K, g)
         return
     assert zq.gemm_variant_name(zq.gemm_choose_variant(M, N, K, bits, 0)) == "skinny"
     _integers(zq, orc, -1, bits, M, N, K, g, 6600)

@@ -108,13 +108,26 @@ def test_lines_between_the_direct_kernels_and_the_others(M, N, K, bits, x_bits, 
     assert name.startswith(want), name
 
 
-# FP16 activations, 65 to 128 tokens, tiles in place of two streaming launches: no K split, however large the workspace (one that
-# other linears share)
-@pytest.mark.parametrize("M,N,K", [(104, 12288, 4096), (80, 13056, 3584), (90, 16384, 4096), (100, 16384, 8192)])
-def test_fp16_tiles_ahead_of_streaming_do_not_split(M, N, K):
+# FP16 activations, 65 to 128 tokens, tiles in place of two streaming launches: split in two where the workspace holds what its query
+# names, one that other linears share too; unsplit with less, and where there are more than 128 tiles
+@pytest.mark.parametrize("M,N,K,splits", [(104, 12288, 4096, True), (80, 13056, 3584, True), (90, 16384, 4096, True), (116, 11520, 3840, True),
+                                          (100, 16400, 8192, False)])
+def test_fp16_tiles_ahead_of_streaming(M, N, K, splits):
+    tiles = {"tile128x64", "tile128x128", "tile192x128", "tile256x128"}
     own = zq.gemm_w8a16_workspace_bytes(M, N, K)
-    names = {zq.gemm_schedule(M, N, K, 8, ws, x_bits=16) for ws in (0, own, 64 << 20, 1 << 30)}
-    assert len(names) == 1 and names < {"tile128x64", "tile128x128", "tile192x128", "tile256x128"}, names
+    name = lambda ws: zq.gemm_schedule(M, N, K, 8, ws, x_bits=16)
+    assert name(0) in tiles
+    if splits:
+        assert own == zq.WORKSPACE_FIXED_BYTES + 2 * M * N * 4
+        assert name(own - 1) in tiles and name(own) == name(1 << 30) == "tile128x128_splitk"
+    else:
+        assert name(own) == name(1 << 30) == name(0)
+    zq.tune_set(M, M, N, K, 8, 3, 192, 1)                        # a registered cut goes first; it is the launches' of 64 tokens
+    zq.tune_set(64, 64, N, K, 8, 3, 192, 1)
+    try:
+        assert name(0) == name(1 << 30) == "stream_halves"
+    finally:
+        zq.tune_clear()
 
 
 def test_fp16_call_splits_k_only_where_the_workspace_query_says():
