@@ -849,7 +849,10 @@ bool ragged_pays(int M, int N, int K, int w_bits, int xb) {
 // tiles; 107x2304x6144 15.5 split / 14.2; W8A16 78x8064x2688 17.5 split / 15.6, 149x1280x5120 1.35 times as fast, 245x400x5728
 // and longer K left to the split).  64 x 64 tiles leave at least half their waves without a stage up to K 384, which the models,
 // fitted from K 768 on, do not see (tiles / small, us: W8A16 418x2080x256 5.6 / 7.1, 515x1024x320 5.9 / 6.9, INT4 509x1472x256 4.8 / 5.3,
-// INT8 318x3072x384 5.0 / 5.6).
+// INT8 318x3072x384 5.0 / 5.6).  Above 900 tokens up to 96
+// tiles of 128 x 64 leave most of the chip idle against a K of 1536 and more, for which their model is too low (INT8, LDS tiles / small:
+// 1762x320x4384 18.4 / 13.4, 1630x368x2048 9.0 / 8.0; 37 shapes 1.08, 90 with more tiles or a shorter K 0.98); 64 x 32 tiles leave a K
+// beyond theirs to the split (1821x256x6912 17.3 split / 23.1).
 //
 // One INT8 token against more than 4096 rows of 2304 values streams although the vector kernel is ahead (6336x2304 5.8 / 4.7): the
 // one-token route of the streaming schedule is held there by its test.  The class "simple", by a table entry or forced, runs the
@@ -876,8 +879,10 @@ bool direct_pays(int M, int N, int K, int w_bits, int xb) {
         const int no_split = xb == 2 ? 4096 : shape == kMid64x64 ? 5120 : shape == kMid64x32 ? 6656 : 8192;
         if (K <= no_split) {
             const bool streams = int8 && M <= 128 && K >= 2048 && K < 2560;
-            return us < (streams ? 1.1 : int8 ? (M <= 128 ? 0.88 : 0.85) : 0.95) * tile_us;
+            const bool few_tiles = M > 900 && K >= 1536 && (long)((M + 127) / 128) * ((N + 63) / 64) <= 96;
+            return us < (streams ? 1.1 : int8 ? (M <= 128 ? 0.88 : few_tiles ? 1.0 : 0.85) : 0.95) * tile_us;
         }
+        if (int8 && M > 900 && shape == kMid64x32) return false;
         const double split_us = tile_split_time(M, N, K, xb);
         if (split_us < tile_us) tile_us = split_us;
         return (int8 || K <= 5120) && us < 0.88 * tile_us;

@@ -254,3 +254,13 @@ def test_vector_kernel_by_table_where_the_route_streams():
     finally:
         zq.force_gemm_variant(before)
     assert zq.gemm_kernel(M, 4096, K) == "vector" and zq.gemm_kernel(M, N, K + 16) == "vector"
+
+
+@pytest.mark.parametrize("M,N,K,ws,want", [
+    # INT8, more than 900 tokens against few rows
+    (1762, 320, 4384, False, "small64x64"), (1630, 368, 2048, True, "small64x64"), (3545, 192, 2048, True, "small64x64"),
+    (3694, 256, 4096, False, "tile128x64"), (999, 1024, 576, False, "tile128x64"), (1803, 512, 1152, False, "tile128x64"),
+    (1821, 256, 6912, True, "tile128x128_splitk"), (2595, 176, 7936, True, "tile128x128_splitk"), (842, 1024, 4096, False, "tile128x64"),
+])
+def test_many_tokens_against_few_rows(M, N, K, ws, want):
+    assert zq.gemm_schedule(M, N, K, 8, zq.gemm_workspace_bytes(M, N, K) if ws else 0) == want
