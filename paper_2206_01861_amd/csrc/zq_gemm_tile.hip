@@ -6,13 +6,26 @@
 // bytes of K both operand tiles go from global memory straight into LDS with
 // 16-byte direct loads (no register staging) through a ring of NSTAGE stages;
 // rows are BK bytes with their 16-byte chunks XOR-swizzled so that the
-// ds_read_b128 of a matrix-core fragment (32 rows, one chunk) is free of bank
+// ds_read_b128 of a matrix-core fragment (16 rows, four chunks) is free of bank
 // conflicts.  Each wave computes (BN/WAVES_N) x (BM/WAVES_M) with
-// v_mfma_i32_32x32x32_i8, the weight fragment as the first operand, so every
-// group of four accumulator registers runs along the output columns.  Two
-// fragment sets alternate so the LDS reads of k step s+1 are in flight under
-// the MFMAs of step s; with two waves per SIMD the barrier and epilogue of one
-// wave overlap the matrix-core work of the other.
+// v_mfma_i32_16x16x64_i8, the weight fragment as the first operand, so the
+// four accumulator registers run along the output columns.
+//
+// Why 16x16x64 and not 32x32x32: large products run at the chip's power limit,
+// and the instruction that adds 64 products before it touches an accumulator
+// draws less.  On register operands, 256 workgroups of eight waves with wave
+// tiles of 128 x 64: 4.04 against 3.38 POP/s on uniformly random bytes, 4.13
+// against 3.53 on normal codes (FP16, 16x16x32 against 32x32x16: 1.98 / 1.72);
+// with the fragments read from LDS 3.26 / 2.88, 3.29 / 2.95 (1.62 / 1.46).
+//
+// A k step is a fixed sequence of small groups of matrix-core instructions
+// with the LDS reads of the next step, the refill loads and the conversions
+// dealt out between them (step, step_paired); left to the compiler these
+// bunched up behind the barrier, where both waves of a SIMD wait for them.
+// Both together, us before / after: INT8 16384x24576x6144 2045 / 1870,
+// 4096x12288x4096 180 / 166, 2048x8192x2048 37.5 / 35.3, 333x12288x4096
+// 32.2 / 29.0, INT4 333x16384x4096 34.1 / 31.1, W8A16 16384x18432x6144
+// 3173 / 2935, 4096x4096x4096 125 / 116.
 //
 // The epilogue scales the INT32 accumulators by s_tok[row] * s_w[group], adds
 // the bias and rounds to FP16 (scales and bias were staged in LDS under the
@@ -122,12 +135,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     constexpr int X_STAGE = BM * BK;
     constexpr int STAGE = Cfg::kStage;
     constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-    constexpr int FM = WM / 32, FN = WN / 32;
-    constexpr int KSTEPS = BK / 32;
+    constexpr int FM = WM / 16, FN = WN / 16;
+    constexpr int KSTEPS = BK / 64;
     constexpr int KS_T = KSTEPS / KT;                // k steps of a stage that one team multiplies
     static_assert(KT == 1 || KT == 2, "one or two K teams");
     static_assert(KT == 1 || (QOUT == 0 && KSPLIT == 0), "K teams go with the plain epilogue");
-    static_assert(KT == 1 || FM % KT == 0, "each team finishes a whole number of 32-row blocks");
+    static_assert(WM % (32 * KT) == 0, "each wave finishes a whole number of 32-row blocks");
     constexpr int CPR = BK / 16;                     // 16-byte chunks per row
     constexpr int RPU = 64 / CPR;                    // rows per 1 KB load unit
     constexpr int XU = BM / RPU;                     // load units in the activation tile
@@ -152,7 +165,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     constexpr int XB = A16 ? 2 : 1;                  // bytes per activation value
     static_assert(!A16 || WBITS == 8, "FP16 activations go with INT8 weights");
     static_assert(XT != 3 || WBITS == 4, "packed weight rows in LDS are the INT4 ones");
-    static_assert(!PAIRED || (BK == 128 && KT == 1), "the paired loop is written for four k steps per stage");
+    static_assert(!PAIRED || (BK == 128 && KT == 1), "the paired loop is written for two k steps per stage");
     static_assert(QOUT == 0 || !A16, "the output quantization is built for the INT8 product");
     static_assert(QOUT == 0 || BN == 64 || BN == 128 || BN == 256, "the code tile's swizzle wants a power of two of chunks");
     static_assert(KSPLIT == 0 || QOUT == 0, "a K split leaves the epilogue to the second kernel");
@@ -161,7 +174,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // weight loads per wave per stage; where the units do not split evenly some waves load a unit a
     // second time (the same bytes to the same place), so that every wave issues the same number of loads
     constexpr int LWD = STAGED_W ? 0 : (WU + NW - 1) / NW;
-    using AccT = typename std::conditional<A16, float32x16, int32x16>::type;
+    using AccT = typename std::conditional<A16, float32x4, int32x4>::type;
     constexpr int LPS = LX + LWD;                    // direct loads per wave per stage
     constexpr int TPR4 = BK / 32;                    // INT4: threads per row (16 packed bytes each)
     constexpr int W4_ROWS = NT / TPR4;               // rows per pass
@@ -208,59 +221,39 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     const __amdgpu_buffer_rsrc_t rs_x =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(xq), 0, (int)((size_t)M * xrow_bytes), kRsrcFlags);
 
-    // ---- per-lane source offsets of this wave's direct-load units ---------
-    // Wave w takes units w, w+NW, ...; units below XU are activation rows, the
-    // rest weight rows.  Rows past the matrix edge are clamped to the last row:
-    // loaded, multiplied, never stored.
-    int voff[LPS];
+    // ---- source offsets of this wave's direct-load units -------------------
+    // Wave w takes units w, w+NW, ...; units below XU are activation rows, the rest weight rows.  The units of a wave
+    // lie a multiple of 16 rows apart, so a lane reads the same swizzled chunk of its row in all of them: one register
+    // per operand holds (first row of the tile + lane's row, chunk), and a unit adds its own rows, a scalar.  Rows past
+    // the matrix end lie past the end of the buffer, which the hardware answers with zeros: multiplied, never stored.
     // weight unit of this wave's load i (wave-uniform; a subtraction, not a remainder, which would go
     // through the vector unit and make the LDS address of the load look divergent)
     static_assert(LWD * NW <= 2 * WU || STAGED_W, "a unit is loaded at most twice");
+    static_assert((NW * RPU) % 16 == 0 && (STAGED_W || ((NW * RPUW) % 16 == 0 && BN % 16 == 0)), "one chunk for all units of a wave");
     auto w_unit = [&](int i) {
         const int u = wave + NW * (i - LX);
         return __builtin_amdgcn_readfirstlane(u >= WU ? u - WU : u);
     };
-#pragma unroll
-    for (int i = 0; i < LPS; ++i) {
-        if (i < LX) {
-            const int row = (wave + NW * i) * RPU + lane / CPR;
-            int grow = m0 + row;
-            if (grow > M - 1) grow = M - 1;
-            voff[i] = grow * xrow_bytes + (((lane % CPR) ^ swz<BK>(row)) * 16);
-        } else {
-            const int row = w_unit(i) * RPUW + lane / CPRW;
-            int grow = n0 + row;
-            if (grow > N - 1) grow = N - 1;
-            voff[i] = grow * wrow_bytes + (((lane % CPRW) ^ swz<BKW>(row)) * 16);
-        }
-    }
+    const int xchunk = (lane % CPR) ^ swz<BK>(wave * RPU + lane / CPR);
+    const int wchunk = (lane % CPRW) ^ swz<BKW>(wave * RPUW + lane / CPRW);
+    // (unsigned: rows past the end of a matrix of nearly 2 GiB lie beyond 2^31)
+    const unsigned voff_x = (unsigned)(m0 + lane / CPR) * (unsigned)xrow_bytes + xchunk * 16;
+    const unsigned voff_w = (unsigned)(n0 + lane / CPRW) * (unsigned)wrow_bytes + wchunk * 16;
     // K need not be a multiple of the stage depth: in the last stage the chunks past the end of a
     // row are fetched from an offset beyond the buffer, which the hardware answers with zeros (a
     // plain offset would run into the next row); zero operands add nothing to the product.
-    constexpr int kNowhere = 0x7ffffff0;
+    constexpr unsigned kNowhere = 0x7ffffff0u;
     const int tail_bytes = xrow_bytes % BK;           // valid bytes of the last stage row, 0 = full
     const int tail_bytes_w = tail_bytes / (PAIRED ? 2 : XB);   // the same values of K in a weight row
-    int voff_tail[LPS];
-#pragma unroll
-    for (int i = 0; i < LPS; ++i) {
-        if (i < LX) {
-            const int row = (wave + NW * i) * RPU + lane / CPR;
-            const int chunk = (lane % CPR) ^ swz<BK>(row);
-            voff_tail[i] = (tail_bytes == 0 || chunk * 16 < tail_bytes) ? voff[i] : kNowhere;
-        } else {
-            const int row = w_unit(i) * RPUW + lane / CPRW;
-            const int chunk = (lane % CPRW) ^ swz<BKW>(row);
-            voff_tail[i] = (tail_bytes == 0 || chunk * 16 < tail_bytes_w) ? voff[i] : kNowhere;
-        }
-    }
+    const unsigned voff_x_tail = (tail_bytes == 0 || xchunk * 16 < tail_bytes) ? voff_x : kNowhere;
+    const unsigned voff_w_tail = (tail_bytes == 0 || wchunk * 16 < tail_bytes_w) ? voff_w : kNowhere;
     // INT4 weights: thread -> (row = pass*W4_ROWS + tid/TPR4, 16 packed bytes = 32 codes = chunks 2q, 2q+1)
-    int w4_voff[W4_PASSES];
+    unsigned w4_voff[W4_PASSES];
     if (STAGED_W) {
 #pragma unroll
         for (int p = 0; p < W4_PASSES; ++p) {
-            int grow = n0 + p * W4_ROWS + (int)threadIdx.x / TPR4;
-            if (grow > N - 1) grow = N - 1;
-            w4_voff[p] = grow * wrow_bytes + ((int)threadIdx.x % TPR4) * 16;
+            const unsigned grow = n0 + p * W4_ROWS + (int)threadIdx.x / TPR4;
+            w4_voff[p] = grow * (unsigned)wrow_bytes + ((int)threadIdx.x % TPR4) * 16;
         }
     }
 
@@ -280,30 +273,38 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // offsets or still branches around the loads varies between instantiations; forcing the
     // selection with masks it cannot see through measured level on INT8 and 2-3 % slower on INT4
     // weights and FP16 activations, so the expressions are left as they read best.)
-    auto issue_direct = [&](int kt, int slot, bool beyond) {
-        uint8_t *base = smem + slot * STAGE;
+    struct Refill {
+        uint8_t *base;
+        int so_x, so_w;
+        unsigned vx, vw;
+    };
+    auto refill_of = [&](int kt, int slot, bool beyond) __attribute__((always_inline)) {
         const bool last = kt == nkt - 1;
         // the stage's byte offset inside a row is the same for every lane: said explicitly, so that it is
         // never taken for a per-lane value (which would wrap each load in a loop over its distinct values)
-        const int so_x = __builtin_amdgcn_readfirstlane(beyond ? 0 : kt * BK);
-        const int so_w = __builtin_amdgcn_readfirstlane(beyond ? 0 : kt * BKW);
+        return Refill{smem + slot * STAGE, __builtin_amdgcn_readfirstlane(beyond ? 0 : kt * BK),
+                      __builtin_amdgcn_readfirstlane(beyond ? 0 : kt * BKW),
+                      beyond ? kNowhere : (last ? voff_x_tail : voff_x), beyond ? kNowhere : (last ? voff_w_tail : voff_w)};
+    };
+    auto issue_one = [&](const Refill &r, int i) __attribute__((always_inline)) {
+        if (i < LX)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (lds_void *)(r.base + (wave + NW * i) * 1024), 16,
+                                                     (int)(r.vx + (unsigned)((wave + NW * i) * RPU) * (unsigned)xrow_bytes), r.so_x, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (lds_void *)(r.base + X_STAGE + w_unit(i) * 1024), 16,
+                                                     (int)(r.vw + (unsigned)(w_unit(i) * RPUW) * (unsigned)wrow_bytes), r.so_w, 0, 0);
+    };
+    auto issue_direct = [&](int kt, int slot, bool beyond) __attribute__((always_inline)) {
+        const Refill r = refill_of(kt, slot, beyond);
 #pragma unroll
-        for (int i = 0; i < LPS; ++i) {
-            const int vo = beyond ? kNowhere : (last ? voff_tail[i] : voff[i]);
-            if (i < LX)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (lds_void *)(base + (wave + NW * i) * 1024), 16, vo, so_x,
-                                                         0, 0);
-            else
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (lds_void *)(base + X_STAGE + w_unit(i) * 1024), 16, vo,
-                                                         so_w, 0, 0);
-        }
+        for (int i = 0; i < LPS; ++i) issue_one(r, i);
     };
     int32x4 w4_regs[W4_PASSES];
     auto w4_fetch = [&](int kt, bool beyond) {
 #pragma unroll
         for (int p = 0; p < W4_PASSES; ++p) {
             const bool inside = !beyond && kt * (BK / 2) + ((int)threadIdx.x % TPR4) * 16 < wrow_bytes;
-            w4_regs[p] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, inside ? w4_voff[p] : kNowhere,
+            w4_regs[p] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, (int)(inside ? w4_voff[p] : kNowhere),
                                                                beyond ? 0 : kt * (BK / 2), 0);
         }
     };
@@ -344,130 +345,134 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[fn][fm][e] = 0;
+            for (int e = 0; e < 4; ++e) acc[fn][fm][e] = 0;
 
     const int team = (KT == 1) ? 0 : wave / (WAVES_M * WAVES_N);
     const int wt = (KT == 1) ? wave : wave % (WAVES_M * WAVES_N);
     const int wm = wt % WAVES_M, wn = wt / WAVES_M;
     const int ks0 = team * KS_T;             // first k step of a stage that this wave multiplies
-    const int lr = lane % 32;                // fragment row supplied by this lane
-    const int lc = lane / 32;                // which 16-byte half of the 32-byte k step
-    const int sw = swz<BK>(lr);              // wave and fragment offsets are multiples of 32 rows
+    const int lr = lane % 16;                // fragment row supplied by this lane
+    const int lq = lane / 16;                // which 16-byte quarter of the 64-byte k step
+    const int sw = swz<BK>(lr);              // wave and fragment offsets are multiples of 16 rows
     const int x_off = (wm * WM + lr) * BK;
     const int w_off = X_STAGE + (wn * WN + lr) * BKW;
 
-    // Fragment loads and matrix-core steps of one 32-byte k step, in the order
-    // the MFMAs consume them: a[0], every bx, then the remaining a.
-    auto read_frags = [&](const uint8_t *sb, int ks, int32x4(&a)[FN], int32x4(&bx)[FM]) {
-        const int p = (((ks + ks0) * 2 + lc) ^ sw) * 16;
-        a[0] = *reinterpret_cast<const int32x4 *>(sb + w_off + p);
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) bx[fm] = *reinterpret_cast<const int32x4 *>(sb + x_off + fm * 32 * BK + p);
-#pragma unroll
-        for (int fn = 1; fn < FN; ++fn) a[fn] = *reinterpret_cast<const int32x4 *>(sb + w_off + fn * 32 * BK + p);
+    // Fragment i of a 64-byte k step in the order of use: the FN weight fragments, then the activation fragments.
+    auto read_frag = [&](const uint8_t *sb, int ks, int i, int32x4(&a)[FN], int32x4(&bx)[FM]) __attribute__((always_inline)) {
+        const int p = (((ks + ks0) * 4 + lq) ^ sw) * 16;
+        if (i < FN)
+            a[i] = *reinterpret_cast<const int32x4 *>(sb + w_off + i * 16 * BK + p);
+        else
+            bx[i - FN] = *reinterpret_cast<const int32x4 *>(sb + x_off + (i - FN) * 16 * BK + p);
     };
-    auto mfma_step = [&](const int32x4(&a)[FN], const int32x4(&bx)[FM]) {
+    auto mfma = [&](const auto &a, const int32x4 &bx, AccT &c) __attribute__((always_inline)) {
+        if constexpr (A16)
+            c = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, bx), c, 0, 0, 0);
+        else
+            c = __builtin_amdgcn_mfma_i32_16x16x64_i8(__builtin_bit_cast(int32x4, a), bx, c, 0, 0, 0);
+    };
+    // One k step: FM groups of FN MFMAs, pinned in this order, with everything else dealt out between the groups.
+    // An activation fragment is dead after its group and one of the next step takes its registers; the next step's
+    // fragments (READ) are all requested LEAD groups before the step ends, so that a stage boundary does not wait for
+    // them.  The refill loads of a boundary (REFILL) are spread over the groups as well: issued in one go behind
+    // the barrier, they and their address arithmetic kept the matrix cores of both waves of a SIMD idle.
+    constexpr int LEAD = FM >= 6 ? 2 : (FM >= 3 ? 1 : 0);
+    auto step = [&](const int32x4(&a)[FN], const int32x4(&bx)[FM], int32x4(&na)[FN], int32x4(&nx)[FM], const uint8_t *sx, int nks,
+                    const Refill &r, auto read_c, auto refill_c) __attribute__((always_inline)) {
         if constexpr (!PAIRED) {
+            constexpr bool READ = decltype(read_c)::value, REFILL = decltype(refill_c)::value;
+            constexpr int R = FN + FM, G = FM - LEAD;
 #pragma unroll
-            for (int fn = 0; fn < FN; ++fn)
+            for (int g = 0; g < FM; ++g) {
 #pragma unroll
-                for (int fm = 0; fm < FM; ++fm)
-                    if constexpr (XT == 2)
-                        acc[fn][fm] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a[fn]),
-                                                                              __builtin_bit_cast(half8, bx[fm]),
-                                                                              acc[fn][fm], 0, 0, 0);
-                    else
-                        acc[fn][fm] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[fn], bx[fm], acc[fn][fm], 0, 0, 0);
+                for (int fn = 0; fn < FN; ++fn) mfma(a[fn], bx[g], acc[fn][g]);
+                if constexpr (READ) {
+#pragma unroll
+                    for (int i = 0; i < R; ++i)
+                        if (i >= R * g / G && i < R * (g + 1) / G) read_frag(sx, nks, i, na, nx);
+                }
+                if constexpr (REFILL) {
+#pragma unroll
+                    for (int i = 0; i < LPS; ++i)
+                        if (i >= LPS * g / FM && i < LPS * (g + 1) / FM) issue_one(r, i);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
     // Weight rows half as long as activation rows (PAIRED), told for FP16 activations; with INT8 activations and
     // INT4 weights a stage holds 128 values of K and every count of values below doubles.  A stage holds 64 values of K: 128 bytes (eight chunks) of an activation row, 64 bytes
-    // (four chunks) of a weight row, four k steps of sixteen values.  Lane (row lr, half lc) reads weight
-    // chunk 2*pair + lc once per pair of k steps: its first eight codes feed the first step of the pair, its
-    // last eight the second.  The activations of the same values of K are chunk 4*pair + 2*lc + t for step
-    // t of the pair, so every step reads one 16-byte activation chunk per row as before.
+    // (four chunks) of a weight row, two k steps of 32 values.  Lane (row lr, quarter lq) reads weight
+    // chunk lq once per stage: its first eight codes feed the first step, its
+    // last eight the second.  The activations of the same values of K are chunk 2*lq + t for step
+    // t, so every step reads one 16-byte activation chunk per row as before.
     const int sww = swz<BKW>(lr);
-    auto read_x_paired = [&](const uint8_t *sb, int ks, int32x4(&bx)[FM]) {
-        const int p = (((ks / 2) * 4 + 2 * lc + (ks & 1)) ^ sw) * 16;
-#pragma unroll
-        for (int fm = 0; fm < FM; ++fm) bx[fm] = *reinterpret_cast<const int32x4 *>(sb + x_off + fm * 32 * BK + p);
+    auto read_x_paired = [&](const uint8_t *sb, int ks, int fm, int32x4 &bx) __attribute__((always_inline)) {
+        bx = *reinterpret_cast<const int32x4 *>(sb + x_off + fm * 16 * BK + ((2 * lq + ks) ^ sw) * 16);
     };
-    int32x4 w_raw[FN];                       // the narrow weights of the next pair of k steps
+    int32x4 w_raw[FN];                       // the narrow weights of the next stage
     using WOp = typename std::conditional<A16, half8, int32x4>::type;
-    WOp w_op[2][FN];                        // [step of the pair][fragment]: one set, rewritten once the
+    WOp w_op[2][FN];                        // [step][fragment]: one set, rewritten once the
                                              // second step's MFMAs have been issued (register budget)
-    auto read_w_paired = [&](const uint8_t *sb, int pair) {
-        const int p = ((pair * 2 + lc) ^ sww) * 16;
+    auto read_w_paired = [&](const uint8_t *sb) __attribute__((always_inline)) {
+        const int p = (lq ^ sww) * 16;
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn) w_raw[fn] = *reinterpret_cast<const int32x4 *>(sb + w_off + fn * 32 * BKW + p);
+        for (int fn = 0; fn < FN; ++fn) w_raw[fn] = *reinterpret_cast<const int32x4 *>(sb + w_off + fn * 16 * BKW + p);
     };
-    // first (T = 0) or last (T = 1) eight bytes of w_raw -> the operands of that step of the pair (eight INT8
+    // first (t = 0) or last (t = 1) eight bytes of w_raw -> the operands of that step (eight INT8
     // codes to FP16, or sixteen nibbles to INT8 times 16, both exact)
-    auto convert_w_paired = [&](auto t_c) __attribute__((always_inline)) {
-        constexpr int T = decltype(t_c)::value;
-#pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-            if constexpr (A16) {
-                w_op[T][fn] = cvt8_i8_f16((uint32_t)w_raw[fn][2 * T], (uint32_t)w_raw[fn][2 * T + 1]);
-            } else {
-                uint32_t d0, d1, d2, d3;
-                unpack8_nat((uint32_t)w_raw[fn][2 * T], d0, d1);
-                unpack8_nat((uint32_t)w_raw[fn][2 * T + 1], d2, d3);
-                w_op[T][fn] = int32x4{(int)d0, (int)d1, (int)d2, (int)d3};
-            }
-    };
-    using T0 = std::integral_constant<int, 0>;
-    using T1 = std::integral_constant<int, 1>;
-    // order of issue inside a step: one LDS read per MFMA while reads are left, then the conversion
-    // spread over the remaining MFMAs
-    auto pace_paired = [&](auto reads_c) __attribute__((always_inline)) {
-        constexpr int READS = decltype(reads_c)::value;
-        constexpr int NM = FN * FM;
-        constexpr int VC = 10 * FN;                // VALU instructions of one conversion
-        if constexpr (READS < NM) {
-            constexpr int PER = (VC + NM - READS - 1) / (NM - READS);
-#pragma unroll
-            for (int i = 0; i < NM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                   // MFMA
-                if (i < READS)
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);               // DS read
-                else
-                    __builtin_amdgcn_sched_group_barrier(0x002, PER, 0);             // VALU
-            }
-        } else {                                   // small wave tiles: the reads outnumber the MFMAs
-            constexpr int PER = (READS + NM - 1) / NM;
-#pragma unroll
-            for (int i = 0; i < NM; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x100, PER, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x002, VC, 0);
+    auto convert_w_paired = [&](int t, int fn) __attribute__((always_inline)) {
+        if constexpr (A16) {
+            w_op[t][fn] = cvt8_i8_f16((uint32_t)w_raw[fn][2 * t], (uint32_t)w_raw[fn][2 * t + 1]);
+        } else {
+            uint32_t d0, d1, d2, d3;
+            unpack8_nat((uint32_t)w_raw[fn][2 * t], d0, d1);
+            unpack8_nat((uint32_t)w_raw[fn][2 * t + 1], d2, d3);
+            w_op[t][fn] = int32x4{(int)d0, (int)d1, (int)d2, (int)d3};
         }
     };
-    using RX = std::integral_constant<int, FM>;          // a step that reads activation fragments only
-    using RXW = std::integral_constant<int, FM + FN>;    // ... and the raw weights of the next pair
-    auto mfma_step_paired = [&](const WOp(&a)[FN], const int32x4(&bx)[FM]) {
+    // The step above for these operands.  Group g has the activation fragments up to g behind it; in their place, and
+    // in AHEAD spare ones, come those of the next step (READ_X).  The raw weights of the next stage (NEXT, with the
+    // refill) are requested in the first group, and the conversions of CONV's step (-1: none) are spread over the
+    // groups from CONV_FROM on.  Left to the scheduler the 256x256 tile's accumulators did not stay in their registers.
+    constexpr int AHEAD = 3;
+    auto step_paired = [&](const WOp(&a)[FN], const int32x4(&bx)[FM], int32x4(&nx)[FM], const uint8_t *sx, int nks, const Refill &r,
+                           auto read_x_c, auto next_c, auto conv_c) __attribute__((always_inline)) {
         if constexpr (PAIRED) {
+            constexpr bool READ_X = decltype(read_x_c)::value, NEXT = decltype(next_c)::value;
+            constexpr int CONV = decltype(conv_c)::value;
+            constexpr int CONV_FROM = (NEXT && FM > 2) ? FM / 3 : 0;
 #pragma unroll
-            for (int fn = 0; fn < FN; ++fn)
+            for (int g = 0; g < FM; ++g) {
 #pragma unroll
-                for (int fm = 0; fm < FM; ++fm)
-                    if constexpr (A16)
-                        acc[fn][fm] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[fn], __builtin_bit_cast(half8, bx[fm]),
-                                                                              acc[fn][fm], 0, 0, 0);
-                    else
-                        acc[fn][fm] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[fn], bx[fm], acc[fn][fm], 0, 0, 0);
+                for (int fn = 0; fn < FN; ++fn) mfma(a[fn], bx[g], acc[fn][g]);
+                if (NEXT && g == 0) read_w_paired(sx);
+                if constexpr (READ_X) {
+#pragma unroll
+                    for (int j = 0; j < FM; ++j)
+                        if (j >= (g == 0 ? 0 : g + AHEAD - 1) && j < g + AHEAD) read_x_paired(sx, nks, j, nx[j]);
+                }
+                if constexpr (NEXT) {
+#pragma unroll
+                    for (int i = 0; i < LPS; ++i)
+                        if (i >= LPS * g / FM && i < LPS * (g + 1) / FM) issue_one(r, i);
+                }
+                if constexpr (CONV >= 0) {
+                    constexpr int CG = FM - CONV_FROM;
+                    const int c = g - CONV_FROM;
+#pragma unroll
+                    for (int fn = 0; fn < FN; ++fn)
+                        if (c >= 0 && fn >= FN * c / CG && fn < FN * (c + 1) / CG) convert_w_paired(CONV, fn);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     };
-    // one LDS read after every (FN*FM)/(FN+FM) MFMAs
-    auto interleave = [&]() {
-        constexpr int per_read = (FN * FM) / (FN + FM) > 0 ? (FN * FM) / (FN + FM) : 1;
-#pragma unroll
-        for (int i = 0; i < FN + FM; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, per_read, 0);   // MFMA
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          // DS read
-        }
-    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    using CNone = std::integral_constant<int, -1>;
 
     float *col_scale = reinterpret_cast<float *>(smem + Cfg::kMain);
     float *col_bias = col_scale + BN;
@@ -504,7 +509,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
         const float st_v = A16 ? 1.0f : s_tok[m];         // FP16 activations carry no token scale
         if (c < BN) {
             col_scale[c] = sw_v;
-            col_bias[c] = (bias != nullptr) ? (float)b_v : 0.0f;
+            // columns past the matrix (their products are zero) give an output of zero, so they never raise a row maximum
+            col_bias[c] = (bias != nullptr && n0 + c < N) ? (float)b_v : 0.0f;
         }
         if (c < BM) row_scale[c] = st_v;
     }
@@ -514,12 +520,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
         wait_vmcnt<0>();
     __syncthreads();
     if constexpr (PAIRED) {
-        read_x_paired(smem, 0, b0);
-        read_w_paired(smem, 0);
-        convert_w_paired(T0{});
-        convert_w_paired(T1{});
+        read_w_paired(smem);
+#pragma unroll
+        for (int fm = 0; fm < FM; ++fm) read_x_paired(smem, 0, fm, b0[fm]);
+#pragma unroll
+        for (int fn = 0; fn < FN; ++fn) convert_w_paired(0, fn);
     } else {
-        read_frags(smem, 0, a0, b0);
+#pragma unroll
+        for (int i = 0; i < FN + FM; ++i) read_frag(smem, 0, i, a0, b0);
     }
 
     // One stage of K.  The last stage of the workgroup is a copy of its own (LAST = 1) without the
@@ -527,81 +535,76 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // without the barrier would meet again in front of the last matrix-core step, and the compiler,
     // which tracks LDS reads in flight per path, would make that step wait for the reads issued after
     // the barrier although its operands were read long before it.
-    auto stage = [&](int kt, auto last_c) __attribute__((always_inline)) {
+    // PAR: the fragment set the stage starts on, which alternates where a wave multiplies an odd number of steps per stage.
+    auto stage = [&](int kt, auto last_c, auto par_c) __attribute__((always_inline)) {
         constexpr bool LAST = decltype(last_c)::value;
+        constexpr int PAR = decltype(par_c)::value;
         const uint8_t *sb = smem + (kt % NSTAGE) * STAGE;
         const uint8_t *sn = smem + ((kt + 1) % NSTAGE) * STAGE;
         if constexpr (PAIRED) {
-            // k steps 0..3 = (pair 0, step 0), (pair 0, step 1), (pair 1, step 0), (pair 1, step 1).  The second
-            // step of a pair reads the raw weights of the next pair and converts their first half (whose
-            // registers the first step has finished with) under its own MFMAs; the first step of the next
-            // pair converts the second half under its MFMAs.  One set of converted operands is enough.
-            read_x_paired(sb, 1, b1);
-            mfma_step_paired(w_op[0], b0);
-            convert_w_paired(T1{});
-            pace_paired(RX{});
-            read_x_paired(sb, 2, b0);
-            read_w_paired(sb, 1);
-            mfma_step_paired(w_op[1], b1);
-            convert_w_paired(T0{});
-            pace_paired(RXW{});
-            read_x_paired(sb, 3, b1);
-            mfma_step_paired(w_op[0], b0);
-            convert_w_paired(T1{});
-            pace_paired(RX{});
+            // The first step converts the second half of the stage's raw weights under its MFMAs; the second step
+            // reads the raw weights of the next stage and converts their first half, whose registers the first
+            // step has finished with.
+            step_paired(w_op[0], b0, b1, sb, 1, Refill{}, Yes{}, No{}, C1{});
             if constexpr (!LAST) {
                 wait_vmcnt<(NSTAGE - 2) * LPS>();         // stage kt+1 has landed
                 lds_barrier();
-                issue_direct(kt0 + kt + NSTAGE, kt % NSTAGE, kt + NSTAGE >= n_loc);
-                read_x_paired(sn, 0, b0);
-                read_w_paired(sn, 0);
-            }
-            mfma_step_paired(w_op[1], b1);
-            if constexpr (!LAST) {
-                convert_w_paired(T0{});
-                pace_paired(RXW{});
+                step_paired(w_op[1], b1, b0, sn, 0, refill_of(kt0 + kt + NSTAGE, kt % NSTAGE, kt + NSTAGE >= n_loc), Yes{}, Yes{}, C0{});
+            } else {
+                step_paired(w_op[1], b1, b0, sn, 0, Refill{}, No{}, No{}, CNone{});
             }
             return;
         }
 #pragma unroll
         for (int ks = 0; ks < KS_T; ++ks) {
-            int32x4(&ca)[FN] = (ks & 1) ? a1 : a0;
-            int32x4(&cb)[FM] = (ks & 1) ? b1 : b0;
-            int32x4(&na)[FN] = (ks & 1) ? a0 : a1;
-            int32x4(&nb2)[FM] = (ks & 1) ? b0 : b1;
+            int32x4(&ca)[FN] = ((ks + PAR) & 1) ? a1 : a0;
+            int32x4(&cb)[FM] = ((ks + PAR) & 1) ? b1 : b0;
+            int32x4(&na)[FN] = ((ks + PAR) & 1) ? a0 : a1;
+            int32x4(&nb2)[FM] = ((ks + PAR) & 1) ? b0 : b1;
             if (ks + 1 < KS_T) {
-                read_frags(sb, ks + 1, na, nb2);
-                mfma_step(ca, cb);
-                interleave();
+                step(ca, cb, na, nb2, sb, ks + 1, Refill{}, Yes{}, No{});
+            } else if constexpr (!LAST) {
+                if (!STAGED_W)
+                    wait_vmcnt<(NSTAGE - 2) * LPS>();     // stage kt+1 has landed
+                else
+                    wait_vmcnt<0>();
+                // Weights that pass through registers (INT4 nibbles, INT8 -> FP16): the registers fetched
+                // at the previous boundary have had a whole stage to arrive and share the wait above;
+                // their slot was freed at that boundary.  (Placed at the start of the stage, as before,
+                // the store waited for loads issued one k step earlier, a full memory latency per stage.)
+                if (STAGED_W && kt >= 1 && kt - 1 + NSTAGE < n_loc) w4_store((kt - 1) % NSTAGE);
+                lds_barrier();
+                if (STAGED_W) w4_fetch(kt0 + kt + NSTAGE, kt + NSTAGE >= n_loc);
+                // the first fragments of the next stage arrive under these MFMAs
+                step(ca, cb, na, nb2, sn, 0, refill_of(kt0 + kt + NSTAGE, kt % NSTAGE, kt + NSTAGE >= n_loc), Yes{}, Yes{});
             } else {
-                if constexpr (!LAST) {
-                    if (!STAGED_W)
-                        wait_vmcnt<(NSTAGE - 2) * LPS>();     // stage kt+1 has landed
-                    else
-                        wait_vmcnt<0>();
-                    // Weights that pass through registers (INT4 nibbles, INT8 -> FP16): the registers fetched
-                    // at the previous boundary have had a whole stage to arrive and share the wait above;
-                    // their slot was freed at that boundary.  (Placed at the start of the stage, as before,
-                    // the store waited for loads issued one k step earlier, a full memory latency per stage.)
-                    if (STAGED_W && kt >= 1 && kt - 1 + NSTAGE < n_loc) w4_store((kt - 1) % NSTAGE);
-                    lds_barrier();
-                    issue_direct(kt0 + kt + NSTAGE, kt % NSTAGE, kt + NSTAGE >= n_loc);
-                    if (STAGED_W) w4_fetch(kt0 + kt + NSTAGE, kt + NSTAGE >= n_loc);
-                    read_frags(sn, 0, na, nb2);
-                }
-                mfma_step(ca, cb);
-                if constexpr (!LAST) interleave();     // the first fragments of the next stage arrive under these MFMAs
+                step(ca, cb, na, nb2, sn, 0, Refill{}, No{}, No{});
             }
         }
     };
-    static_assert(KS_T % 2 == 0, "a stage starts on the first fragment set");
-    for (int kt = 0; kt < n_loc - 1; ++kt)     // kt counts this workgroup's stages; kt0 + kt is the stage of K
-        stage(kt, std::false_type{});
-    stage(n_loc - 1, std::true_type{});
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, 1>;
+    if constexpr (KS_T % 2 == 0 || PAIRED) {
+        for (int kt = 0; kt < n_loc - 1; ++kt)     // kt counts this workgroup's stages; kt0 + kt is the stage of K
+            stage(kt, std::false_type{}, P0{});
+        stage(n_loc - 1, std::true_type{}, P0{});
+    } else {
+        int kt = 0;
+        for (; kt + 2 < n_loc; kt += 2) {
+            stage(kt, std::false_type{}, P0{});
+            stage(kt + 1, std::false_type{}, P1{});
+        }
+        if (kt + 2 == n_loc) {
+            stage(kt, std::false_type{}, P0{});
+            stage(kt + 1, std::true_type{}, P1{});
+        } else {
+            stage(kt, std::true_type{}, P0{});
+        }
+    }
 
     // ---- epilogue ---------------------------------------------------------
-    // acc[fn][fm][v]: output column n = wn*WN + fn*32 + 8*(v/4) + 4*(lane/32) + v%4,
-    //                 token row     m = wm*WM + fm*32 + lane%32.
+    // acc[fn][fm][v]: output column n = wn*WN + fn*16 + 4*(lane/16) + v,
+    //                 token row     m = wm*WM + fm*16 + lane%16.
     if constexpr (KSPLIT == 1) {
         // K split: the raw accumulators of this range of K go to partial[split][M][N]; the second
         // kernel adds the splits in order and applies scales, bias and activation.  Each wave turns its
@@ -616,20 +619,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm) {
 #pragma unroll
-            for (int fn = 0; fn < FN; ++fn) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    int32x4 v;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if constexpr (A16)
-                            v[e] = __float_as_int(acc[fn][fm][4 * q + e]);
-                        else
-                            v[e] = acc[fn][fm][4 * q + e];
-                    }
-                    *reinterpret_cast<int32x4 *>(pt + (fm * 32 + lr) * PROW + fn * 32 + 8 * q + 4 * lc) = v;
-                }
-            }
+            for (int fn = 0; fn < FN; ++fn)
+                *reinterpret_cast<int32x4 *>(pt + (fm * 16 + lr) * PROW + fn * 16 + 4 * lq) =
+                    __builtin_bit_cast(int32x4, acc[fn][fm]);
         }
         int32_t *mine = partial + (size_t)split * M * N;
         constexpr int CPW = WN / 4;                   // 16-byte pieces per row of the wave's block
@@ -644,32 +636,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     }
     __syncthreads();                          // all reads of the last stage are done; LDS is reused below
     if constexpr (KT == 2) {
-        // The two teams hold partial products of the same tile.  Each wave hands the half of its 32-row
+        // The two teams hold partial products of the same tile.  Each wave hands the half of its 16-row
         // blocks that its partner wave (same place in the other team) will finish to LDS, one 16-byte piece
-        // per lane and group of four registers, and adds the partner's pieces for the half it keeps.
+        // per lane and accumulator, and adds the partner's pieces for the half it keeps.
         // Integer sums do not depend on the order; the fp32 ones are one addition of the same two
         // numbers on either side.
         constexpr int HALF = FM / 2;
-        int32x4 *xb = reinterpret_cast<int32x4 *>(smem + Cfg::kXchg);
-        constexpr int PER_WAVE = HALF * FN * 4 * 64;          // 16-byte pieces per wave
+        AccT *xb = reinterpret_cast<AccT *>(smem + Cfg::kXchg);
+        constexpr int PER_WAVE = HALF * FN * 64;              // 16-byte pieces per wave
         auto hand_over = [&](auto lo_c) __attribute__((always_inline)) {
             constexpr int LO = decltype(lo_c)::value;         // first block handed over
 #pragma unroll
             for (int fm = 0; fm < HALF; ++fm)
 #pragma unroll
-                for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        int32x4 v;
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if constexpr (A16)
-                                v[e] = __float_as_int(acc[fn][LO + fm][4 * q + e]);
-                            else
-                                v[e] = acc[fn][LO + fm][4 * q + e];
-                        }
-                        xb[wave * PER_WAVE + ((fm * FN + fn) * 4 + q) * 64 + lane] = v;
-                    }
+                for (int fn = 0; fn < FN; ++fn) xb[wave * PER_WAVE + (fm * FN + fn) * 64 + lane] = acc[fn][LO + fm];
         };
         auto take_over = [&](auto lo_c) __attribute__((always_inline)) {
             constexpr int LO = decltype(lo_c)::value;         // first block kept
@@ -677,18 +657,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
 #pragma unroll
             for (int fm = 0; fm < HALF; ++fm)
 #pragma unroll
-                for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int32x4 v = xb[partner * PER_WAVE + ((fm * FN + fn) * 4 + q) * 64 + lane];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if constexpr (A16)
-                                acc[fn][LO + fm][4 * q + e] += __int_as_float(v[e]);
-                            else
-                                acc[fn][LO + fm][4 * q + e] += v[e];
-                        }
-                    }
+                for (int fn = 0; fn < FN; ++fn) acc[fn][LO + fm] += xb[partner * PER_WAVE + (fm * FN + fn) * 64 + lane];
         };
         if (team == 0)
             hand_over(std::integral_constant<int, HALF>{});   // team 0 keeps blocks 0 .. HALF-1
@@ -712,47 +681,44 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
         gen_raw = __hip_atomic_load(q_ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // The column scales and biases of this wave's columns, read once where the registers allow it
     // (they do not depend on the row).
-    constexpr bool HOIST = FN <= 2 && QOUT == 0;      // the in-kernel quantizer keeps the accumulators live longer
-    // The four consecutive columns of a lane's register group lie in one weight group (a group is a
+    constexpr bool HOIST = WN <= 64 && QOUT == 0;     // the in-kernel quantizer keeps the accumulators live longer
+    // The four consecutive columns of a lane's accumulator lie in one weight group (a group is a
     // multiple of 16 columns and the four start at a multiple of 4), so one scale serves all four.
-    float sc_all[HOIST ? FN : 1][4];
-    float4 cb_all[HOIST ? FN : 1][4];
+    float sc_all[HOIST ? FN : 1];
+    float4 cb_all[HOIST ? FN : 1];
     if constexpr (HOIST) {
 #pragma unroll
-        for (int fn = 0; fn < FN; ++fn)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int nl = fn * 32 + 8 * q + 4 * lc;
-                sc_all[fn][q] = col_scale[wn * WN + nl];
-                cb_all[fn][q] = *reinterpret_cast<const float4 *>(col_bias + wn * WN + nl);
-            }
+        for (int fn = 0; fn < FN; ++fn) {
+            const int nl = fn * 16 + 4 * lq;
+            sc_all[fn] = col_scale[wn * WN + nl];
+            cb_all[fn] = *reinterpret_cast<const float4 *>(col_bias + wn * WN + nl);
+        }
     }
     // PLAIN = no activation and no accumulator tap, decided once for the whole epilogue: with the two
     // (wave-uniform) tests inside the loops every group of four values was a basic block of its own
     // and its LDS round trip could not overlap the arithmetic of its neighbours.
     auto rows_pass = [&](auto plain_c, auto lo_c, auto hi_c) __attribute__((always_inline)) {
         constexpr bool PLAIN = decltype(plain_c)::value;
-        constexpr int FM_LO = decltype(lo_c)::value, FM_HI = decltype(hi_c)::value;   // the 32-row blocks this wave finishes
+        constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;   // the 32-row blocks this wave finishes
 #pragma unroll
-        for (int fm = FM_LO; fm < FM_HI; ++fm) {
-            rmax[fm] = 0.0f;
-            const float st = row_scale[wm * WM + fm * 32 + lr];
+        for (int blk = LO; blk < HI; ++blk) {
 #pragma unroll
-            for (int fn = 0; fn < FN; ++fn) {
+            for (int h = 0; h < 2; ++h) {
+                const int fm = 2 * blk + h;
+                rmax[fm] = 0.0f;
+                const float st = row_scale[wm * WM + fm * 16 + lr];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int nl = fn * 32 + 8 * q + 4 * lc;
-                    const float sc = HOIST ? sc_all[HOIST ? fn : 0][q] : col_scale[wn * WN + nl];
-                    const float4 cb = HOIST ? cb_all[HOIST ? fn : 0][q]
-                                            : *reinterpret_cast<const float4 *>(col_bias + wn * WN + nl);
+                for (int fn = 0; fn < FN; ++fn) {
+                    const int nl = fn * 16 + 4 * lq;
+                    const float sc = HOIST ? sc_all[HOIST ? fn : 0] : col_scale[wn * WN + nl];
+                    const float4 cb = HOIST ? cb_all[HOIST ? fn : 0] : *reinterpret_cast<const float4 *>(col_bias + wn * WN + nl);
                     int32x4 v = {0, 0, 0, 0};
                     float fv[4];
                     if constexpr (A16) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) fv[e] = acc[fn][fm][4 * q + e];
+                        for (int e = 0; e < 4; ++e) fv[e] = acc[fn][fm][e];
                     } else {
-                        v = int32x4{acc[fn][fm][4 * q], acc[fn][fm][4 * q + 1], acc[fn][fm][4 * q + 2],
-                                    acc[fn][fm][4 * q + 3]};
+                        v = acc[fn][fm];
                         if (WBITS == 4) {
 #pragma unroll
                             for (int e = 0; e < 4; ++e) v[e] >>= 4;   // exact: every product carried the factor 16
@@ -777,10 +743,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
                         asm("" : "+v"(f[e]));
                         o[e] = (half_t)f[e];
                     }
-                    if (QOUT == 0 || out != nullptr) *reinterpret_cast<half4 *>(ot + lr * OROW + nl * 2) = o;
+                    if (QOUT == 0 || out != nullptr) *reinterpret_cast<half4 *>(ot + (h * 16 + lr) * OROW + nl * 2) = o;
                     if constexpr (!PLAIN && !A16) {
                         if (acc_out != nullptr) {
-                            const int m = mw + fm * 32 + lr;
+                            const int m = mw + fm * 16 + lr;
                             if (m < M && nw + nl < N)
                                 *reinterpret_cast<int32x4 *>(acc_out + (size_t)m * N + nw + nl) = v;
                         }
@@ -791,7 +757,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             const float g = (float)o[e];
-                            acc[fn][fm][4 * q + e] = __float_as_int(g);
+                            acc[fn][fm][e] = __float_as_int(g);
                             rmax[fm] = fmaxf(rmax[fm], fabsf(g));
                         }
                     }
@@ -805,7 +771,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
                     const int row = (i * 64 + lane) / LPR;
                     const int col = ((i * 64 + lane) % LPR) * 8;
                     const int32x4 v = *reinterpret_cast<const int32x4 *>(ot + row * OROW + col * 2);
-                    const int m = mw + fm * 32 + row;
+                    const int m = mw + blk * 32 + row;
                     const int n = nw + col;
                     // Streaming (non-temporal) stores: nothing in this kernel reads the output again, and lines
                     // that do not linger in the L2 need no write-back when the kernel ends (4096x4096x1024:
@@ -818,8 +784,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     };
     const bool plain = QOUT == 0 && act == 0 && acc_out == nullptr;
     using I0 = std::integral_constant<int, 0>;
-    using IH = std::integral_constant<int, FM / 2>;
-    using IF = std::integral_constant<int, FM>;
+    using IH = std::integral_constant<int, WM / 64>;
+    using IF = std::integral_constant<int, WM / 32>;
     if constexpr (KT == 1) {
         if (plain)
             rows_pass(std::true_type{}, I0{}, IF{});
@@ -842,15 +808,16 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     if constexpr (QOUT == 1) {
         // ---- token-wise quantization of the output rows from registers (App. A.2) ----
         // A row of g spans the tiles_n tiles of this band.  Row maxima: lane pair -> the waves along
-        // N (LDS) -> the band (slots in device memory).  Columns past N repeat column N-1 and rows
-        // past M repeat row M-1 (clamped loads), so they never raise a maximum.
+        // N (LDS) -> the band (slots in device memory).  Columns past N are zero (zero products, no bias; GeLU of
+        // zero is zero), so they never raise a maximum; rows past M have maxima that nobody reads.
         float *wave_max = row_scale + BM;              // [WAVES_N][BM]
         float *row_inv = wave_max + WAVES_N * BM;      // [BM]
         const int tid = threadIdx.x;
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm) {
+            rmax[fm] = fmaxf(rmax[fm], __shfl_xor(rmax[fm], 16));
             rmax[fm] = fmaxf(rmax[fm], __shfl_xor(rmax[fm], 32));
-            if (lc == 0) wave_max[wn * BM + wm * WM + fm * 32 + lr] = rmax[fm];
+            if (lq == 0) wave_max[wn * BM + wm * WM + fm * 16 + lr] = rmax[fm];
         }
         __syncthreads();
         const unsigned tag = gen_raw + 1u;             // never 0: untouched slots carry tag 0
@@ -918,28 +885,24 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
         if (tid == 0)
             done_before = __hip_atomic_fetch_add(q_ctl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // Codes: four consecutive columns per lane -> one dword of the BM x BN code tile in LDS (the
-        // stage ring is free now), 16-byte chunks XOR-swizzled by row so that the 32 rows of a
+        // stage ring is free now), 16-byte chunks XOR-swizzled by row so that the 16 rows of a
         // fragment hit different banks; then every row leaves as one contiguous segment.
         constexpr int QCH = BN / 16;                   // 16-byte chunks per row of the code tile
         uint8_t *ct = smem;
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm) {
-            const int row = wm * WM + fm * 32 + lr;
+            const int row = wm * WM + fm * 16 + lr;
             const float inv = row_inv[row];
             const bool poisoned = __float_as_uint(inv) == kPoisonBits;   // the wait of this row ran out
 #pragma unroll
             for (int fn = 0; fn < FN; ++fn) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int col = wn * WN + fn * 32 + 8 * q + 4 * lc;
-                    uint32_t d = pack4_code_bits(
-                        quant_code_bits(__int_as_float(acc[fn][fm][4 * q]), inv),
-                        quant_code_bits(__int_as_float(acc[fn][fm][4 * q + 1]), inv),
-                        quant_code_bits(__int_as_float(acc[fn][fm][4 * q + 2]), inv),
-                        quant_code_bits(__int_as_float(acc[fn][fm][4 * q + 3]), inv));
-                    if (poisoned) d = 0x80808080u;
-                    *reinterpret_cast<uint32_t *>(ct + row * BN + (((col / 16) ^ (row & (QCH - 1))) * 16) + col % 16) = d;
-                }
+                const int col = wn * WN + fn * 16 + 4 * lq;
+                uint32_t d = pack4_code_bits(quant_code_bits(__int_as_float(acc[fn][fm][0]), inv),
+                                             quant_code_bits(__int_as_float(acc[fn][fm][1]), inv),
+                                             quant_code_bits(__int_as_float(acc[fn][fm][2]), inv),
+                                             quant_code_bits(__int_as_float(acc[fn][fm][3]), inv));
+                if (poisoned) d = 0x80808080u;
+                *reinterpret_cast<uint32_t *>(ct + row * BN + (((col / 16) ^ (row & (QCH - 1))) * 16) + col % 16) = d;
             }
         }
         __syncthreads();

@@ -127,6 +127,37 @@ def test_tiles_that_quantize(zq, orc, variant, bits, M, N, K, g):
                  "quantizing tile %d %d-bit %dx%dx%d" % (variant, bits, M, N, K))
 
 
+@pytest.mark.parametrize("bits", [8, 4])
+@pytest.mark.parametrize("variant,M,N,K", [(TILE128, 129, 80, 416), (TILE128, 300, 1104, 544), (TILE256X128, 300, 208, 416),
+                                           (TILE256, 300, 272, 416)])
+def test_columns_past_the_matrix_leave_the_row_maximum(zq, variant, bits, M, N, K):
+    """The last column's products cancel its bias of 30: a tile that gave the columns past it their bias would quantize every
+    row of that tile with a scale some ten times too large.  Exact: the codes and scales of the row quantizer."""
+    rng = zq_inputs.rng_for(11, variant + M + N + K + bits)
+    lim = 127 if bits == 8 else 7
+    codes = rng.integers(-lim, lim + 1, (N, K)).astype(np.int8)
+    codes[-16:-1], codes[-1] = 0, -5                            # the last weight group, of scale 1
+    s_tok = np.full(M, 30.0 / (5.0 * K), np.float32)
+    s_w = np.full(N // 16, 1.0, np.float32)
+    s_w[:-1] = 3.0 / (s_tok[0] * lim * np.sqrt(K))
+    bias = np.zeros(N, np.float16)
+    bias[-1] = 30.0
+    wq = codes if bits == 8 else ((codes[:, 0::2] & 15) | ((codes[:, 1::2] & 15) << 4)).astype(np.uint8)
+    args = (dev(np.ones((M, K), np.int8)), dev(s_tok), dev(wq), dev(s_w), dev(bias))
+    ws = zq.new_workspace(0)
+    prev = zq.force_gemm_variant(variant)
+    try:
+        assert zq.gemm_quantizes_in_kernel(M, N, K, bits, ws.numel())
+        want = zq.zq_gemm_gelu_quant_tokenwise(*args)               # no workspace: the row quantizer
+        got = zq.zq_gemm_gelu_quant_tokenwise(*args, workspace=ws)
+        torch.cuda.synchronize()
+    finally:
+        zq.force_gemm_variant(prev)
+    assert 0.0 < float(want[2].max()) < 12.0 / 127.0
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("M,N,K,g", [(161, 2912, 2896, 91), (236, 2080, 2896, 65)])
 def test_split_class_that_runs_unsplit(zq, orc, M, N, K, g):
     """The class is the K split, the workspace is sized for it, and the unsplit tiles run; forced, or with a table entry that names
