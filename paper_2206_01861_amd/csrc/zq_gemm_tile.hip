@@ -483,44 +483,48 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // that step's fragments in registers, so after the barrier there the slot is free and receives
     // stage kt + NSTAGE, while the first fragments of stage kt + 1 are read under the last MFMAs.
     int32x4 a0[FN], b0[FM], a1[FN], b1[FM];
-#pragma unroll
-    for (int s = 0; s < NSTAGE; ++s) {
+    auto first_stage = [&](int s) __attribute__((always_inline)) {
         issue_direct(kt0 + s, s, s >= n_loc);
         if (STAGED_W && s < n_loc) {
             w4_fetch(kt0 + s, false);
             w4_store(s);
         }
-    }
+    };
+    first_stage(0);
     // Scale prefetch (App. D reads both scale vectors before the product is complete): the
     // per-column weight-group scale and bias and the per-row token scale of this tile go to LDS.
-    // They are requested after the first operand stages, and all three loads of a thread before
-    // any of them is used, so that their round trip runs under the operand loads instead of in
-    // front of them (it used to cost three dependent round trips before the first operand load).
+    // They are requested between the first operand stage and the second.  In front of the first, their address
+    // arithmetic and round trip delayed it; behind the last, where they were, the store to LDS waited for
+    // all stages of the ring to land, since loads complete in order, and so did the first product.
     static_assert(BN <= NT && BM <= NT, "one scale element per thread");
     if constexpr (KSPLIT == 0) {
-        const int c = threadIdx.x;
-        int n = n0 + (c < BN ? c : 0);
-        if (n > N - 1) n = N - 1;
-        int m = m0 + (c < BM ? c : 0);
-        if (m > M - 1) m = M - 1;
-        const float sw_v = s_w[n / gs];
+        const int n = n0 + sc_c < N ? n0 + sc_c : N - 1;
+        const int m = m0 + sc_m < M ? m0 + sc_m : M - 1;
+        sw_v = s_w[n / gs];
+    float sw_v = 0.0f, st_v = 1.0f;                   // FP16 activations carry no token scale
+    half_t b_v = 0;
+    const int sc_c = (int)threadIdx.x < BN ? (int)threadIdx.x : 0, sc_m = (int)threadIdx.x < BM ? (int)threadIdx.x : 0;
         // without a bias the load reads a valid dummy address: no branch around a load in flight
-        const half_t b_v = *(bias != nullptr ? bias + n : reinterpret_cast<const half_t *>(s_w));
-        const float st_v = A16 ? 1.0f : s_tok[m];         // FP16 activations carry no token scale
-        if (c < BN) {
-            col_scale[c] = sw_v;
-            // columns past the matrix (their products are zero) give an output of zero, so they never raise a row maximum
-            col_bias[c] = (bias != nullptr && n0 + c < N) ? (float)b_v : 0.0f;
-        }
-        if (c < BM) row_scale[c] = st_v;
+        b_v = *(bias != nullptr ? bias + n : reinterpret_cast<const half_t *>(s_w));
+        if constexpr (!A16) st_v = s_tok[m];
+        __builtin_amdgcn_sched_barrier(0);
     }
     if (!STAGED_W)
-        wait_vmcnt<(NSTAGE - 1) * LPS>();      // stage 0 has landed; later stages may still be in flight
+        wait_vmcnt<(NSTAGE - 1) * LPS>();      // stage 0 and the scales have landed; later stages may still be in flight
     else
         wait_vmcnt<0>();
-    __syncthreads();
+    if constexpr (KSPLIT == 0) {
+        // threads past the tile's edge write element 0 once more: a store behind a condition would take its load along
+        col_scale[sc_c] = sw_v;
+        // columns past the matrix (their products are zero) give an output of zero, so they never raise a row maximum
+        col_bias[sc_c] = (bias != nullptr && n0 + sc_c < N) ? (float)b_v : 0.0f;
+        row_scale[sc_m] = st_v;
+    }
+    lds_barrier();
     if constexpr (PAIRED) {
         read_w_paired(smem);
+#pragma unroll
+    for (int s = 1; s < NSTAGE; ++s) first_stage(s);
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm) read_x_paired(smem, 0, fm, b0[fm]);
 #pragma unroll
