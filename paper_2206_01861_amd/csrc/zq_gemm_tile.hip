@@ -29,10 +29,13 @@
 //
 // The epilogue scales the INT32 accumulators by s_tok[row] * s_w[group], adds
 // the bias and rounds to FP16 (scales and bias were staged in LDS under the
-// first operand loads), passes 32 rows at a time through a wave-private LDS
-// buffer and writes full contiguous row segments.  INT4 weights are unpacked
-// to INT8 (times 16) on their way into LDS and the factor is shifted out of
-// the accumulator.
+// first operand loads), passes 32 rows at a time through LDS and writes
+// contiguous row segments: tiles of 256 rows whole rows of the tile, which
+// several waves have made, the others each wave its own columns.  Whole rows
+// against own columns, us: INT8 4096x12288x4096 156.5 / 154.9, 2048x6144x2048
+// 26.8 / 25.9, 4096x2048x1024 12.9 / 12.6, FP16 activations 4096x4096x4096 110
+// / 106; tiles of 128 rows lose by the barrier, 1237x1024x4096 13.0 / 13.4.
+// INT4 products carry a factor 16, which is shifted out of the accumulator.
 //
 // QOUT = 1 adds the token-wise quantization of the output rows (App. A.2) to
 // the epilogue: the tiles of a band of token rows exchange their row maxima
@@ -97,8 +100,12 @@ struct TileCfg {
     static constexpr int kThreads = 64 * kWaves;
     static constexpr int kStage = BM * BK + BN * ((XT == 1 || XT == 3) ? BK / 2 : BK);   // XT = 1, 3: weight rows half as long as activation rows
     static constexpr int kWN = BN / WAVES_N;
-    static constexpr int kEpiRow = kWN * 2 + 16;              // padded FP16 row of the wave-private buffer
-    static constexpr int kEpi = kWaves * 32 * kEpiRow;
+    // The epilogue turns 32 rows at a time through LDS, padded against bank conflicts: each wave its own columns in a
+    // buffer of its own, or, in tall tiles (WHOLE), all waves side by side whole rows of the tile in one of two.
+    static constexpr bool kWhole = BM >= 256;
+    static constexpr int kEpiRow = (kWhole ? BN : kWN) * 2 + 16;
+    static constexpr int kEpiRows = 32 * (kWhole ? WAVES_M : kWaves);
+    static constexpr int kEpi = (kWhole ? 2 : 1) * kEpiRows * kEpiRow;
     static constexpr int kMain = NSTAGE * kStage > kEpi ? NSTAGE * kStage : kEpi;
     static constexpr int kLds = kMain + (2 * BN + BM) * 4;    // + column scale, column bias, row scale
     static constexpr int kLdsQ = kLds + (WAVES_N + 1) * BM * 4;   // + per-wave row maxima, row 1/scale
@@ -497,18 +504,20 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // arithmetic and round trip delayed it; behind the last, where they were, the store to LDS waited for
     // all stages of the ring to land, since loads complete in order, and so did the first product.
     static_assert(BN <= NT && BM <= NT, "one scale element per thread");
+    float sw_v = 0.0f, st_v = 1.0f;                   // FP16 activations carry no token scale
+    half_t b_v = 0;
+    const int sc_c = (int)threadIdx.x < BN ? (int)threadIdx.x : 0, sc_m = (int)threadIdx.x < BM ? (int)threadIdx.x : 0;
     if constexpr (KSPLIT == 0) {
         const int n = n0 + sc_c < N ? n0 + sc_c : N - 1;
         const int m = m0 + sc_m < M ? m0 + sc_m : M - 1;
         sw_v = s_w[n / gs];
-    float sw_v = 0.0f, st_v = 1.0f;                   // FP16 activations carry no token scale
-    half_t b_v = 0;
-    const int sc_c = (int)threadIdx.x < BN ? (int)threadIdx.x : 0, sc_m = (int)threadIdx.x < BM ? (int)threadIdx.x : 0;
         // without a bias the load reads a valid dummy address: no branch around a load in flight
         b_v = *(bias != nullptr ? bias + n : reinterpret_cast<const half_t *>(s_w));
         if constexpr (!A16) st_v = s_tok[m];
         __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int s = 1; s < NSTAGE; ++s) first_stage(s);
     if (!STAGED_W)
         wait_vmcnt<(NSTAGE - 1) * LPS>();      // stage 0 and the scales have landed; later stages may still be in flight
     else
@@ -523,8 +532,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     lds_barrier();
     if constexpr (PAIRED) {
         read_w_paired(smem);
-#pragma unroll
-    for (int s = 1; s < NSTAGE; ++s) first_stage(s);
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm) read_x_paired(smem, 0, fm, b0[fm]);
 #pragma unroll
@@ -674,11 +681,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
             take_over(std::integral_constant<int, HALF>{});
     }
     constexpr int OROW = Cfg::kEpiRow;
-    uint8_t *ot = smem + wave * (32 * OROW);  // wave-private: 32 rows of this wave's columns
     const int mw = m0 + wm * WM;              // first token row of this wave
     const int nw = n0 + wn * WN;              // first output column of this wave
-    constexpr int LPR = WN * 2 / 16;          // lanes per output row (16 bytes each)
-    static_assert((32 * LPR) % 64 == 0, "the 32-row block must be a whole number of store instructions");
+    constexpr bool WHOLE = Cfg::kWhole;
+    constexpr int EN = WHOLE ? NT : 64;       // threads that store a buffer's rows, 16 bytes each
+    constexpr int TPRO = (OROW - 16) / 16;    // ... of them for a row
+    constexpr int EROWS = WHOLE ? Cfg::kEpiRows : 32;
+    static_assert((EROWS * TPRO) % EN == 0, "a round is a whole number of store instructions");
+    static_assert(!WHOLE || KT == 1, "");
     float rmax[FM];                           // QOUT: max |g| of this lane's token rows
     unsigned gen_raw = 0;                     // QOUT: generation of this launch, back before it is needed
     if constexpr (QOUT == 1)
@@ -706,6 +716,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
         constexpr int LO = decltype(lo_c)::value, HI = decltype(hi_c)::value;   // the 32-row blocks this wave finishes
 #pragma unroll
         for (int blk = LO; blk < HI; ++blk) {
+            uint8_t *buf = smem + (WHOLE ? blk % 2 * (EROWS * OROW) : wave * (32 * OROW));
+            uint8_t *ot = WHOLE ? buf + wm * (32 * OROW) + wn * (WN * 2) : buf;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int fm = 2 * blk + h;
@@ -767,16 +779,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
                     }
                 }
             }
-            // The wave reads back its own 32 rows (LDS operations of one wave complete in order) and
-            // stores whole row segments.
+            // A wave reads back its own 32 rows (LDS operations of one wave complete in order) and stores row segments
+            // of WN * 2 bytes; in tall tiles any wave stores whole rows of BN * 2 bytes, which several have made.  One
+            // barrier a round is enough with two buffers: whoever writes the third round has passed the second round's
+            // barrier, and so has everyone who has read the first.
             if (QOUT == 0 || out != nullptr) {
+                if constexpr (WHOLE) lds_barrier();
 #pragma unroll
-                for (int i = 0; i < 32 * LPR / 64; ++i) {
-                    const int row = (i * 64 + lane) / LPR;
-                    const int col = ((i * 64 + lane) % LPR) * 8;
-                    const int32x4 v = *reinterpret_cast<const int32x4 *>(ot + row * OROW + col * 2);
-                    const int m = mw + blk * 32 + row;
-                    const int n = nw + col;
+                for (int i = 0; i < EROWS * TPRO / EN; ++i) {
+                    const int piece = i * EN + (WHOLE ? (int)threadIdx.x : lane);
+                    const int row = piece / TPRO, col = piece % TPRO * 8;
+                    const int32x4 v = *reinterpret_cast<const int32x4 *>(buf + row * OROW + col * 2);
+                    const int m = (WHOLE ? m0 + row / 32 * WM + row % 32 : mw + row) + blk * 32;
+                    const int n = (WHOLE ? n0 : nw) + col;
                     // Streaming (non-temporal) stores: nothing in this kernel reads the output again, and lines
                     // that do not linger in the L2 need no write-back when the kernel ends (4096x4096x1024:
                     // 25.3 -> 23.2 us alone, 23.5 -> 23.0 us inside the feed-forward chain).
