@@ -47,9 +47,9 @@
 // over its own range of K stages, and write raw accumulators to a workspace;
 // splitk_finish_kernel adds them and applies the epilogue.
 //
-// KT = 2 (128 x 128 tile, INT8 weights) splits the eight waves into two teams
-// that share every stage and take half of its k steps each, so that a wave
-// owns 64 x 64 instead of 64 x 32; the teams add their accumulators through
+// KT = 2 (128 x 128 and 128 x 64 tiles, INT8 weights) splits the eight waves
+// into two teams that share every stage and take half of its k steps each, so
+// that a wave owns twice the columns; the teams add their accumulators through
 // LDS after the last stage.
 //
 // XT = 1, 2 is the product of FP16 activations with INT8 weights (Sec. 5, the
@@ -76,7 +76,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 // Chunk swizzle: 16 consecutive rows reading the same logical chunk hit 16 different bank groups.
 template <int BK>
 __device__ __forceinline__ int swz(int row) {
-    return (BK == 128) ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3);
+    return (BK == 256) ? (row & 15) : (BK == 128) ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3);
 }
 
 template <int N>
@@ -1164,19 +1164,26 @@ TileShape choose_quant_tile(int M, int N, int K, int w_bits, unsigned shapes) {
 }
 }  // namespace
 
-// INT8 weights on 128 x 128 and 128 x 64 tiles: two K teams of 2 x 2 waves (wave tile 64 x 64, 64 x 32); measured 5-8 %
-// ahead of eight waves side by side on 4096x1024x4096 and 2048x2048x8192, level on 2048x2048x2048.  INT4 weights measured
-// 2-3 % slower with teams on 128 x 128 (the nibble unpack already fills the stage boundary) and keep the 2 x 4 layout.
-// On tiles of up to 192 x 128 the nibbles stay packed in LDS (XT = 3): these tiles wait for their operand loads, and half
-// the weight bytes measured 5-14 % faster (2048x2048x2048 13.5 -> 12.8 us, 4096x1024x4096 27.1 -> 23.7 us; 192x128 on
-// 16384x4096 at 333 tokens 32.5 -> 29.5).  On 256 x 128 both ways are level, and on 256 x 256 tiles, which run at the
-// chip's power limit, the register-side unpack measured 5 % slower than unpacking on the way into LDS (4096x16384x4096
-// 233 -> 245 us), so they keep that.
+// INT8 weights on 128 x 128 tiles: eight waves side by side (2 x 4) up to K 4096, two K teams of 2 x 2 beyond.  The teams read
+// a third fewer fragments per product but exchange accumulators at the end, 0.9 us, which 32 stages of K earn back (us, teams /
+// side by side: 2048x2048x1024 9.1 / 8.3, 700x4096x2304 12.7 / 12.2, 4096x1024x4096 21.5 / 20.4, 2048x2048x4096 21.4 / 21.3,
+// 1800x2304x9216 65.1 / 67.3).  On 128 x 64 tiles, whose stages of 128 bytes are eight matrix instructions a wave between two
+// barriers, the teams go through 256 bytes a stage, three stages instead of five of 128 in flight (us, five of 128 / three of
+// 256: 1237x1024x4096 13.6 / 12.9, 333x4096x4096 15.1 / 14.6, 900x1536x6144 18.8 / 18.5, 1237x1024x1024 6.5 / 6.4; side by side
+// 13.4, 14.8, 19.2, 6.3).  On 128 x 128 two stages of 256 are too few in flight (2048x2048x8192 40.3 -> 42.2).
+//
+// INT4 weights: the nibbles stay packed in LDS (XT = 3) on tiles of up to 192 x 128, which wait for their operand loads
+// (2048x2048x2048 13.5 -> 12.8 us, 4096x1024x4096 27.1 -> 23.7), and on 256 x 256, where unpacking on the way into LDS spilled
+// registers and moves twice the bytes (us, unpacked / packed in LDS: 4096x4096x4096 69.0 / 63.1, 4096x4096x1024 22.9 / 20.5,
+// 8192x8192x4096 232 / 216; three stages instead of two 65, 21.5, 220).  Teams measured 2-3 % slower there.  256 x 128 and 256 x
+// 192 unpack on the way (packed: 4096x2048x1024 13.5 -> 13.7, 4096x3072x4096 52.9 -> 57.8).
 hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st) {
     if (a.w_bits == 8) {
         switch (shape) {
-            case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 5, 8, 0, 0, 0, 2>(a, st);
-            case kTile128x128: return launch_tile_t<128, 128, 2, 2, 128, 4, 8, 0, 0, 0, 2>(a, st);
+            case kTile128x64: return launch_tile_t<128, 64, 2, 2, 256, 3, 8, 0, 0, 0, 2>(a, st);
+            case kTile128x128:
+                if (a.K <= 4096) return launch_tile_t<128, 128, 2, 4, 128, 4, 8>(a, st);
+                return launch_tile_t<128, 128, 2, 2, 128, 4, 8, 0, 0, 0, 2>(a, st);
             case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 3, 8>(a, st);
             case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 8>(a, st);
             case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 8>(a, st);
@@ -1189,7 +1196,7 @@ hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st) 
         case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 3>(a, st);
         case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 4>(a, st);
         case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 4>(a, st);
-        default: return launch_tile_t<256, 256, 2, 4, 128, 2, 4>(a, st);
+        default: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 3>(a, st);
     }
 }
 
@@ -1286,7 +1293,7 @@ hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st) {
         case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3, 1>(a, st);
         case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 3, 1>(a, st);
         case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 4, 0, 1>(a, st);
-        case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 0, 1>(a, st);
+        case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 3, 1>(a, st);
         default: return hipErrorInvalidValue;
     }
 }

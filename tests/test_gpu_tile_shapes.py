@@ -209,3 +209,24 @@ def test_streaming_class_that_runs_tiles(zq, orc, bits, M, N, K, g, beyond):
         return
     assert zq.gemm_variant_name(zq.gemm_choose_variant(M, N, K, bits, 0)) == "skinny"
     _integers(zq, orc, -1, bits, M, N, K, g, 6600)
+
+
+# Forms of a tile shape at the ends of their ranges.  128x64 for INT8 goes through K 256 bytes a stage, three stages deep;
+# 128x128 for INT8 has one team of waves up to K 4096 and two beyond; 256x256 for INT4 keeps the nibbles packed in LDS, two
+# stages deep; tiles of 256 rows store whole rows of the tile.
+@pytest.mark.parametrize("bits,tile,M,N,K,g", [
+    (8, "tile128x64", 129, 80, 16, 5), (8, "tile128x64", 65, 64, 256, 4), (8, "tile128x64", 257, 1040, 272, 65),
+    (8, "tile128x64", 300, 144, 752, 9), (8, "tile128x64", 300, 1040, 1040, 13), (8, "tile128x64", 333, 208, 5136, 13),
+    (8, "tile128x128", 137, 8304, 4096, 519), (8, "tile128x128", 137, 8304, 4112, 519),
+    (4, "tile256x256", 257, 528, 32, 33), (4, "tile256x256", 300, 272, 128, 17), (4, "tile256x256", 511, 272, 160, 1),
+    (4, "tile256x256", 270, 528, 384, 3), (4, "tile256x256", 2398, 8208, 544, 27), (8, "tile256x256", 479, 528, 144, 33),
+    (8, "tile256x128", 1550, 7392, 272, 7), (8, "tile256x192", 1886, 6800, 272, 25),
+])
+def test_forms_of_a_tile_shape(zq, orc, bits, tile, M, N, K, g):
+    print("form", bits, tile, M, N, K, flush=True)
+    before = zq.force_gemm_variant(VARIANT[tile])
+    try:
+        assert zq.gemm_schedule(M, N, K, bits, 0) == tile
+    finally:
+        zq.force_gemm_variant(before)
+    _integers(zq, orc, VARIANT[tile], bits, M, N, K, g, 6200)
