@@ -52,12 +52,11 @@
 // that a wave owns twice the columns; the teams add their accumulators through
 // LDS after the last stage.
 //
-// XT = 1, 2 is the product of FP16 activations with INT8 weights (Sec. 5, the
+// XT = 1 is the product of FP16 activations with INT8 weights (Sec. 5, the
 // W8A16 setting): FP16 matrix-core instructions, fp32 accumulators, the
-// weights made FP16 exactly either after the fragment read (XT = 1: INT8 in
-// LDS) or on their way into LDS (XT = 2).  XT = 3 is XT = 1's operand path
-// for INT4 weights under INT8 activations: the nibbles stay packed in LDS
-// (direct loads, half the bytes) and are unpacked after the fragment read.
+// weights INT8 in LDS and made FP16 exactly after the fragment read.  XT = 2 is
+// the same operand path for INT4 weights under INT8 activations: the nibbles
+// stay packed in LDS and are unpacked after the fragment read.
 //
 // Workgroup ids are remapped so that the workgroups an XCD receives
 // (round-robin by id) cover a compact block of tiles and share operand panels
@@ -76,7 +75,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 // Chunk swizzle: 16 consecutive rows reading the same logical chunk hit 16 different bank groups.
 template <int BK>
 __device__ __forceinline__ int swz(int row) {
-    return (BK == 256) ? (row & 15) : (BK == 128) ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3);
+    return (BK == 128) ? ((row & 7) ^ ((row >> 3) & 1)) : ((row >> 2) & 3);
 }
 
 template <int N>
@@ -98,7 +97,7 @@ template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int NSTAGE, int KT =
 struct TileCfg {
     static constexpr int kWaves = WAVES_M * WAVES_N * KT;
     static constexpr int kThreads = 64 * kWaves;
-    static constexpr int kStage = BM * BK + BN * ((XT == 1 || XT == 3) ? BK / 2 : BK);   // XT = 1, 3: weight rows half as long as activation rows
+    static constexpr int kStage = BM * BK + BN * (XT != 0 ? BK / 2 : BK);   // XT = 1, 2: weight rows half as long as activation rows
     static constexpr int kWN = BN / WAVES_N;
     // The epilogue turns 32 rows at a time through LDS, padded against bank conflicts: each wave its own columns in a
     // buffer of its own, or, in tall tiles (WHOLE), all waves side by side whole rows of the tile in one of two.
@@ -151,27 +150,23 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     constexpr int CPR = BK / 16;                     // 16-byte chunks per row
     constexpr int RPU = 64 / CPR;                    // rows per 1 KB load unit
     constexpr int XU = BM / RPU;                     // load units in the activation tile
-    // XT = 1, 2: FP16 activations (W8A16); the MFMA is the FP16 one and an activation row of a stage is still
-    // BK bytes, now BK/2 values of K.
-    // XT = 1: the weight rows stay INT8 in LDS (BK/2 bytes per stage, direct loads like the activations) and
+    // XT = 1: FP16 activations (W8A16); the MFMA is the FP16 one and an activation row of a stage is still
+    // BK bytes, now BK/2 values of K.  The weight rows stay INT8 in LDS (BK/2 bytes per stage) and
     // become FP16 in registers after the fragment read: one 16-byte read holds the weights of two k
     // steps, converted exactly by cvt8_i8_f16.  So that a lane's sixteen weights meet the right
     // activations, the k steps of a stage take the activation chunks in a permuted order (see
     // read_x_paired): a sum over K does not depend on the order of K.
-    // XT = 2: the weights take the register path of the INT4 weights (16 source bytes -> two 16-byte
-    // chunks) with the same conversion instead of the nibble unpack, and sit in LDS as FP16.
-    // XT = 3: INT8 activations, INT4 weights packed in LDS (again BK/2 bytes of a weight row per stage):
+    // XT = 2: INT8 activations, INT4 weights packed in LDS (again BK/2 bytes of a weight row per stage):
     // XT = 1's loop with the nibble unpack as the conversion and the INT8 MFMA.
-    constexpr bool A16 = XT == 1 || XT == 2;
-    constexpr bool PAIRED = XT == 1 || XT == 3;      // weight rows half as long as activation rows, widened after the fragment read
+    constexpr bool A16 = XT == 1;
+    constexpr bool PAIRED = XT != 0;                 // weight rows half as long as activation rows, widened after the fragment read
     constexpr int BKW = PAIRED ? BK / 2 : BK;        // bytes of a weight row per stage
     constexpr int CPRW = BKW / 16;
     constexpr int RPUW = 64 / CPRW;
     constexpr int WU = BN / RPUW;
-    constexpr bool STAGED_W = (WBITS == 4 && XT != 3) || (XT == 2);   // weights that pass through registers on their way into LDS
     constexpr int XB = A16 ? 2 : 1;                  // bytes per activation value
     static_assert(!A16 || WBITS == 8, "FP16 activations go with INT8 weights");
-    static_assert(XT != 3 || WBITS == 4, "packed weight rows in LDS are the INT4 ones");
+    static_assert((WBITS == 4) == (XT == 2), "INT4 weights are packed in LDS");
     static_assert(!PAIRED || (BK == 128 && KT == 1), "the paired loop is written for two k steps per stage");
     static_assert(QOUT == 0 || !A16, "the output quantization is built for the INT8 product");
     static_assert(QOUT == 0 || BN == 64 || BN == 128 || BN == 256, "the code tile's swizzle wants a power of two of chunks");
@@ -180,12 +175,9 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     constexpr int LX = XU / NW;                      // activation loads per wave per stage
     // weight loads per wave per stage; where the units do not split evenly some waves load a unit a
     // second time (the same bytes to the same place), so that every wave issues the same number of loads
-    constexpr int LWD = STAGED_W ? 0 : (WU + NW - 1) / NW;
+    constexpr int LWD = (WU + NW - 1) / NW;
     using AccT = typename std::conditional<A16, float32x4, int32x4>::type;
     constexpr int LPS = LX + LWD;                    // direct loads per wave per stage
-    constexpr int TPR4 = BK / 32;                    // INT4: threads per row (16 packed bytes each)
-    constexpr int W4_ROWS = NT / TPR4;               // rows per pass
-    constexpr int W4_PASSES = (BN + W4_ROWS - 1) / W4_ROWS;
 
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -235,8 +227,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // the matrix end lie past the end of the buffer, which the hardware answers with zeros: multiplied, never stored.
     // weight unit of this wave's load i (wave-uniform; a subtraction, not a remainder, which would go
     // through the vector unit and make the LDS address of the load look divergent)
-    static_assert(LWD * NW <= 2 * WU || STAGED_W, "a unit is loaded at most twice");
-    static_assert((NW * RPU) % 16 == 0 && (STAGED_W || ((NW * RPUW) % 16 == 0 && BN % 16 == 0)), "one chunk for all units of a wave");
+    static_assert(LWD * NW <= 2 * WU, "a unit is loaded at most twice");
+    static_assert((NW * RPU) % 16 == 0 && (NW * RPUW) % 16 == 0 && BN % 16 == 0, "one chunk for all units of a wave");
     auto w_unit = [&](int i) {
         const int u = wave + NW * (i - LX);
         return __builtin_amdgcn_readfirstlane(u >= WU ? u - WU : u);
@@ -254,16 +246,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     const int tail_bytes_w = tail_bytes / (PAIRED ? 2 : XB);   // the same values of K in a weight row
     const unsigned voff_x_tail = (tail_bytes == 0 || xchunk * 16 < tail_bytes) ? voff_x : kNowhere;
     const unsigned voff_w_tail = (tail_bytes == 0 || wchunk * 16 < tail_bytes_w) ? voff_w : kNowhere;
-    // INT4 weights: thread -> (row = pass*W4_ROWS + tid/TPR4, 16 packed bytes = 32 codes = chunks 2q, 2q+1)
-    unsigned w4_voff[W4_PASSES];
-    if (STAGED_W) {
-#pragma unroll
-        for (int p = 0; p < W4_PASSES; ++p) {
-            const unsigned grow = n0 + p * W4_ROWS + (int)threadIdx.x / TPR4;
-            w4_voff[p] = grow * (unsigned)wrow_bytes + ((int)threadIdx.x % TPR4) * 16;
-        }
-    }
-
     const int nkt = (xrow_bytes + BK - 1) / BK;
     // stages kt0 .. kt0 + n_loc - 1 are this workgroup's; all of them without a K split
     int kt0 = 0, n_loc = nkt;
@@ -306,45 +288,6 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
 #pragma unroll
         for (int i = 0; i < LPS; ++i) issue_one(r, i);
     };
-    int32x4 w4_regs[W4_PASSES];
-    auto w4_fetch = [&](int kt, bool beyond) {
-#pragma unroll
-        for (int p = 0; p < W4_PASSES; ++p) {
-            const bool inside = !beyond && kt * (BK / 2) + ((int)threadIdx.x % TPR4) * 16 < wrow_bytes;
-            w4_regs[p] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, (int)(inside ? w4_voff[p] : kNowhere),
-                                                               beyond ? 0 : kt * (BK / 2), 0);
-        }
-    };
-    auto w4_store = [&](int slot) {
-        uint8_t *base = smem + slot * STAGE + X_STAGE;
-#pragma unroll
-        for (int p = 0; p < W4_PASSES; ++p) {
-            const int row = p * W4_ROWS + (int)threadIdx.x / TPR4;
-            const int q = (int)threadIdx.x % TPR4;
-            if (BN % W4_ROWS == 0 || row < BN) {   // the last pass may reach past the tile
-                uint32_t d[8];
-                if (XT == 2) {
-                    const uint32x4_t lo = __builtin_bit_cast(
-                        uint32x4_t, cvt8_i8_f16((uint32_t)w4_regs[p][0], (uint32_t)w4_regs[p][1]));
-                    const uint32x4_t hi = __builtin_bit_cast(
-                        uint32x4_t, cvt8_i8_f16((uint32_t)w4_regs[p][2], (uint32_t)w4_regs[p][3]));
-                    d[0] = lo[0]; d[1] = lo[1]; d[2] = lo[2]; d[3] = lo[3];
-                    d[4] = hi[0]; d[5] = hi[1]; d[6] = hi[2]; d[7] = hi[3];
-                } else {
-                    unpack8_nat((uint32_t)w4_regs[p][0], d[0], d[1]);
-                    unpack8_nat((uint32_t)w4_regs[p][1], d[2], d[3]);
-                    unpack8_nat((uint32_t)w4_regs[p][2], d[4], d[5]);
-                    unpack8_nat((uint32_t)w4_regs[p][3], d[6], d[7]);
-                }
-                const int s = swz<BK>(row);
-                *reinterpret_cast<int32x4 *>(base + row * BK + (((2 * q) ^ s) * 16)) =
-                    int32x4{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
-                *reinterpret_cast<int32x4 *>(base + row * BK + (((2 * q + 1) ^ s) * 16)) =
-                    int32x4{(int)d[4], (int)d[5], (int)d[6], (int)d[7]};
-            }
-        }
-    };
-
     // ---- accumulators -----------------------------------------------------
     AccT acc[FN][FM];
 #pragma unroll
@@ -490,14 +433,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
     // that step's fragments in registers, so after the barrier there the slot is free and receives
     // stage kt + NSTAGE, while the first fragments of stage kt + 1 are read under the last MFMAs.
     int32x4 a0[FN], b0[FM], a1[FN], b1[FM];
-    auto first_stage = [&](int s) __attribute__((always_inline)) {
-        issue_direct(kt0 + s, s, s >= n_loc);
-        if (STAGED_W && s < n_loc) {
-            w4_fetch(kt0 + s, false);
-            w4_store(s);
-        }
-    };
-    first_stage(0);
+    issue_direct(kt0, 0, false);                      // (a workgroup has at least one stage)
     // Scale prefetch (App. D reads both scale vectors before the product is complete): the
     // per-column weight-group scale and bias and the per-row token scale of this tile go to LDS.
     // They are requested between the first operand stage and the second.  In front of the first, their address
@@ -517,11 +453,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int s = 1; s < NSTAGE; ++s) first_stage(s);
-    if (!STAGED_W)
-        wait_vmcnt<(NSTAGE - 1) * LPS>();      // stage 0 and the scales have landed; later stages may still be in flight
-    else
-        wait_vmcnt<0>();
+    for (int s = 1; s < NSTAGE; ++s) issue_direct(kt0 + s, s, s >= n_loc);
+    wait_vmcnt<(NSTAGE - 1) * LPS>();          // stage 0 and the scales have landed; later stages may still be in flight
     if constexpr (KSPLIT == 0) {
         // threads past the tile's edge write element 0 once more: a store behind a condition would take its load along
         col_scale[sc_c] = sw_v;
@@ -575,17 +508,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N * KT, (WAVES_M * WAVES_N * K
             if (ks + 1 < KS_T) {
                 step(ca, cb, na, nb2, sb, ks + 1, Refill{}, Yes{}, No{});
             } else if constexpr (!LAST) {
-                if (!STAGED_W)
-                    wait_vmcnt<(NSTAGE - 2) * LPS>();     // stage kt+1 has landed
-                else
-                    wait_vmcnt<0>();
-                // Weights that pass through registers (INT4 nibbles, INT8 -> FP16): the registers fetched
-                // at the previous boundary have had a whole stage to arrive and share the wait above;
-                // their slot was freed at that boundary.  (Placed at the start of the stage, as before,
-                // the store waited for loads issued one k step earlier, a full memory latency per stage.)
-                if (STAGED_W && kt >= 1 && kt - 1 + NSTAGE < n_loc) w4_store((kt - 1) % NSTAGE);
+                wait_vmcnt<(NSTAGE - 2) * LPS>();         // stage kt+1 has landed
                 lds_barrier();
-                if (STAGED_W) w4_fetch(kt0 + kt + NSTAGE, kt + NSTAGE >= n_loc);
                 // the first fragments of the next stage arrive under these MFMAs
                 step(ca, cb, na, nb2, sn, 0, refill_of(kt0 + kt + NSTAGE, kt % NSTAGE, kt + NSTAGE >= n_loc), Yes{}, Yes{});
             } else {
@@ -1164,23 +1088,28 @@ TileShape choose_quant_tile(int M, int N, int K, int w_bits, unsigned shapes) {
 }
 }  // namespace
 
+// Stages in flight: as many as the shape needs and no more.  A deeper ring is not ahead of time, it delays the first stage
+// and holds LDS (us, more / fewer stages: INT8 128 x 64 five / four 1237x1024x4096 13.6 / 12.6, 2000x2048x1024 11.7 / 10.9; INT4
+// 128 x 64 five / four 200x4096x4096 15.2 / 14.3, 1237x1024x4096 15.7 / 14.8, 256 x 128 three / two 1024x6144x2048 18.4 / 18.2;
+// FP16 activations 256 x 128 three / two 4096x2048x1024 24.4 / 22.5, 4000x2048x4096 74.1 / 73.0, 192 x 128 four / three
+// 333x12288x6144 73.9 / 70.6), but INT8 192 x 128 wants its third for weights from memory (333x12288x4096 29.6, two 36.2).
+//
 // INT8 weights on 128 x 128 tiles: eight waves side by side (2 x 4) up to K 4096, two K teams of 2 x 2 beyond.  The teams read
 // a third fewer fragments per product but exchange accumulators at the end, 0.9 us, which 32 stages of K earn back (us, teams /
 // side by side: 2048x2048x1024 9.1 / 8.3, 700x4096x2304 12.7 / 12.2, 4096x1024x4096 21.5 / 20.4, 2048x2048x4096 21.4 / 21.3,
-// 1800x2304x9216 65.1 / 67.3).  On 128 x 64 tiles, whose stages of 128 bytes are eight matrix instructions a wave between two
-// barriers, the teams go through 256 bytes a stage, three stages instead of five of 128 in flight (us, five of 128 / three of
-// 256: 1237x1024x4096 13.6 / 12.9, 333x4096x4096 15.1 / 14.6, 900x1536x6144 18.8 / 18.5, 1237x1024x1024 6.5 / 6.4; side by side
-// 13.4, 14.8, 19.2, 6.3).  On 128 x 128 two stages of 256 are too few in flight (2048x2048x8192 40.3 -> 42.2).
+// 1800x2304x9216 65.1 / 67.3).  On 128 x 64 tiles, with eight matrix instructions a wave and stage, the teams stay ahead
+// (1237x1024x4096 13.4 side by side, 12.6).
 //
-// INT4 weights: the nibbles stay packed in LDS (XT = 3) on tiles of up to 192 x 128, which wait for their operand loads
-// (2048x2048x2048 13.5 -> 12.8 us, 4096x1024x4096 27.1 -> 23.7), and on 256 x 256, where unpacking on the way into LDS spilled
-// registers and moves twice the bytes (us, unpacked / packed in LDS: 4096x4096x4096 69.0 / 63.1, 4096x4096x1024 22.9 / 20.5,
-// 8192x8192x4096 232 / 216; three stages instead of two 65, 21.5, 220).  Teams measured 2-3 % slower there.  256 x 128 and 256 x
-// 192 unpack on the way (packed: 4096x2048x1024 13.5 -> 13.7, 4096x3072x4096 52.9 -> 57.8).
+// INT4 nibbles stay packed in LDS (XT = 2) on every shape: half the weight bytes move, and unpacking on the way into LDS
+// spilled registers on 256 x 256 (us, unpacked on the way / packed: 4096x4096x4096 69.0 / 63.1, 4096x4096x1024 22.9 / 20.5,
+// 8192x8192x4096 232 / 216; 256 x 192 4096x3072x4096 52.4 / 50.2; 256 x 128 4000x2048x4096 41.4 / 40.0, 1024x6144x2048 20.2 / 18.2;
+// 4096x1024x4096 on 128 x 128 27.1 / 23.7).  Likewise INT8 weights under FP16 activations on 256 x 192 (FP16 in LDS / INT8 in LDS:
+// 4096x3072x4096 99.2 / 93.4, 2048x6144x2048 58.0 / 54.6).  Their 128 x 64 tiles take four waves: a wave converts weights for
+// 64 x 32 instead of 32 x 32 (1237x1024x2048 17.6 / 14.5, 300x4096x1024 10.6 / 9.1).
 hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st) {
     if (a.w_bits == 8) {
         switch (shape) {
-            case kTile128x64: return launch_tile_t<128, 64, 2, 2, 256, 3, 8, 0, 0, 0, 2>(a, st);
+            case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 4, 8, 0, 0, 0, 2>(a, st);
             case kTile128x128:
                 if (a.K <= 4096) return launch_tile_t<128, 128, 2, 4, 128, 4, 8>(a, st);
                 return launch_tile_t<128, 128, 2, 2, 128, 4, 8, 0, 0, 0, 2>(a, st);
@@ -1191,12 +1120,12 @@ hipError_t launch_gemm_tile(const GemmArgs &a, TileShape shape, hipStream_t st) 
         }
     }
     switch (shape) {
-        case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 5, 4, 3>(a, st);
-        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3>(a, st);
-        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 3>(a, st);
-        case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 4>(a, st);
-        case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 4>(a, st);
-        default: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 3>(a, st);
+        case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 4, 4, 2>(a, st);
+        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 2>(a, st);
+        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 2>(a, st);
+        case kTile256x128: return launch_tile_t<256, 128, 2, 4, 128, 2, 4, 2>(a, st);
+        case kTile256x192: return launch_tile_t<256, 192, 2, 4, 128, 2, 4, 2>(a, st);
+        default: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 2>(a, st);
     }
 }
 
@@ -1241,10 +1170,8 @@ hipError_t launch_gemm_tile_splitk(const GemmArgs &a, hipStream_t st) {
     if (ks < 2 || a.workspace == nullptr ||
         a.workspace_bytes < kWsFixedBytes + (size_t)ks * a.M * a.N * sizeof(int32_t))
         return hipErrorInvalidValue;
-    // INT4 weights packed in LDS (XT = 3), as in the unsplit 128 x 128 schedule: 4096x16384 at 256 / 512 tokens
-    // 38.6 -> 35.3 / 56.4 -> 52.0 us
     hipError_t e = (a.w_bits == 8) ? launch_tile_t<128, 128, 2, 4, 128, 4, 8, 0, 0, 1>(a, st, ks)
-                                   : launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3, 0, 1>(a, st, ks);
+                                   : launch_tile_t<128, 128, 2, 4, 128, 4, 4, 2, 0, 1>(a, st, ks);
     if (e != hipSuccess) return e;
     return launch_splitk_finish<0>(a, ks, st);
 }
@@ -1279,21 +1206,23 @@ hipError_t launch_gemm_tile_quant(const GemmArgs &a, hipStream_t st) {
     const TileShape shape = choose_quant_tile(a.M, a.N, a.K, a.w_bits, a.quant_shapes);
     if (a.w_bits == 8) {
         switch (shape) {
-            case kTile128x64: return launch_tile_t<128, 64, 4, 2, 128, 5, 8, 0, 1>(a, st);
-            case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 8, 0, 1>(a, st);
-            case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 3, 8, 0, 1>(a, st);
-            case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 8, 0, 1>(a, st);
+            case kTile128x64: return launch_tile_t<128, 64, 4, 2, 128, 4, 8, 0, 1>(a, st);
+            case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 3, 8, 0, 1>(a, st);
+            case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 2, 8, 0, 1>(a, st);
+            case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 2, 8, 0, 1>(a, st);
             case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 8, 0, 1>(a, st);
             default: return hipErrorInvalidValue;
         }
     }
-    // nibbles packed in LDS (XT = 3) where the plain call has them so: 589x6144x1536 19.2 -> 18.5 us on 128x128
+    // us, on the stages and waves these had / have: INT8 333x4096x1024 (128 x 64) 12.9 / 12.6, 1237x4096x1024 (192 x 128) 18.5 /
+    // 18.1, 1700x4096x1024 (256 x 128) 21.4 / 21.0; INT4 333x4096x1024 14.9 / 13.6, 4096x4096x1024 (256 x 256, nibbles unpacked on
+    // the way into LDS) 38.1 / 33.8
     switch (shape) {
-        case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 5, 4, 3, 1>(a, st);
-        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 4, 3, 1>(a, st);
-        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 4, 3, 1>(a, st);
-        case kTile256x128: return launch_tile_t<256, 128, 4, 2, 128, 3, 4, 0, 1>(a, st);
-        case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 3, 1>(a, st);
+        case kTile128x64: return launch_tile_t<128, 64, 4, 2, 128, 4, 4, 2, 1>(a, st);
+        case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 3, 4, 2, 1>(a, st);
+        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 3, 4, 2, 1>(a, st);
+        case kTile256x128: return launch_tile_t<256, 128, 2, 4, 128, 2, 4, 2, 1>(a, st);
+        case kTile256x256: return launch_tile_t<256, 256, 2, 4, 128, 2, 4, 2, 1>(a, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1370,13 +1299,11 @@ hipError_t launch_gemm_a16_tile(const A16Args &a16, bool split, hipStream_t st) 
         return launch_splitk_finish<1>(a, ks, st);
     }
     switch (choose_tile(kTileA16, a.M, a.N, a.K, kAllTileShapes, nullptr)) {
-        case kTile128x64: return launch_tile_t<128, 64, 4, 2, 128, 5, 8, 1>(a, st);
+        case kTile128x64: return launch_tile_t<128, 64, 2, 2, 128, 4, 8, 1>(a, st);
         case kTile128x128: return launch_tile_t<128, 128, 2, 4, 128, 4, 8, 1>(a, st);
-        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 4, 8, 1>(a, st);
-        case kTile256x128: return launch_tile_t<256, 128, 2, 4, 128, 3, 8, 1>(a, st);
-        // the 256x192 tile keeps its weights FP16 in LDS (XT = 2): with three weight fragments per wave the
-        // register-side conversion made the compiler copy the accumulators every stage
-        case kTile256x192: return launch_tile_t<256, 192, 4, 2, 128, 2, 8, 2>(a, st);
+        case kTile192x128: return launch_tile_t<192, 128, 2, 4, 128, 3, 8, 1>(a, st);
+        case kTile256x128: return launch_tile_t<256, 128, 2, 4, 128, 2, 8, 1>(a, st);
+        case kTile256x192: return launch_tile_t<256, 192, 2, 4, 128, 2, 8, 1>(a, st);
         default: return launch_tile_t<256, 256, 2, 4, 128, 2, 8, 1>(a, st);
     }
 }
