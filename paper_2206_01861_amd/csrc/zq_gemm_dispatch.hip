@@ -102,9 +102,9 @@ int variant_of(TileShape shape) {
 // The K split of the tiles is a class by a model that knows 128x128 tiles only, and what a workspace is sized for.  A call runs
 // the best unsplit tile instead where that is faster by its own model, also without the second launch (INT8, 842x1024x4096 15.9
 // -> 13.6 us, 1007x1600x6400 24.9 -> 21.2, 200x2560x3072 14.8 -> 12.3).  At five per cent 5 of 15 shapes of the class change
-// over and none loses; at equal times or above 512x2048x8192 would (25.3 -> 27.4).  INT4 weights and FP16 activations keep the
-// split: their models draw even only where it is ahead (INT4 784x1600x6400 24.4 against 27.2, W8A16 433x3072x3072 24.7, 26.9).
-// So does one row of tiles, where the weights come from memory and half the chip would not ask for them (123x4480x4480 17.0,
+// over and none loses; at equal times or above 512x2048x8192 would (25.3 -> 27.4).  INT4 weights at 0.9: 12 of 120 shapes of the
+// class, by 6 % (161x6560x6080 23.2 -> 20.5, 235x4448x5632 18.2 -> 18.1); at 0.95 some lose 4 %, at equal times 10.  (FP16
+// activations: see a16_route.)  One row of tiles keeps the split, where the weights come from memory and half the chip would not ask for them (123x4480x4480 17.0,
 // 18.9).
 //
 // Streaming holds 65 to 128 tokens where K is long, a class of the time before tiles narrower than 128x128.  128x64 tiles that
@@ -115,14 +115,14 @@ int variant_of(TileShape shape) {
 // 5792x2560 are held by their tests.
 int tiles_if_faster(int variant, int M, int N, int K, int w_bits, size_t workspace_bytes) {
     TuneEntry e;
-    const bool split = variant == kGemmTileSplitK && w_bits == 8 && M > 128;
+    const bool split = variant == kGemmTileSplitK && M > 128;
     const bool streams = variant == kGemmSkinny && M > 64 &&
                          (w_bits == 4 ? N > 8192 && K >= 2560 : N > 6144 && N <= 16384 && (M <= 100 || N >= 12288));
     if (!split && !streams) return variant;
     if (tune_lookup(M, N, K, w_bits, &e) && gemm_variant_supports(e.variant, M, N, K, w_bits, workspace_bytes)) return variant;
     double us;
     const TileShape shape = choose_tile(tile_kind(w_bits), M, N, K, kAllTileShapes, &us);
-    return streams || us < 0.95 * tile_split_time(M, N, K, 1) ? variant_of(shape) : variant;
+    return streams || us < (w_bits == 8 ? 0.95 : 0.9) * tile_split_time(M, N, K, 1) ? variant_of(shape) : variant;
 }
 
 unsigned tile_shapes_of(int variant) {

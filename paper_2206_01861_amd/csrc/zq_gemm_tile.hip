@@ -971,10 +971,10 @@ int tile_splits(int M, int N, int K, int x_bytes, double *us = nullptr) {
 // Tile shapes, and the time a launch of them takes.  A compute unit holds one workgroup, so a launch lasts (rounds of
 // tiles) x (time of a tile): a + rounds * stages * b + (rounds - 1) * c microseconds, with a stage of 128 bytes of an
 // activation row.  b grows from b0, with few compute units at work, to b1 with all of them (power, L2 and memory shared):
-// the last, partly filled round is charged in between.  Fitted to 317 shapes each (72 to 8192 tokens, 768 to 24576
-// columns, K 768 to 24576; 70 for FP16 activations).  Against 7151 random shapes its error is 5 to 15 % rms (most where
-// weights from memory meet few tokens); the choice by it costs 0.1 % (INT8), 0.5 % (INT4) and 2.9 % (FP16 activations) on
-// average over the best shape, 4, 5 and 20 % in one of a hundred.
+// the last, partly filled round is charged in between.  INT8: fitted to 317 shapes (72 to 8192 tokens, 768 to 24576 columns, K
+// 768 to 24576); INT4 and FP16 activations: 300 (72 to 6000 tokens, K to 16384), each on all six, with the order that the
+// tests name as a condition.  The choice by it costs 0.3 % (INT8, INT4) and 0.1 % (FP16 activations) on average over the best
+// shape, 8, 6 and 2 % in one of a hundred.
 // What the smaller shapes are for, INT8, in microseconds: 128x64 and 128x128 fill the chip at some hundred tokens
 // (4096x4096 at 333 tokens: 15.6 on 128x64 tiles, 20.2 on 128x128, 41 on 256x192), 192x128 and 256x128 carry a third
 // stage in flight, which tiles of 256x192 have no LDS for and weights that come from HBM need (12288x4096 at 333: 28.2 on
@@ -989,11 +989,11 @@ constexpr TileCost kTileCost[3][kTileShapes] = {
     {{128, 64, 4.62, 0.265, 0.370, 2.19}, {128, 128, 5.60, 0.338, 0.542, 3.37}, {192, 128, 4.76, 0.577, 0.819, 3.50},
      {256, 128, 5.34, 0.644, 0.974, 4.56}, {256, 192, 5.84, 0.842, 1.311, 6.46}, {256, 256, 6.07, 1.003, 1.659, 6.78}},
     // INT4 weights
-    {{128, 64, 4.41, 0.430, 0.465, 2.54}, {128, 128, 4.25, 0.428, 0.571, 2.71}, {192, 128, 4.83, 0.545, 0.759, 3.95},
-     {256, 128, 4.78, 0.751, 0.991, 4.48}, {256, 192, 5.82, 0.981, 1.320, 6.88}, {256, 256, 6.12, 1.048, 1.520, 9.83}},
+    {{128, 64, 3.94, 0.303, 0.340, 2.09}, {128, 128, 3.41, 0.353, 0.614, 2.10}, {192, 128, 4.51, 0.499, 0.754, 2.99},
+     {256, 128, 4.12, 0.715, 1.006, 3.12}, {256, 192, 5.63, 0.888, 1.274, 4.78}, {256, 256, 7.55, 1.025, 1.546, 5.73}},
     // FP16 activations
-    {{128, 64, 5.10, 0.414, 0.476, 2.16}, {128, 128, 4.74, 0.389, 0.599, 2.38}, {192, 128, 5.24, 0.540, 0.783, 3.91},
-     {256, 128, 5.96, 0.632, 0.998, 5.49}, {256, 192, 6.54, 0.911, 1.398, 6.56}, {256, 256, 6.91, 1.051, 1.644, 9.34}},
+    {{128, 64, 4.36, 0.282, 0.347, 1.82}, {128, 128, 3.57, 0.423, 0.588, 1.89}, {192, 128, 4.51, 0.512, 0.752, 2.86},
+     {256, 128, 4.98, 0.713, 0.922, 3.36}, {256, 192, 5.98, 0.887, 1.169, 5.99}, {256, 256, 7.38, 1.075, 1.478, 7.00}},
 };
 
 // The same for launches that quantize their output in the kernel (GeLU, row maxima exchanged between the tiles of a band, codes
@@ -1004,8 +1004,8 @@ constexpr TileCost kTileCost[3][kTileShapes] = {
 constexpr TileCost kQuantTileCost[2][kTileShapes] = {
     {{128, 64, 9.38, 0.028, 0.436, 6.92}, {128, 128, 9.58, 0.268, 0.716, 6.56}, {192, 128, 10.74, 0.434, 1.010, 7.59},
      {256, 128, 12.35, 0.507, 1.166, 9.32}, {256, 192, 0, 0, 0, 0}, {256, 256, 16.17, 0.930, 1.885, 13.32}},
-    {{128, 64, 10.94, 0.057, 0.546, 7.80}, {128, 128, 9.56, 0.254, 0.744, 6.38}, {192, 128, 10.82, 0.427, 0.998, 7.83},
-     {256, 128, 11.73, 0.651, 1.272, 8.99}, {256, 192, 0, 0, 0, 0}, {256, 256, 16.32, 0.952, 1.918, 13.47}},
+    {{128, 64, 7.33, 0.358, 0.541, 5.11}, {128, 128, 9.54, 0.274, 0.660, 3.16}, {192, 128, 11.23, 0.394, 0.843, 8.66},
+     {256, 128, 12.26, 0.490, 1.129, 9.36}, {256, 192, 0, 0, 0, 0}, {256, 256, 18.88, 0.869, 1.656, 14.78}},
 };
 
 // A tile that quantizes its rows waits for its band, so a band that the chip does not take in whole keeps the compute units of its
@@ -1013,7 +1013,8 @@ constexpr TileCost kQuantTileCost[2][kTileShapes] = {
 // 1318x5888x1472 on 128x128: 506 tiles are three rounds, 44.7 us, not two; 256x256 34.7).  And the maxima of a band come 16 at a
 // time, 0.6 us each (442x4096x1024, bands of 64 tiles of 128x64 14.7 us, of 32 of 128x128 13.7).  Against 2400 other shapes
 // (65 to 8192 tokens, 768 to 16384 columns, K 768 to 6144) 5 % rms; the choice costs 0.02 % on average over the best shape (0.27 %
-// without the two terms, 29 % at worst) and takes 0.962 of the time that 128x128 and 256x256 alone take.
+// without the two terms, 29 % at worst) and takes 0.962 of the time that 128x128 and 256x256 alone take.  The INT4 line is a later
+// fit, to 225 shapes: its choice costs 0.7 %.
 double quant_tile_time(const TileCost &t, int M, int N, int K) {
     const long tiles_n = (N + t.bn - 1) / t.bn, tiles = (long)((M + t.bm - 1) / t.bm) * tiles_n;
     const double stages = (double)((K + 127) / 128);

@@ -230,3 +230,15 @@ def test_forms_of_a_tile_shape(zq, orc, bits, tile, M, N, K, g):
     finally:
         zq.force_gemm_variant(before)
     _integers(zq, orc, VARIANT[tile], bits, M, N, K, g, 6200)
+
+
+# Shapes of the K split's class that run unsplit tiles (see test_schedule_query.py)
+@pytest.mark.parametrize("bits,M,N,K,g", [(4, 161, 6560, 6080, 410), (16, 378, 3872, 3776, 2), (16, 67, 8128, 1472, 4)])
+def test_split_class_that_runs_unsplit_by_its_model(zq, orc, bits, M, N, K, g):
+    print("unsplit by model", bits, M, N, K, flush=True)
+    if bits == 4:
+        assert zq.gemm_schedule(M, N, K, 4, zq.gemm_workspace_bytes(M, N, K, 4)) in VARIANT
+        _integers(zq, orc, -1, 4, M, N, K, g, 6300)
+    else:
+        assert zq.gemm_schedule(M, N, K, 8, zq.gemm_w8a16_workspace_bytes(M, N, K), x_bits=16) in VARIANT
+        _fp16(zq, orc, M, N, K, g, 6300)

@@ -264,3 +264,13 @@ def test_vector_kernel_by_table_where_the_route_streams():
 ])
 def test_many_tokens_against_few_rows(M, N, K, ws, want):
     assert zq.gemm_schedule(M, N, K, 8, zq.gemm_workspace_bytes(M, N, K) if ws else 0) == want
+
+
+# (bits, M, N, K): the class is the K split with room for it; unsplit tiles run below a share of its modelled time
+@pytest.mark.parametrize("M,N,K,bits,x_bits,splits", [
+    (161, 6560, 6080, 4, 8, False), (256, 4096, 16384, 4, 8, True), (178, 6464, 7296, 4, 8, False), (105, 5440, 11840, 4, 8, True),
+    (1237, 1024, 2048, 8, 16, False), (67, 8128, 1472, 8, 16, False), (378, 3872, 3776, 8, 16, False), (245, 6528, 13632, 8, 16, True),
+])
+def test_split_or_unsplit_by_the_models(M, N, K, bits, x_bits, splits):
+    name = zq.gemm_schedule(M, N, K, bits, 1 << 30, x_bits=x_bits)
+    assert (name == "tile128x128_splitk") == splits and name.startswith("tile")
