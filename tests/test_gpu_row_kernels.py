@@ -121,3 +121,17 @@ def test_long_rows_of_the_quantizer(zq, orc, M, K):
     xq_o, s_o = orc.quant_tokenwise(x.astype(np.float32))
     assert_bit_equal(host(s_tok), s_o, "s_tok")
     assert_bit_equal(host(xq), xq_o, "xq")
+
+
+def test_gelu_tanh_keeps_the_digits_of_small_results(zq):
+    """Every finite FP16 input up to 4 in size against 64 bits.  The exponent's argument z, at most 15.8, carries three roundings
+    of 2^-24 of itself (z * ln 2 * 3 * 2^-24 = 2e-6 in the result), exponential, sum, reciprocal and product a few 2^-24 more."""
+    h = torch.arange(65536, dtype=torch.int32).to(torch.int16).view(torch.float16)
+    h = h[torch.isfinite(h)]
+    x = h[: h.numel() // 64 * 64].view(-1, 64).cuda()
+    _, _, y = zq.zq_gelu_quant_tokenwise(x, None, approx_tanh=True, y_dtype=torch.float32)
+    u = x.double()
+    want = u * torch.sigmoid(2.0 * (2.0 / np.pi) ** 0.5 * (u + 0.044715 * u ** 3))
+    near = (u.abs() <= 4.0) & (want.abs() > 2.0 ** -120)
+    assert ((y.double() - want).abs()[near] <= 3e-6 * want.abs()[near]).all()
+    assert ((y.double() - want).abs() <= 2.0 ** -22 * u.abs() + 2.0 ** -120).all()
